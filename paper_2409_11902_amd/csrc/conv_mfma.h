@@ -30,7 +30,18 @@ struct GatherParams {
                         // one of every second row), as an image of half the extent read with stride 1
     uint32_t m_wc, m_ppi, m_pwd, m_kbs, m_img; // division magics of Wc, Hc*Wc, PWd, kbs, PH*PWd
     uint32_t m_gx, m_ph;                       // ... of the 8-pixel groups of an input row and of PH (in-place copy)
+    // conv_tile.hip
+    int tile;           // the launch runs there
+    int gw, GX;         // pixels of a staged item; items of an input row
+    int store_px;       // pixels per store of the epilogue: 8, 4, 2 or 1
+    int buf_bytes, lds_bytes; // a staging buffer; all of the workgroup's LDS
+    uint32_t wofs[9], toff[9]; // per tap: byte offset of its filter fragments; LDS byte offset within the patch
 };
+
+// conv_tile.hip: nine-tap launches with large wave tiles (see there)
+bool shape_tile(GatherParams &p, int *variant);
+hipError_t launch_tile(const GatherParams &p, int variant, hipStream_t st);
+int describe_tile(const GatherParams &p, int variant, char *buf, size_t len);
 
 size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
 // Text description of the launch shape(s) chosen; false when the geometry is not covered.

@@ -1035,6 +1035,7 @@ bool shape_gather(GatherParams &p, int *variant)
 
 hipError_t run_gather(const GatherParams &p, int variant, hipStream_t st)
 {
+    if (p.tile) return launch_tile(p, variant, st);
     switch (variant) {
     case 0: return launch_gather<2, 1, 4>(p, st);
     case 1: return launch_gather<2, 2, 2>(p, st);
@@ -1054,6 +1055,14 @@ bool supported(const Geom &g, int dtype)
     const long lim = 1L << 30;
     if ((long)g.N * g.H * g.W * round_up(g.C, 16) >= lim || (long)g.N * g.P * g.Q * round_up(g.K, 16) >= lim) return false;
     if ((long)g.R * g.S * round_up(g.K, 64) * round_up(g.C, 64) >= lim) return false;
+    return true;
+}
+
+bool use_tile()
+{
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_TILE")) return atoi(f) != 0;
+#endif
     return true;
 }
 
@@ -1080,6 +1089,8 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
     if (p.decim) {
         p.Hin = g.H / 2; p.Win = g.W / 2; p.is = 1;
     }
+    p.KCin = g.C;
+    if (use_tile() && shape_tile(p, variant)) { p.tile = 1; return true; }
     return shape_gather(p, variant);
 }
 
@@ -1111,7 +1122,12 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                     ++p.ntaps;
                 }
             if (p.ntaps == 0) { *empty_class = true; continue; }
-            if (!shape_gather(p, &variant[*ncls])) return false;
+            p.KCin = g.K;
+            if (use_tile() && shape_tile(p, &variant[*ncls])) {
+                p.tile = 1;
+                base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
+                base.tile = 1;
+            } else if (!shape_gather(p, &variant[*ncls])) return false;
             cls[(*ncls)++] = p;
         }
     return true;
@@ -1123,6 +1139,7 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
 // 3.8 us gained per call at 230 input elements per filter element, 1.5 us lost at 3.5).
 bool dx_reads_in_place(const Geom &g, const GatherParams (&cls)[4], int ncls)
 {
+    if (ncls == 1 && cls[0].tile) return true;
     bool direct = g.Q % 2 == 0 && (long)g.N * g.K * g.P * g.Q >= 8L * g.R * g.S * g.K * g.C;
     for (int k = 0; k < ncls; ++k) direct = direct && cls[k].IPT * cls[k].PH * ((g.Q + 7) / 8) * (KC / 8) * cls[k].T <= 512;
     return direct;
@@ -1130,6 +1147,7 @@ bool dx_reads_in_place(const Geom &g, const GatherParams (&cls)[4], int ncls)
 
 int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
 {
+    if (p.tile) return describe_tile(p, variant, buf, len);
     static const int shape[6][3] = {{2, 1, 4}, {2, 2, 2}, {2, 4, 1}, {1, 1, 4}, {1, 2, 2}, {1, 4, 1}}; // NI, WM, WN
     const int *v = shape[variant];
     const int runs = (p.ngrp + p.gpw - 1) / p.gpw, mt = (p.Mp / 64 + v[1] - 1) / v[1];
@@ -1211,8 +1229,8 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     const bool fuse0 = Z && !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4);
     // Where the pooled map cannot come out of the repack anyway, X is read where it lies under the
     // same conditions as dY in the data gradient (no channels-last copy, only the filter repack).
-    const bool direct = !p.decim && g.W % 2 == 0 && (long)g.N * g.C * g.H * g.W >= 8L * g.R * g.S * g.K * g.C &&
-                        p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512;
+    const bool direct = p.tile || (!p.decim && g.W % 2 == 0 && (long)g.N * g.C * g.H * g.W >= 8L * g.R * g.S * g.K * g.C &&
+                        p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512);
     const bool fuse = fuse0; // (with `direct` the repack launch forms Z without writing the channels-last copy)
     *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp,
                          (const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr,

@@ -1,0 +1,62 @@
+"""GPU parity of the nine-tap kernel with large wave tiles (conv_tile.hip) at the edges of what it takes: rows of
+odd length and of every store width, tiles that end inside a block, several images per tile and a batch they do not
+divide, ragged channel counts on both sides, stride 2, items that fill a thread once and twice."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2409_11902_amd import binding as B
+from paper_2409_11902_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# bfloat16 keeps 8 significant bits: rounding to nearest moves a value by at most half a unit in the last place, 2^-8
+# of it, and an image's rel-L2 by no more (1.65e-3 in the mean over mantissas, 1.98e-3 seen on an image of 1600
+# values); the float sums (at most 9 * 136 terms of products exact in float) add about sqrt(1224) * 2^-24 = 2e-6
+TOL = 2.0 ** -8 + 1e-5
+
+CASES = [
+    # name, N, C, K, H, W, stride
+    ("16-byte stores, one block short", 80, 32, 64, 20, 28, 1),
+    ("8-byte stores, rows of 14", 165, 64, 128, 14, 14, 1),
+    ("4-byte stores", 80, 40, 72, 9, 22, 1),
+    ("2-byte stores, rows of 7", 330, 32, 136, 7, 7, 1),
+    ("odd rows longer than an item", 80, 24, 80, 12, 9, 1),
+    ("odd rows, odd planes", 40, 35, 65, 11, 27, 1),
+    ("batch not a multiple of the images per tile", 1201, 16, 64, 5, 6, 1),
+    ("wide rows, two items per thread", 24, 33, 64, 30, 56, 1),
+    ("whole blocks only", 165, 32, 64, 16, 16, 1),
+    ("stride 2", 160, 32, 80, 28, 28, 2),
+    ("stride 2, odd extents", 160, 20, 130, 27, 15, 2),
+    ("channels past one block of 32", 80, 65, 33, 18, 20, 1),
+    ("256 output channels", 160, 40, 256, 10, 14, 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_forward_and_data_gradient(case):
+    import torch
+    from gpu_util import Guarded, download, upload, workspace
+    name, N, C, K, H, W, st = case
+    spec = synth.LayerSpec(name, N, C, K, H, W, stride=st)
+    t = synth.make_inputs(spec, "conv-tile")
+    d = B.desc_from_spec(spec)
+    assert B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS).startswith("tile="), "the case is here for that kernel"
+    X, Wt, b, dY = (upload(t[n], spec.dtype) for n in ("X", "W", "b", "dY"))
+    hp, wp, _, _ = B.cac_pooled_shape(d)
+    Y, Z = Guarded((N, K, spec.P, spec.Q), torch.bfloat16), Guarded((N, C, hp, wp), torch.bfloat16)
+    dX = Guarded((N, C, H, W), torch.bfloat16)
+    B.conv_fwd_and_compress(d, X, Wt, b, Y.t, Z.t, workspace(d, B.OP_FWD_AND_COMPRESS))
+    B.conv_bwd_data(d, Wt, dY, dX.t, workspace(d, B.OP_BWD_DATA))
+    torch.cuda.synchronize()
+    Y.check("Y"), Z.check("Z"), dX.check("dX")
+    g = oracle.ConvGeom(N, C, K, H, W, 3, 3, st, st, 1, 1)
+    f = {n: t[n].astype(np.float64) for n in ("X", "W", "b", "dY")}
+    for out, want in ((Y, oracle.conv_fwd(g, f["X"], f["W"], f["b"])), (dX, oracle.conv_dx(g, f["W"], f["dY"]))):
+        got = download(out.t)
+        # every image by itself: an error in the last one must not hide behind the others
+        for n in range(N):
+            err = np.linalg.norm(got[n] - want[n]) / np.linalg.norm(want[n])
+            assert err <= TOL, (name, n, err)
