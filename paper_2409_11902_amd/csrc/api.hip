@@ -338,7 +338,8 @@ int conv_fwd_and_compress(const cac_desc *d, const void *X, const void *W, const
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     bool pooled = false;
-    if (!launch_fwd_mfma(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, Z, ws, st, &e, &pooled))
+    if (!launch_fwd_mfma(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, Z, ws, st, &e, &pooled) &&
+        !launch_fwd_lds(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, st, &e))
         e = launch_fwd_generic(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, st);
     if ((rc = launched(e, "forward convolution"))) return rc;
     if (pooled) return CAC_OK;
@@ -393,7 +394,8 @@ int conv_bwd_data(const cac_desc *d, const void *W, const void *dY, void *dX, vo
     if ((rc = check_ptr(W, "W")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dX, "dX"))) return rc;
     if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_DATA, ws, ws_bytes, nullptr))) return rc;
     hipError_t e = hipSuccess;
-    if (!launch_dx_mfma(g, d->dtype, W, dY, dX, ws, (hipStream_t)stream, &e))
+    if (!launch_dx_mfma(g, d->dtype, W, dY, dX, ws, (hipStream_t)stream, &e) &&
+        !launch_dx_lds(g, d->dtype, W, dY, dX, (hipStream_t)stream, &e))
         e = launch_dx_generic(g, d->dtype, W, dY, dX, (hipStream_t)stream);
     return launched(e, "data gradient");
 }
@@ -415,7 +417,7 @@ int conv_bwd_weight_and_data(const cac_desc *d, const void *Z, const void *W, co
     hipError_t e = hipSuccess;
     if (!launch_dx_mfma(g, d->dtype, W, dY, dX, ws_dx, st, &e, &tail)) {
         if ((rc = launched(launch_dw_reduce(tail, st), "weight gradient (slice sum)"))) return rc;
-        e = launch_dx_generic(g, d->dtype, W, dY, dX, st);
+        if (!launch_dx_lds(g, d->dtype, W, dY, dX, st, &e)) e = launch_dx_generic(g, d->dtype, W, dY, dX, st);
     }
     return launched(e, "data gradient");
 }

@@ -1,0 +1,252 @@
+// Forward convolution and data gradient for the float path and for every geometry the MFMA kernels do not take
+// (filters of more than nine taps, strides above 2): an LDS-tiled multiply-add kernel in float arithmetic, gfx950.
+//
+// The sum is the gather of conv_mfma.hip,
+//   out[n, m, i*os + a0, j*os + b0] = bias[m] + sum_taps sum_kc W'[m][kc][tap] * in[n, kc, i*is + dh, j*is + dw],
+// forward with os = 1, is = stride, (dh, dw) = (r - ph, s - pw), the data gradient with is = 1, os = stride and one
+// class (a0, b0) per parity, all classes in one launch.
+//
+// The layers that come here are small (the single 16 -> 16 float layer of the lists is 38 MFLOP), so what bounds
+// them is latency: one output per thread with its operands fetched from the caches inside the loop took 30 us
+// (forward) and 19 us (data gradient) on that layer; this kernel takes 10.8 us for either.  A workgroup of 256
+// threads owns 16 output channels x 64 or 256 pixels; it stages the input patch of CC channels (zero-padded, as
+// floats) and the filter's part ([tap][channel][16 outputs]) in LDS, eight loads per thread in flight (one at a time:
+// 17 us), and a thread keeps 4 outputs x 1 or 4 pixels: a step is one 16-byte broadcast read of the filter and 1 or
+// 4 reads of the patch along the lanes for 4 or 16 multiply-adds, the reads of 8 (4) channels ahead of their sums
+// (one channel at a time: 13.8 us).  64 pixels per workgroup when 256 would leave less than four workgroups per
+// compute unit.
+#include "common.h"
+
+namespace cac {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ uint32_t fdiv(uint32_t x, uint32_t magic) { return magic ? __umulhi(x, magic) : x; }
+
+constexpr uint32_t kNoLoad = 0x80000000u;
+constexpr int kTMP = 20; // floats of a filter entry in LDS: 16 outputs, padded against bank conflicts of the writes
+// element at a byte offset; zero at or past the tensor's end
+template <typename T> __device__ __forceinline__ float load(rsrc_t rs, uint32_t off)
+{
+    if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+    else return bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0));
+}
+
+struct ConvLdsParams {
+    const void *in, *W, *bias;
+    void *out;
+    int N, M, KC, Hin, Win, Hout, Wout; // KC: input channels of the sum
+    int R, S, sh, sw, ph, pw;           // of the convolution
+    int C;                              // input channels of the convolution (the filter's row length)
+    int Hc, Wc, ppi;                    // grid of output pixels of a class (the largest one)
+    int IPT, tiles, ngrp;               // images per workgroup; tiles per image; image groups
+    int PH, PWd;                        // staged patch of one image
+    int cw_log2;                        // lanes of a patch row while staging, log2 (6: a whole wave, in turns)
+    uint32_t m_wc, m_ppi, m_rpc, m_ph, m_rs; // division magics (m_wc, m_ppi, m_rs: 0 for 1; the others are of at least 2)
+};
+
+// T: storage type; PX: pixels per thread; DX: data gradient; CC: channels staged per pass.
+template <typename T, int PX, bool DX, int CC> __global__ void __launch_bounds__(256) conv_lds_kernel(ConvLdsParams p)
+{
+    constexpr int TM = 16, PT = 64 * PX;
+    extern __shared__ __align__(16) float lds[];
+    const int RS = p.R * p.S;
+    float *sw = lds, *sx = lds + RS * CC * kTMP; // [tap][CC][TM + 4], [CC][IPT][PH][PWd], 64 floats of nobody's
+    const int lane = threadIdx.x & 63, mg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int cls = DX ? blockIdx.z : 0, os_h = DX ? p.sh : 1, os_w = DX ? p.sw : 1, is_h = DX ? 1 : p.sh, is_w = DX ? 1 : p.sw;
+    const int a0 = cls / os_w, b0 = cls - a0 * os_w;
+    const int grp = blockIdx.x / p.tiles, tau = blockIdx.x - grp * p.tiles;
+    const int n0 = grp * p.IPT, pix0 = tau * PT, i0 = fdiv(pix0, p.m_wc), m0 = blockIdx.y * TM;
+    // offsets of the taps of this class: the smallest one starts the patch (floor division, also of negatives)
+    auto floor_div = [](int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); };
+    const int dhmin = DX ? -floor_div(p.R - 1 - a0 - p.ph, p.sh) : -p.ph, dwmin = DX ? -floor_div(p.S - 1 - b0 - p.pw, p.sw) : -p.pw;
+    const int hin0 = i0 * is_h + dhmin;
+
+    int n[PX], oi[PX], oj[PX], base[PX];
+    bool ok[PX];
+#pragma unroll
+    for (int k = 0; k < PX; ++k) {
+        const int idx = lane + 64 * k;
+        int g = 0, px = pix0 + idx;
+        if (p.IPT > 1) {
+            g = fdiv(idx, p.m_ppi);
+            px = idx - g * p.ppi;
+        }
+        const int i = fdiv(px, p.m_wc), j = px - i * p.Wc;
+        n[k] = n0 + g;
+        oi[k] = i * os_h + a0;
+        oj[k] = j * os_w + b0;
+        const bool in_tile = g < p.IPT && px < p.ppi; // (what the staged patch covers)
+        ok[k] = in_tile && n[k] < p.N && oi[k] < p.Hout && oj[k] < p.Wout;
+        base[k] = in_tile ? (g * p.PH + (i - i0) * is_h) * p.PWd + j * is_w : 0;
+    }
+    f32x4 acc[PX];
+#pragma unroll
+    for (int k = 0; k < PX; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const rsrc_t rs_in = make_rsrc(p.in, (uint32_t)p.N * p.KC * p.Hin * p.Win * (uint32_t)sizeof(T));
+    const rsrc_t rs_w = make_rsrc(p.W, (uint32_t)p.M * p.KC * RS * (uint32_t)sizeof(T));
+    const int rpc = p.IPT * p.PH, xplane = rpc * p.PWd, nrows = CC * rpc;
+    const int woff = RS * CC * kTMP, xdump = CC * xplane + lane; // (a place of every lane's own past the patch)
+    const int rpw = 64 >> p.cw_log2, cmask = (1 << p.cw_log2) - 1;
+    constexpr int kRows = (DX ? CC : TM) / 4;           // rows of the filter's part per wave
+    const int L = (DX ? TM : CC) * RS;                  // elements of a row
+    for (int c0 = 0; c0 < p.KC; c0 += CC) {
+        if (c0) __syncthreads();
+        // The patch, row by row (channel, image, patch row): one per wave and turn, or several short ones side by side.
+        // Eight loads per thread are in flight before the first value is stored, without a branch between them: what
+        // does not exist is read past the tensor (zero) and, outside the row, stored past the patch.
+        for (int w0 = 0; w0 < p.PWd; w0 += 64) {
+            const int col = w0 + (lane & cmask), w = dwmin + col;
+            const bool cok = (w >= 0) & (w < p.Win), cin = col < p.PWd;
+            for (int r0 = mg * rpw + (lane >> p.cw_log2); r0 < nrows; r0 += 32 * rpw) {
+                float x[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const uint32_t rho = r0 + 4 * q * rpw;
+                    const int c = __umulhi(rho, p.m_rpc), t = rho - c * rpc, g = __umulhi(t, p.m_ph), h = hin0 + t - g * p.PH;
+                    const bool ok = cok & (rho < (uint32_t)nrows) & (c0 + c < p.KC) & (n0 + g < p.N) & (h >= 0) & (h < p.Hin);
+                    const uint32_t off = (uint32_t)((((n0 + g) * p.KC + c0 + c) * p.Hin + h) * p.Win + w);
+                    x[q] = load<T>(rs_in, ok ? off * (uint32_t)sizeof(T) : kNoLoad);
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int rho = r0 + 4 * q * rpw;
+                    sx[cin & (rho < nrows) ? rho * p.PWd + col : xdump] = x[q];
+                }
+            }
+        }
+        // The filter: rows of W [o][c][tap], their runs of (channel, tap) -- forward -- or (output, tap) -- data gradient
+        // -- along the lanes; where an element of a run goes does not depend on the row.
+        for (int x0 = 0; x0 < L; x0 += 128) {
+            float v[2][kRows];
+            int dst[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int xi = x0 + 64 * k + lane, q = RS > 1 ? __umulhi(xi, p.m_rs) : xi, tap = xi - q * RS;
+                const bool cok = (xi < L) & (xi < (DX ? (p.M - m0) * RS : (p.KC - c0) * RS));
+                dst[k] = xi < L ? (DX ? tap * CC * kTMP + q : (tap * CC + q) * kTMP) : -1;
+#pragma unroll
+                for (int j = 0; j < kRows; ++j) {
+                    const int row = mg + 4 * j, o = DX ? c0 + row : m0 + row;
+                    const uint32_t off = (uint32_t)((o * p.C + (DX ? m0 : c0)) * RS + xi);
+                    v[k][j] = load<T>(rs_w, cok & (o < (DX ? p.KC : p.M)) ? off * (uint32_t)sizeof(T) : kNoLoad);
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int j = 0; j < kRows; ++j) {
+                    const int row = mg + 4 * j;
+                    lds[dst[k] >= 0 ? dst[k] + (DX ? row * kTMP : row) : xdump + woff] = v[k][j];
+                }
+        }
+        __syncthreads();
+        for (int r = 0; r < p.R; ++r) {
+            const int th = a0 + p.ph - r, dh = DX ? floor_div(th, p.sh) : r - p.ph;
+            if (DX && th != dh * p.sh) continue;
+            for (int s = 0; s < p.S; ++s) {
+                const int tw = b0 + p.pw - s, dw = DX ? floor_div(tw, p.sw) : s - p.pw;
+                if (DX && tw != dw * p.sw) continue;
+                int xo = (dh - dhmin) * p.PWd + (dw - dwmin);
+                asm volatile("" : "+s"(xo)); // (no 16 running addresses per pixel carried from tap to tap)
+                const float *x = sx + xo;
+                const f32x4 *w = (const f32x4 *)(sw + (r * p.S + s) * CC * kTMP) + mg;
+                // (the reads of a batch of channels before their sums: left alone, the compiler waits for every read)
+                constexpr int CBT = CC < 8 ? CC : 16 / (PX == 1 ? 2 : PX);
+#pragma unroll
+                for (int cb = 0; cb < CC; cb += CBT) {
+                    f32x4 wv[CBT];
+                    float xv[CBT][PX];
+#pragma unroll
+                    for (int c = 0; c < CBT; ++c) {
+                        wv[c] = w[(cb + c) * (kTMP / 4)];
+#pragma unroll
+                        for (int k = 0; k < PX; ++k) xv[c][k] = x[(cb + c) * xplane + base[k]];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int c = 0; c < CBT; ++c)
+#pragma unroll
+                        for (int k = 0; k < PX; ++k)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[k][e] = __builtin_fmaf(xv[c][k], wv[c][e], acc[k][e]);
+                }
+            }
+        }
+    }
+    T *out = (T *)p.out;
+    const T *bias = (const T *)p.bias;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int m = m0 + mg * 4 + e;
+        if (m >= p.M) break;
+        const float b = !DX && bias ? Elem<T>::load(bias + m) : 0.f;
+#pragma unroll
+        for (int k = 0; k < PX; ++k)
+            if (ok[k]) Elem<T>::store(out + (((long)n[k] * p.M + m) * p.Hout + oi[k]) * p.Wout + oj[k], acc[k][e] + b);
+    }
+}
+
+template <typename T, bool DX> bool launch(const Geom &g, const void *in, const void *W, const void *bias, void *out, hipStream_t st, hipError_t *err)
+{
+    auto magic = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+    ConvLdsParams p{};
+    p.in = in; p.W = W; p.bias = bias; p.out = out;
+    p.N = g.N; p.C = g.C; p.R = g.R; p.S = g.S; p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;
+    p.M = DX ? g.C : g.K; p.KC = DX ? g.K : g.C;
+    p.Hin = DX ? g.P : g.H; p.Win = DX ? g.Q : g.W; p.Hout = DX ? g.H : g.P; p.Wout = DX ? g.W : g.Q;
+    // (32-bit byte offsets with 2^31 reserved for what does not exist)
+    if ((long)p.N * p.KC * p.Hin * p.Win * (long)sizeof(T) >= 1L << 31 || (long)p.M * p.KC * g.R * g.S * (long)sizeof(T) >= 1L << 31) return false;
+    const int os_h = DX ? g.sh : 1, os_w = DX ? g.sw : 1, is_h = DX ? 1 : g.sh, is_w = DX ? 1 : g.sw;
+    p.Hc = (p.Hout + os_h - 1) / os_h; p.Wc = (p.Wout + os_w - 1) / os_w;
+    if ((long)p.Hc * p.Wc * p.Wc >= 1L << 32) return false; // (division by multiplication is exact below)
+    p.ppi = p.Hc * p.Wc;
+    const int span_h = DX ? (g.R - 1) / g.sh + 1 : g.R, span_w = DX ? (g.S - 1) / g.sw + 1 : g.S;
+    const int mblocks = (p.M + 15) / 16, classes = os_h * os_w;
+    if (mblocks > 65535 || classes > 65535) return false;
+    const long wgs4 = (long)((p.ppi + 255) / 256) * g.N * mblocks * classes;
+    const int px = wgs4 >= 1024 ? 4 : 1, pt = 64 * px; // (four workgroups per compute unit hide each other's staging)
+    p.IPT = 2L * p.ppi <= pt ? min(pt / p.ppi, g.N) : 1;
+    p.tiles = p.IPT > 1 ? 1 : (p.ppi + pt - 1) / pt;
+    p.ngrp = (g.N + p.IPT - 1) / p.IPT;
+    const long rows = p.IPT > 1 ? p.Hc : min((long)p.Hc, (long)(pt + p.Wc - 2) / p.Wc + 1);
+    const long ph = max(2L, (rows - 1) * is_h + span_h), pw = (long)(p.Wc - 1) * is_w + span_w;
+    if ((long)p.tiles * p.ngrp > 0x7fffffffL) return false;
+    for (int cc : {16, 4}) {
+        const long bytes = 4 * ((long)g.R * g.S * cc * kTMP + (long)cc * p.IPT * ph * pw + 64);
+        if (bytes > 64 * 1024) continue;
+        p.PH = (int)ph; p.PWd = (int)pw;
+        p.cw_log2 = 0;
+        while (p.cw_log2 < 6 && (1 << p.cw_log2) < p.PWd) ++p.cw_log2;
+        p.m_wc = magic(p.Wc); p.m_ppi = magic(p.ppi); p.m_ph = magic(p.PH); p.m_rpc = magic(p.IPT * p.PH);
+        p.m_rs = magic(g.R * g.S);
+        const dim3 grid(p.tiles * p.ngrp, mblocks, classes);
+#define CAC_LDS(PX, CC) hipLaunchKernelGGL((conv_lds_kernel<T, PX, DX, CC>), grid, dim3(256), (size_t)bytes, st, p)
+        if (cc == 16) {
+            if (px == 4) CAC_LDS(4, 16); else CAC_LDS(1, 16);
+        } else {
+            if (px == 4) CAC_LDS(4, 4); else CAC_LDS(1, 4);
+        }
+#undef CAC_LDS
+        *err = hipGetLastError();
+        return true;
+    }
+    return false; // rows too long or a filter too large for LDS
+}
+
+} // namespace
+
+bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err)
+{
+    return dtype == CAC_F32 ? launch<float, false>(g, X, W, b, Y, st, err) : launch<bf16_t, false>(g, X, W, b, Y, st, err);
+}
+
+bool launch_dx_lds(const Geom &g, int dtype, const void *W, const void *dY, void *dX, hipStream_t st, hipError_t *err)
+{
+    return dtype == CAC_F32 ? launch<float, true>(g, dY, W, nullptr, dX, st, err) : launch<bf16_t, true>(g, dY, W, nullptr, dX, st, err);
+}
+
+} // namespace cac

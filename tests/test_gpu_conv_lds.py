@@ -1,0 +1,61 @@
+"""GPU parity of the LDS-tiled float forward / data-gradient kernel (conv_lds.hip) at the edges of what it takes:
+one and four pixels per thread, rows that share a wave and rows longer than one, several images per workgroup,
+channel counts around its blocks of 16 and 4, strides with pixels that no tap reaches, large filters, and shapes
+that do not fit LDS (the plain kernels)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2409_11902_amd import binding as B
+from paper_2409_11902_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # name, dtype, N, C, K, H, W, R, S, stride_h, stride_w, pad_h, pad_w
+    ("one pixel per thread", "f32", 3, 16, 16, 32, 32, 3, 3, 1, 1, 1, 1),
+    ("four pixels per thread", "f32", 40, 20, 33, 40, 52, 3, 3, 1, 1, 1, 1),
+    ("several images per workgroup", "f32", 37, 17, 15, 3, 5, 3, 3, 1, 1, 1, 1),
+    ("one pixel images", "f32", 70, 5, 18, 1, 1, 1, 1, 1, 1, 0, 0),
+    ("rows longer than a wave", "f32", 2, 9, 16, 6, 150, 3, 3, 1, 1, 1, 1),
+    ("four channels per pass", "f32", 1, 11, 17, 5, 400, 3, 5, 1, 1, 1, 2),
+    ("stride 3 past a 1x1 filter", "f32", 4, 16, 19, 13, 11, 1, 1, 3, 3, 0, 0),
+    ("uneven strides and pads", "f32", 3, 18, 35, 17, 14, 3, 5, 2, 3, 2, 0),
+    ("7x7 stride 2", "f32", 2, 3, 24, 30, 26, 7, 7, 2, 2, 3, 3),
+    ("too long for LDS", "f32", 1, 3, 4, 3, 5000, 3, 3, 1, 1, 1, 1),
+    ("bf16 5x5", "bf16", 8, 33, 16, 15, 17, 5, 5, 1, 1, 2, 2),
+    ("bf16 stride 3", "bf16", 5, 16, 40, 19, 16, 3, 3, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_forward_and_data_gradient(case):
+    import torch
+    from gpu_util import Guarded, download, upload
+    name, dtype, N, C, K, H, W, R, S, sh, sw, ph, pw = case
+    dt = synth.F32 if dtype == "f32" else synth.BF16
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    d = B.make_desc(N, C, K, H, W, R, S, sh, sw, ph, pw, 1, 1, dtype=B.F32 if dtype == "f32" else B.BF16)
+    assert B.cac_workspace_size(d, B.OP_FWD_AND_COMPRESS) == 0, "no MFMA plan: the case is here for the float kernel"
+    P, Q = B.cac_out_shape(d)
+    rng = np.random.default_rng(sum(map(ord, name)))
+    make = lambda *s: synth.to_storage(rng.standard_normal(s, dtype=np.float32), dt)  # noqa: E731
+    X, Wt, b, dY = make(N, C, H, W), make(K, C, R, S), make(K), make(N, K, P, Q)
+    Y, Z, dX = Guarded((N, K, P, Q), td), Guarded((N, C, H, W), td), Guarded((N, C, H, W), td)
+    B.conv_fwd_and_compress(d, upload(X, dt), upload(Wt, dt), upload(b, dt), Y.t, Z.t)
+    B.conv_bwd_data(d, upload(Wt, dt), upload(dY, dt), dX.t)
+    torch.cuda.synchronize()
+    Y.check("Y"), Z.check("Z"), dX.check("dX")
+    g = oracle.ConvGeom(N, C, K, H, W, R, S, sh, sw, ph, pw)
+    f = [a.astype(np.float64) for a in (X, Wt, b, dY)]
+    # float sums of at most 35 * 49 terms of either sign: sqrt(1715) * 2^-24 = 2.5e-6 of the result; a bfloat16 result
+    # is rounded once, by at most 2^-8 of every value
+    tol = 1e-5 + (0 if dtype == "f32" else 2.0 ** -8)
+    for what, out, want in (("Y", Y, oracle.conv_fwd(g, f[0], f[1], f[2])), ("dX", dX, oracle.conv_dx(g, f[1], f[3]))):
+        got = download(out.t)
+        assert np.array_equal(got == 0, want == 0) or what == "Y", "pixels that no tap reaches are exactly zero, and only they"
+        for n in range(N):
+            norm = np.linalg.norm(want[n])
+            assert np.linalg.norm(got[n] - want[n]) <= tol * norm, (name, what, n)
