@@ -31,7 +31,7 @@ struct GatherParams {
     uint32_t m_wc, m_ppi, m_pwd, m_kbs, m_img; // division magics of Wc, Hc*Wc, PWd, kbs, PH*PWd
     uint32_t m_gx, m_ph;                       // ... of the 8-pixel groups of an input row and of PH (in-place copy)
     // conv_tile.hip
-    int tile;           // the launch runs there
+    int tile;           // the launch runs there (2: in conv_dx2.hip)
     int gw, GX;         // pixels of a staged item; items of an input row
     int store_px;       // pixels per store of the epilogue: 8, 4, 2 or 1
     int buf_bytes, lds_bytes; // a staging buffer; all of the workgroup's LDS
@@ -42,6 +42,10 @@ struct GatherParams {
 bool shape_tile(GatherParams &p, int *variant);
 hipError_t launch_tile(const GatherParams &p, int variant, hipStream_t st);
 int describe_tile(const GatherParams &p, int variant, char *buf, size_t len);
+// conv_dx2.hip: the 3 x 3 stride-2 data gradient, all parity classes in one launch
+bool shape_dx2(const Geom &g, GatherParams &p, int *variant);
+hipError_t launch_dx2(const GatherParams &p, int variant, hipStream_t st);
+int describe_dx2(const GatherParams &p, int variant, char *buf, size_t len);
 
 size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
 // Text description of the launch shape(s) chosen; false when the geometry is not covered.

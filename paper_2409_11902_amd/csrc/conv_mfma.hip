@@ -1035,7 +1035,7 @@ bool shape_gather(GatherParams &p, int *variant)
 
 hipError_t run_gather(const GatherParams &p, int variant, hipStream_t st)
 {
-    if (p.tile) return launch_tile(p, variant, st);
+    if (p.tile) return p.tile == 2 ? launch_dx2(p, variant, st) : launch_tile(p, variant, st);
     switch (variant) {
     case 0: return launch_gather<2, 1, 4>(p, st);
     case 1: return launch_gather<2, 2, 2>(p, st);
@@ -1106,6 +1106,12 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
     base.os = g.sh; base.is = 1; base.ntaps_total = g.R * g.S;
     *ncls = 0;
     *empty_class = false;
+    if (GatherParams p = base; p.KCin = g.K, use_tile() && shape_dx2(g, p, &variant[0])) {
+        p.tile = 2;
+        base.KCp = p.KCp;
+        cls[(*ncls)++] = p;
+        return true;
+    }
     for (int a0 = 0; a0 < g.sh; ++a0)
         for (int b0 = 0; b0 < g.sw; ++b0) {
             GatherParams p = base;
@@ -1147,7 +1153,7 @@ bool dx_reads_in_place(const Geom &g, const GatherParams (&cls)[4], int ncls)
 
 int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
 {
-    if (p.tile) return describe_tile(p, variant, buf, len);
+    if (p.tile) return p.tile == 2 ? describe_dx2(p, variant, buf, len) : describe_tile(p, variant, buf, len);
     static const int shape[6][3] = {{2, 1, 4}, {2, 2, 2}, {2, 4, 1}, {1, 1, 4}, {1, 2, 2}, {1, 4, 1}}; // NI, WM, WN
     const int *v = shape[variant];
     const int runs = (p.ngrp + p.gpw - 1) / p.gpw, mt = (p.Mp / 64 + v[1] - 1) / v[1];

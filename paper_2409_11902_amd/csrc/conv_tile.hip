@@ -28,39 +28,21 @@
 
 #include "common.h"
 #include "conv_mfma.h"
+#include "tile_stage.h"
 
 namespace cac {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-constexpr uint32_t kNoLoad = 0x80000000u;
-constexpr uint32_t kNoElem = 0x40000000u;
+using namespace tile;
 constexpr int KC = 32;       // channels of a stage
 constexpr int KCS = KC + 8;  // LDS elements per patch pixel: 80 bytes, an odd number of 16-byte units
 constexpr int TAPS = 9, STEPS = TAPS * (KC / 16);
-constexpr uint32_t kFrag = 64 * 16; // bytes of one fragment of the repacked filter
 
-__device__ __forceinline__ uint32_t fdiv(uint32_t x, uint32_t magic) { return magic ? __umulhi(x, magic) : x; }
-typedef __attribute__((address_space(3))) u32x4 *lds_u32x4_ptr;
-typedef __attribute__((address_space(3))) u32x2 *lds_u32x2_ptr;
-typedef __attribute__((address_space(3))) uint32_t *lds_u32_ptr;
-typedef __attribute__((address_space(3))) uint16_t *lds_u16_ptr;
-__device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(uintptr_t)addr; }
-
-// Keeps the compiler from computing what follows from `x` ahead of this point (and outside of loops).
-__device__ __forceinline__ void opaque(uint32_t &x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void opaque_s(uint32_t &x) { asm volatile("" : "+s"(x)); }
-
-constexpr int kDumpBytes = 256 * 8;     // 8 bytes for every lane of a workgroup
 constexpr int kEpRow = 64 * 2 + 16;     // LDS bytes of an epilogue row: 64 pixels of one channel
 constexpr int kEpWave = 32 * kEpRow;    // 32 channels per pass
 
-// GW: pixels of a staged item: 8, or 7 for rows of odd length (an item that starts on an odd element
-// is read from the dword below, whose eight elements hold seven of the item).
+// ITEMS, GW: see PatchStage; D: steps of filter fragments in flight; EPI: pixels per store.
 template <int NI, int WM, int WN, int ITEMS, int GW, int D, int EPI>
 __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
 {
@@ -84,83 +66,8 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int hin0 = i0 * p.is + p.dhmin, win0 = p.dwmin;
     const int m0 = (blockIdx.y * WM + wm) * 64;
 
-    // ---- staging: an item is 8 channels x GW pixels of one patch row
-    const int GX = p.GX, nitems = p.IPT * p.PH * GX * 4;
-    const uint32_t plane = (uint32_t)p.Hin * p.Win;
-    const int co = tid & 3;
-    uint32_t e0[ITEMS], l0[ITEMS], m8[ITEMS];
-#pragma unroll
-    for (int q = 0; q < ITEMS; ++q) {
-        const int it = tid + 256 * q;
-        const int rest = it >> 2;
-        const int rows = fdiv(rest, p.m_gx), gx = rest - rows * GX;
-        const int g = fdiv(rows, p.m_ph), pr = rows - g * p.PH;
-        const int hin = hin0 + pr, w0 = gx * GW;
-        const bool ok = (it < nitems) & (hin >= 0) & (hin < p.Hin) & (n_base + g < p.N);
-        uint32_t m = 0;
-#pragma unroll
-        for (int k = 0; k < GW; ++k) {
-            const int w = w0 + k;
-            m |= (ok & (w < p.Win) & (w >= win0) & (w < win0 + p.PWd)) ? 1u << k : 0u;
-        }
-        m8[q] = m;
-        e0[q] = ok ? (uint32_t)((g * p.KCin + co * 8) * p.Hin + hin) * p.Win + w0 : kNoElem;
-        l0[q] = lds0 + (uint32_t)(((g * p.PH + pr) * p.PWd + (w0 - win0)) * KCS + co * 8) * 2u;
-    }
-    const rsrc_t rs_in = make_rsrc(p.in, (uint32_t)p.N * p.KCin * plane * 2u);
-    // A stage is brought in NB batches of CB channels per item, one after the other through the same registers.
-    constexpr int NB = 2, CB = 8 / NB;
-    u32x4 r[ITEMS][CB];
-    uint32_t par = 0; // parity of the stage's first element (rows of odd length only)
-    auto fetch = [&](int s, int h) {
-        const uint32_t sbase = (uint32_t)(n_base * p.KCin + s * KC + CB * h) * plane;
-        const int nvalid = p.KCin - (s * KC + co * 8 + CB * h); // channels of this lane's items that exist
-        if (GW == 7) par = sbase & 1u;
-#pragma unroll
-        for (int q = 0; q < ITEMS; ++q) {
-            uint32_t e = e0[q] + sbase; // (no item: still far outside the tensor)
-            opaque(e); // (the addresses of the stages are not to be kept in registers)
-#pragma unroll
-            for (int i = 0; i < CB; ++i) {
-                const uint32_t ei = i < nvalid ? e : kNoElem;
-                r[q][i] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, (GW == 7 ? ei & ~1u : ei) * 2u, 0, 0);
-                e += plane;
-            }
-        }
-    };
-    // rows that were read from the dword below an odd element: down by one element
-    auto align_rows = [&]() {
-        if constexpr (GW == 7) {
-#pragma unroll
-            for (int q = 0; q < ITEMS; ++q)
-#pragma unroll
-                for (int i = 0; i < CB; ++i) {
-                    const uint32_t sh = ((e0[q] + par + i * plane) & 1u) * 16u;
-                    u32x4 v = r[q][i];
-                    v[0] = __builtin_amdgcn_alignbit(v[1], v[0], sh);
-                    v[1] = __builtin_amdgcn_alignbit(v[2], v[1], sh);
-                    v[2] = __builtin_amdgcn_alignbit(v[3], v[2], sh);
-                    v[3] = v[3] >> sh;
-                    r[q][i] = v;
-                }
-        }
-    };
-    const uint32_t dump = lds0 + 2 * buf_bytes + tid * 8;
-    auto put_px = [&](uint32_t buf, int h, int px) {
-        if (px >= GW) return;
-#pragma unroll
-        for (int q = 0; q < ITEMS; ++q) {
-            uint32_t v[CB / 2]; // pixel px of the channels: half px%2 of dword px/2 of every row
-#pragma unroll
-            for (int k = 0; k < CB / 2; ++k) {
-                const uint32_t lo = r[q][2 * k][px / 2], hi = r[q][2 * k + 1][px / 2];
-                v[k] = (px & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-            }
-            // (a pixel that is not wanted goes to a place of the lane's own past the buffers: no branch)
-            const uint32_t a = (m8[q] & (1u << px)) ? l0[q] + buf + (px * (KCS * 2) + 2 * CB * h) : dump;
-            *(lds_u32x2_ptr)(uintptr_t)a = u32x2{v[0], v[1]};
-        }
-    };
+    PatchStage<ITEMS, GW, KC> in;
+    in.init(p, lds0, lds0 + 2 * buf_bytes, n_base, hin0);
 
     // ---- this lane's pixels
     uint32_t pbase[NI];
@@ -206,24 +113,13 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
         for (int mi = 0; mi < MI; ++mi)
             wr[q][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, p.wofs[q >> 1] + (q & 1) * kstep + mi * kFrag, 0);
 
-#pragma unroll
-    for (int h = 0; h < NB; ++h) {
-        fetch(0, h);
-        if (h == 0) {
-            for (uint32_t i = tid; i < 2 * buf_bytes / 16; i += 256) *(lds_u32x4_ptr)(uintptr_t)(lds0 + 16 * i) = u32x4{0, 0, 0, 0};
-            __syncthreads(); // (the zeros of one thread lie where another writes pixels)
-        }
-        align_rows();
-#pragma unroll
-        for (int px = 0; px < GW; ++px) put_px(0, h, px);
-    }
-    __syncthreads(); // buffer 0 holds stage 0
+    in.start(lds0, buf_bytes);
 
     for (int s = 0; s < nkb; ++s) {
         const uint32_t buf = (s & 1) ? buf_bytes : 0u, nbuf = buf_bytes - buf;
         uint32_t so = (uint32_t)s * 2 * kstep; // this stage's filter fragments (of tap 0)
         opaque_s(so);
-        fetch(s + 1, 0); // (past the end: nothing is loaded)
+        in.fetch(s + 1, 0); // (past the end: nothing is loaded)
         u32x4 bq[2][NL > 0 ? NL : 1];
 #pragma unroll
         for (int ni = 0; ni < NL; ++ni) bq[0][ni] = lds16(pbase[ni] + p.toff[0]);
@@ -250,14 +146,14 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi) wr[q % D][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, so2 + mi * kFrag, 0);
             }
-            constexpr int W = STEPS / NB; // steps of a batch: loads at the first, the pixels to LDS at the last four
+            constexpr int W = STEPS / 2; // steps of a half: loads at the first, the pixels to LDS at the last four
             const int h = q / W, qq = q % W;
-            if (qq == W - 5) align_rows();
+            if (qq == W - 5) in.align_rows();
             if (qq >= W - 4) {
-                put_px(nbuf, h, 2 * (qq - (W - 4)));
-                put_px(nbuf, h, 2 * (qq - (W - 4)) + 1);
+                in.put_px(nbuf, h, 2 * (qq - (W - 4)));
+                in.put_px(nbuf, h, 2 * (qq - (W - 4)) + 1);
             }
-            if (qq == W - 1 && h + 1 < NB) fetch(s + 1, h + 1);
+            if (qq == W - 1 && h == 0) in.fetch(s + 1, 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         // on to the other buffer
@@ -382,7 +278,7 @@ bool shape_tile(GatherParams &p, int *variant)
         b.dhmin = min(b.dhmin, p.dh[t]); dhmax = max(dhmax, p.dh[t]);
         b.dwmin = min(b.dwmin, p.dw[t]); dwmax = max(dwmax, p.dw[t]);
     }
-    auto magic = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
+    const auto magic = magic_of;
     b.PWd = (p.Wc - 1) * p.is + (dwmax - b.dwmin) + 1;
     b.nkb = b.kbs = b.KCp / KC;
     b.ksplit = 1; b.T = 1; b.part = nullptr;

@@ -1,4 +1,5 @@
-"""GPU parity of the nine-tap kernel with large wave tiles (conv_tile.hip) at the edges of what it takes: rows of
+"""GPU parity of the nine-tap kernel with large wave tiles (conv_tile.hip) and of the stride-2 data gradient that
+computes all parity classes in one launch (conv_dx2.hip) at the edges of what they take: rows of
 odd length and of every store width, tiles that end inside a block, several images per tile and a batch they do not
 divide, ragged channel counts on both sides, stride 2, items that fill a thread once and twice."""
 from __future__ import annotations
@@ -60,3 +61,40 @@ def test_forward_and_data_gradient(case):
         for n in range(N):
             err = np.linalg.norm(got[n] - want[n]) / np.linalg.norm(want[n])
             assert err <= TOL, (name, n, err)
+
+
+STRIDE2 = [
+    # name, N, C, K, H, W: dY rows of a multiple of 4, of 2, of odd length; a last input row that only some classes have
+    ("16-byte stores", 3, 64, 96, 16, 24),
+    ("8-byte stores, odd height", 5, 40, 33, 13, 20),
+    ("4-byte stores, rows of 7", 9, 72, 64, 14, 14),
+    ("odd rows, odd height", 4, 33, 65, 11, 18),
+    ("several images per tile, batch not a multiple", 23, 32, 40, 7, 8),
+    ("one row of pixels", 6, 16, 16, 1, 6),
+    ("one column of pairs", 6, 20, 16, 9, 2),
+    ("tile ends inside a block", 2, 130, 70, 30, 28),
+    ("long rows", 1, 16, 48, 6, 120),
+]
+
+
+@pytest.mark.parametrize("case", STRIDE2, ids=[c[0] for c in STRIDE2])
+def test_stride_2_data_gradient(case):
+    import torch
+    from gpu_util import Guarded, download, upload, workspace
+    name, N, C, K, H, W = case
+    spec = synth.LayerSpec(name, N, C, K, H, W, stride=2)
+    t = synth.make_inputs(spec, "conv-dx2", tensors=("W", "dY"))
+    d = B.desc_from_spec(spec)
+    assert "four parity classes" in B.cac_describe_plan(d, B.OP_BWD_DATA), "the case is here for that kernel"
+    Wt, dY = upload(t["W"], spec.dtype), upload(t["dY"], spec.dtype)
+    dX = Guarded((N, C, H, W), torch.bfloat16)
+    B.conv_bwd_data(d, Wt, dY, dX.t, workspace(d, B.OP_BWD_DATA))
+    torch.cuda.synchronize()
+    dX.check("dX")
+    want = oracle.conv_dx(oracle.ConvGeom(N, C, K, H, W, 3, 3, 2, 2, 1, 1), t["W"].astype(np.float64), t["dY"].astype(np.float64))
+    got = download(dX.t)
+    for n in range(N):
+        for a0 in range(min(2, H)):
+            for b0 in range(2):     # every class of every image by itself
+                w = want[n, :, a0::2, b0::2]
+                assert np.linalg.norm(got[n, :, a0::2, b0::2] - w) <= TOL * np.linalg.norm(w), (name, n, a0, b0)
