@@ -31,10 +31,17 @@ struct GatherParams {
     uint32_t m_wc, m_ppi, m_pwd, m_kbs, m_img; // division magics of Wc, Hc*Wc, PWd, kbs, PH*PWd
     uint32_t m_gx, m_ph;                       // ... of the 8-pixel groups of an input row and of PH (in-place copy)
     // conv_tile.hip
-    int tile;           // the launch runs there (2: in conv_dx2.hip)
+    int tile;           // the launch runs there (2: in conv_dx2.hip, 3: in conv_pw.hip)
     int gw, GX;         // pixels of a staged item; items of an input row
     int store_px;       // pixels per store of the epilogue: 8, 4, 2 or 1
     int buf_bytes, lds_bytes; // a staging buffer; all of the workgroup's LDS
+    // conv_pw.hip
+    bf16_t *Z;          // the input's 2 x 2 mean record, written on the way, or null
+    int pw_pool;        // the launch can form that record
+    int tile_px;        // pixels of a tile
+    int w_direct;       // the filter fragments are read from W itself ([M][KCin])
+    uint32_t w_kstep, w_bytes; // bytes from one 16-channel step of the filter to the next; of all of it
+    uint32_t m_w2;      // division magic of two image rows
     uint32_t wofs[9], toff[9]; // per tap: byte offset of its filter fragments; LDS byte offset within the patch
 };
 
@@ -46,6 +53,10 @@ int describe_tile(const GatherParams &p, int variant, char *buf, size_t len);
 bool shape_dx2(const Geom &g, GatherParams &p, int *variant);
 hipError_t launch_dx2(const GatherParams &p, int variant, hipStream_t st);
 int describe_dx2(const GatherParams &p, int variant, char *buf, size_t len);
+// conv_pw.hip: 1 x 1 stride-1 layers
+bool shape_pw(GatherParams &p, bool pool, int *variant);
+hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st);
+int describe_pw(const GatherParams &p, int variant, char *buf, size_t len);
 
 size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
 // Text description of the launch shape(s) chosen; false when the geometry is not covered.

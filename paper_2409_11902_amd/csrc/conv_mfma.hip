@@ -1035,7 +1035,7 @@ bool shape_gather(GatherParams &p, int *variant)
 
 hipError_t run_gather(const GatherParams &p, int variant, hipStream_t st)
 {
-    if (p.tile) return p.tile == 2 ? launch_dx2(p, variant, st) : launch_tile(p, variant, st);
+    if (p.tile) return p.tile == 3 ? launch_pw(p, variant, st) : p.tile == 2 ? launch_dx2(p, variant, st) : launch_tile(p, variant, st);
     switch (variant) {
     case 0: return launch_gather<2, 1, 4>(p, st);
     case 1: return launch_gather<2, 2, 2>(p, st);
@@ -1090,6 +1090,13 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
         p.Hin = g.H / 2; p.Win = g.W / 2; p.is = 1;
     }
     p.KCin = g.C;
+    if (use_tile() && shape_pw(p, !g.pmax && g.kh == 2 && g.kw == 2, variant)) {
+        p.tile = 3;
+        p.w_direct = p.w_direct && g.C % 16 == 0; // (rows of W are whole fragments)
+        p.w_kstep = p.w_direct ? 32u : (uint32_t)p.Mp * 32u;
+        p.w_bytes = p.w_direct ? (uint32_t)g.K * g.C * 2u : (uint32_t)p.Mp * p.KCp * 2u;
+        return true;
+    }
     if (use_tile() && shape_tile(p, variant)) { p.tile = 1; return true; }
     return shape_gather(p, variant);
 }
@@ -1129,7 +1136,13 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 }
             if (p.ntaps == 0) { *empty_class = true; continue; }
             p.KCin = g.K;
-            if (use_tile() && shape_tile(p, &variant[*ncls])) {
+            if (use_tile() && shape_pw(p, false, &variant[*ncls])) {
+                p.tile = 3;
+                p.w_direct = 0;
+                p.w_kstep = (uint32_t)p.Mp * 32u;
+                p.w_bytes = (uint32_t)p.Mp * p.KCp * 2u;
+                base.tile = 3;
+            } else if (use_tile() && shape_tile(p, &variant[*ncls])) {
                 p.tile = 1;
                 base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
                 base.tile = 1;
@@ -1153,6 +1166,7 @@ bool dx_reads_in_place(const Geom &g, const GatherParams (&cls)[4], int ncls)
 
 int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
 {
+    if (p.tile == 3) return describe_pw(p, variant, buf, len);
     if (p.tile) return p.tile == 2 ? describe_dx2(p, variant, buf, len) : describe_tile(p, variant, buf, len);
     static const int shape[6][3] = {{2, 1, 4}, {2, 2, 2}, {2, 4, 1}, {1, 1, 4}, {1, 2, 2}, {1, 4, 1}}; // NI, WM, WN
     const int *v = shape[variant];
@@ -1237,6 +1251,19 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     // same conditions as dY in the data gradient (no channels-last copy, only the filter repack).
     const bool direct = p.tile || (!p.decim && g.W % 2 == 0 && (long)g.N * g.C * g.H * g.W >= 8L * g.R * g.S * g.K * g.C &&
                         p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512);
+    if (p.tile == 3) {
+        // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
+        if (!p.w_direct)
+            *err = launch_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, (const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W, st);
+        if (*err != hipSuccess) return true;
+        p.in = (const bf16_t *)X;
+        p.wt = p.w_direct ? (const bf16_t *)W : wt;
+        p.bias = (const bf16_t *)b; p.out = (bf16_t *)Y;
+        p.Z = p.pw_pool ? (bf16_t *)Z : nullptr;
+        *pooled = p.Z != nullptr;
+        *err = run_gather(p, variant, st);
+        return true;
+    }
     const bool fuse = fuse0; // (with `direct` the repack launch forms Z without writing the channels-last copy)
     *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp,
                          (const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr,

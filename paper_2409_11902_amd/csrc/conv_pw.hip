@@ -1,0 +1,349 @@
+// 1 x 1 stride-1 convolution, forward and data gradient, as a GEMM on the tensors as they lie:
+//   out[n][m][px] = bias[m] + sum_k W'[m][k] * in[n][k][px],   px over the whole plane (rows do not matter).
+//
+// These layers are bound by HBM (256 -> 64 at 56 x 56, batch 64: 129 MB for 6.6 GFLOP).  The gather launches of
+// conv_mfma.hip write and read a channels-last copy of the input first (forward with a 2 x 2 pooled record: 37 us
+// for the copy alone on that layer) and have two MFMA steps per 32 channels to hide anything behind.  Here a
+// workgroup of four waves owns 64 or 128 output channels x 256 pixels and goes through the input in stages of 64
+// channels:
+//   - a thread moves one item of 8 channels x 8 pixels per stage -- eight loads, the next stage's always in flight
+//     while this one is multiplied --, transposes it in registers and writes it to one of two LDS buffers as
+//     [pixel][channel]; the lanes of a wave lie along the pixels (along the channels, every lane is a cache access of
+//     its own: 57 instead of 41 us on the layer above, the vector cache busy throughout);
+//   - the filter fragments of a stage are all requested before the next stage's input, so that waiting for them
+//     does not mean waiting for HBM (loads return in order);
+//   - with a 2 x 2 mean record over rows of a multiple of 4 pixels an item is 8 channels x 2 rows x 4 pixels, and
+//     the thread pools what it holds: Z costs its own bytes only (same sum order and rounding as the stand-alone
+//     kernel, bit-identical);
+//   - the result leaves through LDS as in conv_tile.hip.
+// Per call (bench layers, batch 64, inputs resident): 256 -> 64 at 56 x 56 forward 74 -> 39 us, 64 -> 256 61 -> 39,
+// 512 -> 2048 at 7 x 7 44 -> 29, data gradients 53 -> 34, 49 -> 29, 47 -> 43.  Two stages of input in flight (for 64
+// channels per workgroup, which have the registers) measured 2-10 % slower: the stages are not bound by latency.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <mutex>
+#include <type_traits>
+
+#include "common.h"
+#include "conv_mfma.h"
+#include "tile_stage.h"
+
+namespace cac {
+
+namespace {
+
+using namespace tile;
+
+constexpr int KC = 64, KCS = KC + 8, KSTEPS = KC / 16, OCT = KC / 8;
+constexpr int kPT = 256, kGroups = kPT / 8; // pixels of a tile; items along the pixels
+constexpr int kEpRow = 64 * 2 + 16, kEpWave = 32 * kEpRow;
+constexpr int kBuf = kPT * KCS * 2 + kPT / 4 * 16; // (with the largest padding, see pad_of)
+
+// FUSE: items of 2 rows x 4 pixels, Z written on the way.  GW: pixels of an item otherwise: 8, or 7 for planes of odd
+// size (read from the dword below an odd start).  EPI: pixels per store.
+template <int NI, int WM, int WN, bool FUSE, int GW, int EPI>
+__global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
+{
+    constexpr int MI = 2;
+    static_assert(WN * NI * 32 == kPT && WM * WN == 4, "");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int tau = blockIdx.x % p.tiles_per_img, n_base = blockIdx.x / p.tiles_per_img * p.IPT;
+    const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb;
+    const int pix0 = p.IPT > 1 ? 0 : tau * p.tile_px;
+    const int m0 = (blockIdx.y * WM + wm) * 64;
+
+    // ---- this thread's item: 8 channels, pixels from px0 on of image n_base + ig
+    // (lanes along the pixels: a wave's load then covers whole lines of one or two channel rows; with the lanes along the
+    // channels every lane was a cache access of its own, 64 to the load, and the vector cache bound the kernel)
+    const int gidx = tid % kGroups, oct = tid / kGroups;
+    // LDS: 16 bytes more after every 8 (4) pixels, so that the items of neighbouring lanes start in different banks
+    auto pad_of = [](int px) { return FUSE ? (px >> 2) * 16 : GW == 8 ? (px >> 3) * 16 : 0; };
+    int ig = 0, px0, lpx; // first pixel in the plane; in LDS
+    bool item = true;
+    if constexpr (FUSE) {
+        const int pair = fdiv(gidx, p.m_gx), c4 = gidx - pair * p.GX;
+        lpx = pair * 2 * p.Win + c4 * 4;
+        px0 = pix0 + lpx;
+        item = lpx < p.tile_px && px0 < ppi;
+    } else {
+        ig = p.IPT > 1 ? fdiv(gidx, p.m_gx) : 0;
+        const int gx = gidx - ig * p.GX;
+        px0 = pix0 + gx * GW;
+        lpx = gidx * GW;
+        item = ig < p.IPT && px0 < ppi;
+    }
+    item = item && n_base + ig < p.N;
+    const uint32_t e0 = item ? (uint32_t)((n_base + ig) * K + oct * 8) * ppi + px0 : kNoElem;
+    const uint32_t l0 = lds0 + (uint32_t)(lpx * KCS + oct * 8) * 2u + pad_of(lpx);
+    const rsrc_t rs_in = make_rsrc(p.in, (uint32_t)p.N * K * ppi * 2u);
+    typedef std::conditional_t<FUSE, u32x2, u32x4> item_t;
+    constexpr int ROWS = FUSE ? 2 : 1;
+    item_t r[8][ROWS];
+    auto fetch = [&](int s) {
+        uint32_t e = e0 + (uint32_t)(s * KC) * ppi;
+        opaque(e);
+        const int nvalid = K - (s * KC + oct * 8); // channels that exist (none past the last stage)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t ei = i < nvalid ? e : kNoElem;
+            if constexpr (FUSE) {
+                r[i][0] = __builtin_amdgcn_raw_buffer_load_b64(rs_in, ei * 2u, 0, 0);
+                r[i][1] = __builtin_amdgcn_raw_buffer_load_b64(rs_in, (ei + p.Win) * 2u, 0, 0);
+            } else {
+                r[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, (GW == 7 ? ei & ~1u : ei) * 2u, 0, 0);
+            }
+            e += ppi;
+        }
+    };
+    // the item of stage s: Z, then to LDS
+    const rsrc_t rs_z = make_rsrc(p.Z, (uint32_t)p.N * K * (ppi / 4) * 2u);
+    auto put = [&](int s, uint32_t buf) {
+        if (!item) return; // (the pixels of items that do not exist are never stored, whatever LDS holds for them)
+        if constexpr (FUSE) {
+            if (blockIdx.y == 0) {
+                const int nvalid = K - (s * KC + oct * 8);
+                // plane * (ppi / 4) + pooled row * Wp + pooled column; px0 = 2 * pooled row * W + 2 * pooled column
+                const int prow = fdiv(px0, p.m_w2), pcol = (px0 - prow * 2 * p.Win) >> 1;
+                uint32_t z = ((uint32_t)(n_base * K + s * KC + oct * 8) * (ppi / 4) + prow * (p.Win / 2) + pcol) * 2u;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    uint32_t h[2];
+#pragma unroll
+                    for (int jj = 0; jj < 2; ++jj) {
+                        const uint32_t t0 = r[i][0][jj], t1 = r[i][1][jj];
+                        float sum = 0.f;
+                        sum += __uint_as_float(t0 << 16);
+                        sum += __uint_as_float(t0 & 0xffff0000u);
+                        sum += __uint_as_float(t1 << 16);
+                        sum += __uint_as_float(t1 & 0xffff0000u);
+                        h[jj] = f32_to_bf16(sum * 0.25f);
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b32(h[0] | (h[1] << 16), rs_z, i < nvalid ? z : kNoLoad, 0, 0);
+                    z += (uint32_t)(ppi / 4) * 2u;
+                }
+            }
+        }
+        if constexpr (GW == 7) {
+            const uint32_t par = e0 + (uint32_t)(s * KC) * ppi;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t sh = ((par + i * ppi) & 1u) * 16u;
+                auto &v = r[i][0];
+#pragma unroll
+                for (int k = 0; k + 1 < (int)(sizeof(item_t) / 4); ++k) v[k] = __builtin_amdgcn_alignbit(v[k + 1], v[k], sh);
+                v[sizeof(item_t) / 4 - 1] >>= sh;
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < ROWS; ++a)
+#pragma unroll
+            for (int px = 0; px < (FUSE ? 4 : GW); ++px) {
+                u32x4 v; // pixel px of the 8 channels
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t lo = r[2 * k][a][px / 2], hi = r[2 * k + 1][a][px / 2];
+                    v[k] = (px & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                }
+                *(lds_u32x4_ptr)(uintptr_t)(l0 + buf + (a ? p.Win * (KCS * 2) + pad_of(p.Win) : 0) + px * (KCS * 2)) = v;
+            }
+    };
+
+    // ---- this lane's pixels
+    uint32_t pbase[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        const int idx = (wn * NI + ni) * 32 + l32;
+        pbase[ni] = lds0 + 16u * half + (uint32_t)(idx * KCS * 2 + pad_of(idx));
+    }
+    // ---- filter fragments: offset of the lane, of a 16-channel step, of a block of 32 output channels
+    const rsrc_t rs_w = make_rsrc(p.wt, p.w_bytes);
+    const uint32_t wlane = p.w_direct ? (m0 + l32 < p.M ? (uint32_t)((m0 + l32) * K + 8 * half) * 2u : kNoLoad)
+                                      : (m0 < p.Mp ? (uint32_t)(m0 >> 5) * kFrag + lane * 16u : kNoLoad);
+    const uint32_t wlane1 = p.w_direct ? (m0 + 32 + l32 < p.M ? (uint32_t)((m0 + 32 + l32) * K + 8 * half) * 2u : kNoLoad)
+                                       : (m0 < p.Mp ? (uint32_t)((m0 >> 5) + 1) * kFrag + lane * 16u : kNoLoad);
+    const int ksteps_all = p.KCp / 16;
+
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[mi][ni][j] = 0.f;
+    u32x4 w[KSTEPS][MI];
+    auto fetch_w = [&](int s, int kk) {
+        // (16-channel steps past the last one: zeros)
+        const int step = s * KSTEPS + kk;
+        const uint32_t so = (uint32_t)min(step, ksteps_all - 1) * p.w_kstep;
+        w[kk][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, step < ksteps_all ? wlane : kNoLoad, so, 0);
+        w[kk][1] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, step < ksteps_all ? wlane1 : kNoLoad, so, 0);
+    };
+    fetch(0);
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) fetch_w(0, kk);
+    put(0, 0);
+    fetch(1);
+    __syncthreads();
+    for (int s = 0; s < nkb; ++s) {
+        const uint32_t buf = (s & 1) ? kBuf : 0u, nbuf = kBuf - buf;
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                union { u32x4 u; bf16x8 v; } a0, a1, b;
+                b.u = lds16(pbase[ni] + buf + 32 * kk);
+                a0.u = w[kk][0];
+                a1.u = w[kk][1];
+                acc[0][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b.v, a0.v, acc[0][ni], 0, 0, 0);
+                acc[1][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b.v, a1.v, acc[1][ni], 0, 0, 0);
+            }
+            fetch_w(s + 1, kk); // (behind the input of stage s + 1, ahead of that of stage s + 2)
+        }
+        if (s + 1 < nkb) {
+            put(s + 1, nbuf);
+            fetch(s + 2); // (past the end: nothing is loaded)
+        }
+        __syncthreads();
+    }
+    // ---- epilogue: bias, bfloat16; two pixel blocks x 32 channels at a time through LDS as [channel][pixel] rows, every
+    // wave in a part of its own
+    const uint32_t plane_out = (uint32_t)ppi;
+    const rsrc_t rs_out = make_rsrc(p.out, (uint32_t)p.N * p.M * plane_out * 2u);
+    const uint32_t ep = lds0 + wave * kEpWave;
+    uint32_t el = lane;
+    opaque(el);
+    const uint32_t eh = el >> 5, e32 = el & 31;
+    float bias[MI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+        const int m = m0 + mi * 32 + e32;
+        bias[mi] = (p.bias && m < p.M) ? bf16_to_f32(p.bias[m]) : 0.f;
+    }
+    constexpr int LPR = 64 / EPI, RPI = 64 / LPR; // lanes of a row; rows per pass over the lanes
+#pragma unroll
+    for (int pass = 0; pass < NI / 2; ++pass) {
+        const int seg = el % LPR, idx = (wn * NI + pass * 2) * 32 + seg * EPI;
+        int g = 0, px = pix0 + idx;
+        if (p.IPT > 1) { // (an image's pixels in LDS are whole items)
+            g = fdiv(idx, p.m_ppi);
+            px = idx - g * (p.GX * GW);
+        }
+        const int n = n_base + g;
+        const bool px_ok = (px < ppi) & (g < p.IPT) & (n < p.N) & (p.IPT > 1 || idx < p.tile_px);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                const f32x16 &a = acc[mi][pass * 2 + nb];
+                const float bb = bias[mi];
+#pragma unroll
+                for (int jq = 0; jq < 4; ++jq)
+                    *(lds_u32x2_ptr)(uintptr_t)(ep + e32 * kEpRow + (nb * 32 + 8 * jq + 4 * eh) * 2) =
+                        u32x2{f32x2_to_bf16x2(a[4 * jq] + bb, a[4 * jq + 1] + bb), f32x2_to_bf16x2(a[4 * jq + 2] + bb, a[4 * jq + 3] + bb)};
+            }
+            // (the wave reads what it wrote itself: LDS serves a wave's requests in order)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int it = 0; it < 32 / RPI; ++it) {
+                const int row = it * RPI + el / LPR, m = m0 + mi * 32 + row;
+                const uint32_t off = (px_ok & (m < p.M)) ? ((uint32_t)(n * p.M + m) * plane_out + px) * 2u : kNoLoad;
+                const uint32_t src = ep + row * kEpRow + seg * (EPI * 2);
+                if constexpr (EPI == 8) __builtin_amdgcn_raw_buffer_store_b128(lds16(src), rs_out, off, 0, 0);
+                else if constexpr (EPI == 4) __builtin_amdgcn_raw_buffer_store_b64(*(lds_u32x2_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+                else if constexpr (EPI == 2) __builtin_amdgcn_raw_buffer_store_b32(*(lds_u32_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b16(*(lds_u16_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+}
+
+template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+{
+    auto kern = conv_pw_kernel<NI, WM, WN, FUSE, GW, EPI>;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
+    if (attr_err != hipSuccess) return attr_err;
+    const dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 64 + WM - 1) / WM);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 2 * kBuf, st, p);
+    return hipGetLastError();
+}
+template <int NI, int WM, int WN> hipError_t launch_shape(const GatherParams &p, hipStream_t st)
+{
+    if (p.Z) return launch_fixed<NI, WM, WN, true, 8, 8>(p, st); // (rows of a multiple of 4, an even number of them)
+    if (p.gw == 7) return launch_fixed<NI, WM, WN, false, 7, 1>(p, st);
+    return p.store_px == 8 ? launch_fixed<NI, WM, WN, false, 8, 8>(p, st) : p.store_px == 4 ? launch_fixed<NI, WM, WN, false, 8, 4>(p, st)
+                                                                                  : launch_fixed<NI, WM, WN, false, 8, 2>(p, st);
+}
+struct Shape { int ni, wm, wn; hipError_t (*launch)(const GatherParams &, hipStream_t); };
+const Shape kShapes[] = {{2, 1, 4, launch_shape<2, 1, 4>}, {4, 2, 2, launch_shape<4, 2, 2>}};
+
+} // namespace
+
+// Plans a 1 x 1 stride-1 launch (p: N, M, Mp, KCin, Hin, Win, Hc, Wc filled in); false when it is not its own.
+// pool: the 2 x 2 mean record of the input is wanted (p.pw_pool tells whether the launch forms it).
+bool shape_pw(GatherParams &p, bool pool, int *variant)
+{
+    if (p.ntaps != 1 || p.os != 1 || p.is != 1 || p.decim || p.dh[0] || p.dw[0] || p.Hin != p.Hc || p.Win != p.Wc) return false;
+    GatherParams q = p;
+    const int ppi = p.Hc * p.Wc;
+    q.KCp = (p.KCin + 15) / 16 * 16;
+    q.nkb = q.kbs = (p.KCin + KC - 1) / KC;
+    q.ksplit = 1; q.gpw = 1; q.part = nullptr; q.T = 1;
+    q.gw = ppi % 2 ? 7 : 8;
+    q.store_px = ppi % 8 == 0 ? 8 : ppi % 4 == 0 ? 4 : ppi % 2 == 0 ? 2 : 1;
+    q.pw_pool = pool && p.Win % 4 == 0 && p.Hin % 2 == 0 && p.Win / 4 <= kGroups && ppi >= kPT / 2 && 2L * ppi * p.Win < 1L << 32;
+    if (q.pw_pool) {
+        q.GX = p.Win / 4;
+        q.IPT = 1;
+        q.tile_px = min(kGroups / q.GX, p.Hin / 2) * 2 * p.Win;
+    } else {
+        const int gi = (ppi + q.gw - 1) / q.gw; // items along a plane
+        q.IPT = 2 * gi <= kGroups ? min(kGroups / gi, p.N) : 1;
+        q.GX = gi;
+        q.tile_px = q.IPT > 1 ? ppi : kGroups * q.gw;
+    }
+    q.tiles_per_img = q.IPT > 1 ? 1 : (ppi + q.tile_px - 1) / q.tile_px;
+    q.ngrp = (p.N + q.IPT - 1) / q.IPT;
+    q.m_gx = magic_of(q.GX); q.m_ppi = magic_of(q.GX * q.gw); q.m_w2 = magic_of(2 * p.Win);
+    const long px_tiles = (long)q.tiles_per_img * q.ngrp;
+    if (px_tiles > 0x7fffffffL) return false;
+    // 128 output channels per workgroup where that still gives every compute unit a workgroup: half the input traffic
+    // (64 -> 256 at 56 x 56, batch 64: 39 against 50 us; 256 -> 1024 at 14 x 14 backwards, 128 workgroups: 29 against 23).
+    int v = q.Mp > 64 && px_tiles * ((q.Mp + 127) / 128) >= 256;
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_PW_SHAPE")) v = atoi(f);
+#endif
+    const long wgs = px_tiles * ((q.Mp / 64 + kShapes[v].wm - 1) / kShapes[v].wm);
+    // A handful of workgroups with a long sum each: the launches of conv_mfma.hip share out the channels (512 -> 128 at
+    // 28 x 28, batch 4, 32 workgroups of 8 stages: 18.8 against 20.1 us; 2048 -> 512 at 7 x 7, batch 8: 36 against 42).
+    if (wgs < 64 && q.nkb >= 8) return false;
+    // Fragments from W itself touch 32 lines each, repacked ones 8, but save the repack launch: faster on small inputs
+    // (256 -> 64 at 56 x 56, batch 2: 12.2 against 14.2 us) and while a workgroup of 128 channels has few stages
+    // (512 -> 128 at 28 x 28, 2048 of them: 28.6 against 29.9 us; 384 -> 359 at 9 x 33, batch 139, 5000: 65 against 59).
+    q.w_direct = v == 1 ? wgs * q.nkb <= 2560 : q.nkb <= 2 || (q.nkb <= 8 && wgs * q.nkb <= 256);
+    *variant = v;
+    p = q;
+    return true;
+}
+
+hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st) { return kShapes[variant].launch(p, st); }
+
+int describe_pw(const GatherParams &p, int variant, char *buf, size_t len)
+{
+    const Shape &v = kShapes[variant];
+    return snprintf(buf, len, "pointwise tile=%dch x %dpx ch/pass=%d img/tile=%d grid=%dx%dx1 lds=%dB%s, input read in place", 64 * v.wm, p.tile_px, KC, p.IPT,
+                    p.tiles_per_img * p.ngrp, (p.Mp / 64 + v.wm - 1) / v.wm, 2 * kBuf, p.pw_pool ? ", pooled on the way" : "");
+}
+
+} // namespace cac
