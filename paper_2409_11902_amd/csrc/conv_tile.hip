@@ -20,6 +20,8 @@
 // 98 -> 71 us; 128 -> 128 at 28 x 28, batch 128, 51 -> 36 us; 64 -> 64 at 56 x 56, batch 64, 43 -> 28 us.
 // Eight steps of filter fragments in flight instead of three, or a whole stage fetched at once through 32
 // registers, measured the same or slower; 64 x 224 pixels per wave with 512 registers does not fit (spills).
+// 64 output channels x 512 pixels in stages of 16 channels (a patch of 32 leaves LDS for one workgroup only):
+// 64 -> 64 at 56 x 56, batch 128, data gradient 47 -> 40 us against 256 pixels in stages of 32.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -35,20 +37,20 @@ namespace cac {
 namespace {
 
 using namespace tile;
-constexpr int KC = 32;       // channels of a stage
-constexpr int KCS = KC + 8;  // LDS elements per patch pixel: 80 bytes, an odd number of 16-byte units
-constexpr int TAPS = 9, STEPS = TAPS * (KC / 16);
+constexpr int TAPS = 9;
 
 constexpr int kEpRow = 64 * 2 + 16;     // LDS bytes of an epilogue row: 64 pixels of one channel
 constexpr int kEpWave = 32 * kEpRow;    // 32 channels per pass
 
 // ITEMS, GW: see PatchStage; D: steps of filter fragments in flight; EPI: pixels per store.
-template <int NI, int WM, int WN, int ITEMS, int GW, int D, int EPI>
+template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI>
 __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
 {
     constexpr int MI = 2;
     constexpr int PT = WN * NI * 32;
-    static_assert(WM * WN == 4 && STEPS % D == 0, "");
+    // A stage of KC = 32 channels is 18 steps and comes in two halves of 4 channels per item; one of 16 is 9 steps in one.
+    constexpr int KSTEPS = KC / 16, STEPS = TAPS * KSTEPS, KCS = KC + 8, PARTS = KSTEPS;
+    static_assert(WM * WN == 4 && STEPS % D == 0 && (KC == 16 || KC == 32), "");
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const uint32_t buf_bytes = p.buf_bytes;
@@ -66,7 +68,7 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int hin0 = i0 * p.is + p.dhmin, win0 = p.dwmin;
     const int m0 = (blockIdx.y * WM + wm) * 64;
 
-    PatchStage<ITEMS, GW, KC> in;
+    PatchStage<ITEMS, GW, KC, 8 / PARTS> in;
     in.init(p, lds0, lds0 + 2 * buf_bytes, n_base, hin0);
 
     // ---- this lane's pixels
@@ -111,13 +113,13 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     for (int q = 0; q < D; ++q)
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
-            wr[q][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, p.wofs[q >> 1] + (q & 1) * kstep + mi * kFrag, 0);
+            wr[q][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, p.wofs[q / KSTEPS] + (q % KSTEPS) * kstep + mi * kFrag, 0);
 
     in.start(lds0, buf_bytes);
 
     for (int s = 0; s < nkb; ++s) {
         const uint32_t buf = (s & 1) ? buf_bytes : 0u, nbuf = buf_bytes - buf;
-        uint32_t so = (uint32_t)s * 2 * kstep; // this stage's filter fragments (of tap 0)
+        uint32_t so = (uint32_t)s * KSTEPS * kstep; // this stage's filter fragments (of tap 0)
         opaque_s(so);
         in.fetch(s + 1, 0); // (past the end: nothing is loaded)
         u32x4 bq[2][NL > 0 ? NL : 1];
@@ -128,7 +130,7 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
         for (int q = 0; q < STEPS; ++q) {
             if (q + 1 < STEPS) {
 #pragma unroll
-                for (int ni = 0; ni < NL; ++ni) bq[(q + 1) & 1][ni] = lds16(pbase[ni] + p.toff[(q + 1) >> 1] + 32 * ((q + 1) & 1));
+                for (int ni = 0; ni < NL; ++ni) bq[(q + 1) & 1][ni] = lds16(pbase[ni] + p.toff[(q + 1) / KSTEPS] + 32 * ((q + 1) % KSTEPS));
             }
 #pragma unroll
             for (int ni = 0; ni < NL; ++ni)
@@ -142,18 +144,18 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
             // refill the ring with the fragments of step q + D (past the last stage: the next tap's, never used)
             if constexpr (NL > 0) {
                 const int q2 = q + D < STEPS ? q + D : q + D - STEPS;
-                const uint32_t so2 = p.wofs[q2 >> 1] + so + ((q2 & 1) + (q + D < STEPS ? 0 : 2)) * kstep;
+                const uint32_t so2 = p.wofs[q2 / KSTEPS] + so + (q2 % KSTEPS + (q + D < STEPS ? 0 : KSTEPS)) * kstep;
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi) wr[q % D][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, so2 + mi * kFrag, 0);
             }
-            constexpr int W = STEPS / 2; // steps of a half: loads at the first, the pixels to LDS at the last four
+            constexpr int W = STEPS / PARTS; // steps of a part: loads at the first, the pixels to LDS at the last four
             const int h = q / W, qq = q % W;
             if (qq == W - 5) in.align_rows();
             if (qq >= W - 4) {
                 in.put_px(nbuf, h, 2 * (qq - (W - 4)));
                 in.put_px(nbuf, h, 2 * (qq - (W - 4)) + 1);
             }
-            if (qq == W - 1 && h == 0) in.fetch(s + 1, 1);
+            if (qq == W - 1 && h + 1 < PARTS) in.fetch(s + 1, h + 1);
             __builtin_amdgcn_sched_barrier(0);
         }
         // on to the other buffer
@@ -231,9 +233,9 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     else run_wave(std::integral_constant<int, 0>{});
 }
 
-template <int NI, int WM, int WN, int ITEMS, int GW, int D, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
 {
-    auto kern = conv_tile_kernel<NI, WM, WN, ITEMS, GW, D, EPI>;
+    auto kern = conv_tile_kernel<NI, WM, WN, KC, ITEMS, GW, D, EPI>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
@@ -242,25 +244,30 @@ template <int NI, int WM, int WN, int ITEMS, int GW, int D, int EPI> hipError_t 
     hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, p);
     return hipGetLastError();
 }
-template <int NI, int WM, int WN, int D, int EPI> hipError_t launch_items(const GatherParams &p, hipStream_t st)
+template <int NI, int WM, int WN, int KC, int D, int EPI> hipError_t launch_items(const GatherParams &p, hipStream_t st)
 {
-    const bool one = p.IPT * p.PH * p.GX * 4 <= 256;
-    if (p.gw == 8) return one ? launch_fixed<NI, WM, WN, 1, 8, D, EPI>(p, st) : launch_fixed<NI, WM, WN, 2, 8, D, EPI>(p, st);
-    return one ? launch_fixed<NI, WM, WN, 1, 7, D, EPI>(p, st) : launch_fixed<NI, WM, WN, 2, 7, D, EPI>(p, st);
+    const bool one = p.IPT * p.PH * p.GX * (KC / 8) <= 256;
+    if (p.gw == 8) {
+        if constexpr (KC == 16) return launch_fixed<NI, WM, WN, KC, 1, 8, D, EPI>(p, st); // (never planned with two items)
+        else return one ? launch_fixed<NI, WM, WN, KC, 1, 8, D, EPI>(p, st) : launch_fixed<NI, WM, WN, KC, 2, 8, D, EPI>(p, st);
+    }
+    if constexpr (KC == 16) return launch_fixed<NI, WM, WN, KC, 1, 7, D, EPI>(p, st);
+    else return one ? launch_fixed<NI, WM, WN, KC, 1, 7, D, EPI>(p, st) : launch_fixed<NI, WM, WN, KC, 2, 7, D, EPI>(p, st);
 }
-template <int NI, int WM, int WN, int D> hipError_t launch_shape(const GatherParams &p, hipStream_t st)
+template <int NI, int WM, int WN, int KC, int D> hipError_t launch_shape(const GatherParams &p, hipStream_t st)
 {
-    return p.store_px == 8 ? launch_items<NI, WM, WN, D, 8>(p, st) : p.store_px == 4 ? launch_items<NI, WM, WN, D, 4>(p, st)
-           : p.store_px == 2 ? launch_items<NI, WM, WN, D, 2>(p, st) : launch_items<NI, WM, WN, D, 1>(p, st);
+    return p.store_px == 8 ? launch_items<NI, WM, WN, KC, D, 8>(p, st) : p.store_px == 4 ? launch_items<NI, WM, WN, KC, D, 4>(p, st)
+           : p.store_px == 2 ? launch_items<NI, WM, WN, KC, D, 2>(p, st) : launch_items<NI, WM, WN, KC, D, 1>(p, st);
 }
 
-struct Shape { int ni, wm, wn; hipError_t (*launch)(const GatherParams &, hipStream_t); };
+struct Shape { int ni, wm, wn, kc; hipError_t (*launch)(const GatherParams &, hipStream_t); };
 const Shape kShapes[] = {
-    {4, 2, 2, launch_shape<4, 2, 2, 3>},
-    {4, 4, 1, launch_shape<4, 4, 1, 3>},
-    {2, 1, 4, launch_shape<2, 1, 4, 6>},
-    {2, 2, 2, launch_shape<2, 2, 2, 6>},
-    {2, 4, 1, launch_shape<2, 4, 1, 6>},
+    {4, 2, 2, 32, launch_shape<4, 2, 2, 32, 3>},
+    {4, 4, 1, 32, launch_shape<4, 4, 1, 32, 3>},
+    {2, 1, 4, 32, launch_shape<2, 1, 4, 32, 6>},
+    {2, 2, 2, 32, launch_shape<2, 2, 2, 32, 6>},
+    {2, 4, 1, 32, launch_shape<2, 4, 1, 32, 6>},
+    {4, 1, 4, 16, launch_shape<4, 1, 4, 16, 3>}, // 64 channels x 512 pixels: the patch of 32 channels would leave room for one workgroup
 };
 
 } // namespace
@@ -270,7 +277,6 @@ bool shape_tile(GatherParams &p, int *variant)
 {
     if (p.ntaps != TAPS || p.os != 1) return false;
     GatherParams b = p;
-    b.KCp = (p.KCin + KC - 1) / KC * KC;
     b.dhmin = b.dwmin = 1 << 30;
     int dhmax = -(1 << 30), dwmax = -(1 << 30);
     for (int t = 0; t < TAPS; ++t) {
@@ -280,32 +286,28 @@ bool shape_tile(GatherParams &p, int *variant)
     }
     const auto magic = magic_of;
     b.PWd = (p.Wc - 1) * p.is + (dwmax - b.dwmin) + 1;
-    b.nkb = b.kbs = b.KCp / KC;
     b.ksplit = 1; b.T = 1; b.part = nullptr;
     const int ppi = p.Hc * p.Wc;
-    b.m_wc = magic(p.Wc); b.m_ppi = magic(ppi); b.m_pwd = magic(b.PWd); b.m_kbs = magic(b.nkb);
+    b.m_wc = magic(p.Wc); b.m_ppi = magic(ppi); b.m_pwd = magic(b.PWd);
     b.gw = p.Win % 2 ? 7 : 8;
     b.GX = (p.Win + b.gw - 1) / b.gw;
     b.m_gx = magic(b.GX);
     b.store_px = ppi % 8 == 0 ? 8 : ppi % 4 == 0 ? 4 : ppi % 2 == 0 ? 2 : 1;
-    const uint32_t kblks = b.KCp / 16, mblks = b.Mp / 32;
-    for (int t = 0; t < TAPS; ++t) {
-        b.wofs[t] = (uint32_t)t * kblks * mblks * kFrag;
-        b.toff[t] = (uint32_t)((p.dh[t] - b.dhmin) * b.PWd + (p.dw[t] - b.dwmin)) * KCS * 2u;
-    }
     int f = -1, f_ipt = 0;
 #ifdef CAC_TUNING
     if (const char *force = getenv("CAC_TILE_SHAPE")) sscanf(force, "%d,%d", &f, &f_ipt);
 #endif
     GatherParams best{};
     double best_cost = 1e300;
-    long best_wgs = 0;
     for (int v = 0; v < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++v) {
         if (f >= 0 && v != f) continue;
         const Shape &sh = kShapes[v];
         if (sh.wm * 64 > b.Mp && sh.wm > 1) continue;
         GatherParams q = b;
-        const int pt = sh.wn * sh.ni * 32;
+        const int pt = sh.wn * sh.ni * 32, kcs = sh.kc + 8; // (LDS elements per patch pixel: an odd number of 16-byte units)
+        q.T = sh.kc;
+        q.KCp = (p.KCin + sh.kc - 1) / sh.kc * sh.kc;
+        q.nkb = q.kbs = q.KCp / sh.kc;
         q.IPT = 2 * ppi <= pt ? pt / ppi : 1;
         if (f_ipt) q.IPT = f_ipt;
         if (q.IPT > 1) {
@@ -316,16 +318,28 @@ bool shape_tile(GatherParams &p, int *variant)
             const int rows = min(q.Hc, (pt + q.Wc - 2) / q.Wc + 1);
             q.PH = (rows - 1) * q.is + (dhmax - q.dhmin) + 1;
         }
-        if (q.IPT * q.PH * q.GX * 4 > 512) continue;
+        const int items = q.IPT * q.PH * q.GX * (sh.kc / 8);
+        if (items > (sh.kc == 16 ? 256 : 512)) continue;
         q.patch_px = q.IPT * q.PH * q.PWd;
-        q.buf_bytes = max(q.patch_px * KCS * 2, 2 * kEpWave);
+        q.buf_bytes = max(q.patch_px * kcs * 2, 2 * kEpWave);
         q.lds_bytes = 2 * q.buf_bytes + kDumpBytes;
         if (q.lds_bytes > 160 * 1024) continue;
         q.m_ph = magic(q.PH);
+        for (int t = 0; t < TAPS; ++t) {
+            q.wofs[t] = (uint32_t)t * (q.KCp / 16) * (q.Mp / 32) * kFrag;
+            q.toff[t] = (uint32_t)((p.dh[t] - q.dhmin) * q.PWd + (p.dw[t] - q.dwmin)) * kcs * 2u;
+        }
         q.ngrp = (q.N + q.IPT - 1) / q.IPT;
         const int mtiles = (q.Mp / 64 + sh.wm - 1) / sh.wm;
         const long wgs = (long)q.tiles_per_img * q.ngrp * mtiles;
         q.gpw = 1;
+        // Few workgroups: the launches of conv_mfma.hip, which keep two stages of loads in flight and share out the
+        // channels of a tile, are the faster ones (512 -> 512 at 4 x 4, batch 128, 64 workgroups here: 28 against 38 us;
+        // 240 -> 272 at 12 x 12, batch 24, 144 workgroups: 2 us; 128 -> 128 at 16 x 16, batch 128, 256 workgroups: even).
+        // For rows of odd length they need an element-by-element repack, for planes that are no multiple of 4 pixels
+        // they store single elements, and lose from 64 workgroups on (512 -> 512 at 7 x 7, batch 64, 104 workgroups:
+        // 43.2 against 41.5 us; 72 -> 100 at 27 x 30, batch 24, 192 workgroups: 25 against 18 us).
+        if (f < 0 && wgs < (p.Win % 2 || ppi % 4 ? 64 : 160)) continue;
         // Cycles of a compute unit.  A stage is 18 steps of 2 x NI MFMAs of 32 cycles, of which a pair of resident
         // workgroups keeps the matrix pipe busy for the fractions measured (a single one for less); a wave's last
         // tile may have fewer live blocks; each pair pays a start and an epilogue.
@@ -334,23 +348,18 @@ bool shape_tile(GatherParams &p, int *variant)
         live /= (double)q.tiles_per_img * sh.ni;
         const double k = (double)((wgs + 255) / 256);
         const bool pairs = k > 1 && q.lds_bytes <= 80 * 1024;
-        const double eff = sh.ni == 4 ? (pairs ? 0.78 : 0.55) : (pairs ? (sh.wm == 4 ? 0.50 : 0.52) : 0.45);
-        const double items = q.IPT * q.PH * q.GX * 4 > 256 ? 1.1 : 1.0;
-        const double cost = k * q.nkb * STEPS * 2.0 * sh.ni * 32 * live * items / eff + (pairs ? (k + 1) / 2 : k) * 6000.0;
+        // (stages of 16 channels: twice the barriers; in rows of odd length the shifts of a whole item come at once)
+        const double eff = sh.ni == 4 ? (pairs ? (sh.kc == 16 ? 0.70 : 0.78) : 0.55) / (sh.kc == 16 && q.gw == 7 ? 1.35 : 1.0)
+                                      : (pairs ? (sh.wm == 4 ? 0.50 : 0.52) : 0.45);
+        const double twice = items > 256 ? 1.1 : 1.0;
+        const double cost = k * q.nkb * (TAPS * (sh.kc / 16)) * 2.0 * sh.ni * 32 * live * twice / eff + (pairs ? (k + 1) / 2 : k) * 6000.0;
         if (cost < best_cost) {
             best_cost = cost;
             best = q;
-            best_wgs = wgs;
             *variant = v;
         }
     }
-    // Few workgroups: the launches of conv_mfma.hip, which keep two stages of loads in flight and share out the
-    // channels of a tile, are the faster ones (512 -> 512 at 4 x 4, batch 128, 64 workgroups here: 28 against 38 us;
-    // 240 -> 272 at 12 x 12, batch 24, 144 workgroups: 2 us; 128 -> 128 at 16 x 16, batch 128, 256 workgroups: even).
-    // For rows of odd length they need an element-by-element repack, for planes that are no multiple of 4 pixels
-    // they store single elements, and lose from 64 workgroups on (512 -> 512 at 7 x 7, batch 64, 104 workgroups:
-    // 43.2 against 41.5 us; 72 -> 100 at 27 x 30, batch 24, 192 workgroups: 25 against 18 us).
-    if (best_cost > 1e299 || (f < 0 && best_wgs < (p.Win % 2 || ppi % 4 ? 64 : 160))) return false;
+    if (best_cost > 1e299) return false;
     p = best;
     return true;
 }

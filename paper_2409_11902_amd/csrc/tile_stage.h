@@ -26,16 +26,16 @@ __device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(
 __device__ __forceinline__ void opaque(uint32_t &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void opaque_s(uint32_t &x) { asm volatile("" : "+s"(x)); }
 
-constexpr int kDumpBytes = 256 * 8; // past the buffers: 8 bytes for every lane of a workgroup
+constexpr int kDumpBytes = 256 * 16; // past the buffers: 16 bytes for every lane of a workgroup
 
 // A stage is KC channels of the patch, IPT images of PH x PWd pixels, in LDS as [pixel][KC + 8] elements.  An item is 8
 // channels x GW pixels of one patch row: GW = 8, or 7 for rows of odd length (an item that starts on an odd element is
-// read from the dword below, whose eight elements hold seven of the item).  A thread moves ITEMS items of a stage in two
-// halves of 4 channels, one after the other through the same registers.  Pixels outside the image are never written:
+// read from the dword below, whose eight elements hold seven of the item).  A thread moves ITEMS items of a stage in
+// parts of CB channels, one after the other through the same registers.  Pixels outside the image are never written:
 // both buffers start as zeros.
-template <int ITEMS, int GW, int KC> struct PatchStage {
+template <int ITEMS, int GW, int KC, int CB = 4> struct PatchStage {
     static constexpr int KCS = KC + 8;      // an odd number of 16-byte units
-    static constexpr int CB = 4, OCT = KC / 8;
+    static constexpr int OCT = KC / 8;
     uint32_t e0[ITEMS], l0[ITEMS], m8[ITEMS];
     u32x4 r[ITEMS][CB];
     uint32_t par, plane, dump;
@@ -50,7 +50,7 @@ template <int ITEMS, int GW, int KC> struct PatchStage {
         KCin = p.KCin;
         plane = (uint32_t)p.Hin * p.Win;
         par = 0;
-        dump = dump_base + tid * 8;
+        dump = dump_base + tid * 16;
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             const int it = tid + 256 * q;
@@ -71,7 +71,7 @@ template <int ITEMS, int GW, int KC> struct PatchStage {
         }
         rs_in = make_rsrc(p.in, (uint32_t)p.N * KCin * plane * 2u);
     }
-    // loads of half h of stage s (past the last stage: nothing)
+    // loads of part h of stage s (past the last stage: nothing)
     __device__ __forceinline__ void fetch(int s, int h)
     {
         const uint32_t sbase = (uint32_t)(n_base * KCin + s * KC + CB * h) * plane;
@@ -107,7 +107,7 @@ template <int ITEMS, int GW, int KC> struct PatchStage {
                 }
         }
     }
-    // pixel px of the items, half h, to the buffer at offset buf
+    // pixel px of the items, part h, to the buffer at offset buf
     __device__ __forceinline__ void put_px(uint32_t buf, int h, int px)
     {
         if (px >= GW) return;
@@ -121,14 +121,15 @@ template <int ITEMS, int GW, int KC> struct PatchStage {
             }
             // (a pixel that is not wanted goes to a place of the lane's own past the buffers: no branch)
             const uint32_t a = (m8[q] & (1u << px)) ? l0[q] + buf + (px * (KCS * 2) + 2 * CB * h) : dump;
-            *(lds_u32x2_ptr)(uintptr_t)a = u32x2{v[0], v[1]};
+            if constexpr (CB == 8) *(lds_u32x4_ptr)(uintptr_t)a = u32x4{v[0], v[1], v[2], v[3]};
+            else *(lds_u32x2_ptr)(uintptr_t)a = u32x2{v[0], v[1]};
         }
     }
     // both buffers zero, the first stage in buffer 0
     __device__ __forceinline__ void start(uint32_t lds0, uint32_t buf_bytes)
     {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < 8 / CB; ++h) {
             fetch(0, h);
             if (h == 0) {
                 for (uint32_t i = threadIdx.x; i < 2 * buf_bytes / 16; i += 256) *(lds_u32x4_ptr)(uintptr_t)(lds0 + 16 * i) = u32x4{0, 0, 0, 0};

@@ -33,6 +33,8 @@ CASES = [
     ("stride 2, odd extents", 160, 20, 130, 27, 15, 2),
     ("channels past one block of 32", 80, 65, 33, 18, 20, 1),
     ("256 output channels", 160, 40, 256, 10, 14, 1),
+    ("stages of 16 channels, last one partial", 90, 37, 64, 31, 52, 1),
+    ("stages of 16 channels, odd rows", 170, 48, 60, 22, 41, 1),
 ]
 
 
