@@ -66,8 +66,11 @@ template <int ha, int hb> __device__ __forceinline__ uint32_t halves(uint32_t a,
 typedef __attribute__((address_space(3))) const u32x4 *lds_u32x4_ptr;
 __device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(uintptr_t)addr; }
 
-constexpr int kMaxDy = 8; // 16-byte dY items a thread moves per chunk
-constexpr int kMaxZ = 4;  // 16-byte Z items a thread moves per chunk
+// 16-byte items of dY and of Z a thread moves per chunk, at most (every chunk issues so many loads, wanted or not).
+// Uncompressed records of 3 x 3 stride-2 layers (WIDEZ: pooling tiles of one column) hold many Z items to every dY item:
+// with the split of the others a chunk was one output row, half of a row pair left empty.
+constexpr int max_dy(bool widez) { return widez ? 4 : 8; }
+constexpr int max_z(bool widez) { return widez ? 8 : 4; }
 
 // A window of one xhat row held in registers: the last dword of the block left
 // of the current position and NB blocks starting at it.
@@ -145,9 +148,10 @@ __device__ __forceinline__ u32x4 mask8(int left)
 // SC: the number of 8-pixel segments per output row when it is known at compile
 // time (0: read from the plan).  With SC the walk along a row is unrolled and the
 // segment offsets become immediates of the LDS reads.
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, bool WIDEZ>
 __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParams p)
 {
+    constexpr int kMaxDy = max_dy(WIDEZ), kMaxZ = max_z(WIDEZ);
     constexpr int T = R * S;
     constexpr int NT = 64 * WM * WN * KS; // threads of each kind: MFMA waves, then as many copy waves
     constexpr int TILE_O = 32 * MI * WM, TILE_C = 32 * NI * WN;
@@ -827,10 +831,10 @@ struct Variant {
     hipError_t (*launch)(const DwMfmaParams &, dim3, hipStream_t);
 };
 
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, bool WIDEZ = false>
 hipError_t launch_fixed(const DwMfmaParams &p, dim3 grid, hipStream_t st)
 {
-    auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL>;
+    auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ>;
     // (per instantiation; once per process, whichever host thread comes first)
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
@@ -861,6 +865,9 @@ hipError_t launch_variant(const DwMfmaParams &p, dim3 grid, hipStream_t st)
         case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7>(p, grid, st);
         default: break;
         }
+    }
+    if constexpr (S == 3 && SG == 2) {
+        if (p.kw_log2 == 0) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true>(p, grid, st);
     }
     return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
 }
@@ -936,7 +943,8 @@ bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
         if (q.LDY > NT || q.LPC > NT) return false;
         q.dy_passes = (tile_o * q.LDY + NT - 1) / NT;
         q.z_passes = (tile_c * q.LPC + NT - 1) / NT;
-        if (q.dy_passes > kMaxDy || q.z_passes > kMaxZ) return false;
+        const bool widez = var.R == 3 && var.SG == 2 && kwl == 0; // (as in launch_variant)
+        if (q.dy_passes > max_dy(widez) || q.z_passes > max_z(widez)) return false;
         if ((tile_o * q.LDY) % NT || (tile_c * q.LPC) % NT) return false; // passes cover the tile exactly
         // strides: an odd number of 16-byte units so that the 32 lanes of a half
         // wave (one output channel / input channel each) read distinct LDS banks
