@@ -22,6 +22,17 @@ struct Geom {
 
 typedef uint16_t bf16_t; // raw bfloat16 bits
 
+// Division by multiplication: kernels take floor(x / d) as __umulhi(x, magic_of(d)), 0 standing for d = 1.  The quotient
+// is right for every x < n when (n - 1) * (magic * d - 2^32) < 2^32; past that the last pixels of a row come out as
+// pixel -1 of the next one.  Planners whose x grows with the tensor ask before they take a layer.
+inline uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
+inline bool divides_exactly(uint64_t n, uint32_t d)
+{
+    if (d <= 1 || n <= 1) return true;
+    const uint64_t err = (uint64_t)magic_of(d) * d - ((uint64_t)1 << 32);
+    return n <= (uint64_t)1 << 32 && (n - 1) * err < (uint64_t)1 << 32; // (both factors below 2^32)
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
 // Round to nearest even; NaN stays NaN (quiet).

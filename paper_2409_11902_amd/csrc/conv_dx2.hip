@@ -237,6 +237,7 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant)
     b.os = 2; b.is = 1; b.ntaps = b.ntaps_total = 9;
     b.ksplit = 1; b.gpw = 1; b.part = nullptr;
     const int ppi = g.P * g.Q;
+    if (!divides_exactly(ppi, g.Q)) return false; // (a pixel's row and column)
     b.gw = g.Q % 2 ? 7 : 8;
     b.GX = (g.Q + b.gw - 1) / b.gw;
     b.store_px = g.Q % 4 == 0 ? 4 : g.Q % 2 == 0 ? 2 : 1;

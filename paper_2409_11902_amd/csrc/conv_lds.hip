@@ -192,7 +192,6 @@ template <typename T, int PX, bool DX, int CC> __global__ void __launch_bounds__
 
 template <typename T, bool DX> bool launch(const Geom &g, const void *in, const void *W, const void *bias, void *out, hipStream_t st, hipError_t *err)
 {
-    auto magic = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
     ConvLdsParams p{};
     p.in = in; p.W = W; p.bias = bias; p.out = out;
     p.N = g.N; p.C = g.C; p.R = g.R; p.S = g.S; p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;
@@ -221,8 +220,8 @@ template <typename T, bool DX> bool launch(const Geom &g, const void *in, const 
         p.PH = (int)ph; p.PWd = (int)pw;
         p.cw_log2 = 0;
         while (p.cw_log2 < 6 && (1 << p.cw_log2) < p.PWd) ++p.cw_log2;
-        p.m_wc = magic(p.Wc); p.m_ppi = magic(p.ppi); p.m_ph = magic(p.PH); p.m_rpc = magic(p.IPT * p.PH);
-        p.m_rs = magic(g.R * g.S);
+        p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(p.ppi); p.m_ph = magic_of(p.PH); p.m_rpc = magic_of(p.IPT * p.PH);
+        p.m_rs = magic_of(g.R * g.S);
         const dim3 grid(p.tiles * p.ngrp, mblocks, classes);
 #define CAC_LDS(PX, CC) hipLaunchKernelGGL((conv_lds_kernel<T, PX, DX, CC>), grid, dim3(256), (size_t)bytes, st, p)
         if (cc == 16) {

@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(256) zero_fill_kernel(bf16_t *dst, long n)
 // other memory traffic is LDS reads, so their load counter never waits on the long-latency
 // patch loads.
 constexpr int kMaxItems = 12; // 16-byte patch items a copy thread moves per stage, at most (kernel parameter ITEMS: 6 or 12)
-// floor(x / d) for small x (x * d < 2^32) with magic = ceil(2^32 / d), 0 standing for d = 1
+// floor(x / d) with magic = magic_of(d), for the x that divides_exactly allows
 __device__ __forceinline__ uint32_t fdiv(uint32_t x, uint32_t magic) { return magic ? __umulhi(x, magic) : x; }
 constexpr uint32_t kNoElem = 0x40000000u;
 
@@ -944,8 +944,8 @@ bool shape_gather(GatherParams &p, int *variant)
     p.nkb = (p.KCp + KC - 1) / KC;
     p.part = nullptr;
     const int ppi = p.Hc * p.Wc;
-    auto magic = [](uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };
-    p.m_wc = magic(p.Wc); p.m_ppi = magic(ppi); p.m_pwd = magic(p.PWd);
+    if (!divides_exactly(ppi, p.Wc)) return false; // (a pixel's row and column)
+    p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(ppi); p.m_pwd = magic_of(p.PWd);
     const bool whole_planes = p.os == 1 && p.Hc == p.Hout && p.Wc == p.Wout && ppi % 4 == 0;
     const char *force = nullptr;
     int f_wm = 0, f_ni = 0, f_ks = 0;
@@ -993,8 +993,8 @@ bool shape_gather(GatherParams &p, int *variant)
             q.t_log2 = q.T == 4 ? 2 : q.T == 2 ? 1 : 0;
             q.kcs = KC * q.T + 8;
             q.nkb = (q.KCp + KC * q.T - 1) / (KC * q.T);
-            q.m_img = magic(q.PH * q.PWd);
-            q.m_gx = magic((q.Win + 7) / 8); q.m_ph = magic(q.PH);
+            q.m_img = magic_of(q.PH * q.PWd);
+            q.m_gx = magic_of((q.Win + 7) / 8); q.m_ph = magic_of(q.PH);
             q.ngrp = (q.N + q.IPT - 1) / q.IPT;
             const int mtiles = (q.Mp / 64 + wm - 1) / wm;
             const long wgs1 = (long)q.tiles_per_img * q.ngrp * mtiles;
@@ -1004,9 +1004,10 @@ bool shape_gather(GatherParams &p, int *variant)
                 q.ksplit = ks;
                 q.wide_store = whole_planes && ks == 1 && ppi % 8 == 0; // 16-byte runs of pixels, aligned
                 q.kbs = q.nkb / ks;
-                q.m_kbs = magic(q.kbs);
+                q.m_kbs = magic_of(q.kbs);
                 // a few units per workgroup (a longer pipeline) as long as every CU still gets a workgroup
                 q.gpw = (int)max(1L, min((long)((8 + q.kbs - 1) / q.kbs), wgs1 * ks / 256));
+                if (!divides_exactly((uint64_t)q.gpw * q.kbs, q.kbs)) continue; // (a stage's unit: beyond 2^16 channel blocks)
                 const long runs = (q.ngrp + q.gpw - 1) / q.gpw;
                 const long wgs = (long)q.tiles_per_img * runs * mtiles * ks;
                 // cycles per step as measured (vector-cache bound below NI = 4), two-step prefetch 1.35 x

@@ -284,14 +284,14 @@ bool shape_tile(GatherParams &p, int *variant)
         b.dhmin = min(b.dhmin, p.dh[t]); dhmax = max(dhmax, p.dh[t]);
         b.dwmin = min(b.dwmin, p.dw[t]); dwmax = max(dwmax, p.dw[t]);
     }
-    const auto magic = magic_of;
     b.PWd = (p.Wc - 1) * p.is + (dwmax - b.dwmin) + 1;
     b.ksplit = 1; b.T = 1; b.part = nullptr;
     const int ppi = p.Hc * p.Wc;
-    b.m_wc = magic(p.Wc); b.m_ppi = magic(ppi); b.m_pwd = magic(b.PWd);
+    if (!divides_exactly(ppi, p.Wc)) return false; // (a pixel's row and column)
+    b.m_wc = magic_of(p.Wc); b.m_ppi = magic_of(ppi); b.m_pwd = magic_of(b.PWd);
     b.gw = p.Win % 2 ? 7 : 8;
     b.GX = (p.Win + b.gw - 1) / b.gw;
-    b.m_gx = magic(b.GX);
+    b.m_gx = magic_of(b.GX);
     b.store_px = ppi % 8 == 0 ? 8 : ppi % 4 == 0 ? 4 : ppi % 2 == 0 ? 2 : 1;
     int f = -1, f_ipt = 0;
 #ifdef CAC_TUNING
@@ -324,7 +324,7 @@ bool shape_tile(GatherParams &p, int *variant)
         q.buf_bytes = max(q.patch_px * kcs * 2, 2 * kEpWave);
         q.lds_bytes = 2 * q.buf_bytes + kDumpBytes;
         if (q.lds_bytes > 160 * 1024) continue;
-        q.m_ph = magic(q.PH);
+        q.m_ph = magic_of(q.PH);
         for (int t = 0; t < TAPS; ++t) {
             q.wofs[t] = (uint32_t)t * (q.KCp / 16) * (q.Mp / 32) * kFrag;
             q.toff[t] = (uint32_t)((p.dh[t] - q.dhmin) * q.PWd + (p.dw[t] - q.dwmin)) * kcs * 2u;

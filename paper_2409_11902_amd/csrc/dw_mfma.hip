@@ -823,7 +823,6 @@ __global__ void __launch_bounds__(256) dw_reduce_kernel(const float *__restrict_
     dw_reduce_body<SY, V>(part, dW, total, nslices, blockIdx.x);
 }
 
-uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
 
 // Kernel table: filter/stride family x workgroup shape.
 struct Variant {

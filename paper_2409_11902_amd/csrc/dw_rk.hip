@@ -492,7 +492,6 @@ __global__ void __launch_bounds__(512) dw_rk_kernel(DwRkParams p)
     }
 }
 
-uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
 
 template <int SS, bool PART> hipError_t launch_ss(const DwRkParams &p, dim3 grid, hipStream_t st)
 {

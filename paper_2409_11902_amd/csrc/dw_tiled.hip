@@ -102,7 +102,6 @@ __global__ void __launch_bounds__(256) dw_tiled_kernel(DwTiledParams p)
     }
 }
 
-uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
 
 template <typename T, int R, int SG> hipError_t launch_rs(const DwTiledParams &p, dim3 grid, hipStream_t st)
 {

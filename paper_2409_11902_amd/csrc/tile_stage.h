@@ -143,7 +143,5 @@ template <int ITEMS, int GW, int KC, int CB = 4> struct PatchStage {
     }
 };
 
-inline uint32_t magic_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
-
 } // namespace tile
 } // namespace cac
