@@ -924,6 +924,7 @@ bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
         q = base;
         q.NBI = nbi; q.PR = pr;
         q.RB = (g.P + pr - 1) / pr;
+        if (!divides_exactly((uint64_t)((g.N + nbi - 1) / nbi) * q.RB, q.RB)) return false; // (a chunk's images and rows)
         q.LR = nbi * pr;
         q.LRpad = (q.LR + 1) & ~1;
         int nz = 1;

@@ -563,6 +563,7 @@ bool dw_rk_plan(const Geom &g, int dtype, DwRkPlan *plan)
     p.tiles_c = (g.C + 127) / 128;
     const int ntiles = p.tiles_o * p.tiles_c;
     p.nunits = ((g.N + p.NBIu - 1) / p.NBIu) * p.RB;
+    if (!divides_exactly(p.nunits, p.RB)) return false; // (a unit's images and rows)
     const int nchunks = (p.nunits + 1) / 2;
     int want = max(1, 256 / ntiles);              // one workgroup per compute unit ...
     want = min(want, max(1, nchunks / 2));        // ... each with at least two chunks

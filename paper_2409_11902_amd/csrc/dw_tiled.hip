@@ -157,6 +157,8 @@ bool dw_tiled_plan(const Geom &g, int dtype, DwTiledPlan *plan)
     p.lds_bytes = 4 * (16 * p.dy_stride + 16 * p.x_stride);
     p.RB = (g.P + p.PR - 1) / p.PR;
     p.nunits = g.N * p.RB;
+    // (a unit's image and rows, a pixel's pooling tile)
+    if (!divides_exactly(p.nunits, p.RB) || !divides_exactly(g.H, g.kh) || !divides_exactly(g.W, g.kw)) return false;
     const int want = max(1, min(p.nunits, 1024 / ntiles));
     p.units_per_slice = (p.nunits + want - 1) / want;
     p.nslices = (p.nunits + p.units_per_slice - 1) / p.units_per_slice;
