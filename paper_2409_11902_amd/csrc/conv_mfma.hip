@@ -1177,8 +1177,16 @@ int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
                     p.ksplit, 2 * p.patch_px * p.kcs * 2 + (p.wide_store ? 4 * 64 * ((v[0] < 2 ? v[0] : 2) * 64 + 16) : 0));
 }
 
+// The forward launch reads X where it lies: the kernels made for it, and the gather under the same conditions as dY in the
+// data gradient.  (A pooled map that falls out of the repack launch then does so without the channels-last copy.)
+bool fwd_reads_in_place(const Geom &g, const GatherParams &p)
+{
+    return p.tile || (!p.decim && g.W % 2 == 0 && (long)g.N * g.C * g.H * g.W >= 8L * g.R * g.S * g.K * g.C &&
+                      p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512);
+}
+
 // Workspace: [channels-last input][repacked filter][float sums of shared-out channels], each
-// part starting at a multiple of 256 bytes.
+// part starting at a multiple of 256 bytes; nothing for an operand that is read where it lies.
 struct WsLayout { size_t in, wt, part; };
 WsLayout ws_layout(size_t in_elems, size_t wt_elems, const GatherParams &p)
 {
@@ -1188,6 +1196,17 @@ WsLayout ws_layout(size_t in_elems, size_t wt_elems, const GatherParams &p)
     l.wt = up(wt_elems * 2);
     l.part = p.ksplit > 1 ? (size_t)p.ksplit * p.N * p.M * p.Hc * p.Wc * sizeof(float) : 0;
     return l;
+}
+WsLayout fwd_layout(const Geom &g, const GatherParams &p)
+{
+    const size_t in = (size_t)p.N * p.Hin * p.Win * p.KCp; // (Hin, Win: of the pixels a decimated copy keeps)
+    return ws_layout(fwd_reads_in_place(g, p) ? 0 : in, p.w_direct ? 0 : (size_t)p.ntaps_total * p.Mp * p.KCp, p);
+}
+WsLayout dx_layout(const Geom &g, const GatherParams &base, const GatherParams (&cls)[4], int ncls)
+{
+    const size_t in = (size_t)base.N * base.Hin * base.Win * base.KCp;
+    // (only a stride-1 data gradient, a single class, ever shares out its channels)
+    return ws_layout(dx_reads_in_place(g, cls, ncls) ? 0 : in, (size_t)base.ntaps_total * base.Mp * base.KCp, ncls == 1 ? cls[0] : base);
 }
 
 } // namespace
@@ -1200,7 +1219,8 @@ bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, siz
     if (!data_grad) {
         if (!plan_fwd(g, dtype, p, &variant[0])) return false;
         const int n = describe_one(p, variant[0], buf, len);
-        if (p.decim && n > 0 && (size_t)n + 1 < len) snprintf(buf + n, len - n, "; the copy of the input keeps one pixel of every 2 x 2 tile");
+        const char *note = p.decim ? "; the copy of the input keeps one pixel of every 2 x 2 tile" : !p.tile && fwd_reads_in_place(g, p) ? "; X read in place" : "";
+        if (n > 0 && (size_t)n + 1 < len) snprintf(buf + n, len - n, "%s", note);
         return true;
     }
     if (!plan_dx(g, dtype, p, cls, variant, &ncls, &empty)) return false;
@@ -1221,15 +1241,8 @@ size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad)
     GatherParams p{}, cls[4];
     int variant[4], ncls = 0;
     bool empty = false;
-    const size_t RS = (size_t)g.R * g.S;
-    if (!data_grad) {
-        if (!plan_fwd(g, dtype, p, &variant[0])) return 0;
-        const WsLayout l = ws_layout((size_t)g.N * g.H * g.W * p.KCp, RS * p.Mp * p.KCp, p);
-        return l.in + l.wt + l.part;
-    }
-    if (!plan_dx(g, dtype, p, cls, variant, &ncls, &empty)) return 0;
-    // (only a stride-1 data gradient, a single class, ever shares out its channels)
-    const WsLayout l = ws_layout((size_t)g.N * g.P * g.Q * p.KCp, RS * p.Mp * p.KCp, ncls == 1 ? cls[0] : p);
+    if (!(data_grad ? plan_dx(g, dtype, p, cls, variant, &ncls, &empty) : plan_fwd(g, dtype, p, &variant[0]))) return 0;
+    const WsLayout l = data_grad ? dx_layout(g, p, cls, ncls) : fwd_layout(g, p);
     return l.in + l.wt + l.part;
 }
 
@@ -1243,15 +1256,12 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     GatherParams p{};
     int variant;
     if (!plan_fwd(g, dtype, p, &variant)) return false;
-    const WsLayout l = ws_layout((size_t)g.N * g.H * g.W * p.KCp, (size_t)g.R * g.S * p.Mp * p.KCp, p);
+    const WsLayout l = fwd_layout(g, p);
     bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
     p.part = l.part ? (float *)((char *)ws + l.in + l.wt) : nullptr;
     // whole 2 x 2 tiles, rows a multiple of 8 pixels: the pooled map falls out of the repack
     const bool fuse0 = Z && !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4);
-    // Where the pooled map cannot come out of the repack anyway, X is read where it lies under the
-    // same conditions as dY in the data gradient (no channels-last copy, only the filter repack).
-    const bool direct = p.tile || (!p.decim && g.W % 2 == 0 && (long)g.N * g.C * g.H * g.W >= 8L * g.R * g.S * g.K * g.C &&
-                        p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512);
+    const bool direct = fwd_reads_in_place(g, p);
     if (p.tile == 3) {
         // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
         if (!p.w_direct)
@@ -1289,7 +1299,7 @@ bool launch_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, voi
     int variant[4], ncls = 0;
     bool empty_class = false;
     if (!plan_dx(g, dtype, base, cls, variant, &ncls, &empty_class)) return false;
-    const WsLayout l = ws_layout((size_t)g.N * g.P * g.Q * base.KCp, (size_t)g.R * g.S * base.Mp * base.KCp, ncls == 1 ? cls[0] : base);
+    const WsLayout l = dx_layout(g, base, cls, ncls);
     bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
     for (int k = 0; k < ncls; ++k) cls[k].part = cls[k].ksplit > 1 ? (float *)((char *)ws + l.in + l.wt) : nullptr;
     // pixels no output pixel's tap reaches (possible when stride > filter) stay zero
