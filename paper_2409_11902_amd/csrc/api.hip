@@ -305,7 +305,8 @@ int cac_describe_plan(const cac_desc *d, int op, char *buf, size_t buf_len)
                  tl.p.PR, tl.p.XR, tl.p.XW, tl.p.lds_bytes, tl.p.nunits, tl.p.nslices, tl.p.tiles_o * tl.p.tiles_c, tl.grid,
                  tl.partial_bytes);
     } else if ((op == CAC_OP_FWD_AND_COMPRESS || op == CAC_OP_BWD_DATA) &&
-               describe_conv_mfma(g, d->dtype, op == CAC_OP_BWD_DATA, buf, buf_len)) {
+               (describe_conv_mfma(g, d->dtype, op == CAC_OP_BWD_DATA, buf, buf_len) ||
+                describe_lds(g, d->dtype, op == CAC_OP_BWD_DATA, buf, buf_len))) {
     } else if (op == CAC_OP_COMPRESS || op == CAC_OP_GRAD_COSINE) {
         snprintf(buf, buf_len, "streaming kernel");
     } else if (op == CAC_OP_BN_BWD) {

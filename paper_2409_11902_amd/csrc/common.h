@@ -73,6 +73,7 @@ hipError_t launch_compress_generic(const Geom &g, int dtype, const void *X, void
 // conv_lds.hip: false when the geometry does not fit LDS (status in *err otherwise)
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err);
 bool launch_dx_lds(const Geom &g, int dtype, const void *W, const void *dY, void *dX, hipStream_t st, hipError_t *err);
+bool describe_lds(const Geom &g, int dtype, bool data_grad, char *buf, size_t len);
 hipError_t launch_fwd_generic(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y,
                               hipStream_t st);
 hipError_t launch_dx_generic(const Geom &g, int dtype, const void *W, const void *dY, void *dX, hipStream_t st);

@@ -15,6 +15,8 @@
 // 4 reads of the patch along the lanes for 4 or 16 multiply-adds, the reads of 8 (4) channels ahead of their sums
 // (one channel at a time: 13.8 us).  64 pixels per workgroup when 256 would leave less than four workgroups per
 // compute unit.
+#include <stdio.h>
+
 #include "common.h"
 
 namespace cac {
@@ -114,7 +116,7 @@ template <typename T, int PX, bool DX, int CC> __global__ void __launch_bounds__
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
                     const int rho = r0 + 4 * q * rpw;
-                    sx[cin & (rho < nrows) ? rho * p.PWd + col : xdump] = x[q];
+                    sx[(cin & (rho < nrows)) ? rho * p.PWd + col : xdump] = x[q];
                 }
             }
         }
@@ -132,7 +134,7 @@ template <typename T, int PX, bool DX, int CC> __global__ void __launch_bounds__
                 for (int j = 0; j < kRows; ++j) {
                     const int row = mg + 4 * j, o = DX ? c0 + row : m0 + row;
                     const uint32_t off = (uint32_t)((o * p.C + (DX ? m0 : c0)) * RS + xi);
-                    v[k][j] = load<T>(rs_w, cok & (o < (DX ? p.KC : p.M)) ? off * (uint32_t)sizeof(T) : kNoLoad);
+                    v[k][j] = load<T>(rs_w, (cok & (o < (DX ? p.KC : p.M))) ? off * (uint32_t)sizeof(T) : kNoLoad);
                 }
             }
 #pragma unroll
@@ -190,24 +192,33 @@ template <typename T, int PX, bool DX, int CC> __global__ void __launch_bounds__
     }
 }
 
-template <typename T, bool DX> bool launch(const Geom &g, const void *in, const void *W, const void *bias, void *out, hipStream_t st, hipError_t *err)
+// A launch of the kernel: its parameters but for the tensors, pixels per thread, channels per pass.
+struct ConvLdsPlan {
+    ConvLdsParams p;
+    int px, cc, lds_bytes;
+    dim3 grid;
+};
+
+// False when the geometry is not this kernel's (rows too long or a filter too large for LDS, tensors past 32-bit offsets).
+bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
 {
+    const long eb = dtype == CAC_F32 ? 4 : 2;
     ConvLdsParams p{};
-    p.in = in; p.W = W; p.bias = bias; p.out = out;
     p.N = g.N; p.C = g.C; p.R = g.R; p.S = g.S; p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;
-    p.M = DX ? g.C : g.K; p.KC = DX ? g.K : g.C;
-    p.Hin = DX ? g.P : g.H; p.Win = DX ? g.Q : g.W; p.Hout = DX ? g.H : g.P; p.Wout = DX ? g.W : g.Q;
+    p.M = dx ? g.C : g.K; p.KC = dx ? g.K : g.C;
+    p.Hin = dx ? g.P : g.H; p.Win = dx ? g.Q : g.W; p.Hout = dx ? g.H : g.P; p.Wout = dx ? g.W : g.Q;
     // (32-bit byte offsets with 2^31 reserved for what does not exist)
-    if ((long)p.N * p.KC * p.Hin * p.Win * (long)sizeof(T) >= 1L << 31 || (long)p.M * p.KC * g.R * g.S * (long)sizeof(T) >= 1L << 31) return false;
-    const int os_h = DX ? g.sh : 1, os_w = DX ? g.sw : 1, is_h = DX ? 1 : g.sh, is_w = DX ? 1 : g.sw;
+    if ((long)p.N * p.KC * p.Hin * p.Win * eb >= 1L << 31 || (long)p.M * p.KC * g.R * g.S * eb >= 1L << 31) return false;
+    const int os_h = dx ? g.sh : 1, os_w = dx ? g.sw : 1, is_h = dx ? 1 : g.sh, is_w = dx ? 1 : g.sw;
     p.Hc = (p.Hout + os_h - 1) / os_h; p.Wc = (p.Wout + os_w - 1) / os_w;
     if ((long)p.Hc * p.Wc * p.Wc >= 1L << 32) return false; // (division by multiplication is exact below)
     p.ppi = p.Hc * p.Wc;
-    const int span_h = DX ? (g.R - 1) / g.sh + 1 : g.R, span_w = DX ? (g.S - 1) / g.sw + 1 : g.S;
+    const int span_h = dx ? (g.R - 1) / g.sh + 1 : g.R, span_w = dx ? (g.S - 1) / g.sw + 1 : g.S;
     const int mblocks = (p.M + 15) / 16, classes = os_h * os_w;
     if (mblocks > 65535 || classes > 65535) return false;
     const long wgs4 = (long)((p.ppi + 255) / 256) * g.N * mblocks * classes;
-    const int px = wgs4 >= 1024 ? 4 : 1, pt = 64 * px; // (four workgroups per compute unit hide each other's staging)
+    plan->px = wgs4 >= 1024 ? 4 : 1; // (four workgroups per compute unit hide each other's staging)
+    const int pt = 64 * plan->px;
     p.IPT = 2L * p.ppi <= pt ? min(pt / p.ppi, g.N) : 1;
     p.tiles = p.IPT > 1 ? 1 : (p.ppi + pt - 1) / pt;
     p.ngrp = (g.N + p.IPT - 1) / p.IPT;
@@ -222,30 +233,54 @@ template <typename T, bool DX> bool launch(const Geom &g, const void *in, const 
         while (p.cw_log2 < 6 && (1 << p.cw_log2) < p.PWd) ++p.cw_log2;
         p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(p.ppi); p.m_ph = magic_of(p.PH); p.m_rpc = magic_of(p.IPT * p.PH);
         p.m_rs = magic_of(g.R * g.S);
-        const dim3 grid(p.tiles * p.ngrp, mblocks, classes);
-#define CAC_LDS(PX, CC) hipLaunchKernelGGL((conv_lds_kernel<T, PX, DX, CC>), grid, dim3(256), (size_t)bytes, st, p)
-        if (cc == 16) {
-            if (px == 4) CAC_LDS(4, 16); else CAC_LDS(1, 16);
-        } else {
-            if (px == 4) CAC_LDS(4, 4); else CAC_LDS(1, 4);
-        }
-#undef CAC_LDS
-        *err = hipGetLastError();
+        plan->p = p;
+        plan->cc = cc;
+        plan->lds_bytes = (int)bytes;
+        plan->grid = dim3(p.tiles * p.ngrp, mblocks, classes);
         return true;
     }
-    return false; // rows too long or a filter too large for LDS
+    return false;
+}
+
+template <typename T, bool DX> hipError_t launch(const ConvLdsPlan &l, hipStream_t st)
+{
+#define CAC_LDS(PX, CC) hipLaunchKernelGGL((conv_lds_kernel<T, PX, DX, CC>), l.grid, dim3(256), l.lds_bytes, st, l.p)
+    if (l.cc == 16) {
+        if (l.px == 4) CAC_LDS(4, 16); else CAC_LDS(1, 16);
+    } else {
+        if (l.px == 4) CAC_LDS(4, 4); else CAC_LDS(1, 4);
+    }
+#undef CAC_LDS
+    return hipGetLastError();
 }
 
 } // namespace
 
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err)
 {
-    return dtype == CAC_F32 ? launch<float, false>(g, X, W, b, Y, st, err) : launch<bf16_t, false>(g, X, W, b, Y, st, err);
+    ConvLdsPlan l;
+    if (!plan_lds(g, dtype, false, &l)) return false;
+    l.p.in = X; l.p.W = W; l.p.bias = b; l.p.out = Y;
+    *err = dtype == CAC_F32 ? launch<float, false>(l, st) : launch<bf16_t, false>(l, st);
+    return true;
 }
 
 bool launch_dx_lds(const Geom &g, int dtype, const void *W, const void *dY, void *dX, hipStream_t st, hipError_t *err)
 {
-    return dtype == CAC_F32 ? launch<float, true>(g, dY, W, nullptr, dX, st, err) : launch<bf16_t, true>(g, dY, W, nullptr, dX, st, err);
+    ConvLdsPlan l;
+    if (!plan_lds(g, dtype, true, &l)) return false;
+    l.p.in = dY; l.p.W = W; l.p.bias = nullptr; l.p.out = dX;
+    *err = dtype == CAC_F32 ? launch<float, true>(l, st) : launch<bf16_t, true>(l, st);
+    return true;
+}
+
+bool describe_lds(const Geom &g, int dtype, bool data_grad, char *buf, size_t len)
+{
+    ConvLdsPlan l;
+    if (!plan_lds(g, dtype, data_grad, &l)) return false;
+    snprintf(buf, len, "conv_lds tile=16ch x %dpx (%d per thread) ch/pass=%d img/tile=%d patch=%dx%d grid=%ux%ux%u lds=%dB", 64 * l.px, l.px, l.cc, l.p.IPT,
+             l.p.PH, l.p.PWd, l.grid.x, l.grid.y, l.grid.z, l.lds_bytes);
+    return true;
 }
 
 } // namespace cac

@@ -29,6 +29,10 @@ CASES = [
     ("bf16 stride 3", "bf16", 5, 16, 40, 19, 16, 3, 3, 3, 3, 1, 1),
 ]
 
+# what the forward plan has to contain (the data gradient's too, unless it is the plain kernel)
+PLANS = {"four pixels per thread": "(4 per thread) ch/pass=16", "four channels per pass": "(1 per thread) ch/pass=4", "too long for LDS": "generic kernel",
+         "several images per workgroup": "img/tile=4", "one pixel images": "img/tile=64"}
+
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_forward_and_data_gradient(case):
@@ -39,6 +43,9 @@ def test_forward_and_data_gradient(case):
     td = torch.float32 if dtype == "f32" else torch.bfloat16
     d = B.make_desc(N, C, K, H, W, R, S, sh, sw, ph, pw, 1, 1, dtype=B.F32 if dtype == "f32" else B.BF16)
     assert B.cac_workspace_size(d, B.OP_FWD_AND_COMPRESS) == 0, "no MFMA plan: the case is here for the float kernel"
+    fwd, dx = (B.cac_describe_plan(d, op) for op in (B.OP_FWD_AND_COMPRESS, B.OP_BWD_DATA))
+    assert PLANS.get(name, "(1 per thread) ch/pass=") in fwd, fwd
+    assert fwd.startswith("conv_lds") == dx.startswith("conv_lds") == (name != "too long for LDS"), (fwd, dx)
     P, Q = B.cac_out_shape(d)
     rng = np.random.default_rng(sum(map(ord, name)))
     make = lambda *s: synth.to_storage(rng.standard_normal(s, dtype=np.float32), dt)  # noqa: E731
