@@ -66,3 +66,38 @@ def test_forward_and_data_gradient(case):
         for n in range(N):
             norm = np.linalg.norm(want[n])
             assert np.linalg.norm(got[n] - want[n]) <= tol * norm, (name, what, n)
+
+
+@pytest.mark.parametrize("case", [
+    # name, dtype, N, C, K, H, W, R, S, stride, pad
+    ("3x3", "f32", 2, 16, 18, 9, 11, 3, 3, 1, 1),
+    ("3x3, four pixels per thread", "f32", 40, 16, 16, 40, 52, 3, 3, 1, 1),
+    ("5x5 stride 2", "f32", 3, 5, 16, 12, 13, 5, 5, 2, 2),
+    ("bf16 5x5", "bf16", 2, 9, 16, 10, 10, 5, 5, 1, 2),
+], ids=lambda c: c[0])
+def test_taps_outside_the_image_are_skipped(case):
+    """An infinite or NaN weight makes an output non-finite only where its tap meets a pixel: padding is no pixel."""
+    import torch
+    from gpu_util import Guarded, download, upload
+    name, dtype, N, C, K, H, W, R, S, st, pad = case
+    dt, td = (synth.F32, torch.float32) if dtype == "f32" else (synth.BF16, torch.bfloat16)
+    d = B.make_desc(N, C, K, H, W, R, S, st, st, pad, pad, 1, 1, dtype=B.F32 if dtype == "f32" else B.BF16, has_bias=0)
+    assert all(B.cac_describe_plan(d, op).startswith("conv_lds") for op in (B.OP_FWD_AND_COMPRESS, B.OP_BWD_DATA))
+    P, Q = B.cac_out_shape(d)
+    rng = np.random.default_rng(5)
+    make = lambda *s: synth.to_storage(rng.standard_normal(s, dtype=np.float32), dt)  # noqa: E731
+    X, Wt, dY = make(N, C, H, W), make(K, C, R, S), make(N, K, P, Q)
+    Wt[0, 1, 0, 0], Wt[K - 1, 0, R - 1, 1], Wt[2, C - 1, 1, S - 1] = np.inf, np.nan, -np.inf
+    Y, Z, dX = Guarded((N, K, P, Q), td), Guarded((N, C, H, W), td), Guarded((N, C, H, W), td)
+    B.conv_fwd_and_compress(d, upload(X, dt), upload(Wt, dt), None, Y.t, Z.t)
+    B.conv_bwd_data(d, upload(Wt, dt), upload(dY, dt), dX.t)
+    torch.cuda.synchronize()
+    g = oracle.ConvGeom(N, C, K, H, W, R, S, st, st, pad, pad)
+    f = [a.astype(np.float64) for a in (X, Wt, dY)]
+    tol = 1e-5 + (0 if dtype == "f32" else 2.0 ** -8)   # as above
+    for what, out, want in (("Y", Y, oracle.conv_fwd(g, f[0], f[1], np.zeros(K))), ("dX", dX, oracle.conv_dx(g, f[1], f[2]))):
+        out.check(what)
+        got, ok = download(out.t), np.isfinite(want)
+        assert 0 < ok.sum() < ok.size
+        assert np.array_equal(np.isfinite(got), ok), (name, what)
+        assert np.linalg.norm(got[ok] - want[ok]) <= tol * np.linalg.norm(want[ok]), (name, what)
