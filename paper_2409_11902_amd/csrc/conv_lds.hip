@@ -15,7 +15,10 @@
 // 4 reads of the patch along the lanes for 4 or 16 multiply-adds, the reads of 8 (4) channels ahead of their sums
 // (one channel at a time: 13.8 us).  64 pixels per workgroup when 256 would leave less than four workgroups per
 // compute unit.
+#include <math.h>
 #include <stdio.h>
+
+#include <algorithm>
 
 #include "common.h"
 
@@ -254,8 +257,9 @@ struct ConvLdsPlan {
     dim3 grid;
 };
 
-// False when the geometry is not this kernel's (rows too long or a filter too large for LDS, tensors past 32-bit offsets).
-bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
+// The launch with px pixels per thread and cc channels per pass; false when it is not possible (rows too long or a filter
+// too large for LDS, tensors past 32-bit offsets).
+bool shape_lds(const Geom &g, int dtype, bool dx, int px, int cc, ConvLdsPlan *plan)
 {
     const long eb = dtype == CAC_F32 ? 4 : 2;
     ConvLdsParams p{};
@@ -269,32 +273,93 @@ bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
     if ((long)p.Hc * p.Wc * p.Wc >= 1L << 32) return false; // (division by multiplication is exact below)
     p.ppi = p.Hc * p.Wc;
     const int span_h = dx ? (g.R - 1) / g.sh + 1 : g.R, span_w = dx ? (g.S - 1) / g.sw + 1 : g.S;
-    const int mblocks = (p.M + 15) / 16, classes = os_h * os_w;
+    const int mblocks = (p.M + 15) / 16, classes = os_h * os_w, pt = 64 * px;
     if (mblocks > 65535 || classes > 65535) return false;
-    const long wgs4 = (long)((p.ppi + 255) / 256) * g.N * mblocks * classes;
-    plan->px = wgs4 >= 1024 ? 4 : 1; // (four workgroups per compute unit hide each other's staging)
-    const int pt = 64 * plan->px;
     p.IPT = 2L * p.ppi <= pt ? min(pt / p.ppi, g.N) : 1;
     p.tiles = p.IPT > 1 ? 1 : (p.ppi + pt - 1) / pt;
     p.ngrp = (g.N + p.IPT - 1) / p.IPT;
-    const long rows = p.IPT > 1 ? p.Hc : min((long)p.Hc, (long)(pt + p.Wc - 2) / p.Wc + 1);
-    const long ph = max(2L, (rows - 1) * is_h + span_h), pw = (long)(p.Wc - 1) * is_w + span_w;
+    const long rows = p.IPT > 1 ? p.Hc : std::min((long)p.Hc, (long)(pt + p.Wc - 2) / p.Wc + 1);
+    const long ph = std::max(2L, (rows - 1) * is_h + span_h), pw = (long)(p.Wc - 1) * is_w + span_w;
     if ((long)p.tiles * p.ngrp > 0x7fffffffL) return false;
-    for (int cc : {16, 4}) {
-        const long bytes = 4 * ((long)g.R * g.S * cc * kTMP + (long)cc * p.IPT * ph * pw + 64);
-        if (bytes > 64 * 1024) continue;
-        p.PH = (int)ph; p.PWd = (int)pw;
-        p.cw_log2 = 0;
-        while (p.cw_log2 < 6 && (1 << p.cw_log2) < p.PWd) ++p.cw_log2;
-        p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(p.ppi); p.m_ph = magic_of(p.PH); p.m_rpc = magic_of(p.IPT * p.PH);
-        p.m_rs = magic_of(g.R * g.S);
-        plan->p = p;
-        plan->cc = cc;
-        plan->lds_bytes = (int)bytes;
-        plan->grid = dim3(p.tiles * p.ngrp, mblocks, classes);
-        return true;
-    }
-    return false;
+    const long bytes = 4 * ((long)g.R * g.S * cc * kTMP + (long)cc * p.IPT * ph * pw + 64);
+    if (bytes > 64 * 1024) return false;
+    p.PH = (int)ph; p.PWd = (int)pw;
+    p.cw_log2 = 0;
+    while (p.cw_log2 < 6 && (1 << p.cw_log2) < p.PWd) ++p.cw_log2;
+    p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(p.ppi); p.m_ph = magic_of(p.PH); p.m_rpc = magic_of(p.IPT * p.PH);
+    p.m_rs = magic_of(g.R * g.S);
+    plan->p = p;
+    plan->px = px;
+    plan->cc = cc;
+    plan->lds_bytes = (int)bytes;
+    plan->grid = dim3(p.tiles * p.ngrp, mblocks, classes);
+    return true;
+}
+
+// Microseconds of a launch, and of the plain kernel on the same layer: a pass costs its batches of eight loads of the
+// patch, its loads of the filter and its taps x channels, once as the latency of a workgroup and once as the work of 256
+// compute units; a step of the plain kernel's loop likewise, and every channel (forward) a new line of the input.  Fitted to
+// 10000 random layers in each direction (1-256 channels, maps of 2-400, filters of 1-11, strides 1-3, both types): 15 %
+// and 19 % rms for this kernel, 25 % and 22 % for the plain one.
+struct LdsCost { double start, x, f, mul1, mul4, wg, wx, wf, wmul1, wmul4; };
+const LdsCost kLdsCost[2] = {{0.0, 0.93, 0.0985, 0.0150, 0.0613, 0.06, 0.52, 0.0102, 0.0123, 0.0378},
+                             {4.3, 1.39, 0.1067, 0.0344, 0.0851, 0.39, 0.42, 0.0543, 0.0153, 0.0380}};
+struct PlainCost { double start, step, line, wstep, wg; };
+const PlainCost kPlainCost[2] = {{0.5, 0.154, 0.194, 0.0715, 0.55}, {5.4, 0.125, 0.0, 0.0679, 0.41}};
+
+double cost_lds(const Geom &g, bool dx, const ConvLdsPlan &l)
+{
+    const LdsCost &c = kLdsCost[dx];
+    auto cdiv = [](long a, long b) { return (double)((a + b - 1) / b); };
+    const int RS = g.R * g.S, rpw = 64 >> l.p.cw_log2;
+    const double passes = cdiv(l.p.KC, l.cc), nx = cdiv(l.p.PWd, 64) * cdiv((long)l.cc * l.p.IPT * l.p.PH, 32 * rpw);
+    const double nf = cdiv((long)(dx ? 16 : l.cc) * RS, 128) * 2 * ((dx ? l.cc : 16) / 4), mul = (double)RS / l.grid.z * l.cc;
+    const double wgs = (double)l.grid.x * l.grid.y * l.grid.z;
+    return c.start + hypot(passes * (c.x * nx + c.f * nf + mul * (l.px == 4 ? c.mul4 : c.mul1)),
+                           wgs / 256 * (c.wg * (l.px == 4 ? 2 : 1) + passes * (c.wx * nx + c.wf * nf + mul * (l.px == 4 ? c.wmul4 : c.wmul1))));
+}
+
+double cost_plain(const Geom &g, bool dx)
+{
+    const PlainCost &c = kPlainCost[dx];
+    // taps that some pixel has inside the image; a wave of the data gradient runs through those of all its rows
+    auto valid = [](int R, int pad, int n, int out, int st) { return std::max(1.0, std::min(R - 1.0, n - 1.0 + pad) - std::max(0.0, pad - (out - 1.0) * st) + 1.0); };
+    const double rows = valid(g.R, g.ph, g.H, g.P, g.sh) * (dx ? std::min(1.0, (64.0 / g.W + 1.0) / g.sh) : 1.0);
+    const double steps = (dx ? g.K : g.C) * rows * valid(g.S, g.pw, g.W, g.Q, g.sw);
+    const long plane = dx ? (long)g.H * g.W : (long)g.P * g.Q;
+    const double wgs = (double)((plane + 255) / 256) * (((dx ? g.C : g.K) + 7) / 8) * g.N;
+    return c.start + hypot(steps * c.step + (dx ? 0.0 : g.C * c.line), wgs / 256 * (steps * c.wstep + c.wg));
+}
+
+// The launch for a layer; false when it is the plain kernel's: impossible here, or slower.  Sixteen channels per pass (four
+// where LDS has no room for more) and four pixels per thread once that leaves four workgroups to a compute unit, which
+// hide each other's staging, are what layers of 16 channels and more want; another shape, or the plain kernel, is taken
+// where it costs at least a tenth less.  That is so towards few channels, where blocks of 16 are mostly padding (call in
+// us, this shape / plain kernel / as planned: 3 -> 64 3 x 3 at 32 x 32, batch 32, float, 32 / 17 / 16; data gradient of
+// 64 -> 3 31 / 14 / 15; 3 -> 64 at 224 x 224, batch 2, bfloat16, data gradient 305 / 150 / 150), and for a few long rows
+// (4 -> 4 at 3 x 900 21 / 11 / 11).  On 7000 random layers other than those of the fit, 31 % ran more than 5 % slower
+// than on the plain kernel with this shape alone and 3 % do as planned; 16 -> 16 at 32 x 32, batch 8, 32 (plain) / 11.5.
+bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
+{
+    const long plane = dx ? (long)((g.H + g.sh - 1) / g.sh) * ((g.W + g.sw - 1) / g.sw) : (long)g.P * g.Q;
+    const long wgs4 = (plane + 255) / 256 * g.N * (((dx ? g.C : g.K) + 15) / 16) * (dx ? (long)g.sh * g.sw : 1);
+    const int px0 = wgs4 >= 1024 ? 4 : 1, channels = dx ? g.K : g.C;
+    const double plain = cost_plain(g, dx);
+    double usual = 0, least = plain; // (usual: of the first possible shape with px0 pixels, 0 while there is none)
+    ConvLdsPlan first{}, best{};
+    for (int px : {px0, 5 - px0})
+        for (int cc : {16, 4}) {
+            ConvLdsPlan l;
+            if (!shape_lds(g, dtype, dx, px, cc, &l)) continue;
+            const double cost = cost_lds(g, dx, l);
+            if (px == px0 && usual == 0) { usual = cost; first = l; }
+            if (cost < least) { least = cost; best = l; }
+            if (channels > 8) break; // (passes of four only where those of sixteen do not fit: the same work in more passes)
+        }
+    if (least < 0.9 * (usual > 0 ? usual : plain)) *plan = best;
+    else if (usual > 0) *plan = first;
+    else return false;
+    return plan->px != 0;
 }
 
 template <typename T, bool DX> hipError_t launch(const ConvLdsPlan &l, hipStream_t st)

@@ -4,6 +4,8 @@ channel counts around its blocks of 16 and 4, strides with pixels that no tap re
 that do not fit LDS (the plain kernels)."""
 from __future__ import annotations
 
+import re
+
 import numpy as np
 import pytest
 
@@ -27,11 +29,27 @@ CASES = [
     ("too long for LDS", "f32", 1, 3, 4, 3, 5000, 3, 3, 1, 1, 1, 1),
     ("bf16 5x5", "bf16", 8, 33, 16, 15, 17, 5, 5, 1, 1, 2, 2),
     ("bf16 stride 3", "bf16", 5, 16, 40, 19, 16, 3, 3, 3, 3, 1, 1),
+    ("four pixels, sixteen channels", "f32", 40, 32, 64, 40, 52, 3, 3, 1, 1, 1, 1),
+    ("stride 3 past a 1x1 filter, more channels", "f32", 4, 32, 16, 13, 11, 1, 1, 3, 3, 0, 0),
+    ("7x7 stride 2, four pixels", "f32", 8, 6, 64, 112, 112, 7, 7, 2, 2, 3, 3),
+    ("few channels", "f32", 16, 2, 6, 50, 50, 3, 3, 1, 1, 0, 0),
+    ("towards few channels", "f32", 32, 40, 3, 32, 32, 3, 3, 1, 1, 1, 1),
 ]
 
-# what the forward plan has to contain (the data gradient's too, unless it is the plain kernel)
-PLANS = {"four pixels per thread": "(4 per thread) ch/pass=16", "four channels per pass": "(1 per thread) ch/pass=4", "too long for LDS": "generic kernel",
-         "several images per workgroup": "img/tile=4", "one pixel images": "img/tile=64"}
+# pixels per thread and channels per pass of the forward pass and of the data gradient, or "plain"
+PLANS = {
+    "four pixels per thread": ("4x16", "4x16"), "one pixel images": ("1x16", "plain"), "four channels per pass": ("1x4", "plain"),
+    "stride 3 past a 1x1 filter": ("1x16", "plain"), "7x7 stride 2": ("1x4", "1x4"),
+    "too long for LDS": ("plain", "plain"),
+    "four pixels, sixteen channels": ("4x16", "4x16"),
+    "7x7 stride 2, four pixels": ("4x4", "4x4"), "few channels": ("1x4", "plain"), "towards few channels": ("1x16", "plain"),
+}
+IMAGES = {"several images per workgroup": 4, "stride 3 past a 1x1 filter": 3, "one pixel images": 64, "stride 3 past a 1x1 filter, more channels": 3}
+
+
+def plan_of(d, op):
+    m = re.search(r"^conv_lds .*\((\d) per thread\) ch/pass=(\d+) img/tile=(\d+)", B.cac_describe_plan(d, op))
+    return (f"{m[1]}x{m[2]}", int(m[3])) if m else ("plain", 1)
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
@@ -43,9 +61,9 @@ def test_forward_and_data_gradient(case):
     td = torch.float32 if dtype == "f32" else torch.bfloat16
     d = B.make_desc(N, C, K, H, W, R, S, sh, sw, ph, pw, 1, 1, dtype=B.F32 if dtype == "f32" else B.BF16)
     assert B.cac_workspace_size(d, B.OP_FWD_AND_COMPRESS) == 0, "no MFMA plan: the case is here for the float kernel"
-    fwd, dx = (B.cac_describe_plan(d, op) for op in (B.OP_FWD_AND_COMPRESS, B.OP_BWD_DATA))
-    assert PLANS.get(name, "(1 per thread) ch/pass=") in fwd, fwd
-    assert fwd.startswith("conv_lds") == dx.startswith("conv_lds") == (name != "too long for LDS"), (fwd, dx)
+    fwd, dx = (plan_of(d, op) for op in (B.OP_FWD_AND_COMPRESS, B.OP_BWD_DATA))
+    assert (fwd[0], dx[0]) == PLANS.get(name, ("1x16", "1x16"))
+    assert fwd[1] == IMAGES.get(name, 1)
     P, Q = B.cac_out_shape(d)
     rng = np.random.default_rng(sum(map(ord, name)))
     make = lambda *s: synth.to_storage(rng.standard_normal(s, dtype=np.float32), dt)  # noqa: E731
@@ -71,7 +89,7 @@ def test_forward_and_data_gradient(case):
 @pytest.mark.parametrize("case", [
     # name, dtype, N, C, K, H, W, R, S, stride, pad
     ("3x3", "f32", 2, 16, 18, 9, 11, 3, 3, 1, 1),
-    ("3x3, four pixels per thread", "f32", 40, 16, 16, 40, 52, 3, 3, 1, 1),
+    ("3x3, four pixels per thread", "f32", 40, 32, 64, 40, 52, 3, 3, 1, 1),
     ("5x5 stride 2", "f32", 3, 5, 16, 12, 13, 5, 5, 2, 2),
     ("bf16 5x5", "bf16", 2, 9, 16, 10, 10, 5, 5, 1, 2),
 ], ids=lambda c: c[0])
