@@ -1067,6 +1067,9 @@ bool use_tile()
     return true;
 }
 
+// Whole 2 x 2 tiles, rows a multiple of 8 pixels: the pooled map falls out of the repack.
+bool record_in_repack(const Geom &g) { return !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4); }
+
 // Forward pass as a gather GEMM: output channels x output pixels, taps (r - ph, s - pw).
 bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
 {
@@ -1091,7 +1094,7 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
         p.Hin = g.H / 2; p.Win = g.W / 2; p.is = 1;
     }
     p.KCin = g.C;
-    if (use_tile() && shape_pw(p, !g.pmax && g.kh == 2 && g.kw == 2, variant)) {
+    if (use_tile() && shape_pw(p, !g.pmax && g.kh == 2 && g.kw == 2, record_in_repack(g), variant)) {
         p.tile = 3;
         p.w_direct = p.w_direct && g.C % 16 == 0; // (rows of W are whole fragments)
         p.w_kstep = p.w_direct ? 32u : (uint32_t)p.Mp * 32u;
@@ -1137,7 +1140,7 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 }
             if (p.ntaps == 0) { *empty_class = true; continue; }
             p.KCin = g.K;
-            if (use_tile() && shape_pw(p, false, &variant[*ncls])) {
+            if (use_tile() && shape_pw(p, false, false, &variant[*ncls])) {
                 p.tile = 3;
                 p.w_direct = 0;
                 p.w_kstep = (uint32_t)p.Mp * 32u;
@@ -1259,8 +1262,7 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     const WsLayout l = fwd_layout(g, p);
     bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
     p.part = l.part ? (float *)((char *)ws + l.in + l.wt) : nullptr;
-    // whole 2 x 2 tiles, rows a multiple of 8 pixels: the pooled map falls out of the repack
-    const bool fuse0 = Z && !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4);
+    const bool fuse = Z && record_in_repack(g); // (with `direct` the repack launch forms Z without writing the channels-last copy)
     const bool direct = fwd_reads_in_place(g, p);
     if (p.tile == 3) {
         // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
@@ -1275,7 +1277,6 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
         *err = run_gather(p, variant, st);
         return true;
     }
-    const bool fuse = fuse0; // (with `direct` the repack launch forms Z without writing the channels-last copy)
     *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp,
                          (const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr,
                          p.decim);

@@ -28,7 +28,7 @@ CASES = [
     ("4-byte stores", 5, 72, 100, 13, 10, 2, False),
     ("odd planes, several images per tile", 37, 130, 64, 7, 7, 2, False),
     ("odd planes longer than a tile", 4, 100, 96, 17, 19, 1, False),
-    ("small even planes, batch not a multiple", 53, 16, 24, 4, 4, 2, False),
+    ("small even planes, batch not a multiple", 53, 16, 24, 4, 4, 1, False),
     ("one pixel", 70, 400, 33, 1, 1, 1, False),
     ("tile 4", 3, 64, 32, 16, 16, 4, False),
 ]

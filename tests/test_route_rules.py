@@ -1,0 +1,33 @@
+"""Host-only: which kernel a layer is planned for, on both sides of rules whose lines were drawn from measurements."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2409_11902_amd import binding as B
+
+
+@pytest.mark.parametrize("shape,k,plan,pooled", [
+    # N, C, K, H, W.  The 2 x 2 record comes out of the gather's repack for nothing on rows of 4 or a multiple of 8 ...
+    ((168, 45, 20, 8, 8), 2, "gather", False),
+    ((168, 45, 20, 8, 8), 4, "pointwise", False),
+    ((1050, 45, 20, 8, 8), 2, "pointwise", False),      # ... which no longer decides from 256 workgroups on
+    ((168, 45, 20, 9, 9), 2, "pointwise", False),
+    # pooled on the way: only with enough workgroups for the length of the sum
+    ((32, 803, 73, 16, 16), 2, "gather", False),
+    ((64, 803, 73, 16, 16), 2, "gather", False),
+    ((128, 803, 73, 16, 16), 2, "pointwise", True),
+    ((32, 200, 73, 16, 16), 2, "gather", False),
+    ((32, 190, 73, 16, 16), 2, "pointwise", True),
+    # ... and not by the few threads that have channels to move
+    ((198, 10, 14, 68, 68), 2, "pointwise", False),
+    ((20, 10, 14, 68, 68), 2, "pointwise", True),
+    ((198, 33, 14, 68, 68), 2, "pointwise", True),
+    # planes of two or four pixels
+    ((199, 864, 1295, 2, 2), 4, "gather", False),
+    ((199, 864, 1295, 3, 2), 4, "pointwise", False),
+    ((512, 2048, 1000, 1, 1), 1, "pointwise", False),
+])
+def test_pointwise_layers(shape, k, plan, pooled):
+    d = B.make_desc(*shape, 1, 1, pool_kh=k, pool_kw=k)
+    got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
+    assert got.startswith(plan) and ("pooled on the way" in got) == pooled, got
