@@ -67,8 +67,9 @@ typedef __attribute__((address_space(3))) const u32x4 *lds_u32x4_ptr;
 __device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(uintptr_t)addr; }
 
 // 16-byte items of dY and of Z a thread moves per chunk, at most (every chunk issues so many loads, wanted or not).
-// Uncompressed records of 3 x 3 stride-2 layers (WIDEZ: pooling tiles of one column) hold many Z items to every dY item:
-// with the split of the others a chunk was one output row, half of a row pair left empty.
+// Uncompressed records of 3 x 3 stride-2 layers (pooling tiles of one column) hold many Z items to every dY item: with the
+// split of the others a chunk is one output row on wide maps, half of a row pair left empty.  WIDEZ is the other split:
+// longer chunks, but a workgroup waits for more before its first; dw_mfma_plan draws the line.
 constexpr int max_dy(bool widez) { return widez ? 4 : 8; }
 constexpr int max_z(bool widez) { return widez ? 8 : 4; }
 
@@ -866,7 +867,7 @@ hipError_t launch_variant(const DwMfmaParams &p, dim3 grid, hipStream_t st)
         }
     }
     if constexpr (S == 3 && SG == 2) {
-        if (p.kw_log2 == 0) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true>(p, grid, st);
+        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true>(p, grid, st);
     }
     return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
 }
@@ -890,7 +891,7 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 namespace {
 
 // The plan for one entry of the kernel table; false when the geometry does not fit it.
-bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
+bool plan_with(const Geom &g, int vi, bool widez, DwMfmaPlan *plan)
 {
     auto log2_of = [](int k) { return k == 1 ? 0 : k == 2 ? 1 : k == 4 ? 2 : k == 8 ? 3 : -1; };
     const int khl = log2_of(g.kh), kwl = log2_of(g.kw);
@@ -907,6 +908,7 @@ bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
     base.N = g.N; base.C = g.C; base.K = g.K; base.H = g.H; base.W = g.W; base.P = g.P; base.Q = g.Q;
     base.Hp = g.Hp; base.Wp = g.Wp;
     base.kh_log2 = khl; base.kw_log2 = kwl;
+    base.widez = widez;
     base.SEGS = (g.Q + 7) / 8;
     base.Qpad = base.SEGS * 8;
     base.ZV = (g.Wp + 7) / 8;
@@ -943,7 +945,6 @@ bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
         if (q.LDY > NT || q.LPC > NT) return false;
         q.dy_passes = (tile_o * q.LDY + NT - 1) / NT;
         q.z_passes = (tile_c * q.LPC + NT - 1) / NT;
-        const bool widez = var.R == 3 && var.SG == 2 && kwl == 0; // (as in launch_variant)
         if (q.dy_passes > max_dy(widez) || q.z_passes > max_z(widez)) return false;
         if ((tile_o * q.LDY) % NT || (tile_c * q.LPC) % NT) return false; // passes cover the tile exactly
         // strides: an odd number of 16-byte units so that the 32 lanes of a half
@@ -1003,6 +1004,38 @@ bool plan_with(const Geom &g, int vi, DwMfmaPlan *plan)
     return true;
 }
 
+// Workgroup shape.  Splitting the pixels over the waves of a workgroup (KS > 1) cuts the
+// partial sums a workgroup writes by KS at the price of shorter runs between barriers and
+// twice the staging work per MFMA; it pays when a workgroup has only a few chunks to go
+// through.  Among the others: the large tile unless it would be mostly padding.
+bool plan_shape(const Geom &g, bool widez, DwMfmaPlan *plan)
+{
+    DwMfmaPlan whole, split;
+    bool have_whole = false, have_split = false;
+    for (int i = 0; i < kNumVariants; ++i) {
+        const Variant &v = kVariants[i];
+        if (v.R != g.R || v.SG != g.sh) continue;
+        const int to = 32 * v.MI * v.WM, tc = 32 * v.NI * v.WN;
+        if (to > 64 && (g.K <= to / 2 || g.C <= tc / 2)) continue;
+        if (v.KS > 1) {
+            if (!have_split) have_split = plan_with(g, i, widez, &split);
+        } else {
+            if (!have_whole) have_whole = plan_with(g, i, widez, &whole);
+        }
+    }
+    if (!have_whole && !have_split) return false;
+    const int thr = g.R == 1 ? 12 : 24; // measured break-even (chunks per workgroup: split wins at 16, loses at 32)
+    bool use_split = have_split && (!have_whole || split.p.chunks_per_slice <= thr);
+#ifdef CAC_TUNING // development builds: CAC_DW_SHAPE=whole|split overrides the rule
+    if (const char *f = getenv("CAC_DW_SHAPE")) {
+        if (f[0] == 'w' && have_whole) use_split = false;
+        if (f[0] == 's' && have_split) use_split = true;
+    }
+#endif
+    *plan = use_split ? split : whole;
+    return true;
+}
+
 } // namespace
 
 bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
@@ -1018,33 +1051,19 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
     // buffer loads address with 32-bit byte offsets and use 2^31 as "no load"
     if ((long)g.N * g.K * g.P * g.Q >= (1L << 30) || (long)g.N * g.C * g.Hp * g.Wp >= (1L << 30)) return false;
 
-    // Workgroup shape.  Splitting the pixels over the waves of a workgroup (KS > 1) cuts the
-    // partial sums a workgroup writes by KS at the price of shorter runs between barriers and
-    // twice the staging work per MFMA; it pays when a workgroup has only a few chunks to go
-    // through.  Among the others: the large tile unless it would be mostly padding.
-    DwMfmaPlan whole, split;
-    bool have_whole = false, have_split = false;
-    for (int i = 0; i < kNumVariants; ++i) {
-        const Variant &v = kVariants[i];
-        if (v.R != g.R || v.SG != g.sh) continue;
-        const int to = 32 * v.MI * v.WM, tc = 32 * v.NI * v.WN;
-        if (to > 64 && (g.K <= to / 2 || g.C <= tc / 2)) continue;
-        if (v.KS > 1) {
-            if (!have_split) have_split = plan_with(g, i, &split);
-        } else {
-            if (!have_whole) have_whole = plan_with(g, i, &whole);
-        }
-    }
-    if (!have_whole && !have_split) return false;
-    const int thr = g.R == 1 ? 12 : 24; // measured break-even (chunks per workgroup: split wins at 16, loses at 32)
-    bool use_split = have_split && (!have_whole || split.p.chunks_per_slice <= thr);
-#ifdef CAC_TUNING // development builds: CAC_DW_SHAPE=whole|split overrides the rule
-    if (const char *f = getenv("CAC_DW_SHAPE")) {
-        if (f[0] == 'w' && have_whole) use_split = false;
-        if (f[0] == 's' && have_split) use_split = true;
-    }
-#endif
-    *plan = use_split ? split : whole;
+    // The split of the copy registers (calls in us, usual / WIDEZ: 128 -> 256 at 28 x 28, batch 128, 56 chunks to a
+    // workgroup, 73 / 63; 20 -> 76 at 4 x 4, batch 121, two of them, 15.7 / 19.3; of 700 random layers WIDEZ took 0.75 of the
+    // time from sixteen chunks on and 1.05 below eight).  Where only WIDEZ fits -- long rows -- the kernel of dw_tiled.hip is
+    // the other choice: four times as slow in the mean, but 12.4 against 19.3 us for 9 -> 9 at 82 x 82, batch 1.
+    const bool may_widen = f3 && g.sh == 2 && g.kw == 1;
+    if (!plan_shape(g, false, plan))
+        return may_widen && 2.0 * g.N * g.P * g.Q * (double)g.K * g.C * 9 >= 1e8 && plan_shape(g, true, plan);
+    if (!may_widen || plan->p.chunks_per_slice < 12) return true;
+    DwMfmaPlan wide;
+    bool have = plan_shape(g, true, &wide);
+    // (the rule between the tiles counts chunks of the usual length: what it gives the large tile stays there)
+    if (have && kVariants[plan->variant].KS == 1 && kVariants[wide.variant].KS > 1) have = plan_with(g, plan->variant, true, &wide);
+    if (have) *plan = wide;
     return true;
 }
 
