@@ -215,8 +215,8 @@ template <int WM, int WN, int ITEMS, int KC> hipError_t launch_rows(const Gather
 }
 template <int WM, int WN> hipError_t launch_shape(const GatherParams &p, hipStream_t st)
 {
-    const bool one = p.IPT * p.PH * p.GX * (4 * p.T) <= 256;
-    if (p.T == 2) return one ? launch_rows<WM, WN, 1, 64>(p, st) : launch_rows<WM, WN, 2, 64>(p, st);
+    if (p.T == 2) return launch_rows<WM, WN, 1, 64>(p, st); // (never planned with two items per thread)
+    const bool one = p.IPT * p.PH * p.GX * 4 <= 256;
     return one ? launch_rows<WM, WN, 1, 32>(p, st) : launch_rows<WM, WN, 2, 32>(p, st);
 }
 
@@ -262,7 +262,8 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant)
             q.IPT = 2 * ppi <= pt ? min(pt / ppi, g.N) : 1;
             q.tiles_per_img = q.IPT > 1 ? 1 : (ppi + pt - 1) / pt;
             q.PH = (q.IPT > 1 ? g.P : min(g.P, (pt + g.Q - 2) / g.Q + 1)) + 1;
-            if (q.IPT * q.PH * q.GX * (kc / 8) > 512) continue;
+            const int items = q.IPT * q.PH * q.GX * (kc / 8);
+            if (items > (t == 2 ? 256 : 512)) continue; // (64 channels in two items per thread: 32 in one are always the cheaper)
             q.patch_px = q.IPT * q.PH * q.PWd;
             q.buf_bytes = max(q.patch_px * kcs * 2, 2 * kEpWave);
             q.lds_bytes = 2 * q.buf_bytes + kDumpBytes;
@@ -276,8 +277,10 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant)
             // rough cycles of a compute unit: the MFMAs at half rate, a barrier per stage, a start and an epilogue
             const bool pairs = wgs > 256 && q.lds_bytes <= 80 * 1024;
             const double k = (double)((wgs + 255) / 256);
-            const double items = q.IPT * q.PH * q.GX * (kc / 8) <= 256 ? 1.0 : t == 2 ? 1.5 : 1.2; // (two items per thread: spilled registers)
-            const double cost = k * q.nkb * items * (18.0 * 32 * 2 * t / (pairs ? 0.5 : 0.35) + (pairs ? 300 : 600)) + (pairs ? (k + 1) / 2 : k) * 8000.0;
+            // (128 accumulators, nine filter and six pixel fragments leave too little of 256 registers for the staging: one item
+            // per thread spills 4 to 13 of them, two up to 40)
+            const double spilled = items <= 256 ? 1.0 : 1.2;
+            const double cost = k * q.nkb * spilled * (18.0 * 32 * 2 * t / (pairs ? 0.5 : 0.35) + (pairs ? 300 : 600)) + (pairs ? (k + 1) / 2 : k) * 8000.0;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = q;

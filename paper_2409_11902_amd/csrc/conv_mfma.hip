@@ -1145,11 +1145,9 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 p.w_direct = 0;
                 p.w_kstep = (uint32_t)p.Mp * 32u;
                 p.w_bytes = (uint32_t)p.Mp * p.KCp * 2u;
-                base.tile = 3;
             } else if (use_tile() && shape_tile(p, &variant[*ncls])) {
                 p.tile = 1;
                 base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
-                base.tile = 1;
             } else if (!shape_gather(p, &variant[*ncls])) return false;
             cls[(*ncls)++] = p;
         }

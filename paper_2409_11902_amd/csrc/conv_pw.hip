@@ -35,7 +35,7 @@ namespace {
 
 using namespace tile;
 
-constexpr int KC = 64, KCS = KC + 8, KSTEPS = KC / 16, OCT = KC / 8;
+constexpr int KC = 64, KCS = KC + 8, KSTEPS = KC / 16;
 constexpr int kPT = 256, kGroups = kPT / 8; // pixels of a tile; items along the pixels
 constexpr int kEpRow = 64 * 2 + 16, kEpWave = 32 * kEpRow;
 constexpr int kBuf = kPT * KCS * 2 + kPT / 4 * 16; // (with the largest padding, see pad_of)

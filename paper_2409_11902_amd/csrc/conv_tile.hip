@@ -19,7 +19,8 @@
 // utilisation, a large library matrix product reaches 1.29 PFLOP/s on the same box); 512 -> 512 at 7 x 7
 // 98 -> 71 us; 128 -> 128 at 28 x 28, batch 128, 51 -> 36 us; 64 -> 64 at 56 x 56, batch 64, 43 -> 28 us.
 // Eight steps of filter fragments in flight instead of three, or a whole stage fetched at once through 32
-// registers, measured the same or slower; 64 x 224 pixels per wave with 512 registers does not fit (spills).
+// registers, measured the same or slower; 64 x 224 pixels per wave with 512 registers does not fit (spills).  Two 7-pixel
+// items per thread spill 10 to 14 registers, one in stages of 16 channels 2 to 4.
 // 64 output channels x 512 pixels in stages of 16 channels (a patch of 32 leaves LDS for one workgroup only):
 // 64 -> 64 at 56 x 56, batch 128, data gradient 47 -> 40 us against 256 pixels in stages of 32.
 #include <stdio.h>
@@ -65,7 +66,7 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int ppi = p.Hc * p.Wc;
     const int pix0 = p.IPT > 1 ? 0 : tau * PT;
     const int i0 = fdiv(pix0, p.m_wc);
-    const int hin0 = i0 * p.is + p.dhmin, win0 = p.dwmin;
+    const int hin0 = i0 * p.is + p.dhmin;
     const int m0 = (blockIdx.y * WM + wm) * 64;
 
     PatchStage<ITEMS, GW, KC, 8 / PARTS> in;
@@ -305,7 +306,6 @@ bool shape_tile(GatherParams &p, int *variant)
         if (sh.wm * 64 > b.Mp && sh.wm > 1) continue;
         GatherParams q = b;
         const int pt = sh.wn * sh.ni * 32, kcs = sh.kc + 8; // (LDS elements per patch pixel: an odd number of 16-byte units)
-        q.T = sh.kc;
         q.KCp = (p.KCin + sh.kc - 1) / sh.kc * sh.kc;
         q.nkb = q.kbs = q.KCp / sh.kc;
         q.IPT = 2 * ppi <= pt ? pt / ppi : 1;
