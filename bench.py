@@ -10,11 +10,12 @@ The default run covers all five workload configurations in one process.  The
 headline (`value`, `roofline`, `cpu_baseline`) is the deep small-spatial list
 (3x3 512->512 on 14x14 and 7x7 maps, batch 256): the list with the most flops per
 step and the one layer whose weight gradient outlasts launch overheads by far.
-The other configurations are reported under `workloads`: per layer the weight
+The other configurations are summed up under `workloads`, with the pooling-factor
+sweep k = 1, 2, 4 of the ResNet-18/ImageNet list; their layers -- the weight
 gradient against the roof that binds it, the cold compress rate, the bytes
-saved, and for the ResNet-18/ImageNet list the pooling-factor sweep k = 1, 2, 4.
+saved -- go to stderr.
 
-Prints ONE JSON line on stdout; tables go to stderr.
+Prints ONE JSON line on stdout, of a few KB; tables go to stderr.
 """
 from __future__ import annotations
 
@@ -549,6 +550,9 @@ def main():
 
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(specs, args.workload, synth, args.cpu_seconds, np)
+    # the layers of the other workloads are some 13 KB: for the log, not for whoever reads the last line of stdout
+    for w, r in results.items():
+        log("[bench] layers of " + w + ": " + json.dumps(r.pop("per_layer")))
     print(json.dumps(out), flush=True)
 
 

@@ -65,6 +65,49 @@ def test_forward_and_data_gradient(case):
             assert err <= TOL, (name, n, err)
 
 
+GENERAL = [
+    # name, N, C, K, H, W, R, S, pad_h, pad_w, stride: what else the planner sends there -- other paddings, one-row and
+    # one-column filters, and tensors whose last load or store ends in the middle of a dword
+    ("3x3 without padding", 90, 32, 64, 20, 28, 3, 3, 0, 0, 1),
+    ("3x3 without padding, stride 2", 170, 24, 72, 29, 30, 3, 3, 0, 0, 2),
+    ("3x3 padding 2", 80, 40, 48, 18, 20, 3, 3, 2, 2, 1),
+    ("3x3 padding 3 and 1", 80, 17, 64, 15, 24, 3, 3, 3, 1, 1),
+    ("1x9", 90, 32, 64, 20, 28, 1, 9, 0, 0, 1),
+    ("1x9 padding 4", 90, 33, 70, 14, 21, 1, 9, 0, 4, 1),
+    ("9x1", 90, 32, 64, 28, 20, 9, 1, 0, 0, 1),
+    ("9x1 padding 4", 90, 40, 65, 22, 15, 9, 1, 4, 0, 1),
+    ("odd numbers of elements", 101, 35, 65, 11, 27, 3, 3, 1, 1, 1),
+    ("odd numbers of elements, rows of 7", 481, 33, 67, 7, 7, 3, 3, 1, 1, 1),
+]
+
+
+@pytest.mark.parametrize("case", GENERAL, ids=[c[0] for c in GENERAL])
+def test_other_nine_tap_filters(case):
+    import torch
+    from gpu_util import Guarded, download, upload, workspace
+    name, N, C, K, H, W, R, S, ph, pw, st = case
+    d = B.make_desc(N, C, K, H, W, R, S, st, st, ph, pw)
+    fwd, dx = (B.cac_describe_plan(d, op).replace("class(0,0): ", "") for op in (B.OP_FWD_AND_COMPRESS, B.OP_BWD_DATA))
+    assert fwd.startswith("tile=") and (st == 2 or dx.startswith("tile=")), (fwd, dx)
+    P, Q = B.cac_out_shape(d)
+    rng = np.random.default_rng(sum(map(ord, name)))
+    make = lambda *s: synth.to_storage(rng.standard_normal(s, dtype=np.float32), synth.BF16)  # noqa: E731
+    X, Wt, b, dY = make(N, C, H, W), make(K, C, R, S), make(K), make(N, K, P, Q)
+    hp, wp, _, _ = B.cac_pooled_shape(d)
+    Y, Z, dX = (Guarded(s, torch.bfloat16) for s in ((N, K, P, Q), (N, C, hp, wp), (N, C, H, W)))
+    up = lambda a: upload(a, synth.BF16)  # noqa: E731
+    B.conv_fwd_and_compress(d, up(X), up(Wt), up(b), Y.t, Z.t, workspace(d, B.OP_FWD_AND_COMPRESS))
+    B.conv_bwd_data(d, up(Wt), up(dY), dX.t, workspace(d, B.OP_BWD_DATA))
+    torch.cuda.synchronize()
+    Y.check("Y"), Z.check("Z"), dX.check("dX")
+    g = oracle.ConvGeom(N, C, K, H, W, R, S, st, st, ph, pw)
+    f = [a.astype(np.float64) for a in (X, Wt, b, dY)]
+    for what, out, want in (("Y", Y, oracle.conv_fwd(g, f[0], f[1], f[2])), ("dX", dX, oracle.conv_dx(g, f[1], f[3]))):
+        got = download(out.t)
+        for n in range(N):
+            assert np.linalg.norm(got[n] - want[n]) <= TOL * np.linalg.norm(want[n]), (name, what, n)
+
+
 STRIDE2 = [
     # name, N, C, K, H, W: dY rows of a multiple of 4, of 2, of odd length; a last input row that only some classes have
     ("16-byte stores", 3, 64, 96, 16, 24),
@@ -76,6 +119,7 @@ STRIDE2 = [
     ("one column of pairs", 6, 20, 16, 9, 2),
     ("tile ends inside a block", 2, 130, 70, 30, 28),
     ("long rows", 1, 16, 48, 6, 120),
+    ("odd number of dY elements", 5, 33, 65, 13, 14),
 ]
 
 
