@@ -533,7 +533,8 @@ def main():
         out["workloads"] = results
         sweep = k_sweep(results)
         if sweep:
-            out["k_sweep_resnet18_imagenet"] = sweep
+            log("[bench] pooling-factor sweep: " + json.dumps(sweep))
+            out["k_sweep_resnet18_imagenet"] = [{"layer": e["layer"], **{f"dw_us_{k}": e[k]["dw_us"] for k in e if k.startswith("k")}} for e in sweep]
         # compress on the large tensors of the whole run (>= 49 MiB), bytes over time
         big = [e for w in list(results.values()) + [head] for e in w["per_layer"] if e["x_bytes"] >= (49 << 20)]
         if big:
