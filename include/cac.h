@@ -36,10 +36,11 @@
  *     capturing them.
  *   - Extents: N, C_in, C_out, H, W <= 2^24; filter, stride, padding, pooling tile <= 2^15;
  *     every tensor below 2^31 elements (CAC_ERR_UNSUPPORTED otherwise).
- *   - Infinities and NaN: in float forward passes and data gradients, and in bfloat16 ones of more
- *     than nine taps or a stride above 2, a tap that lies in the padding is no term of a sum.  The
- *     matrix-core kernels multiply a zero there: an infinite or NaN weight (for dW: dY) then gives
- *     NaN at pixels whose tap it never met.
+ *   - Infinities and NaN: where cac_describe_plan names a conv_lds or generic kernel -- float, and
+ *     bfloat16 geometries without a matrix-core kernel -- a tap of the forward pass or the data
+ *     gradient that lies in the padding is no term of a sum.  The matrix-core kernels multiply a
+ *     zero there: an infinite or NaN weight (for dW: dY) then gives NaN at pixels whose tap it
+ *     never met.
  *   - No C++ exception crosses this boundary.
  */
 #ifndef CAC_H
