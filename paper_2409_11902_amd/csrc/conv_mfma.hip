@@ -1067,6 +1067,20 @@ bool use_tile()
     return true;
 }
 
+// A 1 x 1 stride-1 launch: conv_pw.hip (p.tile = 3), or the gather where that is the faster one and can (rows that fit LDS).
+bool plan_pw(GatherParams &p, bool pool, bool record_free, int *variant)
+{
+    GatherParams pw = p, ga = p;
+    int pw_variant, ga_variant;
+    bool gather = false;
+    if (!shape_pw(pw, pool, record_free, &pw_variant, &gather)) return false;
+    gather = gather && shape_gather(ga, &ga_variant);
+    p = gather ? ga : pw;
+    p.tile = gather ? 0 : 3;
+    *variant = gather ? ga_variant : pw_variant;
+    return true;
+}
+
 // Whole 2 x 2 tiles, rows a multiple of 8 pixels: the pooled map falls out of the repack.
 bool record_in_repack(const Geom &g) { return !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4); }
 
@@ -1094,8 +1108,8 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
         p.Hin = g.H / 2; p.Win = g.W / 2; p.is = 1;
     }
     p.KCin = g.C;
-    if (use_tile() && shape_pw(p, !g.pmax && g.kh == 2 && g.kw == 2, record_in_repack(g), variant)) {
-        p.tile = 3;
+    if (use_tile() && plan_pw(p, !g.pmax && g.kh == 2 && g.kw == 2, record_in_repack(g), variant)) {
+        if (!p.tile) return true;
         p.w_direct = p.w_direct && g.C % 16 == 0; // (rows of W are whole fragments)
         p.w_kstep = p.w_direct ? 32u : (uint32_t)p.Mp * 32u;
         p.w_bytes = p.w_direct ? (uint32_t)g.K * g.C * 2u : (uint32_t)p.Mp * p.KCp * 2u;
@@ -1140,8 +1154,7 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 }
             if (p.ntaps == 0) { *empty_class = true; continue; }
             p.KCin = g.K;
-            if (use_tile() && shape_pw(p, false, false, &variant[*ncls])) {
-                p.tile = 3;
+            if (use_tile() && plan_pw(p, false, false, &variant[*ncls])) {
                 p.w_direct = 0;
                 p.w_kstep = (uint32_t)p.Mp * 32u;
                 p.w_bytes = (uint32_t)p.Mp * p.KCp * 2u;

@@ -292,8 +292,9 @@ const Shape kShapes[] = {{2, 1, 4, launch_shape<2, 1, 4>}, {4, 2, 2, launch_shap
 
 // Plans a 1 x 1 stride-1 launch (p: N, M, Mp, KCin, Hin, Win, Hc, Wc filled in); false when it is not its own.
 // pool: the 2 x 2 mean record of the input is wanted (p.pw_pool tells whether the launch forms it); record_free: the
-// launches of conv_mfma.hip would form it in their repack.
-bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant)
+// launches of conv_mfma.hip would form it in their repack.  *gather: those launches, where they take the layer, measured
+// the faster ones.
+bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather)
 {
     if (p.ntaps != 1 || p.os != 1 || p.is != 1 || p.decim || p.dh[0] || p.dw[0] || p.Hin != p.Hc || p.Win != p.Wc) return false;
     GatherParams q = p;
@@ -331,17 +332,17 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant)
     const long wgs = px_tiles * ((q.Mp / 64 + kShapes[v].wm - 1) / kShapes[v].wm);
     // A handful of workgroups with a long sum each: the launches of conv_mfma.hip share out the channels (512 -> 128 at
     // 28 x 28, batch 4, 32 workgroups of 8 stages: 18.8 against 20.1 us; 2048 -> 512 at 7 x 7, batch 8: 36 against 42).
-    if (wgs < 64 && q.nkb >= 8) return false;
+    *gather = wgs < 64 && q.nkb >= 8;
     // Planes of two or four pixels fill half of a tile's items at most (512 -> 1024 at 2 x 2, batch 1500, data gradient: 22
     // against 45 us).  Single pixels a seventh, but those the gather copies one by one (1024 -> 1024, batch 2048: 134
     // against 66 us).
-    if (ppi <= 4 && ppi % 2 == 0 && wgs >= 64 && q.nkb >= 4) return false;
+    *gather |= ppi <= 4 && ppi % 2 == 0 && wgs >= 64 && q.nkb >= 4;
     // The same for more of them where the stages pool (803 -> 73 at 16 x 16, batch 32, 64 workgroups: 18.6 against 32.0 us;
     // of 400 random layers those of such lengths ran at 0.9-1.35 of the gather's time, at 0.7 from 256 workgroups on), and
     // for any length where the record would need a launch of its own that the gather's repack saves (45 -> 20 at 8 x 8,
     // batch 168: 10.4 against 13.1 us; from 256 workgroups on 0.83 of the gather's time all the same).
-    if (q.pw_pool && ((wgs < 128 && q.nkb >= 4) || (wgs < 256 && q.nkb >= 8))) return false;
-    if (!q.pw_pool && wgs < 256 && record_free) return false;
+    *gather |= q.pw_pool && ((wgs < 128 && q.nkb >= 4) || (wgs < 256 && q.nkb >= 8));
+    *gather |= !q.pw_pool && wgs < 256 && record_free;
     // Fragments from W itself touch 32 lines each, repacked ones 8, but save the repack launch: faster on small inputs
     // (256 -> 64 at 56 x 56, batch 2: 12.2 against 14.2 us) and while a workgroup of 128 channels has few stages
     // (512 -> 128 at 28 x 28, 2048 of them: 28.6 against 29.9 us; 384 -> 359 at 9 x 33, batch 139, 5000: 65 against 59).

@@ -22,6 +22,10 @@ from paper_2409_11902_amd import binding as B
     ((198, 10, 14, 68, 68), 2, "pointwise", False),
     ((20, 10, 14, 68, 68), 2, "pointwise", True),
     ((198, 33, 14, 68, 68), 2, "pointwise", True),
+    # rows that the gather's LDS has no room for stay
+    ((1, 16, 16, 2, 504), 2, "pointwise", False),
+    ((1, 700, 16, 3, 1000), 1, "pointwise", False),
+    ((2, 700, 16, 8, 104), 2, "gather", False),
     # planes of two or four pixels
     ((199, 864, 1295, 2, 2), 4, "gather", False),
     ((199, 864, 1295, 3, 2), 4, "pointwise", False),
