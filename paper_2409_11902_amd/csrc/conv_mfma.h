@@ -54,7 +54,7 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant);
 hipError_t launch_dx2(const GatherParams &p, int variant, hipStream_t st);
 int describe_dx2(const GatherParams &p, int variant, char *buf, size_t len);
 // conv_pw.hip: 1 x 1 stride-1 layers
-bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather);
+bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather, bool *gather_whole);
 hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st);
 int describe_pw(const GatherParams &p, int variant, char *buf, size_t len);
 

@@ -1072,9 +1072,9 @@ bool plan_pw(GatherParams &p, bool pool, bool record_free, int *variant)
 {
     GatherParams pw = p, ga = p;
     int pw_variant, ga_variant;
-    bool gather = false;
-    if (!shape_pw(pw, pool, record_free, &pw_variant, &gather)) return false;
-    gather = gather && shape_gather(ga, &ga_variant);
+    bool gather, gather_whole;
+    if (!shape_pw(pw, pool, record_free, &pw_variant, &gather, &gather_whole)) return false;
+    gather = (gather || gather_whole) && shape_gather(ga, &ga_variant) && (gather || ga.ksplit == 1);
     p = gather ? ga : pw;
     p.tile = gather ? 0 : 3;
     *variant = gather ? ga_variant : pw_variant;

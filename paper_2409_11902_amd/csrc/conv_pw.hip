@@ -293,8 +293,8 @@ const Shape kShapes[] = {{2, 1, 4, launch_shape<2, 1, 4>}, {4, 2, 2, launch_shap
 // Plans a 1 x 1 stride-1 launch (p: N, M, Mp, KCin, Hin, Win, Hc, Wc filled in); false when it is not its own.
 // pool: the 2 x 2 mean record of the input is wanted (p.pw_pool tells whether the launch forms it); record_free: the
 // launches of conv_mfma.hip would form it in their repack.  *gather: those launches, where they take the layer, measured
-// the faster ones.
-bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather)
+// the faster ones; *gather_whole: where they also need no finishing launch.
+bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather, bool *gather_whole)
 {
     if (p.ntaps != 1 || p.os != 1 || p.is != 1 || p.decim || p.dh[0] || p.dw[0] || p.Hin != p.Hc || p.Win != p.Wc) return false;
     GatherParams q = p;
@@ -330,6 +330,10 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     if (const char *f = getenv("CAC_PW_SHAPE")) v = atoi(f);
 #endif
     const long wgs = px_tiles * ((q.Mp / 64 + kShapes[v].wm - 1) / kShapes[v].wm);
+    // Fragments from W itself touch 32 lines each, repacked ones 8, but save the repack launch: faster on small inputs
+    // (256 -> 64 at 56 x 56, batch 2: 12.2 against 14.2 us) and while a workgroup of 128 channels has few stages
+    // (512 -> 128 at 28 x 28, 2048 of them: 28.6 against 29.9 us; 384 -> 359 at 9 x 33, batch 139, 5000: 65 against 59).
+    q.w_direct = v == 1 ? wgs * q.nkb <= 2560 : q.nkb <= 2 || (q.nkb <= 8 && wgs * q.nkb <= 256);
     // A handful of workgroups with a long sum each: the launches of conv_mfma.hip share out the channels (512 -> 128 at
     // 28 x 28, batch 4, 32 workgroups of 8 stages: 18.8 against 20.1 us; 2048 -> 512 at 7 x 7, batch 8: 36 against 42).
     *gather = wgs < 64 && q.nkb >= 8;
@@ -337,16 +341,21 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     // against 45 us).  Single pixels a seventh, but those the gather copies one by one (1024 -> 1024, batch 2048: 134
     // against 66 us).
     *gather |= ppi <= 4 && ppi % 2 == 0 && wgs >= 64 && q.nkb >= 4;
-    // The same for more of them where the stages pool (803 -> 73 at 16 x 16, batch 32, 64 workgroups: 18.6 against 32.0 us;
-    // of 400 random layers those of such lengths ran at 0.9-1.35 of the gather's time, at 0.7 from 256 workgroups on), and
-    // for any length where the record would need a launch of its own that the gather's repack saves (45 -> 20 at 8 x 8,
-    // batch 168: 10.4 against 13.1 us; from 256 workgroups on 0.83 of the gather's time all the same).
-    *gather |= q.pw_pool && ((wgs < 128 && q.nkb >= 4) || (wgs < 256 && q.nkb >= 8));
-    *gather |= !q.pw_pool && wgs < 256 && record_free;
-    // Fragments from W itself touch 32 lines each, repacked ones 8, but save the repack launch: faster on small inputs
-    // (256 -> 64 at 56 x 56, batch 2: 12.2 against 14.2 us) and while a workgroup of 128 channels has few stages
-    // (512 -> 128 at 28 x 28, 2048 of them: 28.6 against 29.9 us; 384 -> 359 at 9 x 33, batch 139, 5000: 65 against 59).
-    q.w_direct = v == 1 ? wgs * q.nkb <= 2560 : q.nkb <= 2 || (q.nkb <= 8 && wgs * q.nkb <= 256);
+    // The same for more of them, or for shorter sums, where the stages pool, and every tile of output channels pools anew
+    // (1299 -> 1095 at 12 x 12, batch 8, 144 workgroups: 28.9 against 54.2 us; 803 -> 73 at 16 x 16, batch 32, 64 of them:
+    // 18.6 against 32.0).  Of random layers those within the lines ran at 1.1-1.65 of the gather's time in the mean, those
+    // just past them at 0.75-1.04.  Fewer than eight stages only if rows of W are not whole items: the filter's repack, a
+    // launch of its own here, then takes longer (250 -> 16 at 16 x 16, batch 6: 14.4 against 13.3 us; but 256 -> 64 at
+    // 56 x 56, batch 2: 11.7 against 15.8; 256 -> 128, batch 4, which repacks too: 14.2 against 16.2).
+    if (q.pw_pool && (q.nkb >= 8 || (q.nkb >= 4 && q.KCin % 8))) {
+        const bool one = wgs == px_tiles; // one tile of output channels
+        *gather |= one ? wgs < (q.nkb >= 16 ? 128 : q.nkb >= 8 || record_free ? 64 : 0)
+                       : wgs < (q.nkb >= 8 ? 256 : record_free ? 128 : 64);
+    }
+    // For any length where the record would need a launch of its own here that the gather's repack saves (45 -> 20 at 8 x 8,
+    // batch 168: 10.4 against 13.1 us; 1.2 of its time in the mean, 0.83 from 256 workgroups on), unless the gather shares
+    // out its channels, which is a launch more as well (1.0).
+    *gather_whole = !q.pw_pool && wgs < 256 && record_free;
     *variant = v;
     p = q;
     return true;

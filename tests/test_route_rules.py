@@ -12,12 +12,26 @@ from paper_2409_11902_amd import binding as B
     ((168, 45, 20, 8, 8), 4, "pointwise", False),
     ((1050, 45, 20, 8, 8), 2, "pointwise", False),      # ... which no longer decides from 256 workgroups on
     ((168, 45, 20, 9, 9), 2, "pointwise", False),
+    ((30, 160, 48, 8, 8), 2, "gather", False),
+    ((30, 448, 48, 8, 8), 2, "pointwise", False),       # ... nor where the gather would share out its channels
     # pooled on the way: only with enough workgroups for the length of the sum
-    ((32, 803, 73, 16, 16), 2, "gather", False),
-    ((64, 803, 73, 16, 16), 2, "gather", False),
+    ((16, 803, 73, 16, 16), 2, "gather", False),
+    ((127, 803, 73, 16, 16), 2, "gather", False),
     ((128, 803, 73, 16, 16), 2, "pointwise", True),
-    ((32, 200, 73, 16, 16), 2, "gather", False),
+    ((32, 201, 73, 16, 16), 2, "gather", False),
+    ((64, 201, 73, 16, 16), 2, "pointwise", True),
+    ((31, 201, 73, 12, 12), 2, "gather", False),
+    ((32, 201, 73, 12, 12), 2, "pointwise", True),
     ((32, 190, 73, 16, 16), 2, "pointwise", True),
+    # ... more of them where a second tile of output channels pools the same input once more
+    ((63, 201, 64, 16, 16), 2, "gather", False),
+    ((64, 201, 64, 16, 16), 2, "pointwise", True),
+    ((31, 201, 64, 12, 12), 2, "pointwise", True),
+    ((60, 201, 73, 16, 16), 2, "gather", False),
+    ((60, 200, 73, 16, 16), 2, "pointwise", True),      # (rows of W that are whole items)
+    ((64, 803, 64, 16, 16), 2, "pointwise", True),
+    ((127, 1300, 64, 16, 16), 2, "gather", False),
+    ((128, 1300, 64, 16, 16), 2, "pointwise", True),
     # ... and not by the few threads that have channels to move
     ((198, 10, 14, 68, 68), 2, "pointwise", False),
     ((20, 10, 14, 68, 68), 2, "pointwise", True),
