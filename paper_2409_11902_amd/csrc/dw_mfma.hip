@@ -146,10 +146,16 @@ __device__ __forceinline__ u32x4 mask8(int left)
     return m;
 }
 
+// FL: log2 of the columns of one phase that a pooled value covers (-1: half a column, an uncompressed record under stride
+// 2), built into the 3 x 3 stride-2 kernels; kAnyFl: read from the plan.  With all forms of the expansion in one kernel
+// the copy waves of two phases spilled 158 registers (WIDEZ: 233) to scratch, more traffic than the operands: 128 -> 256 at
+// 28 x 28, batch 128, uncompressed 61 -> 42 us; 150 random layers, tiles of 1, 2 and 4, 0.72 of the time, none slower.
+constexpr int kAnyFl = -2;
+
 // SC: the number of 8-pixel segments per output row when it is known at compile
 // time (0: read from the plan).  With SC the walk along a row is unrolled and the
 // segment offsets become immediates of the LDS reads.
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, bool WIDEZ>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, bool WIDEZ, int FL>
 __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParams p)
 {
     constexpr int kMaxDy = max_dy(WIDEZ), kMaxZ = max_z(WIDEZ);
@@ -228,7 +234,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
         const uint32_t z_lds = rows_elems + TILE_O * p.dy_ostride + zc * p.x_cstride + z_row * slot_w;
         const uint32_t z_lstep = z_cpp * p.x_cstride;
         const bool dy_odd = p.Q & 1, z_odd = p.Wp & 1;
-        const int f_log2 = p.kw_log2 - (SG == 2 ? 1 : 0);        // columns of one phase per pooled value, log2
+        const int f_log2 = FL != kAnyFl ? FL : p.kw_log2 - (SG == 2 ? 1 : 0); // columns of one phase per pooled value, log2
         const bool ragged = (p.W & ((1 << p.kw_log2) - 1)) != 0; // the last pooling tile reaches past W
         const rsrc_t rs_dy = make_rsrc(p.dY, (uint32_t)p.N * p.K * p.P * p.Q * 2u);
         const rsrc_t rs_z = make_rsrc(p.Z, (uint32_t)p.N * p.C * p.Hp * p.Wp * 2u);
@@ -831,10 +837,10 @@ struct Variant {
     hipError_t (*launch)(const DwMfmaParams &, dim3, hipStream_t);
 };
 
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, bool WIDEZ = false>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, bool WIDEZ = false, int FL = kAnyFl>
 hipError_t launch_fixed(const DwMfmaParams &p, dim3 grid, hipStream_t st)
 {
-    auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ>;
+    auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ, FL>;
     // (per instantiation; once per process, whichever host thread comes first)
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
@@ -867,9 +873,16 @@ hipError_t launch_variant(const DwMfmaParams &p, dim3 grid, hipStream_t st)
         }
     }
     if constexpr (S == 3 && SG == 2) {
-        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true>(p, grid, st);
+        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true, -1>(p, grid, st);
+        switch (p.kw_log2) {
+        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, -1>(p, grid, st);
+        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 0>(p, grid, st);
+        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 1>(p, grid, st);
+        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 2>(p, grid, st);
+        }
+    } else {
+        return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
     }
-    return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
 }
 
 const Variant kVariants[] = {
@@ -1051,7 +1064,7 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
     // buffer loads address with 32-bit byte offsets and use 2^31 as "no load"
     if ((long)g.N * g.K * g.P * g.Q >= (1L << 30) || (long)g.N * g.C * g.Hp * g.Wp >= (1L << 30)) return false;
 
-    // The split of the copy registers (calls in us, usual / WIDEZ: 128 -> 256 at 28 x 28, batch 128, 56 chunks to a
+    // The split of the copy registers (calls in us, usual / WIDEZ, both while they spilled: 128 -> 256 at 28 x 28, batch 128, 56 chunks to a
     // workgroup, 73 / 63; 20 -> 76 at 4 x 4, batch 121, two of them, 15.7 / 19.3; of 700 random layers WIDEZ took 0.75 of the
     // time from sixteen chunks on and 1.05 below eight).  Where only WIDEZ fits -- long rows -- the kernel of dw_tiled.hip is
     // the other choice: four times as slow in the mean, but 12.4 against 19.3 us for 9 -> 9 at 82 x 82, batch 1.

@@ -1,6 +1,6 @@
-"""GPU parity of the 3 x 3 stride-2 weight gradient from an uncompressed record (tiles of one column), whose copy waves
+"""GPU parity of the 3 x 3 stride-2 weight gradient.  From an uncompressed record (tiles of one column), whose copy waves
 split their registers differently: odd and even maps, rows of one to eight segments, ragged channels, tiles of 1 x 1
-and 2 x 1."""
+and 2 x 1.  From pooled records: every width of tile, which each have a kernel, with whole and with ragged tiles."""
 from __future__ import annotations
 
 import numpy as np
@@ -29,14 +29,12 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
-def test_weight_gradient(case):
+def check(name, N, C, K, H, W, kh, kw, wide):
     import torch
     from gpu_util import Guarded, download, upload, workspace
-    name, N, C, K, H, W, kh, wide = case
     spec = synth.LayerSpec(name, N, C, K, H, W, stride=2)
     t = synth.make_inputs(spec, "dw-uncompressed-s2", tensors=("X", "dY"))
-    d = B.desc_from_spec(spec, pool_kh=kh, pool_kw=1)
+    d = B.desc_from_spec(spec, pool_kh=kh, pool_kw=kw)
     plan = B.cac_describe_plan(d, B.OP_BWD_WEIGHT_COMPRESSED)
     assert plan.startswith("dw_mfma") and ("registers split towards Z" in plan) == wide, plan
     hp, wp, _, _ = B.cac_pooled_shape(d)
@@ -46,9 +44,21 @@ def test_weight_gradient(case):
     torch.cuda.synchronize()
     Z.check("Z"), dW.check("dW")
     g = oracle.ConvGeom(N, C, K, H, W, 3, 3, 2, 2, 1, 1)
-    want = oracle.conv_dw(g, oracle.inflate(download(Z.t), H, W, kh, 1), t["dY"].astype(np.float64))
+    want = oracle.conv_dw(g, oracle.inflate(download(Z.t), H, W, kh, kw), t["dY"].astype(np.float64))
     # identical bfloat16 operands, exact products: only the order of at most N * P * Q float additions differs, about
     # sqrt(42140) * 2^-24 = 1.2e-5 of the result's norm; any wrong term is orders above
     for tap in range(9):
         w = want[:, :, tap // 3, tap % 3]
         assert np.linalg.norm(download(dW.t)[:, :, tap // 3, tap % 3] - w) <= 2e-5 * np.linalg.norm(w), (name, tap)
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_weight_gradient(case):
+    name, N, C, K, H, W, kh, wide = case
+    check(name, N, C, K, H, W, kh, 1, wide)
+
+
+@pytest.mark.parametrize("kw", [2, 4, 8])
+@pytest.mark.parametrize("shape", [(9, 33, 65, 27, 29), (300, 128, 260, 14, 16)], ids=["ragged, pixels over the waves", "64 x 64 tile"])
+def test_weight_gradient_pooled(shape, kw):
+    check(f"tiles of {kw} columns", *shape, kw, kw, False)
