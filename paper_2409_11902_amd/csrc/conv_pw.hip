@@ -267,6 +267,252 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
     }
 }
 
+// ---- few pixels: every wave its own tile, the channels of a tile shared by KS waves
+// On small maps the kernel above has a workgroup or less for a compute unit, four waves that wait for the same loads and
+// barriers (2048 -> 512 at 7 x 7, batch 64: 128 workgroups of 32 stages in a row, 37 us, matrix pipe 6 % busy).  Here a wave
+// owns 64 output channels x 64 pixels and stages them for itself: its 64 lanes are the 64 items of a stage (8 along the
+// pixels, 8 along the channels), its part of LDS is its own, and no barrier stands between two stages, so that the eight or
+// twelve waves of a compute unit are at different points and fill each other's gaps.  Items of a tile follow one another
+// from image to image.  KS waves take every KS-th stage of one tile and add their sums through LDS, in wave order.
+// EPI = 16, planes of an odd size up to 56: a tile is whole images, whose 64 channels are one run of memory each, and the
+// result leaves in 16-byte stores of that run instead of element by element.
+constexpr int kWt = 64, kWtItems = 8;                            // pixels of a wave's tile; items along them
+constexpr int kWtBytes = kWt * KCS * 2 + kWtItems * 16;         // a wave's staging buffer
+constexpr int kBlk = 64 * 16 * 4;                                // the sums of one 32 x 32 block
+constexpr int kWtRow = 32 * 2 + 16;                              // epilogue: a channel's 32 pixels
+constexpr int wt_lds(int KS)
+{
+    const int red = KS > 1 ? 4 * (KS - 1) * (4 / KS) * kBlk : 0;
+    return red > 4 * kWtBytes ? red : 4 * kWtBytes;
+}
+
+template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) conv_pw_wave_kernel(GatherParams p)
+{
+    constexpr int PT = 4 / KS, KEEP = 4 / KS; // pixel tiles of a workgroup; blocks of 32 x 32 that a wave finishes
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int ks = wave % KS, pt = wave / KS;
+    // every XCD works on consecutive pixel tiles, all output channels of one after the other: its L2 keeps the pixels
+    const int per_xcd = gridDim.x >> 3, v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), mtiles = p.Mp / 64;
+    if (v >= p.tiles_per_img * mtiles) return; // (tiles_per_img: groups of PT pixel tiles)
+    const int grp = v / mtiles, m0 = (v - grp * mtiles) * 64;
+    const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb, nitems = p.N * p.GX;
+    constexpr bool RUNS = EPI == 16;
+    const int f0 = (grp * PT + pt) * (RUNS ? p.IPT * p.GX : kWtItems); // the tile's first item
+
+    const int gidx = lane & 7, oct = lane >> 3;
+    const int n_it = fdiv(f0 + gidx, p.m_gx);
+    const bool item = f0 + gidx < nitems && (!RUNS || gidx < p.IPT * p.GX);
+    const uint32_t e0 = item ? (uint32_t)(n_it * K + oct * 8) * ppi + (f0 + gidx - n_it * p.GX) * GW : kNoElem;
+    auto pad_of = [](int px) { return GW == 8 ? (px >> 3) * 16 : 0; };
+    const uint32_t wbase = lds0 + wave * kWtBytes, l0 = wbase + (uint32_t)(gidx * GW * KCS + oct * 8) * 2u + pad_of(gidx * GW);
+    const rsrc_t rs_in = make_rsrc(p.in, (uint32_t)p.N * K * ppi * 2u);
+    u32x4 r[8];
+    auto fetch = [&](int s) {
+        uint32_t e = e0 + (uint32_t)(s * KC) * ppi;
+        opaque(e);
+        const int nvalid = s < nkb ? K - (s * KC + oct * 8) : 0; // channels that exist
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t ei = i < nvalid ? e : kNoElem;
+            r[i] = __builtin_amdgcn_raw_buffer_load_b128(rs_in, (GW == 7 ? ei & ~1u : ei) * 2u, 0, 0);
+            e += ppi;
+        }
+    };
+    auto put = [&](int s) {
+        if constexpr (GW == 7) {
+            const uint32_t par = e0 + (uint32_t)(s * KC) * ppi;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t sh = ((par + i * ppi) & 1u) * 16u;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) r[i][k] = __builtin_amdgcn_alignbit(r[i][k + 1], r[i][k], sh);
+                r[i][3] >>= sh;
+            }
+        }
+#pragma unroll
+        for (int px = 0; px < GW; ++px) {
+            u32x4 x; // pixel px of the 8 channels
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t lo = r[2 * k][px / 2], hi = r[2 * k + 1][px / 2];
+                x[k] = (px & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+            }
+            *(lds_u32x4_ptr)(uintptr_t)(l0 + px * (KCS * 2)) = x;
+        }
+    };
+    // (a wave reads what it wrote itself: LDS serves a wave's requests in order)
+    auto wave_sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    uint32_t pbase[2];
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni) pbase[ni] = wbase + 16u * half + (uint32_t)((ni * 32 + l32) * KCS * 2 + pad_of(ni * 32 + l32));
+    const rsrc_t rs_w = make_rsrc(p.wt, p.w_bytes);
+    uint32_t wlane[2];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+        wlane[mi] = p.w_direct ? (m0 + mi * 32 + l32 < p.M ? (uint32_t)((m0 + mi * 32 + l32) * K + 8 * half) * 2u : kNoLoad)
+                               : (uint32_t)((m0 >> 5) + mi) * kFrag + lane * 16u;
+    const int ksteps_all = p.KCp / 16;
+    u32x4 w[KSTEPS][2];
+    auto fetch_w = [&](int s, int kk) {
+        const int step = s * KSTEPS + kk; // (16-channel steps past the last one: zeros)
+        const uint32_t so = (uint32_t)min(step, ksteps_all - 1) * p.w_kstep;
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) w[kk][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, step < ksteps_all ? wlane[mi] : kNoLoad, so, 0);
+    };
+    f32x16 acc[4]; // block mi + 2 * ni
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[b][j] = 0.f;
+
+    fetch(ks);
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk) fetch_w(ks, kk);
+    for (int s = ks; s < nkb; s += KS) {
+        put(s);
+        wave_sync();
+        fetch(s + KS); // (past the end: nothing is loaded)
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            union { u32x4 u; bf16x8 v; } a[2], b[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                b[i].u = lds16(pbase[i] + 32 * kk);
+                a[i].u = w[kk][i];
+            }
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < 2; ++mi) acc[2 * ni + mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[ni].v, a[mi].v, acc[2 * ni + mi], 0, 0, 0);
+            fetch_w(s + KS, kk);
+        }
+        wave_sync();
+    }
+    // ---- the sums of the KS waves: wave ks finishes blocks [ks * KEEP, (ks + 1) * KEEP) and is handed the others' parts of
+    // them, red[tile][finishing wave][source wave, itself left out][block]
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    typedef __attribute__((address_space(3))) f32x4 *lds_f32x4_ptr;
+    const uint32_t red = lds0 + pt * (KS * (KS - 1) * KEEP * kBlk);
+    f32x16 sum[KEEP];
+    if constexpr (KS > 1) {
+        __syncthreads(); // (all staging buffers are dead)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int dst = b / KEEP;
+            if (dst == ks) continue;
+            const uint32_t a = red + (uint32_t)(((dst * (KS - 1) + (ks < dst ? ks : ks - 1)) * KEEP + b % KEEP) * kBlk) + lane * 16;
+#pragma unroll
+            for (int jq = 0; jq < 4; ++jq)
+                *(lds_f32x4_ptr)(uintptr_t)(a + jq * 1024) = f32x4{acc[b][4 * jq], acc[b][4 * jq + 1], acc[b][4 * jq + 2], acc[b][4 * jq + 3]};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int kb = 0; kb < KEEP; ++kb) {
+            f32x16 own = acc[kb];
+#pragma unroll
+            for (int d = 1; d < KS; ++d)
+                if (d == ks) own = acc[d * KEEP + kb];
+#pragma unroll
+            for (int src = 0; src < KS; ++src) {
+                f32x16 t = own;
+                if (src != ks) {
+                    const uint32_t a = red + (uint32_t)(((ks * (KS - 1) + (src < ks ? src : src - 1)) * KEEP + kb) * kBlk) + lane * 16;
+#pragma unroll
+                    for (int jq = 0; jq < 4; ++jq) {
+                        const f32x4 q = *(lds_f32x4_ptr)(uintptr_t)(a + jq * 1024);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[4 * jq + e] = q[e];
+                    }
+                }
+                if (src == 0) sum[kb] = t;
+                else sum[kb] += t;
+            }
+        }
+        wave_sync();
+    } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) sum[b % KEEP] = acc[b];
+    }
+    // ---- epilogue: bias, bfloat16, [channel][pixel] rows in a part of LDS that only this wave uses (KS > 1: what it was handed)
+    const rsrc_t rs_out = make_rsrc(p.out, (uint32_t)p.N * p.M * ppi * 2u);
+    if constexpr (RUNS) { // [image][channel][pixel] of the whole tile, by the KS waves together
+        const uint32_t run = lds0 + pt * (64 * kWtItems * GW * 2);
+        __syncthreads(); // (what the others were handed, and read, lies there)
+#pragma unroll
+        for (int kb = 0; kb < KEEP; ++kb) {
+            const int b = ks * KEEP + kb, mi = b & 1, ni = b >> 1, m = m0 + mi * 32 + l32;
+            const float bias = (p.bias && m < p.M) ? bf16_to_f32(p.bias[m]) : 0.f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int idx = ni * 32 + 8 * (j / 4) + 4 * half + j % 4, it = idx / GW;
+                const int g = fdiv(it, p.m_gx), px = (it - g * p.GX) * GW + idx - it * GW;
+                if ((g < p.IPT) & (px < ppi))
+                    *(lds_u16_ptr)(uintptr_t)(run + (uint32_t)((g * 64 + mi * 32 + l32) * ppi + px) * 2u) = f32_to_bf16(sum[kb][j] + bias);
+            }
+        }
+        __syncthreads();
+        const int n0 = (grp * PT + pt) * p.IPT, pieces = 8 * ppi, have = min(64, p.M - m0) * ppi / 8; // 16-byte pieces of an image; of them inside
+        for (int q = lane + 64 * ks; q < p.IPT * pieces; q += 64 * KS) {
+            const int g = fdiv(q, p.m_w2), o = q - g * pieces;
+            const uint32_t off = ((n0 + g < p.N) & (o < have)) ? (uint32_t)((n0 + g) * p.M + m0) * ppi * 2u + o * 16u : kNoLoad;
+            __builtin_amdgcn_raw_buffer_store_b128(lds16(run + (uint32_t)q * 16u), rs_out, off, 0, 0);
+        }
+        return;
+    }
+    const uint32_t ep = KS > 1 ? red + (uint32_t)(ks * (KS - 1) * KEEP * kBlk) : wbase;
+    constexpr int LPR = 32 / (RUNS ? 1 : EPI), RPI = 64 / LPR; // lanes of a row; rows per pass over the lanes
+#pragma unroll
+    for (int kb = 0; kb < KEEP; ++kb) {
+        const int b = ks * KEEP + kb, mi = b & 1, ni = b >> 1;
+        const int mb = m0 + mi * 32;
+        const float bias = (p.bias && mb + l32 < p.M) ? bf16_to_f32(p.bias[mb + l32]) : 0.f;
+#pragma unroll
+        for (int jq = 0; jq < 4; ++jq)
+            *(lds_u32x2_ptr)(uintptr_t)(ep + l32 * kWtRow + (8 * jq + 4 * half) * 2) =
+                u32x2{f32x2_to_bf16x2(sum[kb][4 * jq] + bias, sum[kb][4 * jq + 1] + bias), f32x2_to_bf16x2(sum[kb][4 * jq + 2] + bias, sum[kb][4 * jq + 3] + bias)};
+        wave_sync();
+        const int seg = lane % LPR, idx = ni * 32 + seg * EPI, it = idx / GW;
+        const int n = fdiv(f0 + it, p.m_gx), px = (f0 + it - n * p.GX) * GW + idx - it * GW;
+        const bool ok = (it < kWtItems) & (f0 + it < nitems) & (px < ppi);
+#pragma unroll
+        for (int t = 0; t < 32 / RPI; ++t) {
+            const int row = t * RPI + lane / LPR, m = mb + row;
+            const uint32_t off = (ok & (m < p.M)) ? ((uint32_t)(n * p.M + m) * ppi + px) * 2u : kNoLoad;
+            const uint32_t src = ep + row * kWtRow + seg * (EPI * 2);
+            if constexpr (EPI == 8) __builtin_amdgcn_raw_buffer_store_b128(lds16(src), rs_out, off, 0, 0);
+            else if constexpr (EPI == 4) __builtin_amdgcn_raw_buffer_store_b64(*(lds_u32x2_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+            else if constexpr (EPI == 2) __builtin_amdgcn_raw_buffer_store_b32(*(lds_u32_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b16(*(lds_u16_ptr)(uintptr_t)src, rs_out, off, 0, 0);
+        }
+        wave_sync();
+    }
+}
+
+template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherParams &p, hipStream_t st)
+{
+    auto kern = conv_pw_wave_kernel<KS, GW, EPI>;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
+    if (attr_err != hipSuccess) return attr_err;
+    const int total = p.tiles_per_img * (p.Mp / 64);
+    hipLaunchKernelGGL(kern, dim3((total + 7) / 8 * 8), dim3(256), wt_lds(KS), st, p);
+    return hipGetLastError();
+}
+template <int KS> hipError_t launch_wave(const GatherParams &p, hipStream_t st)
+{
+    if (p.gw == 7) return p.store_px == 16 ? launch_wave_fixed<KS, 7, 16>(p, st) : launch_wave_fixed<KS, 7, 1>(p, st);
+    return p.store_px == 8 ? launch_wave_fixed<KS, 8, 8>(p, st) : p.store_px == 4 ? launch_wave_fixed<KS, 8, 4>(p, st)
+                                                                                  : launch_wave_fixed<KS, 8, 2>(p, st);
+}
+
 template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
 {
     auto kern = conv_pw_kernel<NI, WM, WN, FUSE, GW, EPI>;
@@ -287,6 +533,9 @@ template <int NI, int WM, int WN> hipError_t launch_shape(const GatherParams &p,
 }
 struct Shape { int ni, wm, wn; hipError_t (*launch)(const GatherParams &, hipStream_t); };
 const Shape kShapes[] = {{2, 1, 4, launch_shape<2, 1, 4>}, {4, 2, 2, launch_shape<4, 2, 2>}};
+constexpr int kWaveVariant = 2; // from here on: conv_pw_wave_kernel with KS = 1 and 4
+hipError_t (*const kWaves[])(const GatherParams &, hipStream_t) = {launch_wave<1>, launch_wave<4>};
+int waves_of(int variant) { return variant == kWaveVariant ? 1 : 4; }
 
 } // namespace
 
@@ -357,14 +606,57 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     // out its channels, which is a launch more as well (1.0).
     *gather_whole = !q.pw_pool && wgs < 256 && record_free;
     *variant = v;
+    // By waves, where the items are full (planes of 1 to 4 pixels: as above).  Measured on 600 random calls per direction against
+    // the launches above and the gather's: four waves to a tile take 0.4-0.75 of the time up to 256 tiles of 64 x 64 with eight
+    // stages or more (2048 -> 512 at 7 x 7, batch 64: 46.9 -> 28.8 us; the data gradient of 512 -> 2048 43.8 -> 24.4), 0.8-0.95 up to
+    // the lines below and with four to seven stages, 1.05-1.15 past them (wave tiles are 64 channels wide, and their operands
+    // come through L2 once per 64 x 64).  With three stages, or fewer, a hand-over costs what it saves (0.95-1.3), but many
+    // tiles of one wave each keep more loads in flight than the shapes above (0.8-0.95).
+    const int gx = (ppi + q.gw - 1) / q.gw;
+    const bool runs = q.gw == 7 && gx <= kWtItems && q.M % 8 == 0; // tiles of whole images, each a run of whole 16-byte pieces
+    const int ipt = runs ? kWtItems / gx : 1;
+    const long tiles = runs ? (p.N + ipt - 1) / ipt : ((long)p.N * gx + kWtItems - 1) / kWtItems, wt = tiles * (q.Mp / 64);
+    int ks = 0;
+    if (q.nkb >= 4 && wt < (q.nkb >= 8 ? 2048 : 1024)) ks = 4;
+    else if (q.nkb < 3 ? wt >= 2048 : q.nkb >= 4 && q.nkb < 8 && wt >= 4096) ks = 1;
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_PW_WAVE")) if (atoi(f) < 0) ks = 0;
+#endif
+    // Not where the record is pooled on the way, which is worth more than the waves, nor for fewer than eight tiles of a layer
+    // that the gather takes: those are too few to matter (1 in 50 random layers; 0.65 of the time) and keep its channel split
+    // in use and under test.
+    if (ks && !q.pw_pool && (!*gather || wt >= 8) && 2 * ppi > gx * q.gw && divides_exactly((uint64_t)p.N * gx + kWtItems * 4, gx)) {
+        q.GX = gx;
+        q.m_gx = magic_of(gx);
+        q.IPT = ipt;
+        q.ngrp = 1;
+        q.tile_px = kWt;
+        const int pt = 4 / ks;
+        q.tiles_per_img = (int)((tiles + pt - 1) / pt);
+        if (runs) {
+            q.store_px = 16;
+            q.m_w2 = magic_of(8 * ppi); // (16-byte pieces of an image; a tile has at most 448)
+        }
+        // fragments from W itself: 0.85-0.95 of the time with a repack launch for four waves to a tile, 1.04 for many tiles with
+        // long sums; 0.9-0.98 for one wave to a tile with one or two stages
+        q.w_direct = ks == 4 ? wt < 512 || q.nkb < 16 : q.nkb < 3;
+        *variant = kWaveVariant + (ks == 4);
+        *gather = *gather_whole = false;
+    }
     p = q;
     return true;
 }
 
-hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st) { return kShapes[variant].launch(p, st); }
+hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st)
+{
+    return variant >= kWaveVariant ? kWaves[variant - kWaveVariant](p, st) : kShapes[variant].launch(p, st);
+}
 
 int describe_pw(const GatherParams &p, int variant, char *buf, size_t len)
 {
+    if (variant >= kWaveVariant)
+        return snprintf(buf, len, "pointwise by waves tile=64ch x %dpx ch/pass=%d waves/tile=%d grid=%dx1x1 lds=%dB, input read in place", p.store_px == 16 ? p.IPT * p.Hc * p.Wc : kWtItems * p.gw, KC,
+                        waves_of(variant), (p.tiles_per_img * (p.Mp / 64) + 7) / 8 * 8, wt_lds(waves_of(variant)));
     const Shape &v = kShapes[variant];
     return snprintf(buf, len, "pointwise tile=%dch x %dpx ch/pass=%d img/tile=%d grid=%dx%dx1 lds=%dB%s, input read in place", 64 * v.wm, p.tile_px, KC, p.IPT,
                     p.tiles_per_img * p.ngrp, (p.Mp / 64 + v.wm - 1) / v.wm, 2 * kBuf, p.pw_pool ? ", pooled on the way" : "");
