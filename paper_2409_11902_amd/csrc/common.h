@@ -69,6 +69,9 @@ template <> struct Elem<bf16_t> {
 // launch status; operand shapes have been validated by the caller (api.hip).
 // compress.hip: true when the fast kernel covers the geometry and was launched (status in *err)
 bool launch_compress_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err);
+// ... and, bfloat16 only, with a filter's repack in the same launch (false: nothing has been launched)
+struct FilterRepack;
+bool launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st, hipError_t *err);
 hipError_t launch_compress_generic(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st);
 // conv_lds.hip: false when the geometry does not fit LDS (status in *err otherwise)
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err);

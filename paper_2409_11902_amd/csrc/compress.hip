@@ -11,6 +11,7 @@
 // Ragged edges follow the ceil/valid rule: a tile that sticks out is averaged
 // over the elements it really has.
 #include "chunk.h"
+#include "filter_repack.h"
 
 namespace cac {
 
@@ -81,12 +82,12 @@ __device__ __forceinline__ void pool_and_store(const Geom &g, const float (&v)[K
 }
 
 template <typename T, int EPC, int KH, int KW, bool PROD>
-__global__ void __launch_bounds__(256) compress_kernel(Geom g, const T *__restrict__ X, T *__restrict__ Z, int cpr,
-                                                       uint32_t total, double inv_cpr, double inv_hp, Producer pr)
+__device__ __forceinline__ void compress_body(const Geom &g, const T *__restrict__ X, T *__restrict__ Z, int cpr, uint32_t total,
+                                              double inv_cpr, double inv_hp, const Producer &pr, uint32_t block)
 {
     constexpr int OPC = EPC / KW; // pooled values per chunk
     static_assert(OPC >= 1, "");
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x;
+    const uint32_t idx = block * 256u + threadIdx.x;
     if (idx >= total) return;
     // idx -> (plane, pooled row i, chunk c), chunk fastest
     const uint32_t rowi = udiv(idx, inv_cpr);
@@ -163,6 +164,23 @@ __global__ void __launch_bounds__(256) compress_kernel(Geom g, const T *__restri
     }
     pool_and_store<T, EPC, KH, KW>(g, v, rows, w0, j0, Z + zoff);
 }
+template <typename T, int EPC, int KH, int KW, bool PROD>
+__global__ void __launch_bounds__(256) compress_kernel(Geom g, const T *__restrict__ X, T *__restrict__ Z, int cpr,
+                                                       uint32_t total, double inv_cpr, double inv_hp, Producer pr)
+{
+    compress_body<T, EPC, KH, KW, PROD>(g, X, Z, cpr, total, inv_cpr, inv_hp, pr, blockIdx.x);
+}
+// With a filter's repack in the blocks ahead: work of 4-5 us that costs a launch of its own, and a forward pass needs both.
+// Steps of 512 -> 512 at 7 x 7, batch 256: 192.8 -> 188.3 us; 128 -> 256 stride 2 at 28 x 28, batch 128: 120.3 -> 114.5; 72 -> 100 at
+// 27 x 30, batch 24: 49.1 -> 46.3.  (55 registers and 9 KB of LDS where the pooling alone takes 14-43 and none: no loss seen.)
+template <int EPC, int KH, int KW>
+__global__ void __launch_bounds__(256) compress_repack_kernel(Geom g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z, int cpr, uint32_t total,
+                                                              double inv_cpr, double inv_hp, FilterRepack f, unsigned nrep)
+{
+    __shared__ bf16_t sm[kFilterElems];
+    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, sm);
+    else compress_body<bf16_t, EPC, KH, KW, false>(g, X, Z, cpr, total, inv_cpr, inv_hp, Producer{}, blockIdx.x - nrep);
+}
 
 // ---- rows of 10, 12 or 14 elements (bfloat16, 2 x 2 tiles, an even number of rows) --------------
 // With the chunk kernel such a row is one and a half chunks, its pooled row five to seven 2-byte
@@ -172,16 +190,15 @@ __global__ void __launch_bounds__(256) compress_kernel(Geom g, const T *__restri
 // contiguous and start on a multiple of 16 bytes: they are written to a wave-private piece of LDS
 // and leave as whole 16-byte stores.  Sums and rounding as in the chunk kernel (bit-identical).
 template <int W, bool PROD>
-__global__ void __launch_bounds__(256) compress_narrow_kernel(Geom g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z,
-                                                              uint32_t total, double inv_hp, Producer pr)
+__device__ __forceinline__ void compress_narrow_body(const Geom &g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z, uint32_t total,
+                                                     double inv_hp, const Producer &pr, unsigned char *lds, uint32_t block)
 {
     constexpr int WP = W / 2;          // pooled values per thread = dwords per input row
     constexpr int XB = 4 * W;          // bytes of a thread's two rows
     constexpr int ZB = 2 * WP;         // bytes of its pooled row
-    __shared__ __align__(16) unsigned char lds[4 * 64 * (PROD ? XB + 2 * ZB : ZB)];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned char *zbuf = lds + wave * 64 * (PROD ? XB + 2 * ZB : ZB);
-    const uint32_t idx = blockIdx.x * 256u + threadIdx.x, first = idx - lane;
+    const uint32_t idx = block * 256u + threadIdx.x, first = idx - lane;
     const bool live = idx < total;
     const bool whole = first + 64 <= total; // every lane of the wave has a record
 
@@ -232,15 +249,37 @@ __global__ void __launch_bounds__(256) compress_narrow_kernel(Geom g, const bf16
     for (int j = 0; j < WP; ++j) ((bf16_t *)zbuf)[lane * WP + j] = zr[j];
     flush_records<ZB>(zbuf, (unsigned char *)Z, first, lane, whole, live);
 }
+template <int W, bool PROD>
+__global__ void __launch_bounds__(256) compress_narrow_kernel(Geom g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z,
+                                                              uint32_t total, double inv_hp, Producer pr)
+{
+    __shared__ __align__(16) unsigned char lds[4 * 64 * (PROD ? 6 * W : W)]; // (records: 2 rows of X; 1 of Z and of the producer's own)
+    compress_narrow_body<W, PROD>(g, X, Z, total, inv_hp, pr, lds, blockIdx.x);
+}
+template <int W>
+__global__ void __launch_bounds__(256) compress_narrow_repack_kernel(Geom g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z, uint32_t total,
+                                                                     FilterRepack f, unsigned nrep)
+{
+    __shared__ __align__(16) unsigned char lds[kFilterElems * 2 > 4 * 64 * W ? kFilterElems * 2 : 4 * 64 * W];
+    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, (bf16_t *)lds);
+    else compress_narrow_body<W, false>(g, X, Z, total, 0.0, Producer{}, lds, blockIdx.x - nrep);
+}
 
-template <typename T, int EPC> bool launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Producer *prod = nullptr)
+template <typename T, int EPC>
+bool launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Producer *prod = nullptr, const FilterRepack *rep = nullptr)
 {
     const int cpr = (g.W + EPC - 1) / EPC;
     const long total = (long)g.N * g.C * g.Hp * cpr;
     if (total >= (1L << 31) || cpr >= (1 << 16) || g.Hp >= (1 << 16)) return false; // udiv's range
     const dim3 grid((unsigned)((total + 255) / 256));
+    const unsigned nrep = rep ? rep->blocks() : 0;
+    (void)nrep;
 #define CAC_LAUNCH(KH, KW)                                                                                            \
-    if (prod)                                                                                                         \
+    if (rep) {                                                                                                        \
+        if constexpr (sizeof(T) == 2)                                                                                 \
+            hipLaunchKernelGGL((compress_repack_kernel<EPC, KH, KW>), dim3(grid.x + nrep), dim3(256), 0, st, g, (const bf16_t *)X, (bf16_t *)Z, \
+                               cpr, (uint32_t)total, 1.0 / cpr, 1.0 / g.Hp, *rep, nrep);                              \
+    } else if (prod)                                                                                                         \
         hipLaunchKernelGGL((compress_kernel<T, EPC, KH, KW, true>), grid, dim3(256), 0, st, g, (const T *)X, (T *)Z, cpr, \
                            (uint32_t)total, 1.0 / cpr, 1.0 / g.Hp, *prod);                                            \
     else                                                                                                              \
@@ -258,7 +297,8 @@ template <typename T, int EPC> bool launch_epc(const Geom &g, const void *X, voi
 
 } // namespace
 
-static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err, const Producer *prod)
+static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err, const Producer *prod,
+                        const FilterRepack *rep = nullptr)
 {
     if ((long)g.N * g.C * g.H * g.W * 4 >= (1L << 31)) return false; // 32-bit buffer offsets
     bool ok;
@@ -270,7 +310,11 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
         const dim3 grid((unsigned)((total + 255) / 256));
 #define CAC_NARROW(WW)                                                                                                   \
     if (g.W == WW) {                                                                                                     \
-        if (prod)                                                                                                        \
+        if (rep) {                                                                                                       \
+            if constexpr (WW != 28)                                                                                      \
+                hipLaunchKernelGGL((compress_narrow_repack_kernel<WW>), dim3(grid.x + rep->blocks()), dim3(256), 0, st, g, \
+                                   (const bf16_t *)X, (bf16_t *)Z, (uint32_t)total, *rep, rep->blocks());                \
+        } else if (prod)                                                                                                        \
             hipLaunchKernelGGL((compress_narrow_kernel<WW, true>), grid, dim3(256), 0, st, g, (const bf16_t *)X, (bf16_t *)Z,  \
                                (uint32_t)total, 1.0 / g.Hp, *prod);                                                      \
         else                                                                                                             \
@@ -287,7 +331,7 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
         ok = launch_epc<float, 4>(g, X, Z, st, prod);
     } else {
         // narrow maps: 8-byte chunks so that a chunk does not span more than one row's worth
-        ok = g.W >= 8 ? launch_epc<bf16_t, 8>(g, X, Z, st, prod) : (g.kw <= 4 ? launch_epc<bf16_t, 4>(g, X, Z, st, prod) : false);
+        ok = g.W >= 8 ? launch_epc<bf16_t, 8>(g, X, Z, st, prod, rep) : (g.kw <= 4 ? launch_epc<bf16_t, 4>(g, X, Z, st, prod, rep) : false);
     }
     if (ok) *err = hipGetLastError();
     return ok;
@@ -297,6 +341,11 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
 bool launch_compress_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err)
 {
     return launch_fast(g, dtype, X, Z, st, err, nullptr);
+}
+
+bool launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st, hipError_t *err)
+{
+    return launch_fast(g, CAC_BF16, X, Z, st, err, nullptr, &f);
 }
 
 // The producer form: Xn = relu(scale[c] * Y + shift[c]) stored in the tensors' type, Zn = pooled Xn,

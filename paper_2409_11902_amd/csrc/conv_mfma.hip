@@ -26,6 +26,7 @@
 #include "common.h"
 #include "conv_mfma.h"
 #include "dw_reduce.h"
+#include "filter_repack.h"
 
 namespace cac {
 
@@ -49,10 +50,7 @@ constexpr int KCS = KC + 8;  // LDS elements per patch pixel: 80 bytes, an odd n
 //   each; the last block of a plane may be partial (it reads on into the next plane, or zeros
 //   past the tensor, and stores only its own pixels).
 //   Otherwise: 64 x 64 tiles through LDS, element by element.
-// Filter: W [O][C][R][S] -> Wt in MFMA fragment order [R*S][KCp/16][Mp/32][lane 64][8]: lane l of
-//   a wave holds row m = 32*mblk + l%32 and the 8 channels kc = 16*kblk + 8*(l/32) ..., so a wave
-//   reads the A fragment of a (tap, 16-channel block, 32-row block) as one contiguous KiB.
-//   Forward: m = o, kc = c; data gradient: m = c, kc = o.
+// Filter: filter_repack.h.
 // Blocks [0, in_blocks) do the input, the rest the filter.
 struct RepackParams {
     const bf16_t *in;
@@ -63,90 +61,14 @@ struct RepackParams {
     bf16_t *Z;          // pooled copy of `in` written on the way (2 x 2 means), or null
     int Wimg;           // image width (only with Z)
     int decim;          // with Z: `out` takes pixel (2h, 2w) of every 2 x 2 tile only, as an image of half the extent
-    const bf16_t *W;
-    bf16_t *Wt;
-    int O, Cw, RS, Mp, KCp, transpose;
+    FilterRepack f;
 };
 
 __device__ __forceinline__ void repack_body(const RepackParams &p, const int bid)
 {
-    constexpr int kFilterElems = 32 * (16 * 9 + 2); // a 32 x 16 block of (o, c) pairs, 9 taps, padded rows
     __shared__ bf16_t sm[kFilterElems > 64 * 66 ? kFilterElems : 64 * 66];
     if (bid >= p.in_blocks) {
-        // One block per (32-row block, 16-channel block): its part of W -- for every o a contiguous
-        // run of (c, tap) -- goes through LDS as it lies in memory; then every thread gathers the
-        // 8 channels of one lane of one tap's fragment and writes them as 16 bytes, a wave one
-        // contiguous KiB.  Rows are padded to an odd number of dwords against bank conflicts.
-        const int b = bid - p.in_blocks;
-        const int mblks = p.Mp / 32, kblks = p.KCp / 16, mblk = b % mblks, kblk = b / mblks;
-        const int rows = p.transpose ? 16 : 32, cols = p.transpose ? 32 : 16; // o rows, c columns
-        const int o0 = p.transpose ? kblk * 16 : mblk * 32, c0 = p.transpose ? mblk * 32 : kblk * 16;
-        const int L = cols * p.RS, Lp = L + 2;
-        const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-        // a wave takes every fourth row; all of a thread's loads are issued before the first is
-        // used (at most 8 rows of 3 x 64 elements, or 4 rows of 5 x 64)
-        constexpr int kRowsPerWave = 8, kMaxX = 5;
-        const rsrc_t rs = make_rsrc(p.W, (uint32_t)p.O * p.Cw * p.RS * 2u);
-        // Whole blocks whose runs are multiples of 16 bytes and start on such (every row of W does
-        // when Cw * RS is a multiple of 8): 16-byte loads, at most 3 per thread, instead of up to 40
-        // loads of one element each.
-        const int segs = L >> 3;
-        if ((L & 7) == 0 && ((p.Cw * p.RS) & 7) == 0 && c0 + cols <= p.Cw) {
-            u32x4 t4[3];
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int it = threadIdx.x + 256 * q, r = it / segs, sg = it - r * segs, o = o0 + r;
-                const bool ok = it < rows * segs && o < p.O;
-                t4[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? ((uint32_t)(o * p.Cw + c0) * p.RS) * 2u + sg * 16u : kNoLoad, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int it = threadIdx.x + 256 * q, r = it / segs, sg = it - r * segs;
-                if (it < rows * segs) {
-                    uint32_t *d = (uint32_t *)(sm + r * Lp + sg * 8); // (Lp is even: 4-byte aligned)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) d[k] = t4[q][k];
-                }
-            }
-        } else {
-        uint16_t tmp[kRowsPerWave][kMaxX];
-#pragma unroll
-        for (int j = 0; j < kRowsPerWave; ++j) {
-            const int r = wv + 4 * j, o = o0 + r;
-            const int lim = (r < rows && o < p.O) ? min(L, (p.Cw - c0) * p.RS) : 0; // elements of the run inside the tensor
-            const uint32_t base = ((uint32_t)(o * p.Cw + c0) * p.RS) * 2u;
-#pragma unroll
-            for (int k = 0; k < kMaxX; ++k) {
-                const int x = ln + 64 * k;
-                tmp[j][k] = __builtin_amdgcn_raw_buffer_load_b16(rs, x < lim ? base + 2u * x : kNoLoad, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kRowsPerWave; ++j) {
-            const int r = wv + 4 * j;
-#pragma unroll
-            for (int k = 0; k < kMaxX; ++k) {
-                const int x = ln + 64 * k;
-                if (r < rows && x < L) sm[r * Lp + x] = tmp[j][k];
-            }
-        }
-        }
-        __syncthreads();
-        for (int it = threadIdx.x; it < p.RS * 64; it += 256) {
-            const int tap = it >> 6, lane = it & 63, m = lane & 31, k8 = 8 * (lane >> 5);
-            u32x4 v;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                uint32_t h[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int kc = k8 + 2 * k + e;
-                    h[e] = p.transpose ? sm[kc * Lp + m * p.RS + tap] : sm[m * Lp + kc * p.RS + tap];
-                }
-                v[k] = h[0] | (h[1] << 16);
-            }
-            ((u32x4 *)p.Wt)[((long)(tap * kblks + kblk) * mblks + mblk) * 64 + lane] = v;
-        }
+filter_repack(p.f, bid - p.in_blocks, sm);
         return;
     }
     bf16_t (*tile)[66] = (bf16_t (*)[66])sm;
@@ -308,8 +230,8 @@ hipError_t launch_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, in
     // the number of waves per compute unit: give every unit a wave before any gets a second)
     p.in_wpb = items > 64 * 256 ? 4 : 1; // (measured: two waves per block are slower than either)
     p.in_blocks = p.fast ? (int)((items + 64 * p.in_wpb - 1) / (64 * p.in_wpb)) : N * ((Cp + 63) / 64) * ((HW + 63) / 64);
-    p.W = W; p.Wt = Wt; p.O = O; p.Cw = Cw; p.RS = RS; p.Mp = Mp; p.KCp = KCp; p.transpose = transpose;
-    const unsigned nrep = (unsigned)(p.in_blocks + (Mp / 32) * (KCp / 16));
+    p.f = FilterRepack{W, Wt, O, Cw, RS, Mp, KCp, transpose};
+    const unsigned nrep = (unsigned)p.in_blocks + p.f.blocks();
     if (tail && tail->blocks) {
         const DwReduceTail &t = *tail;
 #define CAC_RR(SY, V) hipLaunchKernelGGL((repack_reduce_kernel<SY, V>), dim3(nrep + t.blocks), dim3(256), 0, st, p, nrep, t)
@@ -1277,21 +1199,28 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     const bool direct = fwd_reads_in_place(g, p);
     if (p.tile == 3) {
         // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
-        if (!p.w_direct)
-            *err = launch_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, (const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W, st);
+        if (!p.w_direct) {
+            const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0};
+            if (Z && !p.pw_pool && launch_compress_repack(g, X, Z, f, st, err)) *pooled = true;
+            else *err = launch_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W, st);
+        }
         if (*err != hipSuccess) return true;
         p.in = (const bf16_t *)X;
         p.wt = p.w_direct ? (const bf16_t *)W : wt;
         p.bias = (const bf16_t *)b; p.out = (bf16_t *)Y;
         p.Z = p.pw_pool ? (bf16_t *)Z : nullptr;
-        *pooled = p.Z != nullptr;
+        *pooled = *pooled || p.Z;
         *err = run_gather(p, variant, st);
         return true;
     }
-    *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp,
-                         (const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr,
-                         p.decim);
-    *pooled = fuse;
+    // nothing to do for the input but the record: the filter's blocks go ahead of the pooling ones in one launch
+    const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0};
+    if (Z && direct && !fuse && launch_compress_repack(g, X, Z, f, st, err)) *pooled = true;
+    else {
+        *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C,
+                             p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr, p.decim);
+        *pooled = fuse;
+    }
     if (*err != hipSuccess) return true;
     p.in = direct ? (const bf16_t *)X : in;
     p.nchw = direct;
