@@ -8,7 +8,7 @@
 // of dY and the pooled values under them, so that a pooled value is read once per tile):
 //   1. partial sums: a block per (channel, slice of the channel's chunks over all images); a
 //      channel is shared out over as many slices as it takes to have about 2048 blocks;
-//   2. the slices of a channel added in a fixed order (skipped when a channel is one slice);
+//   2. the slices of a channel added in a fixed order (up to eight slices: by the threads of the last launch, on the way);
 //   3. the element-wise pass, one thread per chunk, 16-byte stores.
 // Everything is summed in an order that depends on the shape only: results are reproducible.
 // Also here, for the helpers it shares: the bias gradient db = sum of dY over n, p, q (db_kernel).
@@ -49,13 +49,20 @@ __device__ __forceinline__ void load_chunk(const Geom &g, rsrc_t rs_dy, const T 
 #pragma unroll
     for (int a = 0; a < KH; ++a)
         Chunk<T, EPC>::load(rs_dy, (plane * g.H + h0 + a) * g.W + ch * EPC, a < rows, g.W & 1, v[a]);
-    const T *z = Zin + ((long)plane * g.Hp + i) * g.Wp + ch * OPC;
+    if constexpr (sizeof(T) == 2 && OPC == 4) { // (two or three dwords instead of four values)
+        float z[4];
+        Chunk<T, 4>::load(make_rsrc(Zin, (uint32_t)g.N * g.C * g.Hp * g.Wp * 2u), (plane * g.Hp + i) * g.Wp + ch * OPC, true, g.Wp & 1, z);
 #pragma unroll
-    for (int o = 0; o < OPC; ++o) xh[o] = ch * OPC + o < g.Wp ? (Elem<T>::load(z + o) - mu) * is : 0.f;
+        for (int o = 0; o < OPC; ++o) xh[o] = ch * OPC + o < g.Wp ? (z[o] - mu) * is : 0.f;
+    } else {
+        const T *z = Zin + ((long)plane * g.Hp + i) * g.Wp + ch * OPC;
+#pragma unroll
+        for (int o = 0; o < OPC; ++o) xh[o] = ch * OPC + o < g.Wp ? (Elem<T>::load(z + o) - mu) * is : 0.f;
+    }
 }
 
 template <typename T, int EPC, int KH, int KW>
-__global__ void __launch_bounds__(kT) bn_partial_kernel(Geom g, BnPlan q, const T *__restrict__ Zin, const T *__restrict__ dY,
+__global__ void __launch_bounds__(kT, KH * EPC <= 16 ? 8 : 5) bn_partial_kernel(Geom g, BnPlan q, const T *__restrict__ Zin, const T *__restrict__ dY,
                                                         const float *__restrict__ mean, const float *__restrict__ invstd,
                                                         float *__restrict__ o_dy, float *__restrict__ o_dx)
 {
@@ -66,23 +73,35 @@ __global__ void __launch_bounds__(kT) bn_partial_kernel(Geom g, BnPlan q, const 
     const rsrc_t rs = make_rsrc(dY, (uint32_t)g.N * g.C * g.H * g.W * (uint32_t)sizeof(T));
     const uint32_t end = min((uint32_t)(s + 1) * q.per_slice, q.per_channel);
     float sdy = 0.f, sdx = 0.f;
-    for (uint32_t it = (uint32_t)s * q.per_slice + threadIdx.x; it < end; it += kT) {
-        const uint32_t n = udiv(it, q.inv_ipp), rem = it - n * q.ipp;
-        const uint32_t i = udiv(rem, q.inv_cpr), ch = rem - i * q.cpr;
-        float v[KH][EPC], xh[OPC];
-        int rows;
-        load_chunk<T, EPC, KH, KW>(g, rs, Zin, n * g.C + c, (int)i, (int)ch, mu, is, v, xh, rows);
-        const int left = g.W - (int)ch * EPC; // columns of the chunk inside the row
+    // U chunks of a thread are requested before the first is added up (512 x 28 x 28, batch 64, where a thread has three or four:
+    // 19.5 -> 17.2 us; four at a time cost waves in flight and gain nothing more)
+    constexpr int U = 2;
+    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += U * kT) {
+        float v[U][KH][EPC], xh[U][OPC];
+        int left[U]; // columns of the chunk inside the row
 #pragma unroll
-        for (int o = 0; o < OPC; ++o) {
-            float t = 0.f; // the tile's dY, row by row (rows past the plane are zeros already)
+        for (int u = 0; u < U; ++u) {
+            const uint32_t it = min(it0 + u * kT, end - 1); // (a chunk past the end: the last one again, and not added)
+            const uint32_t n = udiv(it, q.inv_ipp), rem = it - n * q.ipp;
+            const uint32_t i = udiv(rem, q.inv_cpr), ch = rem - i * q.cpr;
+            int rows;
+            load_chunk<T, EPC, KH, KW>(g, rs, Zin, n * g.C + c, (int)i, (int)ch, mu, is, v[u], xh[u], rows);
+            left[u] = g.W - (int)ch * EPC;
+        }
 #pragma unroll
-            for (int a = 0; a < KH; ++a)
+        for (int u = 0; u < U; ++u) {
+            if (it0 + u * kT >= end) break;
 #pragma unroll
-                for (int b = 0; b < KW; ++b)
-                    if (o * KW + b < left) t += v[a][o * KW + b];
-            sdy += t;
-            sdx += t * xh[o];
+            for (int o = 0; o < OPC; ++o) {
+                float t = 0.f; // the tile's dY, row by row (rows past the plane are zeros already)
+#pragma unroll
+                for (int a = 0; a < KH; ++a)
+#pragma unroll
+                    for (int b = 0; b < KW; ++b)
+                        if (o * KW + b < left[u]) t += v[u][a][o * KW + b];
+                sdy += t;
+                sdx += t * xh[u][o];
+            }
         }
     }
     sdy = wave_sum(sdy);
@@ -112,11 +131,38 @@ __global__ void __launch_bounds__(64) bn_finish_kernel(int S, const float *__res
     }
 }
 
+// What the element-wise pass takes its channel sums from: S <= kFold partial sums each, which every thread adds (in the order
+// of wave_sum) and the first thread of a channel writes to dbeta and dgamma -- a few loads that all threads of a channel
+// share, against a launch of 4.7 us --, or, S = 1, the sums themselves.
+constexpr int kFold = 8;
+struct Sums {
+    const float *dy, *dx;
+    int S;
+    float *dbeta, *dgamma;
+    __device__ __forceinline__ float of(const float *p, uint32_t c) const
+    {
+        if (S == 1) return p[c];
+        float a[kFold];
+#pragma unroll
+        for (int k = 0; k < kFold; ++k) a[k] = k < S ? p[c * S + k] : 0.f;
+        return ((a[0] + a[4]) + (a[2] + a[6])) + ((a[1] + a[5]) + (a[3] + a[7]));
+    }
+    // first: the calling thread is the channel's first one
+    __device__ __forceinline__ void get(uint32_t c, bool first, float &sdy, float &sdx) const
+    {
+        sdy = of(dy, c);
+        sdx = of(dx, c);
+        if (first && S > 1) {
+            dbeta[c] = sdy;
+            dgamma[c] = sdx;
+        }
+    }
+};
+
 template <typename T, int EPC, int KH, int KW>
 __global__ void __launch_bounds__(kT) bn_dx_kernel(Geom g, BnPlan q, const T *__restrict__ Zin, const T *__restrict__ dY,
                                                    const float *__restrict__ mean, const float *__restrict__ invstd,
-                                                   const float *__restrict__ gamma, const float *__restrict__ dgamma,
-                                                   const float *__restrict__ dbeta, T *__restrict__ dX)
+                                                   const float *__restrict__ gamma, Sums sums, T *__restrict__ dX)
 {
     constexpr int OPC = EPC / KW;
     const uint32_t idx = blockIdx.x * (uint32_t)kT + threadIdx.x;
@@ -126,7 +172,9 @@ __global__ void __launch_bounds__(kT) bn_dx_kernel(Geom g, BnPlan q, const T *__
     const uint32_t c = plane - udiv(plane, q.inv_c) * (uint32_t)g.C;
     const float inv_m = 1.0f / ((float)g.N * (float)(g.H * g.W));
     const float mu = mean[c], is = invstd[c], k = gamma[c] * is;
-    const float mdy = dbeta[c] * inv_m, mdx = dgamma[c] * inv_m;
+    float sdy, sdx;
+    sums.get(c, idx == c * q.ipp, sdy, sdx);
+    const float mdy = sdy * inv_m, mdx = sdx * inv_m;
     const rsrc_t rs = make_rsrc(dY, (uint32_t)g.N * g.C * g.H * g.W * (uint32_t)sizeof(T));
     float v[KH][EPC], xh[OPC];
     int rows;
@@ -180,17 +228,24 @@ __global__ void __launch_bounds__(kT) bn_partial_narrow_kernel(Geom g, BnPlan q,
     const rsrc_t rs = make_rsrc(dY, q.total * (uint32_t)R::XB), rs_z = make_rsrc(Zin, q.total * (uint32_t)(2 * R::WP));
     const uint32_t end = min((uint32_t)(s + 1) * q.per_slice, q.per_channel);
     float sdy = 0.f, sdx = 0.f;
-    for (uint32_t it = (uint32_t)s * q.per_slice + threadIdx.x; it < end; it += kT) {
-        const uint32_t n = udiv(it, q.inv_hp), i = it - n * g.Hp; // the channel's records: image by image
-        uint32_t d[4 * R::NL];
-        float xh[8 * R::NZ];
-        R::load(rs, rs_z, (n * g.C + c) * g.Hp + i, true, mu, is, d, xh);
+    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += 2 * kT) {
+        uint32_t d[2][4 * R::NL];
+        float xh[2][8 * R::NZ];
 #pragma unroll
-        for (int j = 0; j < R::WP; ++j) {
-            float t = 0.f;
-            t += bf_lo(d[j]); t += bf_hi(d[j]); t += bf_lo(d[R::WP + j]); t += bf_hi(d[R::WP + j]);
-            sdy += t;
-            sdx += t * xh[j];
+        for (int u = 0; u < 2; ++u) { // (two records requested before the first is added up)
+            const uint32_t it = it0 + u * kT, n = udiv(min(it, end - 1), q.inv_hp), i = min(it, end - 1) - n * g.Hp; // image by image
+            R::load(rs, rs_z, (n * g.C + c) * g.Hp + i, it < end, mu, is, d[u], xh[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (it0 + u * kT >= end) break;
+#pragma unroll
+            for (int j = 0; j < R::WP; ++j) {
+                float t = 0.f;
+                t += bf_lo(d[u][j]); t += bf_hi(d[u][j]); t += bf_lo(d[u][R::WP + j]); t += bf_hi(d[u][R::WP + j]);
+                sdy += t;
+                sdx += t * xh[u][j];
+            }
         }
     }
     sdy = wave_sum(sdy);
@@ -210,8 +265,7 @@ __global__ void __launch_bounds__(kT) bn_partial_narrow_kernel(Geom g, BnPlan q,
 template <int W>
 __global__ void __launch_bounds__(kT) bn_dx_narrow_kernel(Geom g, BnPlan q, const bf16_t *__restrict__ Zin, const bf16_t *__restrict__ dY,
                                                           const float *__restrict__ mean, const float *__restrict__ invstd,
-                                                          const float *__restrict__ gamma, const float *__restrict__ dgamma,
-                                                          const float *__restrict__ dbeta, bf16_t *__restrict__ dX)
+                                                          const float *__restrict__ gamma, Sums sums, bf16_t *__restrict__ dX)
 {
     typedef Narrow<W> R;
     __shared__ __align__(16) unsigned char lds[4 * 64 * R::XB];
@@ -223,7 +277,9 @@ __global__ void __launch_bounds__(kT) bn_dx_narrow_kernel(Geom g, BnPlan q, cons
     const uint32_t c = plane - udiv(plane, q.inv_c) * (uint32_t)g.C;
     const float inv_m = 1.0f / ((float)g.N * (float)(g.H * g.W));
     const float mu = mean[c], is = invstd[c], k = gamma[c] * is;
-    const float mdy = dbeta[c] * inv_m, mdx = dgamma[c] * inv_m;
+    float sdy, sdx;
+    sums.get(c, rec == c * (uint32_t)g.Hp, sdy, sdx);
+    const float mdy = sdy * inv_m, mdx = sdx * inv_m;
     const rsrc_t rs = make_rsrc(dY, q.total * (uint32_t)R::XB), rs_z = make_rsrc(Zin, q.total * (uint32_t)(2 * R::WP));
     uint32_t d[4 * R::NL];
     float xh[8 * R::NZ];
@@ -299,6 +355,15 @@ template <int EPC> bool make_plan(const Geom &g, BnPlan *q)
     return true;
 }
 
+// The sums of the first launch, finished by a launch of its own where a channel has many slices.
+Sums finish_sums(const Geom &g, const BnPlan &q, float *o_dy, float *o_dx, float *dgamma, float *dbeta, hipStream_t st)
+{
+    if (q.S == 1) return Sums{dbeta, dgamma, 1, dbeta, dgamma};
+    if (q.S <= kFold) return Sums{o_dy, o_dx, q.S, dbeta, dgamma};
+    hipLaunchKernelGGL(bn_finish_kernel, dim3((unsigned)g.C), dim3(64), 0, st, q.S, o_dy, o_dx, dgamma, dbeta);
+    return Sums{dbeta, dgamma, 1, dbeta, dgamma};
+}
+
 // false: a pooling tile the chunk kernels do not take
 template <typename T, int EPC>
 bool launch_t(const Geom &g, const BnPlan &q, const void *Zin, const void *dY, const float *mean, const float *invstd, const float *gamma,
@@ -310,9 +375,9 @@ bool launch_t(const Geom &g, const BnPlan &q, const void *Zin, const void *dY, c
     {                                                                                                                               \
         hipLaunchKernelGGL((bn_partial_kernel<T, EPC, KH, KW>), dim3((unsigned)(g.C * q.S)), dim3(kT), 0, st, g, q, (const T *)Zin,  \
                            (const T *)dY, mean, invstd, o_dy, o_dx);                                                                \
-        if (!one) hipLaunchKernelGGL(bn_finish_kernel, dim3((unsigned)g.C), dim3(64), 0, st, q.S, o_dy, o_dx, dgamma, dbeta);       \
+        const Sums sums = finish_sums(g, q, o_dy, o_dx, dgamma, dbeta, st);                                                         \
         hipLaunchKernelGGL((bn_dx_kernel<T, EPC, KH, KW>), dim3(cdiv(q.total, kT)), dim3(kT), 0, st, g, q, (const T *)Zin,           \
-                           (const T *)dY, mean, invstd, gamma, dgamma, dbeta, (T *)dX);                                             \
+                           (const T *)dY, mean, invstd, gamma, sums, (T *)dX);                                                      \
         return true;                                                                                                                \
     }
     if (g.kh == 2 && g.kw == 2) CAC_BN(2, 2)
@@ -365,9 +430,9 @@ void launch_narrow(const Geom &g, const BnPlan &q, const void *Zin, const void *
     float *o_dy = one ? dbeta : ws, *o_dx = one ? dgamma : ws + (size_t)g.C * q.S;
     hipLaunchKernelGGL((bn_partial_narrow_kernel<W>), dim3((unsigned)(g.C * q.S)), dim3(kT), 0, st, g, q, (const bf16_t *)Zin, (const bf16_t *)dY,
                        mean, invstd, o_dy, o_dx);
-    if (!one) hipLaunchKernelGGL(bn_finish_kernel, dim3((unsigned)g.C), dim3(64), 0, st, q.S, o_dy, o_dx, dgamma, dbeta);
+    const Sums sums = finish_sums(g, q, o_dy, o_dx, dgamma, dbeta, st);
     hipLaunchKernelGGL((bn_dx_narrow_kernel<W>), dim3(cdiv(q.total, kT)), dim3(kT), 0, st, g, q, (const bf16_t *)Zin, (const bf16_t *)dY, mean,
-                       invstd, gamma, dgamma, dbeta, (bf16_t *)dX);
+                       invstd, gamma, sums, (bf16_t *)dX);
 }
 
 } // namespace
@@ -402,11 +467,11 @@ bool launch_bn_bwd_fast(const Geom &g, int dtype, const void *Zin, const void *d
         float *o_dy = one ? dbeta : (float *)ws, *o_dx = one ? dgamma : (float *)ws + (size_t)g.C * q.S;
         hipLaunchKernelGGL((bn_partial_kernel<bf16_t, 8, 2, 2>), dim3((unsigned)(g.C * q.S)), dim3(kT), 0, st, g, q, (const bf16_t *)Zin,
                            (const bf16_t *)dY, mean, invstd, o_dy, o_dx);
-        if (!one) hipLaunchKernelGGL(bn_finish_kernel, dim3((unsigned)g.C), dim3(64), 0, st, q.S, o_dy, o_dx, dgamma, dbeta);
+        const Sums sums = finish_sums(g, q, o_dy, o_dx, dgamma, dbeta, st);
         BnPlan r = q;
         r.total = (uint32_t)((long)g.N * g.C * g.Hp);
         hipLaunchKernelGGL((bn_dx_narrow_kernel<28>), dim3(cdiv(r.total, kT)), dim3(kT), 0, st, g, r, (const bf16_t *)Zin, (const bf16_t *)dY,
-                           mean, invstd, gamma, dgamma, dbeta, (bf16_t *)dX);
+                           mean, invstd, gamma, sums, (bf16_t *)dX);
         *err = hipGetLastError();
         return true;
     }
