@@ -36,6 +36,7 @@
 // input row h to the slot of Z row h/kh.
 
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 #include "dw_mfma.h"
@@ -487,24 +488,29 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
         Window<2> aw[MI];
         u32x4 b[R][NI][NPH];
     };
-    // all MFMAs of one step: the window supplies the shifted dY fragments
+    // the MFMAs of one filter column of a step: the window supplies the shifted dY fragments
+    auto mfma_cols = [&](const Ops &o, auto col) {
+        constexpr int s = decltype(col)::value;
+        if constexpr (s < S) {
+            bf16x8 af[MI];
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) af[mi] = make_frag<2, 1, a_of(s), 0>(o.aw[mi]);
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) {
+                    union { u32x4 u; bf16x8 v; } bf;
+                    bf.u = o.b[r][ni][b_of(s)];
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi)
+                        acc[mi][ni][r * S + s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bf.v, acc[mi][ni][r * S + s], 0, 0, 0);
+                }
+        }
+    };
     auto mfma_step = [&](const Ops &o) {
-#define CAC_COL(s)                                                                                          \
-    if constexpr (s < S) {                                                                                  \
-        bf16x8 af[MI];                                                                                      \
-        _Pragma("unroll") for (int mi = 0; mi < MI; ++mi) af[mi] = make_frag<2, 1, a_of(s), 0>(o.aw[mi]);   \
-        _Pragma("unroll") for (int r = 0; r < R; ++r)                                                       \
-        _Pragma("unroll") for (int ni = 0; ni < NI; ++ni)                                                   \
-        {                                                                                                   \
-            union { u32x4 u; bf16x8 v; } bf;                                                                \
-            bf.u = o.b[r][ni][b_of(s)];                                                                     \
-            _Pragma("unroll") for (int mi = 0; mi < MI; ++mi)                                               \
-                acc[mi][ni][r * S + s] =                                                                    \
-                    __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[mi], bf.v, acc[mi][ni][r * S + s], 0, 0, 0); \
-        }                                                                                                   \
-    }
-        CAC_COL(1) CAC_COL(0) CAC_COL(2)
-#undef CAC_COL
+        mfma_cols(o, std::integral_constant<int, 1>{});
+        mfma_cols(o, std::integral_constant<int, 0>{});
+        mfma_cols(o, std::integral_constant<int, 2>{});
     };
     // Interleaving hint for one step: after every MFMA one LDS read (while any are
     // left) and a few VALU instructions, so that the next step's operand requests,
@@ -687,28 +693,48 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
                 if (++t == nsteps) break;
             }
         } else {
-            // two column phases double the xhat operands: a second operand set does not
-            // fit the register file next to the accumulators, so these (few) layers
-            // request each step's operands right before using them
+            // Two column phases double the xhat operands, and a second operand set does not fit the register file next to the
+            // accumulators.  But a phase's operands are free as soon as its own columns are multiplied: the middle column is
+            // all that phase 0 serves, so the next step's phase 0 and window are requested before the six MFMAs of the outer
+            // columns, and its phase 1 after them, in front of the next middle column (418 -> 562 at 21 x 21, batch 236, tiles of 2:
+            // 259 -> 234 us; layers that wait for their copy waves instead, 128 -> 256 at 28 x 28 uncompressed: 42.9 either way).
             for (int t = 0; t < nsteps; ++t) {
-                mfma_step(X);
-                if (t + 1 == nsteps) break;
+                mfma_cols(X, std::integral_constant<int, 1>{});
+                Window<2> nw[MI];
                 if (seg + 1 < segs) {
 #pragma unroll
-                    for (int mi = 0; mi < MI; ++mi) X.aw[mi].prev3 = X.aw[mi].blk[0][3];
-                    request(X, ra, rx, seg + 1, seg + 2 == segs);
+                    for (int mi = 0; mi < MI; ++mi) nw[mi].prev3 = X.aw[mi].blk[0][3];
                     ++seg;
-                } else {
+                } else { // (past the last step: the last row pair again, for nobody)
                     ra = ac + 2 * e_next[0];
 #pragma unroll
                     for (int r = 0; r < R; ++r) rx[r] = xc + 2 * e_next[1 + r];
                     e_next = lds16(tab + 32 * min(rp + 2 * KS, nrp - 1));
 #pragma unroll
-                    for (int mi = 0; mi < MI; ++mi) X.aw[mi].prev3 = 0;
-                    request(X, ra, rx, 0, segs == 1);
+                    for (int mi = 0; mi < MI; ++mi) nw[mi].prev3 = 0;
                     seg = 0;
                     rp += KS;
                 }
+                const bool tail = seg + 1 == segs;
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) {
+                    nw[mi].blk[0] = lds16(ra + mi * astep + 16 * seg);
+                    nw[mi].blk[1] = lds16(tail ? lds0 : ra + mi * astep + 16 * seg + 16);
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) X.b[r][ni][0] = lds16(rx[r] + ni * xstep + 16 * seg);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_cols(X, std::integral_constant<int, 0>{});
+                mfma_cols(X, std::integral_constant<int, 2>{});
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni) X.b[r][ni][NPH - 1] = lds16(rx[r] + ni * xstep + (NPH - 1) * pw + 16 * seg);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) X.aw[mi] = nw[mi];
             }
         }
 #undef CAC_STEP
