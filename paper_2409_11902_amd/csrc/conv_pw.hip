@@ -16,8 +16,8 @@
 //     the thread pools what it holds: Z costs its own bytes only (same sum order and rounding as the stand-alone
 //     kernel, bit-identical);
 //   - the result leaves through LDS as in conv_tile.hip.
-// Per call (bench layers, batch 64, inputs resident): 256 -> 64 at 56 x 56 forward 74 -> 39 us, 64 -> 256 61 -> 39,
-// 512 -> 2048 at 7 x 7 44 -> 29, data gradients 53 -> 34, 49 -> 29, 47 -> 43.  Two stages of input in flight (for 64
+// Per call (bench layers, batch 64, inputs resident): 256 -> 64 at 56 x 56 forward 74 -> 39 us, 64 -> 256 61 -> 39, their data
+// gradients 53 -> 34 and 49 -> 29 (small maps: conv_pw_wave_kernel below).  Two stages of input in flight (for 64
 // channels per workgroup, which have the registers) measured 2-10 % slower: the stages are not bound by latency.
 #include <stdio.h>
 #include <stdlib.h>
