@@ -69,10 +69,10 @@ __device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(
 
 // 16-byte items of dY and of Z a thread moves per chunk, at most (every chunk issues so many loads, wanted or not).
 // Uncompressed records of 3 x 3 stride-2 layers (pooling tiles of one column) hold many Z items to every dY item: with the
-// split of the others a chunk is one output row on wide maps, half of a row pair left empty.  WIDEZ is the other split:
-// longer chunks, but a workgroup waits for more before its first; dw_mfma_plan draws the line.
-constexpr int max_dy(bool widez) { return widez ? 4 : 8; }
-constexpr int max_z(bool widez) { return widez ? 8 : 4; }
+// split of the others a chunk is one output row on wide maps, half of a row pair left empty.  WIDEZ 1 and 2 are the other splits:
+// longer chunks, but a workgroup waits for more before its first; dw_mfma_plan draws the lines.
+constexpr int max_dy(int widez) { return 8 >> widez; }
+constexpr int max_z(int widez) { return 4 << widez; }
 
 // A window of one xhat row held in registers: the last dword of the block left
 // of the current position and NB blocks starting at it.
@@ -156,7 +156,7 @@ constexpr int kAnyFl = -2;
 // SC: the number of 8-pixel segments per output row when it is known at compile
 // time (0: read from the plan).  With SC the walk along a row is unrolled and the
 // segment offsets become immediates of the LDS reads.
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, bool WIDEZ, int FL>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, int WIDEZ, int FL>
 __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParams p)
 {
     constexpr int kMaxDy = max_dy(WIDEZ), kMaxZ = max_z(WIDEZ);
@@ -863,7 +863,7 @@ struct Variant {
     hipError_t (*launch)(const DwMfmaParams &, dim3, hipStream_t);
 };
 
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, bool WIDEZ = false, int FL = kAnyFl>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, int WIDEZ = 0, int FL = kAnyFl>
 hipError_t launch_fixed(const DwMfmaParams &p, dim3 grid, hipStream_t st)
 {
     auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ, FL>;
@@ -899,12 +899,13 @@ hipError_t launch_variant(const DwMfmaParams &p, dim3 grid, hipStream_t st)
         }
     }
     if constexpr (S == 3 && SG == 2) {
-        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, true, -1>(p, grid, st);
+        if (p.widez == 2) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 2, -1>(p, grid, st);
+        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, -1>(p, grid, st);
         switch (p.kw_log2) {
-        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, -1>(p, grid, st);
-        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 0>(p, grid, st);
-        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 1>(p, grid, st);
-        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, false, 2>(p, grid, st);
+        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, -1>(p, grid, st);
+        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 0>(p, grid, st);
+        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 1>(p, grid, st);
+        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 2>(p, grid, st);
         }
     } else {
         return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
@@ -930,7 +931,7 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 namespace {
 
 // The plan for one entry of the kernel table; false when the geometry does not fit it.
-bool plan_with(const Geom &g, int vi, bool widez, DwMfmaPlan *plan)
+bool plan_with(const Geom &g, int vi, int widez, DwMfmaPlan *plan)
 {
     auto log2_of = [](int k) { return k == 1 ? 0 : k == 2 ? 1 : k == 4 ? 2 : k == 8 ? 3 : -1; };
     const int khl = log2_of(g.kh), kwl = log2_of(g.kw);
@@ -1047,7 +1048,7 @@ bool plan_with(const Geom &g, int vi, bool widez, DwMfmaPlan *plan)
 // partial sums a workgroup writes by KS at the price of shorter runs between barriers and
 // twice the staging work per MFMA; it pays when a workgroup has only a few chunks to go
 // through.  Among the others: the large tile unless it would be mostly padding.
-bool plan_shape(const Geom &g, bool widez, DwMfmaPlan *plan)
+bool plan_shape(const Geom &g, int widez, DwMfmaPlan *plan)
 {
     DwMfmaPlan whole, split;
     bool have_whole = false, have_split = false;
@@ -1090,19 +1091,26 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
     // buffer loads address with 32-bit byte offsets and use 2^31 as "no load"
     if ((long)g.N * g.K * g.P * g.Q >= (1L << 30) || (long)g.N * g.C * g.Hp * g.Wp >= (1L << 30)) return false;
 
-    // The split of the copy registers (calls in us, usual / WIDEZ, both while they spilled: 128 -> 256 at 28 x 28, batch 128, 56 chunks to a
-    // workgroup, 73 / 63; 20 -> 76 at 4 x 4, batch 121, two of them, 15.7 / 19.3; of 700 random layers WIDEZ took 0.75 of the
-    // time from sixteen chunks on and 1.05 below eight).  Where only WIDEZ fits -- long rows -- the kernel of dw_tiled.hip is
-    // the other choice: four times as slow in the mean, but 12.4 against 19.3 us for 9 -> 9 at 82 x 82, batch 1.
+    // The split of the copy registers.  Of 200 random uncompressed layers the first split towards Z took 0.6 of the time from 48
+    // chunks of the usual length per workgroup on, 0.75 from 24, 0.85 from 12, 0.89 (at most 0.91) from 8 and 1.02 (up to 1.44)
+    // below four (128 -> 256 at 28 x 28, batch 128, 56 of them: 66 -> 47 us, 20 -> 76 at 4 x 4, batch 121, two: 15.7 -> 19.3).  The
+    // second pays where it halves the chunks -- two rows of a wide map instead of one, no half-empty row pair -- and a workgroup
+    // has many (64 -> 128 at 56 x 56, batch 128: 50.3 -> 43.6; 224 -> 272 at 36 x 53, batch 97: 213 -> 163; a fifth fewer chunks 120 -> 140;
+    // few chunks up to 1.3 times the time).  Where only a split fits -- long rows -- the kernel of dw_tiled.hip is the other choice:
+    // four times as slow in the mean, but 12.4 against 19.3 us for 9 -> 9 at 82 x 82, batch 1.
     const bool may_widen = f3 && g.sh == 2 && g.kw == 1;
-    if (!plan_shape(g, false, plan))
-        return may_widen && 2.0 * g.N * g.P * g.Q * (double)g.K * g.C * 9 >= 1e8 && plan_shape(g, true, plan);
-    if (!may_widen || plan->p.chunks_per_slice < 12) return true;
-    DwMfmaPlan wide;
-    bool have = plan_shape(g, true, &wide);
-    // (the rule between the tiles counts chunks of the usual length: what it gives the large tile stays there)
-    if (have && kVariants[plan->variant].KS == 1 && kVariants[wide.variant].KS > 1) have = plan_with(g, plan->variant, true, &wide);
-    if (have) *plan = wide;
+    if (!plan_shape(g, 0, plan))
+        return may_widen && 2.0 * g.N * g.P * g.Q * (double)g.K * g.C * 9 >= 1e8 && plan_shape(g, 1, plan);
+    if (!may_widen || plan->p.chunks_per_slice < 8) return true;
+    const int usual = plan->variant;
+    for (int w = 1; w <= 2; ++w) {
+        DwMfmaPlan wide;
+        bool have = plan_shape(g, w, &wide);
+        // (the rule between the tiles counts chunks of the usual length: what it gives the large tile stays there)
+        if (have && kVariants[usual].KS == 1 && kVariants[wide.variant].KS > 1) have = plan_with(g, usual, w, &wide);
+        if (have && (w == 1 || (plan->p.chunks_per_slice >= 24 && 20L * wide.p.nchunks <= 11L * plan->p.nchunks))) *plan = wide;
+        else break;
+    }
     return true;
 }
 

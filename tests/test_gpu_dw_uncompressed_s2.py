@@ -26,6 +26,8 @@ CASES = [
     ("many chunks, odd map", 430, 33, 65, 27, 15, 1, True),
     ("many chunks, 64 x 64 tile", 300, 128, 260, 14, 14, 1, True),
     ("many chunks, tiles of two rows, one column", 400, 48, 64, 22, 26, 2, True),
+    ("chunks of two rows instead of one, 16 Z items per thread", 40, 224, 272, 20, 56, 1, True),
+    ("the same in rows of odd length", 33, 210, 264, 21, 53, 1, True),
 ]
 
 
