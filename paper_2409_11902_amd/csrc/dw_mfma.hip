@@ -1103,12 +1103,22 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
         return may_widen && 2.0 * g.N * g.P * g.Q * (double)g.K * g.C * 9 >= 1e8 && plan_shape(g, 1, plan);
     if (!may_widen || plan->p.chunks_per_slice < 8) return true;
     const int usual = plan->variant;
+    const auto small_tile = [](const DwMfmaPlan &a) { return kVariants[a.variant].KS > 1; };
+    const auto work = [](const DwMfmaPlan &a) { return (double)a.p.nchunks * a.p.tiles_o * a.p.tiles_c; };
     for (int w = 1; w <= 2; ++w) {
+        if (w == 2 && plan->p.chunks_per_slice < 24) break;
         DwMfmaPlan wide;
         bool have = plan_shape(g, w, &wide);
-        // (the rule between the tiles counts chunks of the usual length: what it gives the large tile stays there)
-        if (have && kVariants[usual].KS == 1 && kVariants[wide.variant].KS > 1) have = plan_with(g, usual, w, &wide);
-        if (have && (w == 1 || (plan->p.chunks_per_slice >= 24 && 20L * wide.p.nchunks <= 11L * plan->p.nchunks))) *plan = wide;
+        // The rule between the tiles counts chunks of the usual length: what it gives the large tile stays there.  Nor does
+        // the second split leave the first one's large tile, which it does not fit on rows past 64, for a small one that has
+        // more to copy, a chunk of every tile counted: 354 -> 823 at 94 x 94, batch 12, tiles of 2 x 1, has four times the tiles
+        // for half the chunks, 325 against 776 us; 15 -> 10 at 112 x 112, batch 382, one tile either way, 161 against 76.  (Of 704
+        // layers whose plan a split changes the 146 that this keeps on the large tile take 0.64 of the small one's time,
+        // one of them more than 1.05.)
+        const bool shrinks = have && !small_tile(*plan) && small_tile(wide);
+        if (shrinks && (kVariants[usual].KS == 1 || work(wide) > 1.1 * work(*plan)))
+            have = plan_with(g, plan->variant, w, &wide);
+        if (have && (w == 1 || 20L * wide.p.nchunks <= 11L * plan->p.nchunks)) *plan = wide;
         else break;
     }
     return true;

@@ -49,3 +49,19 @@ def test_pointwise_layers(shape, k, plan, pooled):
     d = B.make_desc(*shape, 1, 1, pool_kh=k, pool_kw=k)
     got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
     assert got.startswith(plan) and ("pooled on the way" in got) == pooled, got
+
+
+@pytest.mark.parametrize("shape,kh,plan", [
+    # N, C, K, H, W.  3 x 3 stride-2 weight gradient from tiles of one column: the split of the copy registers that gives long
+    # rows two output rows per chunk does not fit the 64 x 64 tile there; the 32 x 32 one only where it has no more to copy
+    ((20, 312, 899, 73, 73), 1, "variant=2 tile=64x64 chunk=1img x 1rows"),
+    ((10, 1037, 168, 103, 103), 2, "variant=2 tile=64x64 chunk=1img x 1rows"),
+    ((500, 145, 817, 2, 68), 1, "variant=2 tile=64x64 chunk=1img x 1rows"),
+    ((185, 28, 19, 161, 76), 1, "variant=3 tile=32x32 chunk=1img x 2rows"),
+    ((112, 11, 103, 73, 73), 1, "variant=3 tile=32x32 chunk=1img x 2rows"),
+    ((25, 544, 637, 54, 54), 1, "variant=2 tile=64x64 chunk=1img x 2rows"),
+])
+def test_stride2_weight_gradient_from_tiles_of_one_column(shape, kh, plan):
+    d = B.make_desc(*shape, 3, 3, 2, 2, 1, 1, kh, 1, dtype=B.BF16)
+    got = B.cac_describe_plan(d, B.OP_BWD_WEIGHT_COMPRESSED)
+    assert plan in got, got
