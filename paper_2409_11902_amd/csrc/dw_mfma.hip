@@ -1118,7 +1118,12 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
         const bool shrinks = have && !small_tile(*plan) && small_tile(wide);
         if (shrinks && (kVariants[usual].KS == 1 || work(wide) > 1.1 * work(*plan)))
             have = plan_with(g, plan->variant, w, &wide);
-        if (have && (w == 1 || 20L * wide.p.nchunks <= 11L * plan->p.nchunks)) *plan = wide;
+        // Below twelve chunks the first split pays by longer chunks alone, and in the same tile: tall pooling tiles leave few Z
+        // items, so that the copy registers of dY bound a chunk and the split shortens it (3 -> 536 at 18 x 18, batch 421, tiles
+        // of 8 x 1, nine chunks to a workgroup of the small tile, thirty of the large one: 38 against 54 us).
+        const bool few = w == 1 && plan->p.chunks_per_slice < 12;
+        if (few && have && wide.variant != usual) have = plan_with(g, usual, w, &wide);
+        if (have && (w == 1 ? !few || wide.p.nchunks < plan->p.nchunks : 20L * wide.p.nchunks <= 11L * plan->p.nchunks)) *plan = wide;
         else break;
     }
     return true;

@@ -60,6 +60,12 @@ def test_pointwise_layers(shape, k, plan, pooled):
     ((185, 28, 19, 161, 76), 1, "variant=3 tile=32x32 chunk=1img x 2rows"),
     ((112, 11, 103, 73, 73), 1, "variant=3 tile=32x32 chunk=1img x 2rows"),
     ((25, 544, 637, 54, 54), 1, "variant=2 tile=64x64 chunk=1img x 2rows"),
+    # ... and the first split, where a workgroup has eight to eleven chunks, only in the same tile and for fewer chunks
+    ((421, 3, 536, 18, 18), 8, "variant=3 tile=32x32 chunk=3img x 9rows"),
+    ((11, 400, 368, 40, 40), 8, "variant=3 tile=32x32 chunk=1img x 20rows"),
+    ((112, 614, 3, 5, 198), 8, "passes dy=8"),
+    ((27, 444, 398, 25, 3), 1, "passes dy=4"),
+    ((3, 179, 1397, 6, 79), 1, "passes dy=4"),
 ])
 def test_stride2_weight_gradient_from_tiles_of_one_column(shape, kh, plan):
     d = B.make_desc(*shape, 3, 3, 2, 2, 1, 1, kh, 1, dtype=B.BF16)
