@@ -960,15 +960,22 @@ bool plan_with(const Geom &g, int vi, int widez, DwMfmaPlan *plan)
     base.XW = NPH * base.PW;              // one xhat row in LDS: all phases
     base.tile_o = tile_o; base.tile_c = tile_c;
 
+    auto pow2_at_least = [](int x) { int l = 2; while ((1 << l) < x) ++l; return l; };
     // Fills the chunk-dependent fields; false when the chunk does not fit the
-    // per-thread copy registers or the LDS budget (two buffers).
+    // per-thread copy registers or the LDS budget (two buffers).  `full`: nor does any longer one (its dY only grows).
+    bool full = false;
     auto shape = [&](int nbi, int pr, DwMfmaParams &q) {
         q = base;
         q.NBI = nbi; q.PR = pr;
-        q.RB = (g.P + pr - 1) / pr;
-        if (!divides_exactly((uint64_t)((g.N + nbi - 1) / nbi) * q.RB, q.RB)) return false; // (a chunk's images and rows)
         q.LR = nbi * pr;
         q.LRpad = (q.LR + 1) & ~1;
+        q.rowitems = q.LRpad * q.SEGS;
+        q.ldy_log2 = pow2_at_least(q.rowitems); q.LDY = 1 << q.ldy_log2;
+        full = q.LDY > NT || tile_o * q.LDY > NT * max_dy(widez);
+        if (full) return false;
+        q.dy_passes = (tile_o * q.LDY + NT - 1) / NT;
+        q.RB = (g.P + pr - 1) / pr;
+        if (!divides_exactly((uint64_t)((g.N + nbi - 1) / nbi) * q.RB, q.RB)) return false; // (a chunk's images and rows)
         int nz = 1;
         for (int rb = 0; rb < q.RB; ++rb) {
             const int p0 = rb * pr, p1 = min(p0 + pr, g.P) - 1;
@@ -977,15 +984,10 @@ bool plan_with(const Geom &g, int vi, int widez, DwMfmaPlan *plan)
             nz = max(nz, (hhi >> khl) - zlo + 1);
         }
         q.NZ = nz;
-        q.rowitems = q.LRpad * q.SEGS;
         q.citems = nbi * nz * q.ZV;
-        auto pow2_at_least = [](int x) { int l = 2; while ((1 << l) < x) ++l; return l; };
-        q.ldy_log2 = pow2_at_least(q.rowitems); q.LDY = 1 << q.ldy_log2;
         q.lpc_log2 = pow2_at_least(q.citems);   q.LPC = 1 << q.lpc_log2;
-        if (q.LDY > NT || q.LPC > NT) return false;
-        q.dy_passes = (tile_o * q.LDY + NT - 1) / NT;
         q.z_passes = (tile_c * q.LPC + NT - 1) / NT;
-        if (q.dy_passes > max_dy(widez) || q.z_passes > max_z(widez)) return false;
+        if (q.LPC > NT || q.z_passes > max_z(widez)) return false;
         if ((tile_o * q.LDY) % NT || (tile_c * q.LPC) % NT) return false; // passes cover the tile exactly
         // strides: an odd number of 16-byte units so that the 32 lanes of a half
         // wave (one output channel / input channel each) read distinct LDS banks
@@ -1013,8 +1015,8 @@ bool plan_with(const Geom &g, int vi, int widez, DwMfmaPlan *plan)
         const double cost = steps / useful * (1.0 + 1.5 / per_chunk);     // barrier + refill share
         if (cost < best_cost) { best_cost = cost; best = q; }
     };
-    for (int pr = 1; pr <= g.P; ++pr) consider(1, pr);
-    for (int nbi = 2; nbi <= min(g.N, 64); ++nbi) consider(nbi, g.P);
+    for (int pr = 1; pr <= g.P && !full; ++pr) consider(1, pr);
+    for (int nbi = 2; nbi <= min(g.N, 64) && !full; ++nbi) consider(nbi, g.P);
     if (best_cost > 1e29) return false;
 
     DwMfmaParams &p = plan->p;
