@@ -12,6 +12,8 @@
 //   3. the element-wise pass, one thread per chunk, 16-byte stores.
 // Everything is summed in an order that depends on the shape only: results are reproducible.
 // Also here, for the helpers it shares: the bias gradient db = sum of dY over n, p, q (db_kernel).
+#include <type_traits>
+
 #include "chunk.h"
 
 namespace cac {
@@ -73,10 +75,11 @@ __global__ void __launch_bounds__(kT, KH * EPC <= 16 ? 8 : 5) bn_partial_kernel(
     const rsrc_t rs = make_rsrc(dY, (uint32_t)g.N * g.C * g.H * g.W * (uint32_t)sizeof(T));
     const uint32_t end = min((uint32_t)(s + 1) * q.per_slice, q.per_channel);
     float sdy = 0.f, sdx = 0.f;
-    // U chunks of a thread are requested before the first is added up (512 x 28 x 28, batch 64, where a thread has three or four:
-    // 19.5 -> 17.2 us; four at a time cost waves in flight and gain nothing more)
-    constexpr int U = 2;
-    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += U * kT) {
+    // Two chunks of a thread are requested before the first is added up (512 x 28 x 28, batch 64, where a thread has three or
+    // four: 19.5 -> 17.2 us; four at a time cost waves in flight and gain nothing more); by a wave that has a second one for
+    // its first lane -- an idle second request costs a wave of few chunks up to a tenth of the call.
+    auto chunks = [&](uint32_t it0, auto count) {
+        constexpr int U = decltype(count)::value;
         float v[U][KH][EPC], xh[U][OPC];
         int left[U]; // columns of the chunk inside the row
 #pragma unroll
@@ -103,6 +106,10 @@ __global__ void __launch_bounds__(kT, KH * EPC <= 16 ? 8 : 5) bn_partial_kernel(
                 sdx += t * xh[u][o];
             }
         }
+    };
+    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += 2 * kT) {
+        if (__builtin_amdgcn_readfirstlane(it0) + kT < end) chunks(it0, std::integral_constant<int, 2>{});
+        else chunks(it0, std::integral_constant<int, 1>{});
     }
     sdy = wave_sum(sdy);
     sdx = wave_sum(sdx);
