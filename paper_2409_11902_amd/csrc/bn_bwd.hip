@@ -236,16 +236,19 @@ __global__ void __launch_bounds__(kT) bn_partial_narrow_kernel(Geom g, BnPlan q,
     const rsrc_t rs = make_rsrc(dY, q.total * (uint32_t)R::XB), rs_z = make_rsrc(Zin, q.total * (uint32_t)(2 * R::WP));
     const uint32_t end = min((uint32_t)(s + 1) * q.per_slice, q.per_channel);
     float sdy = 0.f, sdx = 0.f;
-    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += 2 * kT) {
-        uint32_t d[2][4 * R::NL];
-        float xh[2][8 * R::NZ];
+    // U records requested before the first is added up: two gain 0-2 % on rows of 10 and 12, but cost as much on rows of 14, whose
+    // record is four loads already (165 random calls each; 273 channels at 6 x 14, batch 4000: 140 us with one, 150 with two)
+    constexpr int U = W >= 14 ? 1 : 2;
+    for (uint32_t it0 = (uint32_t)s * q.per_slice + threadIdx.x; it0 < end; it0 += U * kT) {
+        uint32_t d[U][4 * R::NL];
+        float xh[U][8 * R::NZ];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) { // (two records requested before the first is added up)
+        for (int u = 0; u < U; ++u) {
             const uint32_t it = it0 + u * kT, n = udiv(min(it, end - 1), q.inv_hp), i = min(it, end - 1) - n * g.Hp; // image by image
             R::load(rs, rs_z, (n * g.C + c) * g.Hp + i, it < end, mu, is, d[u], xh[u]);
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u) {
             if (it0 + u * kT >= end) break;
 #pragma unroll
             for (int j = 0; j < R::WP; ++j) {
