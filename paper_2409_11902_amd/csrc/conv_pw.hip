@@ -606,12 +606,12 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     // out its channels, which is a launch more as well (1.0).
     *gather_whole = !q.pw_pool && wgs < 256 && record_free;
     *variant = v;
-    // By waves, where the items are full (planes of 1 to 4 pixels: as above).  Measured on 600 random calls per direction against
-    // the launches above and the gather's: four waves to a tile take 0.4-0.75 of the time up to 256 tiles of 64 x 64 with eight
-    // stages or more (2048 -> 512 at 7 x 7, batch 64: 46.9 -> 28.8 us; the data gradient of 512 -> 2048 43.8 -> 24.4), 0.8-0.95 up to
-    // the lines below and with four to seven stages, 1.05-1.15 past them (wave tiles are 64 channels wide, and their operands
+    // By waves, where the items are full (planes of 1 to 4 pixels: as above).  Measured on 2885 random calls against the launches
+    // above and the gather's: four waves to a tile take 0.53-0.6 of the time up to 256 tiles of 64 x 64 with eight stages or
+    // more (2048 -> 512 at 7 x 7, batch 64: 46.9 -> 28.8 us; the data gradient of 512 -> 2048 43.8 -> 24.4), 0.73-1.0 up to the line below
+    // and 0.8-0.97 with four to seven stages up to theirs, 1.05-1.15 past them (wave tiles are 64 channels wide, and their operands
     // come through L2 once per 64 x 64).  With three stages, or fewer, a hand-over costs what it saves (0.95-1.3), but many
-    // tiles of one wave each keep more loads in flight than the shapes above (0.8-0.95).
+    // tiles of one wave each keep more loads in flight than the shapes above (0.75-0.93).
     const int gx = (ppi + q.gw - 1) / q.gw;
     const bool runs = q.gw == 7 && gx <= kWtItems && q.M % 8 == 0; // tiles of whole images, each a run of whole 16-byte pieces
     const int ipt = runs ? kWtItems / gx : 1;
@@ -619,6 +619,12 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     int ks = 0;
     if (q.nkb >= 4 && wt < (q.nkb >= 8 ? 2048 : 1024)) ks = 4;
     else if (q.nkb < 3 ? wt >= 2048 : q.nkb >= 4 && q.nkb < 8 && wt >= 4096) ks = 1;
+    // Nor where the shapes above, two workgroups to a compute unit, find the chip just about full -- 385 to 512 of them all start
+    // at once -- and little of their tiles is padding: four waves to a tile then take 1.07 of their time with six tiles of output
+    // channels or more (0.91 with two to four, whose pixels pass L2 less often), one wave to a tile 1.07 on planes of an even
+    // size (0.97 on odd ones); up to 1.28 (816 -> 1824 at 5 x 43, batch 15, 435 workgroups, 30.8 against 39.2 us).  Outside of the
+    // window a last round or a half-empty chip costs those shapes more than that.
+    if (!*gather && wgs > 384 && wgs <= 512 && 5 * wt >= 16 * wgs * kShapes[v].wm && (ks == 4 ? q.Mp >= 384 : q.gw == 8)) ks = 0;
 #ifdef CAC_TUNING
     if (const char *f = getenv("CAC_PW_WAVE")) if (atoi(f) < 0) ks = 0;
 #endif

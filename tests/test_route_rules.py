@@ -71,3 +71,22 @@ def test_stride2_weight_gradient_from_tiles_of_one_column(shape, kh, plan):
     d = B.make_desc(*shape, 3, 3, 2, 2, 1, 1, kh, 1, dtype=B.BF16)
     got = B.cac_describe_plan(d, B.OP_BWD_WEIGHT_COMPRESSED)
     assert plan in got, got
+
+
+@pytest.mark.parametrize("shape,k,waves", [
+    # N, C, K, H, W.  1 x 1: the waves of their own give way where 385 to 512 workgroups of the other kernel hold little padding ...
+    ((15, 816, 1824, 5, 43), 4, 0),
+    ((5, 866, 1280, 29, 38), 1, 0),
+    ((255, 128, 128, 13, 32), 4, 0),
+    ((114, 35, 141, 39, 11), 1, 1),       # ... but not to a quarter of it,
+    ((13, 816, 1824, 5, 43), 4, 4),       # to fewer workgroups,
+    ((259, 128, 128, 13, 32), 4, 1),      # to more,
+    ((45, 2048, 320, 22, 22), 1, 4),      # with four waves to a tile to few tiles of channels,
+    ((30, 96, 256, 33, 41), 4, 1),        # nor with one on planes of an odd size
+    ((64, 512, 2048, 7, 7), 2, 0),
+    ((64, 2048, 512, 7, 7), 2, 4),
+])
+def test_pointwise_layers_by_waves(shape, k, waves):
+    d = B.make_desc(*shape, 1, 1, pool_kh=k, pool_kw=k)
+    got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
+    assert got.startswith("pointwise") and (f"waves/tile={waves}" if waves else "img/tile") in got, got
