@@ -171,8 +171,10 @@ __global__ void __launch_bounds__(256) compress_kernel(Geom g, const T *__restri
     compress_body<T, EPC, KH, KW, PROD>(g, X, Z, cpr, total, inv_cpr, inv_hp, pr, blockIdx.x);
 }
 // With a filter's repack in the blocks ahead: work of 4-5 us that costs a launch of its own, and a forward pass needs both.
-// Steps of 512 -> 512 at 7 x 7, batch 256: 192.8 -> 188.3 us; 128 -> 256 stride 2 at 28 x 28, batch 128: 120.3 -> 114.5; 72 -> 100 at
-// 27 x 30, batch 24: 49.1 -> 46.3.  (55 registers and 9 KB of LDS where the pooling alone takes 14-43 and none: no loss seen.)
+// 362 random 3 x 3 forward calls that share the launch, inputs from memory: 0.88-0.91 of the time in the mean, worst 1.02.  512 -> 512
+// at 7 x 7, batch 256: 75 -> 69 us; 72 -> 100 at 27 x 30, batch 24: 17.8 -> 15.0; 128 -> 256 stride 2 at 28 x 28, batch 128: 43.5 -> 42.2; 64 -> 64
+// at 56 x 56, batch 128, tiles of 4: 51.6 -> 49.9; no gain at 14 x 14, 512 -> 512, batch 256: 220.2, 219.5.
+// (55 registers and 9 KB of LDS where the pooling alone takes 14-43 and none: no loss seen.)
 template <int EPC, int KH, int KW>
 __global__ void __launch_bounds__(256) compress_repack_kernel(Geom g, const bf16_t *__restrict__ X, bf16_t *__restrict__ Z, int cpr, uint32_t total,
                                                               double inv_cpr, double inv_hp, FilterRepack f, unsigned nrep)
@@ -272,14 +274,13 @@ bool launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Pro
     const long total = (long)g.N * g.C * g.Hp * cpr;
     if (total >= (1L << 31) || cpr >= (1 << 16) || g.Hp >= (1 << 16)) return false; // udiv's range
     const dim3 grid((unsigned)((total + 255) / 256));
-    const unsigned nrep = rep ? rep->blocks() : 0;
-    (void)nrep;
+    if (sizeof(T) != 2 && rep) return false; // (the repack is of bfloat16 filters)
 #define CAC_LAUNCH(KH, KW)                                                                                            \
     if (rep) {                                                                                                        \
         if constexpr (sizeof(T) == 2)                                                                                 \
-            hipLaunchKernelGGL((compress_repack_kernel<EPC, KH, KW>), dim3(grid.x + nrep), dim3(256), 0, st, g, (const bf16_t *)X, (bf16_t *)Z, \
-                               cpr, (uint32_t)total, 1.0 / cpr, 1.0 / g.Hp, *rep, nrep);                              \
-    } else if (prod)                                                                                                         \
+            hipLaunchKernelGGL((compress_repack_kernel<EPC, KH, KW>), dim3(grid.x + rep->blocks()), dim3(256), 0, st, g, \
+                               (const bf16_t *)X, (bf16_t *)Z, cpr, (uint32_t)total, 1.0 / cpr, 1.0 / g.Hp, *rep, rep->blocks()); \
+    } else if (prod)                                                                                                  \
         hipLaunchKernelGGL((compress_kernel<T, EPC, KH, KW, true>), grid, dim3(256), 0, st, g, (const T *)X, (T *)Z, cpr, \
                            (uint32_t)total, 1.0 / cpr, 1.0 / g.Hp, *prod);                                            \
     else                                                                                                              \
@@ -314,7 +315,8 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
             if constexpr (WW != 28)                                                                                      \
                 hipLaunchKernelGGL((compress_narrow_repack_kernel<WW>), dim3(grid.x + rep->blocks()), dim3(256), 0, st, g, \
                                    (const bf16_t *)X, (bf16_t *)Z, (uint32_t)total, *rep, rep->blocks());                \
-        } else if (prod)                                                                                                        \
+            else return false;                                                                                           \
+        } else if (prod)                                                                                                 \
             hipLaunchKernelGGL((compress_narrow_kernel<WW, true>), grid, dim3(256), 0, st, g, (const bf16_t *)X, (bf16_t *)Z,  \
                                (uint32_t)total, 1.0 / g.Hp, *prod);                                                      \
         else                                                                                                             \

@@ -68,7 +68,7 @@ __device__ __forceinline__ void repack_body(const RepackParams &p, const int bid
 {
     __shared__ bf16_t sm[kFilterElems > 64 * 66 ? kFilterElems : 64 * 66];
     if (bid >= p.in_blocks) {
-filter_repack(p.f, bid - p.in_blocks, sm);
+        filter_repack(p.f, bid - p.in_blocks, sm);
         return;
     }
     bf16_t (*tile)[66] = (bf16_t (*)[66])sm;
