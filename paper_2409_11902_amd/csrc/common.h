@@ -67,11 +67,12 @@ template <> struct Elem<bf16_t> {
 
 // ---- launchers implemented in the .hip files.  All enqueue on `st` and return the
 // launch status; operand shapes have been validated by the caller (api.hip).
-// compress.hip: true when the fast kernel covers the geometry and was launched (status in *err)
+// compress.hip: the geometries of the fast kernels; true when launched (status in *err)
+bool compress_fast_covers(const Geom &g, int dtype);
 bool launch_compress_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err);
-// ... and, bfloat16 only, with a filter's repack in the same launch (false: nothing has been launched)
+// ... and, bfloat16 only, with a filter's repack in the same launch, of a geometry that is covered
 struct FilterRepack;
-bool launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st, hipError_t *err);
+hipError_t launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st);
 hipError_t launch_compress_generic(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st);
 // conv_lds.hip: false when the geometry does not fit LDS (status in *err otherwise)
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err);

@@ -268,13 +268,11 @@ __global__ void __launch_bounds__(256) compress_narrow_repack_kernel(Geom g, con
 }
 
 template <typename T, int EPC>
-bool launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Producer *prod = nullptr, const FilterRepack *rep = nullptr)
+void launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Producer *prod = nullptr, const FilterRepack *rep = nullptr)
 {
     const int cpr = (g.W + EPC - 1) / EPC;
     const long total = (long)g.N * g.C * g.Hp * cpr;
-    if (total >= (1L << 31) || cpr >= (1 << 16) || g.Hp >= (1 << 16)) return false; // udiv's range
     const dim3 grid((unsigned)((total + 255) / 256));
-    if (sizeof(T) != 2 && rep) return false; // (the repack is of bfloat16 filters)
 #define CAC_LAUNCH(KH, KW)                                                                                            \
     if (rep) {                                                                                                        \
         if constexpr (sizeof(T) == 2)                                                                                 \
@@ -290,23 +288,38 @@ bool launch_epc(const Geom &g, const void *X, void *Z, hipStream_t st, const Pro
     else if (g.kh == 4 && g.kw == 4) { CAC_LAUNCH(4, 4); }
     else if (g.kh == 1 && g.kw == 1) { CAC_LAUNCH(1, 1); }
     else if (g.kh == 2 && g.kw == 4) { CAC_LAUNCH(2, 4); }
-    else if (g.kh == 4 && g.kw == 2) { CAC_LAUNCH(4, 2); }
-    else return false;
+    else { CAC_LAUNCH(4, 2); }
 #undef CAC_LAUNCH
-    return true;
+}
+
+int chunk_elems(const Geom &g, int dtype)
+{
+    return dtype == CAC_BF16 && g.W >= 8 ? 8 : 4; // (narrow maps: 8-byte chunks so that a chunk does not span more than one row's worth)
+}
+// Rows that a thread takes in pairs (see compress_narrow_kernel).  Rows of 28: only the producer form, whose stores of the
+// activation gain more than its strided cold loads lose (plain compression measured 4.05 TB/s this way against 4.9 with
+// the chunk kernel).
+bool row_pairs(const Geom &g, int dtype, bool producer)
+{
+    return dtype == CAC_BF16 && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W == 10 || g.W == 12 || g.W == 14 || (producer && g.W == 28));
 }
 
 } // namespace
 
+bool compress_fast_covers(const Geom &g, int dtype)
+{
+    if ((long)g.N * g.C * g.H * g.W * 4 >= (1L << 31)) return false; // 32-bit buffer offsets
+    if (row_pairs(g, dtype, false)) return true;
+    const int epc = chunk_elems(g, dtype), cpr = (g.W + epc - 1) / epc;
+    if ((long)g.N * g.C * g.Hp * cpr >= (1L << 31) || cpr >= (1 << 16) || g.Hp >= (1 << 16)) return false; // udiv's range
+    return (g.kh == g.kw && (g.kh == 1 || g.kh == 2 || g.kh == 4)) || (g.kh == 2 && g.kw == 4) || (g.kh == 4 && g.kw == 2);
+}
+
 static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st, hipError_t *err, const Producer *prod,
                         const FilterRepack *rep = nullptr)
 {
-    if ((long)g.N * g.C * g.H * g.W * 4 >= (1L << 31)) return false; // 32-bit buffer offsets
-    bool ok;
-    if (dtype == CAC_BF16 && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W == 10 || g.W == 12 || g.W == 14 || (prod && g.W == 28))) {
-        // narrow rows: a thread per pair of rows (see compress_narrow_kernel).  Rows of 28: only the
-        // producer form, whose stores of the activation gain more than its strided cold loads lose
-        // (plain compression measured 4.05 TB/s this way against 4.9 with the chunk kernel)
+    if (!compress_fast_covers(g, dtype)) return false;
+    if (row_pairs(g, dtype, prod)) {
         const long total = (long)g.N * g.C * g.Hp;
         const dim3 grid((unsigned)((total + 255) / 256));
 #define CAC_NARROW(WW)                                                                                                   \
@@ -315,7 +328,6 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
             if constexpr (WW != 28)                                                                                      \
                 hipLaunchKernelGGL((compress_narrow_repack_kernel<WW>), dim3(grid.x + rep->blocks()), dim3(256), 0, st, g, \
                                    (const bf16_t *)X, (bf16_t *)Z, (uint32_t)total, *rep, rep->blocks());                \
-            else return false;                                                                                           \
         } else if (prod)                                                                                                 \
             hipLaunchKernelGGL((compress_narrow_kernel<WW, true>), grid, dim3(256), 0, st, g, (const bf16_t *)X, (bf16_t *)Z,  \
                                (uint32_t)total, 1.0 / g.Hp, *prod);                                                      \
@@ -328,15 +340,11 @@ static bool launch_fast(const Geom &g, int dtype, const void *X, void *Z, hipStr
         *err = hipGetLastError();
         return true;
     }
-    if (dtype == CAC_F32) {
-        if (g.kw > 4) return false;
-        ok = launch_epc<float, 4>(g, X, Z, st, prod);
-    } else {
-        // narrow maps: 8-byte chunks so that a chunk does not span more than one row's worth
-        ok = g.W >= 8 ? launch_epc<bf16_t, 8>(g, X, Z, st, prod, rep) : (g.kw <= 4 ? launch_epc<bf16_t, 4>(g, X, Z, st, prod, rep) : false);
-    }
-    if (ok) *err = hipGetLastError();
-    return ok;
+    if (dtype == CAC_F32) launch_epc<float, 4>(g, X, Z, st, prod);
+    else if (chunk_elems(g, dtype) == 8) launch_epc<bf16_t, 8>(g, X, Z, st, prod, rep);
+    else launch_epc<bf16_t, 4>(g, X, Z, st, prod, rep);
+    *err = hipGetLastError();
+    return true;
 }
 
 // True when the fast kernel covers the geometry (and has been launched).
@@ -345,9 +353,11 @@ bool launch_compress_fast(const Geom &g, int dtype, const void *X, void *Z, hipS
     return launch_fast(g, dtype, X, Z, st, err, nullptr);
 }
 
-bool launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st, hipError_t *err)
+hipError_t launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st)
 {
-    return launch_fast(g, CAC_BF16, X, Z, st, err, nullptr, &f);
+    hipError_t err = hipErrorInvalidValue; // (unless launched)
+    launch_fast(g, CAC_BF16, X, Z, st, &err, nullptr, &f);
+    return err;
 }
 
 // The producer form: Xn = relu(scale[c] * Y + shift[c]) stored in the tensors' type, Zn = pooled Xn,

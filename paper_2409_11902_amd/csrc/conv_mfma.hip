@@ -1121,6 +1121,12 @@ bool fwd_reads_in_place(const Geom &g, const GatherParams &p)
                       p.IPT * p.PH * ((g.W + 7) / 8) * (KC / 8) * p.T <= 512);
 }
 
+// The record's own launch carries the filter's repack: nothing else forms the one, and the other is a launch for nothing else.
+bool record_with_filter(const Geom &g, const GatherParams &p)
+{
+    return (p.tile == 3 ? !p.w_direct && !p.pw_pool : fwd_reads_in_place(g, p) && !record_in_repack(g)) && compress_fast_covers(g, CAC_BF16);
+}
+
 // Workspace: [channels-last input][repacked filter][float sums of shared-out channels], each
 // part starting at a multiple of 256 bytes; nothing for an operand that is read where it lies.
 struct WsLayout { size_t in, wt, part; };
@@ -1156,7 +1162,7 @@ bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, siz
         if (!plan_fwd(g, dtype, p, &variant[0])) return false;
         const int n = describe_one(p, variant[0], buf, len);
         const char *note = p.decim ? "; the copy of the input keeps one pixel of every 2 x 2 tile" : !p.tile && fwd_reads_in_place(g, p) ? "; X read in place" : "";
-        if (n > 0 && (size_t)n + 1 < len) snprintf(buf + n, len - n, "%s", note);
+        if (n > 0 && (size_t)n + 1 < len) snprintf(buf + n, len - n, "%s%s", note, record_with_filter(g, p) ? "; the record in the filter's launch" : "");
         return true;
     }
     if (!plan_dx(g, dtype, p, cls, variant, &ncls, &empty)) return false;
@@ -1196,12 +1202,13 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
     p.part = l.part ? (float *)((char *)ws + l.in + l.wt) : nullptr;
     const bool fuse = Z && record_in_repack(g); // (with `direct` the repack launch forms Z without writing the channels-last copy)
-    const bool direct = fwd_reads_in_place(g, p);
+    const bool direct = fwd_reads_in_place(g, p), with_filter = Z && record_with_filter(g, p);
+    *pooled = with_filter;
     if (p.tile == 3) {
         // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
         if (!p.w_direct) {
             const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0};
-            if (Z && !p.pw_pool && launch_compress_repack(g, X, Z, f, st, err)) *pooled = true;
+            if (with_filter) *err = launch_compress_repack(g, X, Z, f, st);
             else *err = launch_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W, st);
         }
         if (*err != hipSuccess) return true;
@@ -1215,8 +1222,9 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     }
     // nothing to do for the input but the record: the filter's blocks go ahead of the pooling ones in one launch
     const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0};
-    if (Z && direct && !fuse && launch_compress_repack(g, X, Z, f, st, err)) *pooled = true;
-    else {
+    if (with_filter) {
+        *err = launch_compress_repack(g, X, Z, f, st);
+    } else {
         *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C,
                              p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr, p.decim);
         *pooled = fuse;
