@@ -294,12 +294,13 @@ int cac_describe_plan(const cac_desc *d, int op, char *buf, size_t buf_len)
                  rk.partial_bytes);
     } else if (op == CAC_OP_BWD_WEIGHT_COMPRESSED && dw_mfma_plan(g, d->dtype, &plan)) {
         const DwMfmaParams &p = plan.p;
+        static const char *const split[] = {"", " registers split towards Z (4 dY, 8 Z)", " registers split towards Z (2 dY, 16 Z)"};
         snprintf(buf, buf_len,
                  "dw_mfma variant=%d tile=%dx%d chunk=%dimg x %drows (LR=%d/%d SEGS=%d NZ=%d XW=%d) items dy=%d z=%d "
                  "passes dy=%d z=%d lds=%dB chunks=%d slices=%d x %d tiles grid=%u partial=%zuB%s",
                  plan.variant, p.tile_o, p.tile_c, p.NBI, p.PR, p.LR, p.LRpad, p.SEGS, p.NZ, p.XW, p.rowitems, p.citems, p.dy_passes,
                  p.z_passes, p.lds_bytes, p.nchunks, p.nslices, p.tiles_o * p.tiles_c, plan.grid,
-                 plan.partial_bytes, p.dy_direct ? " dY straight into LDS" : p.widez ? " registers split towards Z" : "");
+                 plan.partial_bytes, p.dy_direct ? " dY straight into LDS" : split[p.widez]);
     } else if (DwTiledPlan tl; op == CAC_OP_BWD_WEIGHT_COMPRESSED && dw_tiled_plan(g, d->dtype, &tl)) {
         snprintf(buf, buf_len, "dw_tiled tile=16x16 unit=%d rows (LDS rows %d x %d floats) lds=%dB units=%d slices=%d x %d tiles grid=%u partial=%zuB",
                  tl.p.PR, tl.p.XR, tl.p.XW, tl.p.lds_bytes, tl.p.nunits, tl.p.nslices, tl.p.tiles_o * tl.p.tiles_c, tl.grid,
