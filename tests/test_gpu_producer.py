@@ -119,3 +119,31 @@ def test_batch_norm_backward_from_the_compressed_record(c):
         # pooling factor 1 keeps the activation: the exact backward pass
         e_dg, e_db, e_dx = oracle.bn_bwd(Y.astype(np.float64), dY.astype(np.float64), mean, invstd, gamma)
         assert rel_l2(download(dX.t), e_dx) <= (1e-5 if dt == synth.F32 else 4e-3)
+
+
+# Cases of the channel sums' ways: one slice, two to eight that the element-wise pass adds up, up to 64 of a launch of their own, also
+# for few slices of many threads.  Slices of more than two chunks per thread and of no whole number of them.
+BN_SLICES = [
+    # N, C, H, W, kh, kw, dtype, slices
+    (64, 512, 16, 16, 2, 2, synth.BF16, 4), (128, 512, 7, 7, 2, 2, synth.BF16, 4), (40, 300, 9, 13, 2, 4, synth.BF16, 2),
+    (70, 256, 14, 14, 4, 4, synth.BF16, 3), (60, 300, 9, 12, 4, 2, synth.BF16, 2), (110, 260, 5, 9, 1, 1, synth.BF16, 5),
+    (40, 300, 11, 9, 2, 2, synth.F32, 3), (50, 270, 8, 8, 4, 4, synth.F32, 1), (120, 270, 8, 7, 2, 2, synth.F32, 4),
+    (200, 256, 6, 12, 2, 2, synth.BF16, 3), (40, 300, 28, 28, 2, 2, synth.BF16, 6),
+    # rows of pooled values of odd length under chunks of four of them, tensors of an odd number of elements
+    (3, 50, 9, 22, 2, 2, synth.BF16, 1), (5, 41, 13, 17, 2, 2, synth.BF16, 1), (1, 5, 9, 18, 2, 2, synth.BF16, 1),
+    (4, 20, 7, 9, 2, 2, synth.BF16, 1), (1, 3, 5, 7, 1, 1, synth.BF16, 1), (2, 30, 6, 6, 1, 1, synth.BF16, 1),
+    # long slices
+    (2240, 3, 16, 16, 2, 2, synth.BF16, 64), (2400, 3, 10, 12, 2, 2, synth.F32, 64), (6700, 3, 10, 10, 2, 2, synth.BF16, 64),
+    (5500, 3, 12, 12, 2, 2, synth.BF16, 64), (4700, 3, 14, 14, 2, 2, synth.BF16, 64), (150, 1030, 6, 6, 1, 1, synth.BF16, 1),
+    # few slices of many threads: a launch of their own; tiles of four rows: in the pass all the same
+    (1600, 260, 4, 4, 1, 1, synth.BF16, 7), (7000, 260, 4, 1, 4, 4, synth.BF16, 7),
+]
+
+
+@pytest.mark.parametrize("c", BN_SLICES, ids=[" ".join(map(str, c)) for c in BN_SLICES])
+def test_batch_norm_backward_slices(c):
+    N, C, H, W, kh, kw, dt, slices = c
+    d = B.make_desc(N, C, 8, H, W, 1, 1, 1, 1, 0, 0, kh, kw, dtype=B.F32 if dt == synth.F32 else B.BF16)
+    plan = B.cac_describe_plan(d, B.OP_BN_BWD)
+    assert f"({slices} slices" in plan, plan
+    test_batch_norm_backward_from_the_compressed_record(c[:7])
