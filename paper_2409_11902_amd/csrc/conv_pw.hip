@@ -274,8 +274,8 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
 // pixels, 8 along the channels), its part of LDS is its own, and no barrier stands between two stages, so that the eight or
 // twelve waves of a compute unit are at different points and fill each other's gaps.  Items of a tile follow one another
 // from image to image.  KS waves take every KS-th stage of one tile and add their sums through LDS, in wave order.
-// EPI = 16, planes of an odd size up to 56: a tile is whole images, whose 64 channels are one run of memory each, and the
-// result leaves in 16-byte stores of that run instead of element by element.
+// EPI = 16, planes of an odd size up to 56, KS > 1: a tile is whole images, whose 64 channels are one run of memory each, and
+// the result leaves in 16-byte stores of that run instead of element by element.
 constexpr int kWt = 64, kWtItems = 8;                            // pixels of a wave's tile; items along them
 constexpr int kWtBytes = kWt * KCS * 2 + kWtItems * 16;         // a wave's staging buffer
 constexpr int kBlk = 64 * 16 * 4;                                // the sums of one 32 x 32 block
@@ -508,7 +508,9 @@ template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherPara
 }
 template <int KS> hipError_t launch_wave(const GatherParams &p, hipStream_t st)
 {
-    if (p.gw == 7) return p.store_px == 16 ? launch_wave_fixed<KS, 7, 16>(p, st) : launch_wave_fixed<KS, 7, 1>(p, st);
+    if constexpr (KS > 1)
+        if (p.store_px == 16) return launch_wave_fixed<KS, 7, 16>(p, st);
+    if (p.gw == 7) return launch_wave_fixed<KS, 7, 1>(p, st);
     return p.store_px == 8 ? launch_wave_fixed<KS, 8, 8>(p, st) : p.store_px == 4 ? launch_wave_fixed<KS, 8, 4>(p, st)
                                                                                   : launch_wave_fixed<KS, 8, 2>(p, st);
 }
@@ -613,12 +615,22 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     // come through L2 once per 64 x 64).  With three stages, or fewer, a hand-over costs what it saves (0.95-1.3), but many
     // tiles of one wave each keep more loads in flight than the shapes above (0.75-0.93).
     const int gx = (ppi + q.gw - 1) / q.gw;
-    const bool runs = q.gw == 7 && gx <= kWtItems && q.M % 8 == 0; // tiles of whole images, each a run of whole 16-byte pieces
+    const long items = (long)p.N * gx;
+    bool runs = q.gw == 7 && gx <= kWtItems && q.M % 8 == 0; // tiles of whole images, each a run of whole 16-byte pieces
     const int ipt = runs ? kWtItems / gx : 1;
-    const long tiles = runs ? (p.N + ipt - 1) / ipt : ((long)p.N * gx + kWtItems - 1) / kWtItems, wt = tiles * (q.Mp / 64);
+    long tiles = runs ? (p.N + ipt - 1) / ipt : (items + kWtItems - 1) / kWtItems, wt = tiles * (q.Mp / 64);
     int ks = 0;
-    if (q.nkb >= 4 && wt < (q.nkb >= 8 ? 2048 : 1024)) ks = 4;
-    else if (q.nkb < 3 ? wt >= 2048 : q.nkb >= 4 && q.nkb < 8 && wt >= 4096) ks = 1;
+    if (q.nkb >= 4 && wt < (q.nkb >= 8 ? 2048 : 1024)) {
+        ks = 4;
+    } else {
+        // One wave hands out a run's elements two bytes at a time between barriers that the workgroup's other tiles wait for, and
+        // whole images leave a tile emptier: 1.1 of the time of the shapes above, worst 1.38 (128 -> 1648 at 7 x 7, batch 124: 28.1
+        // against 20.5 us), where items that run on take 0.87, worst 1.12 (420 random calls; 0.80 of the time with runs).
+        runs = false;
+        tiles = (items + kWtItems - 1) / kWtItems;
+        wt = tiles * (q.Mp / 64);
+        if (q.nkb < 3 ? wt >= 2048 : q.nkb >= 4 && q.nkb < 8 && wt >= 4096) ks = 1;
+    }
     // Nor where the shapes above, two workgroups to a compute unit, find the chip just about full -- 385 to 512 of them all start
     // at once -- and little of their tiles is padding: four waves to a tile then take 1.07 of their time with six tiles of output
     // channels or more (0.91 with two to four, whose pixels pass L2 less often), one wave to a tile 1.07 on planes of an even
@@ -631,10 +643,10 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
     // Not where the record is pooled on the way, which is worth more than the waves, nor for fewer than eight tiles of a layer
     // that the gather takes: those are too few to matter (1 in 50 random layers; 0.65 of the time) and keep its channel split
     // in use and under test.
-    if (ks && !q.pw_pool && (!*gather || wt >= 8) && 2 * ppi > gx * q.gw && divides_exactly((uint64_t)p.N * gx + kWtItems * 4, gx)) {
+    if (ks && !q.pw_pool && (!*gather || wt >= 8) && 2 * ppi > gx * q.gw && divides_exactly((uint64_t)items + kWtItems * 4, gx)) {
         q.GX = gx;
         q.m_gx = magic_of(gx);
-        q.IPT = ipt;
+        q.IPT = runs ? ipt : 1;
         q.ngrp = 1;
         q.tile_px = kWt;
         const int pt = 4 / ks;

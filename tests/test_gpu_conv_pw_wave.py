@@ -24,7 +24,8 @@ CASES = [
     (9, 260, 650, 6, 6, 4, 4),       # four
     (9, 260, 330, 5, 6, 4, 4),       # two, an item's last pixels in the next plane
     (1, 1500, 520, 2, 4, 4, 4),      # one item per image, fewer items than a tile has
-    (1400, 72, 100, 7, 7, 1, 1),     # one wave to a tile, 16-byte runs
+    (1400, 72, 100, 7, 7, 1, 1),     # one wave to a tile, whole pieces of output channels or not
+    (130, 40, 1104, 3, 15, 1, 4),
     (1500, 40, 136, 6, 6, 1, 0),
     (700, 260, 450, 9, 7, 1, 0),
 ]

@@ -90,3 +90,17 @@ def test_pointwise_layers_by_waves(shape, k, waves):
     d = B.make_desc(*shape, 1, 1, pool_kh=k, pool_kw=k)
     got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
     assert got.startswith("pointwise") and (f"waves/tile={waves}" if waves else "img/tile") in got, got
+
+
+@pytest.mark.parametrize("shape,pixels", [
+    # N, C, K, H, W.  1 x 1, odd planes: tiles of whole images are for four waves to a tile
+    ((124, 128, 1648, 7, 7), "56px ch/pass=64 waves/tile=1"),
+    ((171, 32, 1104, 3, 15), "56px ch/pass=64 waves/tile=1"),
+    ((420, 64, 912, 5, 7), "56px ch/pass=64 waves/tile=1"),
+    ((32, 256, 1024, 7, 7), "49px ch/pass=64 waves/tile=4"),
+    ((13, 264, 392, 5, 5), "50px ch/pass=64 waves/tile=4"),
+])
+def test_pointwise_wave_tiles_of_odd_planes(shape, pixels):
+    d = B.make_desc(*shape, 1, 1, pool_kh=2, pool_kw=2)
+    got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
+    assert got.startswith("pointwise by waves tile=64ch x " + pixels), got
