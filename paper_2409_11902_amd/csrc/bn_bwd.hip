@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(64) bn_finish_kernel(int S, const float *__res
 
 // What the element-wise pass takes its channel sums from: S <= kFold partial sums each, which every thread adds (in the order
 // of wave_sum) and the first thread of a channel writes to dbeta and dgamma -- a few loads that all threads of a channel
-// share, against a launch of 4.7 us --, or, S = 1, the sums themselves.
+// share, against a launch of their own --, or, S = 1, the sums themselves.
 constexpr int kFold = 8;
 struct Sums {
     const float *dy, *dx;
