@@ -958,7 +958,12 @@ bool shape_gather(GatherParams &p, int *variant)
 
 hipError_t run_gather(const GatherParams &p, int variant, hipStream_t st)
 {
-    if (p.tile) return p.tile == 3 ? launch_pw(p, variant, st) : p.tile == 2 ? launch_dx2(p, variant, st) : launch_tile(p, variant, st);
+    switch (p.tile) {
+    case 1: return launch_tile(p, variant, st);
+    case 2: return launch_dx2(p, variant, st);
+    case 3: return launch_pw(p, variant, st);
+    case 4: return launch_wave(p, variant, st);
+    }
     switch (variant) {
     case 0: return launch_gather<2, 1, 4>(p, st);
     case 1: return launch_gather<2, 2, 2>(p, st);
@@ -1003,6 +1008,41 @@ bool plan_pw(GatherParams &p, bool pool, bool record_free, int *variant)
     return true;
 }
 
+// A launch with other filters: nine taps go to conv_tile.hip, or with few pixels to conv_wave.hip, what they leave to the gather.
+bool plan_other(GatherParams &p, bool fwd, int *variant)
+{
+    GatherParams wave = p, tile = p;
+    int wave_variant;
+    double wave_cost, tile_cost = 1e300;
+    const bool have_tile = use_tile() && shape_tile(tile, variant, &tile_cost);
+    bool have_wave = use_tile() && shape_wave(wave, &wave_variant, &wave_cost);
+    // Where conv_tile.hip has no shape, 300 random layers took 0.59 of the gather's time with waves (both directions, 9 of them over
+    // 1.05).  Two lines remain to the gather: sums over 48 channels and less, which leave a wave without a stage (data
+    // gradients 1.0-1.09 of the time; forward passes up to 4096 pixels 0.7, the input's copy falls away), and a dozen tiles of
+    // less than 0.1 GFLOP, launches and start-up either way, where it shares the channels over workgroups.
+    const long px = (long)p.N * p.Hc * p.Wc;
+    if (have_wave && p.KCin <= 48) have_wave = fwd && px < 4096;
+    if (have_wave && p.KCin <= 256 && (px + 63) / 64 * (p.Mp / 64) <= 12 && 18.0 * px * p.KCin * p.M < 1e8) have_wave = false;
+    // Against conv_tile.hip: 200 random layers, by the ratio of the two planners' cycles; below 0.55 the waves take 0.76 of the
+    // time (48 layers, 2 of them over 1.05), up to 0.7 it is 1.0, above 1.0 1.6.
+    if (have_wave && have_tile) have_wave = wave_cost < 0.55 * tile_cost;
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_WAVE"); f && atoi(f) == 0) have_wave = false;
+#endif
+    if (have_wave) {
+        p = wave;
+        p.tile = 4;
+        *variant = wave_variant;
+        return true;
+    }
+    if (have_tile) {
+        p = tile;
+        p.tile = 1;
+        return true;
+    }
+    return shape_gather(p, variant);
+}
+
 // Whole 2 x 2 tiles, rows a multiple of 8 pixels: the pooled map falls out of the repack.
 bool record_in_repack(const Geom &g) { return !g.pmax && g.kh == 2 && g.kw == 2 && g.H % 2 == 0 && (g.W % 8 == 0 || g.W == 4); }
 
@@ -1037,8 +1077,7 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
         p.w_bytes = p.w_direct ? (uint32_t)g.K * g.C * 2u : (uint32_t)p.Mp * p.KCp * 2u;
         return true;
     }
-    if (use_tile() && shape_tile(p, variant)) { p.tile = 1; return true; }
-    return shape_gather(p, variant);
+    return plan_other(p, true, variant);
 }
 
 // Data gradient: one gather GEMM (input channels x input pixels) per parity class of the input
@@ -1080,10 +1119,8 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 p.w_direct = 0;
                 p.w_kstep = (uint32_t)p.Mp * 32u;
                 p.w_bytes = (uint32_t)p.Mp * p.KCp * 2u;
-            } else if (use_tile() && shape_tile(p, &variant[*ncls])) {
-                p.tile = 1;
-                base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
-            } else if (!shape_gather(p, &variant[*ncls])) return false;
+            } else if (!plan_other(p, false, &variant[*ncls])) return false;
+            else if (p.tile) base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
             cls[(*ncls)++] = p;
         }
     return true;
@@ -1104,6 +1141,7 @@ bool dx_reads_in_place(const Geom &g, const GatherParams (&cls)[4], int ncls)
 int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
 {
     if (p.tile == 3) return describe_pw(p, variant, buf, len);
+    if (p.tile == 4) return describe_wave(p, variant, buf, len);
     if (p.tile) return p.tile == 2 ? describe_dx2(p, variant, buf, len) : describe_tile(p, variant, buf, len);
     static const int shape[6][3] = {{2, 1, 4}, {2, 2, 2}, {2, 4, 1}, {1, 1, 4}, {1, 2, 2}, {1, 4, 1}}; // NI, WM, WN
     const int *v = shape[variant];
@@ -1174,7 +1212,7 @@ bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, siz
         n = describe_one(cls[k], variant[k], buf + at, len - at);
         at += (size_t)max(n, 0);
     }
-    if (at + 1 < len && dx_reads_in_place(g, cls, ncls)) snprintf(buf + at, len - at, "; dY read in place");
+    if (at + 1 < len && dx_reads_in_place(g, cls, ncls) && cls[0].tile != 4) snprintf(buf + at, len - at, "; dY read in place");
     return true;
 }
 

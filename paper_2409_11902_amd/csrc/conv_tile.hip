@@ -273,8 +273,8 @@ const Shape kShapes[] = {
 
 } // namespace
 
-// Fills the tiling of a nine-tap launch; false when no shape takes it.
-bool shape_tile(GatherParams &p, int *variant)
+// Fills the tiling of a nine-tap launch; false when no shape takes it.  *cost_out: clock cycles, roughly.
+bool shape_tile(GatherParams &p, int *variant, double *cost_out)
 {
     if (p.ntaps != TAPS || p.os != 1) return false;
     GatherParams b = p;
@@ -333,8 +333,8 @@ bool shape_tile(GatherParams &p, int *variant)
         const int mtiles = (q.Mp / 64 + sh.wm - 1) / sh.wm;
         const long wgs = (long)q.tiles_per_img * q.ngrp * mtiles;
         q.gpw = 1;
-        // Few workgroups: the launches of conv_mfma.hip, which keep two stages of loads in flight and share out the
-        // channels of a tile, are the faster ones (512 -> 512 at 4 x 4, batch 128, 64 workgroups here: 28 against 38 us;
+        // Few workgroups: conv_wave.hip, whose waves share out the channels of a tile, and the launches of conv_mfma.hip are the
+        // faster ones (against the latter: 512 -> 512 at 4 x 4, batch 128, 64 workgroups here: 28 against 38 us;
         // 240 -> 272 at 12 x 12, batch 24, 144 workgroups: 2 us; 128 -> 128 at 16 x 16, batch 128, 256 workgroups: even).
         // For rows of odd length they need an element-by-element repack, for planes that are no multiple of 4 pixels
         // they store single elements, and lose from 64 workgroups on (512 -> 512 at 7 x 7, batch 64, 104 workgroups:
@@ -361,6 +361,7 @@ bool shape_tile(GatherParams &p, int *variant)
     }
     if (best_cost > 1e299) return false;
     p = best;
+    *cost_out = best_cost;
     return true;
 }
 
