@@ -172,14 +172,15 @@ static hipError_t do_compress(const Geom &g, int dtype, const void *X, void *Z, 
 // The weight gradient with the kernel the descriptor asks for (the reduced-K form where this
 // version has one for the geometry, else the inflating MFMA kernel, else the plain one).
 static int launch_weight_gradient(const Geom &g, int dtype, const void *Z, const void *dY, float *dW, void *ws, hipStream_t st,
-                                  DwReduceTail *defer)
+                                  DwReduceTail *defer, const RepackParams *rep = nullptr, bool *rep_done = nullptr)
 {
     if (defer) defer->blocks = 0;
     DwRkPlan rk;
     if (reduced_k_plan(g, dtype, &rk))
         return launched(launch_dw_rk(rk, Z, dY, dW, ws, st, defer), "weight gradient (reduced K)");
     DwMfmaPlan plan;
-    if (dw_mfma_plan(g, dtype, &plan)) return launched(launch_dw_mfma(plan, Z, dY, dW, ws, st, defer), "weight gradient (MFMA)");
+    if (dw_mfma_plan(g, dtype, &plan)) 
+        return launched(launch_dw_mfma(plan, Z, dY, dW, ws, st, defer, rep, rep_done), "weight gradient (MFMA)");
     DwTiledPlan tl;
     if (dw_tiled_plan(g, dtype, &tl)) return launched(launch_dw_tiled(tl, dtype, Z, dY, dW, ws, st, defer), "weight gradient (tiled)");
     return launched(launch_dw_generic(g, dtype, Z, dY, dW, st), "weight gradient");
@@ -315,12 +316,15 @@ int cac_describe_plan(const cac_desc *d, int op, char *buf, size_t buf_len)
         snprintf(buf, buf_len, "sums and element-wise pass (%zu slices per channel where the chunk kernels take the tile)",
                  n ? n / (2 * sizeof(float) * (size_t)g.C) : (size_t)1);
     } else if (op == CAC_OP_BWD_WEIGHT_AND_DATA) {
-        char dx[64];
         const bool split = (reduced_k_plan(g, d->dtype, &rk)) ? !rk.p.direct
                                                                                            : (dw_mfma_plan(g, d->dtype, &plan) && !plan.p.direct);
-        const bool merged = split && describe_conv_mfma(g, d->dtype, true, dx, sizeof dx);
-        snprintf(buf, buf_len, merged ? "weight gradient, then its slice sum in the launch of the data gradient's repack, then the data gradient"
-                                      : "weight gradient, then data gradient, as in the separate calls");
+        DxPlan dxp;
+        const bool planned = plan_dx_mfma(g, d->dtype, nullptr, nullptr, nullptr, nullptr, &dxp);
+        const bool with_dw = planned && !reduced_k_plan(g, d->dtype, &rk) && dw_mfma_plan(g, d->dtype, &plan) && dw_takes_repack(plan, dxp.rep);
+        if (!planned || !(split || with_dw)) snprintf(buf, buf_len, "weight gradient, then data gradient, as in the separate calls");
+        else if (with_dw) snprintf(buf, buf_len, "weight gradient with the data gradient's repack in its launch, then data gradient%s",
+                                   split ? " and, in the launch of it, the slice sum" : "");
+        else snprintf(buf, buf_len, "weight gradient, then its slice sum in the launch of the data gradient's repack, then the data gradient");
     } else {
         snprintf(buf, buf_len, "generic kernel");
     }
@@ -396,8 +400,10 @@ int conv_bwd_data(const cac_desc *d, const void *W, const void *dY, void *dX, vo
     if ((rc = check_ptr(W, "W")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dX, "dX"))) return rc;
     if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_DATA, ws, ws_bytes, nullptr))) return rc;
     hipError_t e = hipSuccess;
-    if (!launch_dx_mfma(g, d->dtype, W, dY, dX, ws, (hipStream_t)stream, &e) &&
-        !launch_dx_lds(g, d->dtype, W, dY, dX, (hipStream_t)stream, &e))
+    DxPlan dx;
+    if (plan_dx_mfma(g, d->dtype, W, dY, dX, ws, &dx))
+        e = launch_dx_mfma(dx, false, nullptr, (hipStream_t)stream);
+    else if (!launch_dx_lds(g, d->dtype, W, dY, dX, (hipStream_t)stream, &e))
         e = launch_dx_generic(g, d->dtype, W, dY, dX, (hipStream_t)stream);
     return launched(e, "data gradient");
 }
@@ -414,13 +420,17 @@ int conv_bwd_weight_and_data(const cac_desc *d, const void *Z, const void *W, co
     if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_WEIGHT_AND_DATA, ws, ws_bytes, nullptr))) return rc;
     hipStream_t st = (hipStream_t)stream;
     void *ws_dx = ws ? (char *)ws + both_dw_bytes(g, d->dtype) : nullptr;
+    // Two launches where the weight gradient's has room for the repacks of the data gradient: the slice sum rides with the data
+    // gradient then, else with the repacks.
+    DxPlan dx;
+    const bool planned = plan_dx_mfma(g, d->dtype, W, dY, dX, ws_dx, &dx);
     DwReduceTail tail{};
-    if ((rc = launch_weight_gradient(g, d->dtype, Z, dY, (float *)dW, ws, st, &tail))) return rc;
+    bool repacked = false;
+    if ((rc = launch_weight_gradient(g, d->dtype, Z, dY, (float *)dW, ws, st, &tail, planned ? &dx.rep : nullptr, &repacked))) return rc;
+    if (planned) return launched(launch_dx_mfma(dx, repacked, &tail, st), "data gradient");
+    if ((rc = launched(launch_dw_reduce(tail, st), "weight gradient (slice sum)"))) return rc;
     hipError_t e = hipSuccess;
-    if (!launch_dx_mfma(g, d->dtype, W, dY, dX, ws_dx, st, &e, &tail)) {
-        if ((rc = launched(launch_dw_reduce(tail, st), "weight gradient (slice sum)"))) return rc;
-        if (!launch_dx_lds(g, d->dtype, W, dY, dX, st, &e)) e = launch_dx_generic(g, d->dtype, W, dY, dX, st);
-    }
+    if (!launch_dx_lds(g, d->dtype, W, dY, dX, st, &e)) e = launch_dx_generic(g, d->dtype, W, dY, dX, st);
     return launched(e, "data gradient");
 }
 

@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(256) compress_repack_kernel(Geom g, const bf16
                                                               double inv_cpr, double inv_hp, FilterRepack f, unsigned nrep)
 {
     __shared__ bf16_t sm[kFilterElems];
-    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, sm);
+    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, sm, threadIdx.x);
     else compress_body<bf16_t, EPC, KH, KW, false>(g, X, Z, cpr, total, inv_cpr, inv_hp, Producer{}, blockIdx.x - nrep);
 }
 
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256) compress_narrow_repack_kernel(Geom g, con
                                                                      FilterRepack f, unsigned nrep)
 {
     __shared__ __align__(16) unsigned char lds[kFilterElems * 2 > 4 * 64 * W ? kFilterElems * 2 : 4 * 64 * W];
-    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, (bf16_t *)lds);
+    if (blockIdx.x < nrep) filter_repack(f, blockIdx.x, (bf16_t *)lds, threadIdx.x);
     else compress_narrow_body<W, false>(g, X, Z, total, 0.0, Producer{}, lds, blockIdx.x - nrep);
 }
 

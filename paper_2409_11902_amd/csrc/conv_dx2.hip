@@ -40,8 +40,9 @@ constexpr int kNI = 2;                                 // 32-pixel blocks of a w
 constexpr int kEpRow = 64 * 4 + 16;                    // LDS bytes of an epilogue row: 64 pairs of pixels
 constexpr int kEpWave = 32 * kEpRow;
 
-// KC: channels o of a stage (32 or 64); EPI: dwords (pairs of output pixels) per store.
-template <int WM, int WN, int ITEMS, int GW, int KC, int EPI>
+// KC: channels o of a stage (32 or 64); EPI: dwords (pairs of output pixels) per store; TAIL: the launch may have workgroups that add
+// a weight gradient's slices (a form of its own: where all registers are in use the branch alone costs 2-6 %).
+template <int WM, int WN, int ITEMS, int GW, int KC, int EPI, bool TAIL>
 __global__ void __launch_bounds__(256, 2) conv_dx2_kernel(GatherParams p)
 {
     constexpr int PT = WN * kNI * 32, KS = KC / 16;
@@ -51,10 +52,14 @@ __global__ void __launch_bounds__(256, 2) conv_dx2_kernel(GatherParams p)
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    const int tau = blockIdx.x / p.ngrp, n_base = (blockIdx.x - tau * p.ngrp) * p.IPT;
+    int bx = blockIdx.x, by = blockIdx.y, bz = 0;
+    if constexpr (TAIL) {
+        if (!conv_block(p, smem, bx, by, bz)) return;
+    }
+    const int tau = bx / p.ngrp, n_base = (bx - tau * p.ngrp) * p.IPT;
     const int nkb = p.nkb, ppi = p.Hc * p.Wc;
     const int pix0 = p.IPT > 1 ? 0 : tau * PT, i0 = fdiv(pix0, p.m_wc);
-    const int m0 = (blockIdx.y * WM + wm) * 32;
+    const int m0 = (by * WM + wm) * 32;
 
     PatchStage<ITEMS, GW, KC> in;
     in.init(p, lds0, lds0 + 2 * buf_bytes, n_base, i0);
@@ -197,16 +202,22 @@ __global__ void __launch_bounds__(256, 2) conv_dx2_kernel(GatherParams p)
     else run_wave(std::integral_constant<int, 0>{});
 }
 
-template <int WM, int WN, int ITEMS, int GW, int KC, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+template <int WM, int WN, int ITEMS, int GW, int KC, int EPI, bool TAIL> hipError_t launch_kernel(const GatherParams &p, hipStream_t st)
 {
-    auto kern = conv_dx2_kernel<WM, WN, ITEMS, GW, KC, EPI>;
+    auto kern = conv_dx2_kernel<WM, WN, ITEMS, GW, KC, EPI, TAIL>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
-    const dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 32 + WM - 1) / WM);
-    hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, p);
+    dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 32 + WM - 1) / WM);
+    GatherParams q = p;
+    grid = share_grid(q, grid, 256);
+    hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, q);
     return hipGetLastError();
+}
+template <int WM, int WN, int ITEMS, int GW, int KC, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+{
+    return p.tail.blocks ? launch_kernel<WM, WN, ITEMS, GW, KC, EPI, true>(p, st) : launch_kernel<WM, WN, ITEMS, GW, KC, EPI, false>(p, st);
 }
 template <int WM, int WN, int ITEMS, int KC> hipError_t launch_rows(const GatherParams &p, hipStream_t st)
 {

@@ -2,6 +2,7 @@
 #pragma once
 #include "common.h"
 #include "dw_reduce.h"
+#include "filter_repack.h"
 
 namespace cac {
 
@@ -11,6 +12,10 @@ struct GatherParams {
     const bf16_t *bias; // [M] or null
     bf16_t *out;        // [N][M][Hout][Wout]
     float *part;        // [ksplit][N][M][Hout*Wout] float sums when the channels are shared out, else null
+    int tail_wgs;       // workgroups after the launch's own that add a weight gradient's slices (share_grid); up here, in a line
+                        // that every kernel reads first: at the end of this record it was a cache miss of its own ahead of
+                        // everything, 0.5 us of a launch
+    int gx, gy, gz;     // the launch's own workgroups
     int N, M, Mp, KCp;
     int Hin, Win, Hout, Wout;
     int Hc, Wc;         // grid of output pixels of this launch: (h, w) = (i*os + a0, j*os + b0)
@@ -46,7 +51,38 @@ struct GatherParams {
     uint32_t w_kstep, w_bytes; // bytes from one 16-channel step of the filter to the next; of all of it
     uint32_t m_w2;      // division magic of two image rows
     uint32_t wofs[9], toff[9]; // per tap: byte offset of its filter fragments; LDS byte offset within the patch
+    DwReduceTail tail; // a weight gradient's slice sum in workgroups of this launch (share_grid)
 };
+
+// A data gradient's launch has workgroups to add the slices of the same layer's weight gradient: the sum is bound by memory
+// where the launch is bound by the matrix cores or by latency, and a launch of its own costs 4 us and more.  They come after
+// the launch's own, in the room that its last round leaves (in turns with them the sum's workgroups took the places of
+// partners: 512 -> 512 at 14 x 14, batch 256, 14 us more than after them).
+inline dim3 share_grid(GatherParams &p, dim3 grid, int threads)
+{
+    p.gx = grid.x; p.gy = grid.y; p.gz = grid.z;
+    p.tail_wgs = 0;
+    if (!p.tail.blocks) return grid;
+    const unsigned subs = threads / 256, want = (p.tail.blocks + subs - 1) / subs;
+    p.tail_wgs = want < 512 ? want : 512;
+    return dim3(grid.x * grid.y * grid.z + p.tail_wgs);
+}
+// The workgroup's place in the launch's own grid; false when it had slices to add (done then).
+__device__ __forceinline__ bool conv_block(const GatherParams &p, unsigned char *lds, int &bx, int &by, int &bz)
+{
+    bx = blockIdx.x; by = blockIdx.y; bz = blockIdx.z;
+    if (__builtin_expect(p.tail_wgs == 0, 1)) return true;
+    const int own = p.gx * p.gy * p.gz;
+    if (__builtin_expect(bx >= own, 0)) {
+        dw_reduce_share(p.tail, bx - own, p.tail_wgs, lds);
+        return false;
+    }
+    const int row = __builtin_amdgcn_readfirstlane(bx / p.gx);
+    bx -= row * p.gx;
+    bz = __builtin_amdgcn_readfirstlane(row / p.gy);
+    by = row - bz * p.gy;
+    return true;
+}
 
 // conv_tile.hip: nine-tap launches with large wave tiles (see there)
 bool shape_tile(GatherParams &p, int *variant, double *cost);
@@ -70,7 +106,13 @@ size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
 bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, size_t len);
 bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, void *Z, void *ws,
                      hipStream_t st, hipError_t *err, bool *pooled);
-bool launch_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, hipStream_t st,
-                    hipError_t *err, const DwReduceTail *tail = nullptr);
+// A data gradient, planned: what has to be laid out ahead of it (rep), and its launches.
+struct DxPlan {
+    GatherParams cls[4];
+    int variant[4], ncls;
+    RepackParams rep;
+};
+bool plan_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, DxPlan *plan);
+hipError_t launch_dx_mfma(DxPlan &plan, bool repacked, const DwReduceTail *tail, hipStream_t st);
 
 } // namespace cac

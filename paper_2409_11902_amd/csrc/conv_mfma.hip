@@ -41,183 +41,16 @@ constexpr int KCS = KC + 8;  // LDS elements per patch pixel: 80 bytes, an odd n
 
 // ---- repacks ---------------------------------------------------------------------
 
-// Both repacks of a call in one launch.
-//
-// Input: in [N][C][HW] -> out [N][HW][Cp], zeros for c >= C.
-//   HW even (every plane starts at a multiple of 4 bytes): a thread moves an 8 channel x 8 pixel
-//   block: eight 16-byte loads along the pixels (consecutive lanes = consecutive pixel groups of
-//   a channel row), an 8 x 8 transpose in registers (v_perm), eight 16-byte stores of 8 channels
-//   each; the last block of a plane may be partial (it reads on into the next plane, or zeros
-//   past the tensor, and stores only its own pixels).
-//   Otherwise: 64 x 64 tiles through LDS, element by element.
-// Filter: filter_repack.h.
-// Blocks [0, in_blocks) do the input, the rest the filter.
-struct RepackParams {
-    const bf16_t *in;
-    bf16_t *out;        // null: no channels-last copy, the input blocks only form Z
-    int N, C, HW, Cp, in_blocks, fast;
-    int in_wpb;         // waves of an input block that take items (fast path): fewer than 4 spread a small
-                        // input over more compute units, one block each
-    bf16_t *Z;          // pooled copy of `in` written on the way (2 x 2 means), or null
-    int Wimg;           // image width (only with Z)
-    int decim;          // with Z: `out` takes pixel (2h, 2w) of every 2 x 2 tile only, as an image of half the extent
-    FilterRepack f;
-};
-
-__device__ __forceinline__ void repack_body(const RepackParams &p, const int bid)
+__global__ void __launch_bounds__(256) repack_kernel(RepackParams p)
 {
-    __shared__ bf16_t sm[kFilterElems > 64 * 66 ? kFilterElems : 64 * 66];
-    if (bid >= p.in_blocks) {
-        filter_repack(p.f, bid - p.in_blocks, sm);
-        return;
-    }
-    bf16_t (*tile)[66] = (bf16_t (*)[66])sm;
-    if (p.fast) {
-        // item -> (image n, block of up to 8 channel groups, pixel group pg of 8, channel group
-        // within the block), the last fastest: 8 neighbouring lanes read 8 channel rows and
-        // write the 128 contiguous bytes of 64 channels of one pixel; the next lanes move along
-        // the pixels, so every row is read in 128-byte runs too.  With Z, an item is the same 8
-        // pixels of TWO image rows (2h, 2h+1), from which it also forms the 2 x 2 means.
-        const bool pool = p.Z != nullptr && p.Wimg != 4;
-        const bool pool4 = p.Z != nullptr && p.Wimg == 4; // rows of 4 pixels: an item is already two whole rows
-        const int wgs = pool ? p.Wimg / 8 : 1;                 // pixel groups per image row
-        const int pgs = pool ? p.HW / 16 : (p.HW + 7) / 8;     // items along the pixels (the last may be partial)
-        const int cgs = p.Cp / 8, cgw = min(cgs, 8), cgb = (cgs + cgw - 1) / cgw;
-        if ((int)(threadIdx.x >> 6) >= p.in_wpb) return;
-        // (fewer than 2^31 items: 32-bit divisions)
-        const uint32_t item = ((uint32_t)bid * p.in_wpb + (threadIdx.x >> 6)) * 64u + (threadIdx.x & 63);
-        if (item >= (uint32_t)p.N * cgb * pgs * cgw) return;
-        const int cl = item % (uint32_t)cgw;
-        uint32_t t1 = item / (uint32_t)cgw;
-        const int pi = t1 % (uint32_t)pgs;
-        t1 /= (uint32_t)pgs;
-        const int cg = (int)(t1 % (uint32_t)cgb) * cgw + cl, n = t1 / (uint32_t)cgb;
-        if (cg >= cgs) return;
-        // first pixel of the item's (first) row segment
-        const int hh = pool ? pi / wgs : 0, wg = pool ? pi - hh * wgs : 0;
-        const int px0 = pool ? (2 * hh * wgs + wg) * 8 : pi * 8;
-        const rsrc_t rs = make_rsrc(p.in, (uint32_t)p.N * p.C * p.HW * 2u);
-        u32x4 r[2][8];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            if (a == 1 && !pool) break;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = cg * 8 + i;
-                const uint32_t e = ((uint32_t)(n * p.C + c) * p.HW + px0 + a * p.Wimg) * 2u;
-                r[a][i] = __builtin_amdgcn_raw_buffer_load_b128(rs, c < p.C ? e : kNoLoad, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            if (a == 1 && !pool) break;
-            if (!p.out) break; // only the pooled map is wanted
-            if (p.decim && a == 1) break; // (odd rows are not kept)
-            bf16_t *dst = p.decim ? p.out + ((long)n * (p.HW / 4) + hh * (p.Wimg / 2) + wg * 4) * p.Cp + cg * 8
-                                  : p.out + ((long)n * p.HW + px0 + a * p.Wimg) * p.Cp + cg * 8;
-#pragma unroll
-            for (int px = 0; px < 8; ++px) {
-                // pixel px of the 8 channels: half px%2 of dword px/2 of every row
-                u32x4 v;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t lo = r[a][2 * k][px / 2], hi = r[a][2 * k + 1][px / 2];
-                    v[k] = (px & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u) : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-                }
-                if (p.decim) {
-                    if (!(px & 1)) *(u32x4 *)(dst + (long)(px / 2) * p.Cp) = v;
-                } else if (px0 + px < p.HW) {
-                    *(u32x4 *)(dst + (long)px * p.Cp) = v; // (a plane's last item may reach past it)
-                }
-            }
-        }
-        if (pool4) {
-            // Z[n][c][pi][0..1] from pixels (0, 1, 4, 5) and (2, 3, 6, 7) of the item, summed row by
-            // row like the stand-alone kernel does
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = cg * 8 + i;
-                if (c >= p.C) break;
-                uint32_t h2[2];
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj) {
-                    const uint32_t t0 = r[0][i][jj], t1r = r[0][i][2 + jj];
-                    float sum = 0.f;
-                    sum += __uint_as_float(t0 << 16);
-                    sum += __uint_as_float(t0 & 0xffff0000u);
-                    sum += __uint_as_float(t1r << 16);
-                    sum += __uint_as_float(t1r & 0xffff0000u);
-                    h2[jj] = f32_to_bf16(sum * 0.25f);
-                }
-                *(uint32_t *)(p.Z + (((long)n * p.C + c) * (p.HW / 8) + pi) * 2) = h2[0] | (h2[1] << 16);
-            }
-        }
-        if (pool) {
-            // Z[n][c][hh][4*wg .. +3]: the same sum order and rounding as the stand-alone kernel
-            const int Hp = p.HW / p.Wimg / 2, Wp = p.Wimg / 2;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int c = cg * 8 + i;
-                if (c >= p.C) break;
-                uint32_t o[2];
-#pragma unroll
-                for (int j2 = 0; j2 < 2; ++j2) {
-                    uint32_t h2[2];
-#pragma unroll
-                    for (int jj = 0; jj < 2; ++jj) {
-                        const uint32_t t0 = r[0][i][2 * j2 + jj], t1r = r[1][i][2 * j2 + jj];
-                        float sum = 0.f;
-                        sum += __uint_as_float(t0 << 16);
-                        sum += __uint_as_float(t0 & 0xffff0000u);
-                        sum += __uint_as_float(t1r << 16);
-                        sum += __uint_as_float(t1r & 0xffff0000u);
-                        h2[jj] = f32_to_bf16(sum * 0.25f);
-                    }
-                    o[j2] = h2[0] | (h2[1] << 16);
-                }
-                typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-                *(u32x2 *)(p.Z + (((long)n * p.C + c) * Hp + hh) * Wp + wg * 4) = u32x2{o[0], o[1]};
-            }
-        }
-        return;
-    }
-    // block -> (image, 64-channel block, 64-pixel block)
-    const int pbs = (p.HW + 63) / 64, cbs = (p.Cp + 63) / 64;
-    const int pb = bid % pbs, t1 = bid / pbs;
-    const int cb = t1 % cbs, n = t1 / cbs;
-    const int c0 = cb * 64, p0 = pb * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int k = ty; k < 64; k += 4) {
-        const int c = c0 + k, px = p0 + tx;
-        tile[k][tx] = (c < p.C && px < p.HW) ? p.in[((long)n * p.C + c) * p.HW + px] : (bf16_t)0;
-    }
-    __syncthreads();
-    for (int k = ty; k < 64; k += 4) {
-        const int px = p0 + k, c = c0 + tx;
-        if (px < p.HW && c < p.Cp) p.out[((long)n * p.HW + px) * p.Cp + c] = tile[tx][k];
-    }
+    __shared__ bf16_t sm[kRepackElems];
+    repack_body(p, blockIdx.x, sm, threadIdx.x);
 }
 
-__global__ void __launch_bounds__(256) repack_kernel(RepackParams p) { repack_body(p, blockIdx.x); }
-
-// The repacks of a data-gradient call and, in the blocks after them, the slice sum that the
-// weight gradient of the same layer has left over: two small, independent pieces of a backward
-// pass that would otherwise each pay for a launch.
-template <int SY, int V>
-__global__ void __launch_bounds__(256) repack_reduce_kernel(RepackParams p, unsigned nrep, DwReduceTail t)
-{
-    if (blockIdx.x < nrep)
-        repack_body(p, blockIdx.x);
-    else
-        dw_reduce_body<SY, V>(t.part, t.dW, t.total, t.nslices, blockIdx.x - nrep);
-}
-
-// Launches the input and filter repacks of one call.
+// The input and filter repacks of one call.
 // Z, Wimg: see RepackParams (Z null: no pooling; else HW must be a multiple of 2*Wimg and Wimg 4 or a multiple of 8).
-// tail: a deferred weight-gradient slice sum to run in the same launch, or null.
-hipError_t launch_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, int Cp, const bf16_t *W, bf16_t *Wt, int O,
-                         int Cw, int RS, int Mp, int KCp, int transpose, bf16_t *Z, int Wimg, hipStream_t st,
-                         const DwReduceTail *tail = nullptr, int decim = 0)
+RepackParams make_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, int Cp, const bf16_t *W, bf16_t *Wt, int O,
+                         int Cw, int RS, int Mp, int KCp, int transpose, bf16_t *Z, int Wimg, int decim = 0)
 {
     RepackParams p{};
     p.in = in; p.out = out; p.N = N; p.C = C; p.HW = HW; p.Cp = Cp;
@@ -231,9 +64,23 @@ hipError_t launch_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, in
     p.in_wpb = items > 64 * 256 ? 4 : 1; // (measured: two waves per block are slower than either)
     p.in_blocks = p.fast ? (int)((items + 64 * p.in_wpb - 1) / (64 * p.in_wpb)) : N * ((Cp + 63) / 64) * ((HW + 63) / 64);
     p.f = FilterRepack{W, Wt, O, Cw, RS, Mp, KCp, transpose};
-    const unsigned nrep = (unsigned)p.in_blocks + p.f.blocks();
+    return p;
+}
+// The repacks of a data-gradient call and, in the blocks after them, the slice sum that the weight gradient of the same layer has
+// left over: two small, independent pieces of a backward pass that would otherwise each pay for a launch.
+template <int SY, int V> __global__ void __launch_bounds__(256) repack_reduce_kernel(RepackParams p, unsigned nrep, DwReduceTail t)
+{
+    __shared__ __align__(16) bf16_t sm[kRepackElems];
+    if (blockIdx.x < nrep) repack_body(p, blockIdx.x, sm, threadIdx.x);
+    else dw_reduce_body<SY, V, 1>(t, blockIdx.x - nrep, 0, threadIdx.x, sm);
+}
+
+// tail: a deferred weight-gradient slice sum to run in the same launch, or null.
+hipError_t launch_repack(const RepackParams &p, hipStream_t st, const DwReduceTail *tail = nullptr)
+{
     if (tail && tail->blocks) {
         const DwReduceTail &t = *tail;
+        const unsigned nrep = p.blocks();
 #define CAC_RR(SY, V) hipLaunchKernelGGL((repack_reduce_kernel<SY, V>), dim3(nrep + t.blocks), dim3(256), 0, st, p, nrep, t)
         if (t.V == 4) {
             if (t.SY == 16) CAC_RR(16, 4);
@@ -247,17 +94,8 @@ hipError_t launch_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, in
 #undef CAC_RR
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(repack_kernel, dim3(nrep), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(repack_kernel, dim3(p.blocks()), dim3(256), 0, st, p);
     return hipGetLastError();
-}
-
-// Clears n bfloat16 elements: whole 16-byte units, then the (up to 7) elements that remain --
-// not a byte past the tensor.
-__global__ void __launch_bounds__(256) zero_fill_kernel(bf16_t *dst, long n)
-{
-    const long i = (long)blockIdx.x * 256 + threadIdx.x, n16 = n / 8;
-    if (i < n16) ((u32x4 *)dst)[i] = u32x4{0, 0, 0, 0};
-    if (i < n - n16 * 8) dst[n16 * 8 + i] = (bf16_t)0;
 }
 
 // ---- the gather GEMM ----------------------------------------------------------------
@@ -298,10 +136,12 @@ __global__ void __launch_bounds__(512) conv_gather_kernel(GatherParams p)
     const int KCT = KC << t_log2;                   // channels staged per pass
     const uint32_t buf_bytes = (uint32_t)p.patch_px * kcs * 2;
 
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tau = blockIdx.x % p.tiles_per_img, run = blockIdx.x / p.tiles_per_img;
+    const int tau = bx % p.tiles_per_img, run = bx / p.tiles_per_img;
     const int g_begin = run * p.gpw, g_end = min(g_begin + p.gpw, p.ngrp);
-    const int kb0 = blockIdx.z * p.kbs;             // this workgroup's share of the channel blocks
+    const int kb0 = bz * p.kbs;                     // this workgroup's share of the channel blocks
     const int nstages = (g_end - g_begin) * p.kbs;
     const int ppi = p.Hc * p.Wc;
     const int pix0 = p.IPT > 1 ? 0 : tau * PT;      // first class-grid pixel of the tile
@@ -447,7 +287,7 @@ __global__ void __launch_bounds__(512) conv_gather_kernel(GatherParams p)
     // =============================== MFMA waves ===========================================
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id;
     const int wm = wave % WM, wn = wave / WM, half = lane >> 5, l32 = lane & 31;
-    const int m0 = (blockIdx.y * WM + wm) * 64;    // this wave's first output channel
+    const int m0 = (by * WM + wm) * 64;            // this wave's first output channel
     const bool wave_live = m0 < p.Mp;              // waves past the (padded) output channels only keep the barriers
 
     // this lane's pixels: image within the tile, class-grid coordinates, LDS byte offset of their
@@ -726,7 +566,7 @@ __global__ void __launch_bounds__(512) conv_gather_kernel(GatherParams p)
                                     const f32x16 &a = acc[mi][ni];
                                     if (p.part) { // a share of the channels: float sums, finished by gather_finish_kernel
                                         typedef __attribute__((ext_vector_type(4))) float f32x4;
-                                        *(f32x4 *)(p.part + (((long)blockIdx.z * p.N + n) * p.M + m) * ppi + px) =
+                                        *(f32x4 *)(p.part + (((long)bz * p.N + n) * p.M + m) * ppi + px) =
                                             f32x4{a[4 * jq], a[4 * jq + 1], a[4 * jq + 2], a[4 * jq + 3]};
                                         continue;
                                     }
@@ -809,8 +649,10 @@ template <int NI, int WM, int WN, bool TR, int NTT, int ITEMS, bool NCHW> hipErr
     if (attr_err != hipSuccess) return attr_err;
     const int runs = (p.ngrp + p.gpw - 1) / p.gpw;
     dim3 grid(p.tiles_per_img * runs, (p.Mp / 64 + WM - 1) / WM, p.ksplit);
-    const size_t lds = (size_t)2 * p.patch_px * p.kcs * 2 + (p.wide_store ? 4 * 64 * ((NI < 2 ? NI : 2) * 64 + 16) : 0);
-    hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, p);
+    const size_t lds = max((size_t)2 * p.patch_px * p.kcs * 2, (size_t)8192) + (p.wide_store ? 4 * 64 * ((NI < 2 ? NI : 2) * 64 + 16) : 0);
+    GatherParams q = p;
+    grid = share_grid(q, grid, 512);
+    hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, q);
     if (p.ksplit > 1) {
         const long quads = (long)p.N * p.M * p.Hc * p.Wc / 4;
         hipLaunchKernelGGL(gather_finish_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, st, (const float *)p.part,
@@ -1014,15 +856,21 @@ bool plan_other(GatherParams &p, bool fwd, int *variant)
     GatherParams wave = p, tile = p;
     int wave_variant;
     double wave_cost, tile_cost = 1e300;
-    const bool have_tile = use_tile() && shape_tile(tile, variant, &tile_cost);
+    const bool have_tile = use_tile() && shape_tile(tile, variant, &tile_cost); // (*variant: its own until another is chosen)
     bool have_wave = use_tile() && shape_wave(wave, &wave_variant, &wave_cost);
     // Where conv_tile.hip has no shape, 300 random layers took 0.59 of the gather's time with waves (both directions, 9 of them over
     // 1.05).  Two lines remain to the gather: sums over 48 channels and less, which leave a wave without a stage (data
     // gradients 1.0-1.09 of the time; forward passes up to 4096 pixels 0.7, the input's copy falls away), and a dozen tiles of
     // less than 0.1 GFLOP, launches and start-up either way, where it shares the channels over workgroups.
     const long px = (long)p.N * p.Hc * p.Wc;
-    if (have_wave && p.KCin <= 48) have_wave = fwd && px < 4096;
-    if (have_wave && p.KCin <= 256 && (px + 63) / 64 * (p.Mp / 64) <= 12 && 18.0 * px * p.KCin * p.M < 1e8) have_wave = false;
+    const bool few = (p.KCin <= 48 && (!fwd || px >= 4096)) || (p.KCin <= 256 && (px + 63) / 64 * (p.Mp / 64) <= 12 && 18.0 * px * p.KCin * p.M < 1e8);
+    if (GatherParams gather = p; have_wave && few && (have_tile || shape_gather(gather, variant))) {
+        have_wave = false;
+        if (!have_tile) {
+            p = gather;
+            return true;
+        }
+    }
     // Against conv_tile.hip: 200 random layers, by the ratio of the two planners' cycles; below 0.55 the waves take 0.76 of the
     // time (48 layers, 2 of them over 1.05), up to 0.7 it is 1.0, above 1.0 1.6.
     if (have_wave && have_tile) have_wave = wave_cost < 0.55 * tile_cost;
@@ -1247,7 +1095,7 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
         if (!p.w_direct) {
             const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0};
             if (with_filter) *err = launch_compress_repack(g, X, Z, f, st);
-            else *err = launch_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W, st);
+            else *err = launch_repack(make_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W), st);
         }
         if (*err != hipSuccess) return true;
         p.in = (const bf16_t *)X;
@@ -1263,8 +1111,8 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     if (with_filter) {
         *err = launch_compress_repack(g, X, Z, f, st);
     } else {
-        *err = launch_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C,
-                             p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, st, nullptr, p.decim);
+        *err = launch_repack(make_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt,
+                                         g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, p.decim), st);
         *pooled = fuse;
     }
     if (*err != hipSuccess) return true;
@@ -1276,36 +1124,42 @@ bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, con
     return true;
 }
 
-// Data gradient: dX = W^T * dY.  False when the geometry is not covered.
-// tail: a weight-gradient slice sum to run in the repack launch (see repack_reduce_kernel); when
-// this returns false nothing has been launched and the tail is still the caller's to run.
-bool launch_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, hipStream_t st,
-                    hipError_t *err, const DwReduceTail *tail)
+// Data gradient: dX = W^T * dY.  False when the geometry is not covered; nothing has been launched then.
+bool plan_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, DxPlan *plan)
 {
-    GatherParams base{}, cls[4];
-    int variant[4], ncls = 0;
+    GatherParams base{}, (&cls)[4] = plan->cls;
     bool empty_class = false;
-    if (!plan_dx(g, dtype, base, cls, variant, &ncls, &empty_class)) return false;
+    if (!plan_dx(g, dtype, base, cls, plan->variant, &plan->ncls, &empty_class)) return false;
+    const int ncls = plan->ncls;
     const WsLayout l = dx_layout(g, base, cls, ncls);
     bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
-    for (int k = 0; k < ncls; ++k) cls[k].part = cls[k].ksplit > 1 ? (float *)((char *)ws + l.in + l.wt) : nullptr;
-    // pixels no output pixel's tap reaches (possible when stride > filter) stay zero
-    if (empty_class) {
-        // (a fill kernel, not a memset node: callers may capture this call in a HIP graph)
-        const long n = (long)g.N * g.C * g.H * g.W;
-        hipLaunchKernelGGL(zero_fill_kernel, dim3((unsigned)((n / 8 + 256) / 256)), dim3(256), 0, st, (bf16_t *)dX, n);
-    }
     const bool direct = dx_reads_in_place(g, cls, ncls);
-    *err = launch_repack(direct ? nullptr : (const bf16_t *)dY, in, g.N, g.K, g.P * g.Q, base.KCp, (const bf16_t *)W, wt, g.K, g.C,
-                         base.ntaps_total, base.Mp, base.KCp, 1, nullptr, 0, st, tail);
-    for (int k = 0; k < ncls && *err == hipSuccess; ++k) {
+    for (int k = 0; k < ncls; ++k) {
+        cls[k].part = cls[k].ksplit > 1 ? (float *)((char *)ws + l.in + l.wt) : nullptr;
         cls[k].in = direct ? (const bf16_t *)dY : in;
         cls[k].nchw = direct;
         cls[k].KCin = g.K;
         cls[k].wt = wt; cls[k].bias = nullptr; cls[k].out = (bf16_t *)dX;
-        *err = run_gather(cls[k], variant[k], st);
+    }
+    plan->rep = make_repack(direct ? nullptr : (const bf16_t *)dY, in, g.N, g.K, g.P * g.Q, base.KCp, (const bf16_t *)W, wt, g.K, g.C,
+                            base.ntaps_total, base.Mp, base.KCp, 1, nullptr, 0);
+    // pixels no output pixel's tap reaches (possible when stride > filter) stay zero
+    // (cleared by blocks of a kernel, not by a memset node: callers may capture this call in a HIP graph)
+    if (empty_class) {
+        plan->rep.zero = (bf16_t *)dX;
+        plan->rep.zero_n = (long)g.N * g.C * g.H * g.W;
     }
     return true;
+}
+
+// tail: a weight gradient's slice sum, or null.  repacked: plan.rep has run already, in the weight gradient's launch; the sum then
+// runs in the first launch of the data gradient, else in that of the repack.
+hipError_t launch_dx_mfma(DxPlan &plan, bool repacked, const DwReduceTail *tail, hipStream_t st)
+{
+    hipError_t e = repacked ? hipSuccess : launch_repack(plan.rep, st, tail);
+    if (repacked && tail) plan.cls[0].tail = *tail;
+    for (int k = 0; k < plan.ncls && e == hipSuccess; ++k) e = run_gather(plan.cls[k], plan.variant[k], st);
+    return e;
 }
 
 } // namespace cac

@@ -52,10 +52,12 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    const int tau = blockIdx.x % p.tiles_per_img, n_base = blockIdx.x / p.tiles_per_img * p.IPT;
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int tau = bx % p.tiles_per_img, n_base = bx / p.tiles_per_img * p.IPT;
     const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb;
     const int pix0 = p.IPT > 1 ? 0 : tau * p.tile_px;
-    const int m0 = (blockIdx.y * WM + wm) * 64;
+    const int m0 = (by * WM + wm) * 64;
 
     // ---- this thread's item: 8 channels, pixels from px0 on of image n_base + ig
     // (lanes along the pixels: a wave's load then covers whole lines of one or two channel rows; with the lanes along the
@@ -105,7 +107,7 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
     auto put = [&](int s, uint32_t buf) {
         if (!item) return; // (the pixels of items that do not exist are never stored, whatever LDS holds for them)
         if constexpr (FUSE) {
-            if (blockIdx.y == 0) {
+            if (by == 0) {
                 const int nvalid = K - (s * KC + oct * 8);
                 // plane * (ppi / 4) + pooled row * Wp + pooled column; px0 = 2 * pooled row * W + 2 * pooled column
                 const int prow = fdiv(px0, p.m_w2), pcol = (px0 - prow * 2 * p.Win) >> 1;
@@ -295,7 +297,9 @@ template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) con
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = wave % KS, pt = wave / KS;
     // every XCD works on consecutive pixel tiles, all output channels of one after the other: its L2 keeps the pixels
-    const int per_xcd = gridDim.x >> 3, v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), mtiles = p.Mp / 64;
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3), mtiles = p.Mp / 64;
     if (v >= p.tiles_per_img * mtiles) return; // (tiles_per_img: groups of PT pixel tiles)
     const int grp = v / mtiles, m0 = (v - grp * mtiles) * 64;
     const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb, nitems = p.N * p.GX;
@@ -503,7 +507,9 @@ template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherPara
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
     const int total = p.tiles_per_img * (p.Mp / 64);
-    hipLaunchKernelGGL(kern, dim3((total + 7) / 8 * 8), dim3(256), wt_lds(KS), st, p);
+    GatherParams q = p;
+    const dim3 grid = share_grid(q, dim3((total + 7) / 8 * 8), 256);
+    hipLaunchKernelGGL(kern, grid, dim3(256), wt_lds(KS), st, q);
     return hipGetLastError();
 }
 template <int KS> hipError_t launch_wave(const GatherParams &p, hipStream_t st)
@@ -522,8 +528,10 @@ template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
-    const dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 64 + WM - 1) / WM);
-    hipLaunchKernelGGL(kern, grid, dim3(256), 2 * kBuf, st, p);
+    dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 64 + WM - 1) / WM);
+    GatherParams q = p;
+    grid = share_grid(q, grid, 256);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 2 * kBuf, st, q);
     return hipGetLastError();
 }
 template <int NI, int WM, int WN> hipError_t launch_shape(const GatherParams &p, hipStream_t st)

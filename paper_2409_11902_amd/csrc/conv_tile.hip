@@ -61,13 +61,15 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int wm = wave % WM, wn = wave / WM;
     // (an image's tiles are as far apart in dispatch order as can be: its last one often has less to do, and
     // neighbouring workgroups go to different XCDs in turn)
-    const int tau = blockIdx.x / p.ngrp, n_base = (blockIdx.x - tau * p.ngrp) * p.IPT;
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int tau = bx / p.ngrp, n_base = (bx - tau * p.ngrp) * p.IPT;
     const int nkb = p.nkb;
     const int ppi = p.Hc * p.Wc;
     const int pix0 = p.IPT > 1 ? 0 : tau * PT;
     const int i0 = fdiv(pix0, p.m_wc);
     const int hin0 = i0 * p.is + p.dhmin;
-    const int m0 = (blockIdx.y * WM + wm) * 64;
+    const int m0 = (by * WM + wm) * 64;
 
     PatchStage<ITEMS, GW, KC, 8 / PARTS> in;
     in.init(p, lds0, lds0 + 2 * buf_bytes, n_base, hin0);
@@ -242,7 +244,9 @@ template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI> hip
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
     dim3 grid(p.tiles_per_img * p.ngrp, (p.Mp / 64 + WM - 1) / WM);
-    hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, p);
+    GatherParams q = p;
+    grid = share_grid(q, grid, 256);
+    hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, q);
     return hipGetLastError();
 }
 template <int NI, int WM, int WN, int KC, int D, int EPI> hipError_t launch_items(const GatherParams &p, hipStream_t st)

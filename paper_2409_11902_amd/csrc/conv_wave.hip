@@ -48,7 +48,9 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int per_xcd = gridDim.x >> 3, v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3);
     if (v >= p.tiles_per_img * p.mtiles) return; // (tiles_per_img: pixel tiles of all images)
     const int mt = v / p.tiles_per_img, m0 = mt * 32 * MI, F = (v - mt * p.tiles_per_img) * PT; // first pixel, over all images
     const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb, plane = p.Hin * p.Win;
@@ -259,7 +261,9 @@ template <int MI, int KC, int ITEMS, int GW, int KS> hipError_t launch_fixed(con
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((p.tiles_per_img * p.mtiles + 7) / 8 * 8)), dim3(64 * KS), p.lds_bytes, st, p);
+    GatherParams q = p;
+    const dim3 grid = share_grid(q, dim3((unsigned)((p.tiles_per_img * p.mtiles + 7) / 8 * 8)), 64 * KS);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * KS), p.lds_bytes, st, q);
     return hipGetLastError();
 }
 template <int MI, int KC, int ITEMS, int KS> hipError_t launch_shape(const GatherParams &p, hipStream_t st)

@@ -2,6 +2,7 @@
 #pragma once
 #include "common.h"
 #include "dw_reduce.h"
+#include "filter_repack.h"
 
 namespace cac {
 
@@ -9,6 +10,8 @@ struct DwMfmaParams {
     const bf16_t *Z;
     const bf16_t *dY;
     float *out; // dW (direct) or the partial-sum workspace
+    unsigned own_wgs;    // workgroups of the kernel's own; those after them lay out operands of the data gradient
+    int rep_waves;       // MFMA waves that lay out blocks of the data gradient's filter first
     int N, C, K, H, W, P, Q, Hp, Wp;
     int kh_log2, kw_log2;
     // chunk = NBI images x PR output rows
@@ -30,6 +33,7 @@ struct DwMfmaParams {
     int tile_o, tile_c;  // workgroup tile
     int tiles_o, tiles_c, total_wg;
     int direct;
+    int rep_blocks, rep_elems, rep_at; // ... blocks; LDS elements of each; where they start
 };
 
 struct DwMfmaPlan {
@@ -39,9 +43,10 @@ struct DwMfmaPlan {
     int variant;        // index into the kernel table
 };
 
+int dw_takes_repack(const DwMfmaPlan &plan, const RepackParams &rep);
 // False when the geometry is not covered (the caller then uses the generic kernel).
 bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan);
 hipError_t launch_dw_mfma(const DwMfmaPlan &plan, const void *Z, const void *dY, float *dW, void *ws, hipStream_t st,
-                          DwReduceTail *defer = nullptr);
+                          DwReduceTail *defer = nullptr, const RepackParams *rep = nullptr, bool *rep_done = nullptr);
 
 } // namespace cac

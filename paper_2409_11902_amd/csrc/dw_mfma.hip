@@ -157,7 +157,7 @@ constexpr int kAnyFl = -2;
 // time (0: read from the plan).  With SC the walk along a row is unrolled and the
 // segment offsets become immediates of the LDS reads.
 template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, int WIDEZ, int FL>
-__global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParams p)
+__global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParams p, RepackParams rep)
 {
     constexpr int kMaxDy = max_dy(WIDEZ), kMaxZ = max_z(WIDEZ);
     constexpr int T = R * S;
@@ -178,10 +178,19 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     const uint32_t slot_w = NPH * p.PW;                        // one xhat row: all phases
     const uint32_t base0 = slot_w, base1 = base0 + buf_elems;  // the buffers follow the zero row
 
+    if constexpr (NT == 256) {
+        // Past the kernel's own workgroups: what the data gradient of the same layer needs laid out ahead of it, on compute units
+        // that a small layer leaves idle (launch_dw_mfma).
+        if (__builtin_expect(blockIdx.x >= p.own_wgs, 0)) {
+            const int sub = threadIdx.x >> 8;
+            repack_body(rep, 2 * (blockIdx.x - p.own_wgs) + sub, (bf16_t *)smem + sub * kRepackElems, threadIdx.x & 255);
+            return;
+        }
+    }
     // Workgroups are dealt round-robin to the 8 XCDs; renumber them so that each
     // XCD works on consecutive (slice, o-tile, c-tile) triples and re-reads of dY
     // and Z hit its own L2.
-    const int per_xcd = gridDim.x >> 3;
+    const int per_xcd = p.own_wgs >> 3;
     const int v = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (v >= p.total_wg) return;
     const int ntiles = p.tiles_o * p.tiles_c;
@@ -469,6 +478,11 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id;
     const int wm = wave % WM, wn = (wave / WM) % WN, ks = wave / (WM * WN), half = lane >> 5, l32 = lane & 31;
 
+    // The data gradient's filter, while the first chunk is on its way to LDS (2.7-3.3 us): a wave by itself per block of it, in
+    // the part of buffer 1 that holds dY later on, which nobody clears, or past the buffers.
+    if (NT == 256 && __builtin_expect(wave < p.rep_waves, 0))
+        for (int b = v * p.rep_waves + wave; b < p.rep_blocks; b += p.total_wg * p.rep_waves)
+            filter_repack_wave(rep.f, b, sW + p.rep_at + wave * p.rep_elems, lane);
     zero_fill();
     __syncthreads();
 
@@ -850,21 +864,21 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
 }
 
 // The slice sum as a launch of its own (body and description: dw_reduce.h).
-template <int SY, int V>
-__global__ void __launch_bounds__(256) dw_reduce_kernel(const float *__restrict__ part, float *__restrict__ dW, long total, int nslices)
+template <int SY, int V> __global__ void __launch_bounds__(256) dw_reduce_kernel(DwReduceTail t)
 {
-    dw_reduce_body<SY, V>(part, dW, total, nslices, blockIdx.x);
+    __shared__ __align__(16) unsigned char red[SY > 1 ? 4096 : 16];
+    dw_reduce_body<SY, V, 1>(t, blockIdx.x, 0, threadIdx.x, red);
 }
 
 
 // Kernel table: filter/stride family x workgroup shape.
 struct Variant {
     int R, SG, MI, NI, WM, WN, KS;
-    hipError_t (*launch)(const DwMfmaParams &, dim3, hipStream_t);
+    hipError_t (*launch)(const DwMfmaParams &, const RepackParams &, dim3, hipStream_t);
 };
 
 template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, int WIDEZ = 0, int FL = kAnyFl>
-hipError_t launch_fixed(const DwMfmaParams &p, dim3 grid, hipStream_t st)
+hipError_t launch_fixed(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
 {
     auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ, FL>;
     // (per instantiation; once per process, whichever host thread comes first)
@@ -872,43 +886,43 @@ hipError_t launch_fixed(const DwMfmaParams &p, dim3 grid, hipStream_t st)
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL(kern, grid, dim3(128 * WM * WN * KS), p.lds_bytes, st, p);
+    hipLaunchKernelGGL(kern, grid, dim3(128 * WM * WN * KS), p.lds_bytes, st, p, rep);
     return hipGetLastError();
 }
 // Picks the instantiation with the row length built in when there is one.
 template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS>
-hipError_t launch_variant(const DwMfmaParams &p, dim3 grid, hipStream_t st)
+hipError_t launch_variant(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
 {
     if constexpr (S == 3 && SG == 1 && KS == 4) {
         if (p.dy_direct) {
             switch (p.SEGS) {
-            case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, true>(p, grid, st);
-            case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, true>(p, grid, st);
-            case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, true>(p, grid, st);
+            case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, true>(p, rep, grid, st);
+            case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, true>(p, rep, grid, st);
+            case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, true>(p, rep, grid, st);
             default: break;
             }
         }
     }
     if constexpr (S == 3 && SG == 1) {
         switch (p.SEGS) {
-        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1>(p, grid, st);
-        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2>(p, grid, st);
-        case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4>(p, grid, st);
-        case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7>(p, grid, st);
+        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1>(p, rep, grid, st);
+        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2>(p, rep, grid, st);
+        case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4>(p, rep, grid, st);
+        case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7>(p, rep, grid, st);
         default: break;
         }
     }
     if constexpr (S == 3 && SG == 2) {
-        if (p.widez == 2) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 2, -1>(p, grid, st);
-        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, -1>(p, grid, st);
+        if (p.widez == 2) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 2, -1>(p, rep, grid, st);
+        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, -1>(p, rep, grid, st);
         switch (p.kw_log2) {
-        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, -1>(p, grid, st);
-        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 0>(p, grid, st);
-        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 1>(p, grid, st);
-        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 2>(p, grid, st);
+        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, -1>(p, rep, grid, st);
+        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 0>(p, rep, grid, st);
+        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 1>(p, rep, grid, st);
+        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 2>(p, rep, grid, st);
         }
     } else {
-        return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, grid, st);
+        return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, rep, grid, st);
     }
 }
 
@@ -1134,8 +1148,7 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
 hipError_t launch_dw_reduce(const DwReduceTail &t, hipStream_t st)
 {
     if (!t.blocks) return hipSuccess;
-#define CAC_REDUCE(SY, V) \
-    hipLaunchKernelGGL((dw_reduce_kernel<SY, V>), dim3(t.blocks), dim3(256), 0, st, t.part, t.dW, t.total, t.nslices)
+#define CAC_REDUCE(SY, V) hipLaunchKernelGGL((dw_reduce_kernel<SY, V>), dim3(t.blocks), dim3(256), 0, st, t)
     if (t.V == 4) {
         if (t.SY == 16) CAC_REDUCE(16, 4);
         else if (t.SY == 4) CAC_REDUCE(4, 4);
@@ -1149,18 +1162,63 @@ hipError_t launch_dw_reduce(const DwReduceTail &t, hipStream_t st)
     return hipGetLastError();
 }
 
+// LDS of the kernel, in elements (all multiples of 8): a staging buffer, and what laying out a block of the filter takes; the waves
+// that do so in the part of a buffer that holds dY, or four past both buffers where that has no room for two.
+static int buffer_elems(const DwMfmaParams &p) { return p.LRpad * 8 + p.tile_o * p.dy_ostride + p.tile_c * p.x_cstride; }
+static int repack_elems(const FilterRepack &f) { return 16 * (32 * f.RS + 2); }
+static bool repack_past(const DwMfmaParams &p, const FilterRepack &f) { return p.tile_o * p.dy_ostride < 2 * repack_elems(f); }
+static int repack_waves(const DwMfmaParams &p, const FilterRepack &f) { return repack_past(p, f) ? 4 : min(4, p.tile_o * p.dy_ostride / repack_elems(f)); }
+
+// Whether the kernel's launch has room for the data gradient's repacks, which cost 4-10 us in one of their own.
+// 1: with 64 compute units and more to spare, in workgroups of their own there (18 random layers: 0.62-0.93 of the backward pass).
+// 2: a filter of 256 blocks and more, read in 16-byte pieces: every MFMA wave lays out two of them at most while it waits for its
+// first chunk (512 -> 2048, 1 x 1 at 7 x 7, batch 64: backwards 47.3 -> 44.7 us, 512 -> 512, 3 x 3 at 7 x 7, batch 256: 122.2 -> 120.5).
+// Else neither: smaller filters and element-wise ones delay the waves that have a block by 4-6 us (224 -> 32, 1 x 1 at 34 x 34, batch 93,
+// 41.0 -> 43.6), and workgroups behind 256 of the kernel's are a tail as long as the launch.
+int dw_takes_repack(const DwMfmaPlan &plan, const RepackParams &rep)
+{
+    const DwMfmaParams &p = plan.p;
+    const FilterRepack &f = rep.f;
+    if (plan.threads != 256) return 0;
+    if (plan.grid <= 192) return 1;
+    const int blocks = (int)f.blocks();
+    if (rep.in_blocks || rep.zero || blocks < 256 || blocks > 2 * repack_waves(p, f) * p.total_wg || f.Cw % 32 || f.Cw * f.RS % 8) return 0;
+    return repack_past(p, f) && 2 * (p.XW + 2 * buffer_elems(p) + 4 * repack_elems(f)) > 160 * 1024 ? 0 : 2;
+}
+
 // `defer`: when given, the slice sum is not launched; what it has to do is written there instead
 // (blocks = 0 when the main kernel has written dW itself) and the caller sees to it.
+// `rep`: repacks for the same launch; *rep_done says whether it has taken them.
 hipError_t launch_dw_mfma(const DwMfmaPlan &plan, const void *Z, const void *dY, float *dW, void *ws, hipStream_t st,
-                          DwReduceTail *defer)
+                          DwReduceTail *defer, const RepackParams *rep, bool *rep_done)
 {
     DwMfmaParams p = plan.p;
     p.Z = (const bf16_t *)Z;
     p.dY = (const bf16_t *)dY;
     p.out = p.direct ? dW : (float *)ws;
+    p.own_wgs = plan.grid;
     if (defer) defer->blocks = 0;
     const Variant &var = kVariants[plan.variant];
-    hipError_t e = var.launch(p, dim3(plan.grid), st);
+    RepackParams r{};
+    unsigned more = 0;
+    switch (rep ? dw_takes_repack(plan, *rep) : 0) {
+    case 1:
+        r = *rep;
+        r.in_blocks = (r.in_blocks + 1) & ~1; // (two blocks to a workgroup, both of a kind: the same barriers)
+        more = (r.blocks() + 1) / 2;
+        *rep_done = true;
+        break;
+    case 2:
+        r = *rep;
+        p.rep_waves = repack_waves(p, r.f);
+        p.rep_blocks = (int)r.f.blocks();
+        p.rep_elems = repack_elems(r.f);
+        p.rep_at = repack_past(p, r.f) ? p.XW + 2 * buffer_elems(p) : p.XW + buffer_elems(p) + p.LRpad * 8;
+        if (repack_past(p, r.f)) p.lds_bytes = max(p.lds_bytes, 2 * (p.XW + 2 * buffer_elems(p) + 4 * p.rep_elems));
+        *rep_done = true;
+        break;
+    }
+    hipError_t e = var.launch(p, r, dim3(plan.grid + more), st);
     if (e != hipSuccess || p.direct) return e;
     const DwReduceTail t = make_reduce_tail((const float *)ws, dW, (long)p.K * p.C * var.R * var.R, p.nslices);
     if (defer) {

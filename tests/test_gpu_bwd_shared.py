@@ -1,0 +1,61 @@
+"""The combined backward call where its two launches share work -- the data gradient's repacks in the weight gradient's launch, the
+slice sum in the data gradient's -- against the separate calls, bit for bit: every kernel that can carry the slices, filters that
+divide nothing, the channels-last copy of both kinds, cleared pixels, and the filter laid out by the weight gradient's own waves."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2409_11902_amd import binding as B
+from paper_2409_11902_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+ROOM, SUM = "repack in its launch", "in the launch of it, the slice sum"
+CASES = [
+    # name, N, C, K, H, W, R, stride, what the plan says
+    ("waves", 112, 80, 72, 7, 7, 3, 1, (ROOM, SUM)),
+    ("waves, eight to a tile, odd channels", 10, 41, 131, 9, 10, 3, 1, (ROOM, SUM)),
+    ("large wave tiles", 169, 33, 70, 14, 14, 3, 1, (ROOM, SUM)),
+    ("gather in place", 16, 32, 32, 16, 16, 3, 1, (ROOM, SUM)),
+    ("gather, channels-last copy by elements", 24, 45, 39, 7, 9, 3, 1, (ROOM, SUM)),
+    ("gather, channels-last copy in blocks", 6, 70, 37, 6, 6, 3, 1, (ROOM,)),
+    ("gather, four classes", 19, 40, 48, 9, 11, 3, 2, (ROOM, SUM)),
+    ("four parity classes", 19, 40, 48, 10, 12, 3, 2, (ROOM, SUM)),
+    ("pixels to clear", 30, 40, 48, 10, 11, 1, 2, (ROOM, SUM)),
+    ("pointwise", 40, 40, 24, 24, 20, 1, 1, (ROOM, SUM)),
+    ("pointwise by waves", 40, 40, 300, 7, 7, 1, 1, (ROOM, SUM)),
+    ("filter by the waves that wait", 112, 512, 512, 7, 7, 3, 1, (ROOM,)),
+    ("filter by the waves that wait, 1x1", 64, 512, 2048, 7, 7, 1, 1, (ROOM, SUM)),
+    ("no room", 64, 100, 130, 28, 28, 3, 1, ("in the launch of the data gradient's repack",)),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_shared_launches_are_bit_identical_to_the_separate_calls(case):
+    import torch
+    from gpu_util import Guarded, upload, workspace
+    name, N, C, K, H, W, R, st, words = case
+    spec = synth.LayerSpec(name, N, C, K, H, W, R, R, st, R // 2)
+    d = B.desc_from_spec(spec)
+    plan = B.cac_describe_plan(d, B.OP_BWD_WEIGHT_AND_DATA)
+    assert all(w in plan for w in words), plan
+    t = synth.make_inputs(spec, "bwd-shared", tensors=("X", "W", "dY"))
+    X, Wt, dY = (upload(t[n], spec.dtype) for n in ("X", "W", "dY"))
+    hp, wp, _, _ = B.cac_pooled_shape(d)
+    Z = torch.empty((N, C, hp, wp), dtype=torch.bfloat16, device="cuda:0")
+    B.cac_compress(d, X, Z)
+    out = []
+    for both in (False, True, True):
+        dW, dX = Guarded((K, C, R, R), torch.float32), Guarded((N, C, H, W), torch.bfloat16)
+        if both:
+            ws = workspace(d, B.OP_BWD_WEIGHT_AND_DATA)
+            ws.fill_(0xFF)   # stale contents must not matter (all-ones floats are NaN)
+            B.conv_bwd_weight_and_data(d, Z, Wt, dY, dW.t, dX.t, ws)
+        else:
+            B.conv_bwd_weight_compressed(d, Z, dY, dW.t, workspace(d, B.OP_BWD_WEIGHT_COMPRESSED))
+            B.conv_bwd_data(d, Wt, dY, dX.t, workspace(d, B.OP_BWD_DATA))
+        torch.cuda.synchronize()
+        dW.check("dW"), dX.check("dX")
+        out.append((dW.t.view(torch.int32), dX.t.view(torch.int16)))
+    for o in out[1:]:
+        assert torch.equal(out[0][0], o[0]) and torch.equal(out[0][1], o[1]), name
