@@ -328,7 +328,8 @@ bool shape_wave(GatherParams &p, int *variant, double *cost_out)
         q.lds_bytes = max(sh.ks * (q.buf_bytes + 64 * 16), red_bytes(sh.mi, sh.ks) + 32 * sh.mi * kOutRow);
         if (q.lds_bytes > 160 * 1024) continue;
         q.KCp = (p.KCin + sh.kc - 1) / sh.kc * sh.kc;
-        q.nkb = q.kbs = q.KCp / sh.kc;
+        q.nkb = q.KCp / sh.kc;
+        q.kbs = (q.nkb + sh.ks - 1) / sh.ks; // (stages of the busiest wave)
         q.mtiles = (p.M + 32 * sh.mi - 1) / (32 * sh.mi);
         for (int t = 0; t < TAPS; ++t) {
             q.wofs[t] = (uint32_t)t * (q.KCp / 16) * (q.Mp / 32) * kFrag;
@@ -336,10 +337,9 @@ bool shape_wave(GatherParams &p, int *variant, double *cost_out)
         }
         const int resident = min(8 / sh.ks, 160 * 1024 / q.lds_bytes); // workgroups of a compute unit
         const long wgs = tiles * q.mtiles, rounds = (wgs + 256L * resident - 1) / (256L * resident);
-        const int stages = (q.nkb + sh.ks - 1) / sh.ks; // of the busiest wave
         const double busy = (double)min((long)resident * sh.ks, ((wgs + 255) / 256) * sh.ks) / 4; // waves of a SIMD
         const double step = max(32.0 * NI * sh.mi * max(1.0, busy), 150.0);
-        const double cost = rounds * (stages * (TAPS * (sh.kc / 16) * step + 800.0) + 5000.0 + (sh.ks == 8 ? 800.0 : 0.0));
+        const double cost = rounds * (q.kbs * (TAPS * (sh.kc / 16) * step + 800.0) + 5000.0 + (sh.ks == 8 ? 800.0 : 0.0));
         if (cost < best_cost) {
             best_cost = cost;
             best = q;
