@@ -146,75 +146,80 @@ def dw_rk_executed_flops(d: cac_desc) -> int:
     return f.value
 
 
+# The marshalling of a call costs as much as a third of a launch, so it does no more than it must: pointers go as integers (the
+# argument types above take them, None as null), the descriptor as it is, the stream's handle without a stream object around it.
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_torch = None
 
 
 def _stream(stream):
-    if stream is None:
+    global _torch
+    if stream is not None:
+        return stream.cuda_stream
+    if _torch is None:
         import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        _torch = torch
+    if _torch.cuda.is_initialized():
+        c = _torch._C
+        try:
+            return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+        except AttributeError:
+            pass
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _ws(ws):
-    if ws is None:
-        return None, 0
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+    return (None, 0) if ws is None else (ws.data_ptr(), ws.nbytes)
 
 
 def conv_fwd_and_compress(d, X, W, b, Y, Z, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().conv_fwd_and_compress(ctypes.byref(d), _ptr(X), _ptr(W), _ptr(b), _ptr(Y), _ptr(Z), wp, wb,
-                                       _stream(stream)))
+    _check((_lib or lib()).conv_fwd_and_compress(d, _ptr(X), _ptr(W), _ptr(b), _ptr(Y), _ptr(Z), *_ws(ws), _stream(stream)))
 
 
 def cac_compress(d, X, Z, stream=None):
-    _check(lib().cac_compress(ctypes.byref(d), _ptr(X), _ptr(Z), _stream(stream)))
+    _check((_lib or lib()).cac_compress(d, _ptr(X), _ptr(Z), _stream(stream)))
 
 
 def conv_bwd_weight_compressed(d, Z, dY, dW, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().conv_bwd_weight_compressed(ctypes.byref(d), _ptr(Z), _ptr(dY), _ptr(dW), wp, wb, _stream(stream)))
+    _check((_lib or lib()).conv_bwd_weight_compressed(d, _ptr(Z), _ptr(dY), _ptr(dW), *_ws(ws), _stream(stream)))
 
 
 def conv_bwd_weight_compressed_noalloc(d, Z, dY, dW, stream=None):
-    _check(lib().conv_bwd_weight_compressed_noalloc(ctypes.byref(d), _ptr(Z), _ptr(dY), _ptr(dW), _stream(stream)))
+    _check((_lib or lib()).conv_bwd_weight_compressed_noalloc(d, _ptr(Z), _ptr(dY), _ptr(dW), _stream(stream)))
 
 
 def conv_bwd_data(d, W, dY, dX, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().conv_bwd_data(ctypes.byref(d), _ptr(W), _ptr(dY), _ptr(dX), wp, wb, _stream(stream)))
+    _check((_lib or lib()).conv_bwd_data(d, _ptr(W), _ptr(dY), _ptr(dX), *_ws(ws), _stream(stream)))
 
 
 def conv_bwd_weight_and_data(d, Z, W, dY, dW, dX, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().conv_bwd_weight_and_data(ctypes.byref(d), _ptr(Z), _ptr(W), _ptr(dY), _ptr(dW), _ptr(dX), wp, wb,
-                                          _stream(stream)))
+    _check((_lib or lib()).conv_bwd_weight_and_data(d, _ptr(Z), _ptr(W), _ptr(dY), _ptr(dW), _ptr(dX), *_ws(ws), _stream(stream)))
 
 
 def cac_bn_relu_fwd_compress(d, Y, scale, shift, X_next, Z_next, Z_in=None, stream=None):
-    _check(lib().cac_bn_relu_fwd_compress(ctypes.byref(d), _ptr(Y), _ptr(scale), _ptr(shift), _ptr(X_next), _ptr(Z_next),
-                                          _ptr(Z_in), _stream(stream)))
+    _check((_lib or lib()).cac_bn_relu_fwd_compress(d, _ptr(Y), _ptr(scale), _ptr(shift), _ptr(X_next), _ptr(Z_next), _ptr(Z_in),
+                                                    _stream(stream)))
 
 
 def cac_bn_bwd_compressed(d, Z_in, dY, mean, invstd, gamma, dgamma, dbeta, dX, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().cac_bn_bwd_compressed(ctypes.byref(d), _ptr(Z_in), _ptr(dY), _ptr(mean), _ptr(invstd), _ptr(gamma),
-                                       _ptr(dgamma), _ptr(dbeta), _ptr(dX), wp, wb, _stream(stream)))
+    _check((_lib or lib()).cac_bn_bwd_compressed(d, _ptr(Z_in), _ptr(dY), _ptr(mean), _ptr(invstd), _ptr(gamma), _ptr(dgamma),
+                                                 _ptr(dbeta), _ptr(dX), *_ws(ws), _stream(stream)))
 
 
 def cac_probe(kind, src, dst, nbytes, iters=0, stream=None):
-    _check(lib().cac_probe(kind, _ptr(src), _ptr(dst), nbytes, iters, _stream(stream)))
+    _check((_lib or lib()).cac_probe(kind, _ptr(src), _ptr(dst), nbytes, iters, _stream(stream)))
 
 
 def conv_bwd_bias(d, dY, db, stream=None):
-    _check(lib().conv_bwd_bias(ctypes.byref(d), _ptr(dY), _ptr(db), _stream(stream)))
+    _check((_lib or lib()).conv_bwd_bias(d, _ptr(dY), _ptr(db), _stream(stream)))
 
 
 def cac_grad_cosine(d, dW_a, dW_b, out, ws=None, stream=None):
-    wp, wb = _ws(ws)
-    _check(lib().cac_grad_cosine(ctypes.byref(d), _ptr(dW_a), _ptr(dW_b), _ptr(out), wp, wb, _stream(stream)))
+    _check((_lib or lib()).cac_grad_cosine(d, _ptr(dW_a), _ptr(dW_b), _ptr(out), *_ws(ws), _stream(stream)))
 
 
 # ---- host <-> device marshalling (type conversion only, no arithmetic)

@@ -97,18 +97,12 @@ static int check_ptr(const void *p, const char *name)
     return CAC_OK;
 }
 
-static int check_ws(const Geom &g, int dtype, int op, const void *ws, size_t ws_bytes, size_t *need_out);
-
 static int launched(hipError_t e, const char *what)
 {
     if (e != hipSuccess) return fail(CAC_ERR_LAUNCH_FAILED, "%s: %s", what, hipGetErrorString(e));
     return CAC_OK;
 }
 
-static size_t workspace_bytes(const Geom &g, int dtype, int op);
-
-// Part of the combined backward call's workspace that the weight gradient uses (the data
-// gradient's part starts behind it, 256-byte aligned).
 // The reduced-K kernel's plan when the descriptor asks for that form and the kernel covers the
 // geometry.  AUTO asks for it only where it has measured faster than the inflating kernel: from
 // about 24 GFLOP of nominal work per call on.  Below that the two finish within a few microseconds
@@ -125,20 +119,41 @@ static bool reduced_k_plan(const Geom &g, int dtype, DwRkPlan *rk)
     return true;
 }
 
-static size_t both_dw_bytes(const Geom &g, int dtype)
+// The weight gradient, planned: with the kernel the descriptor asks for (the reduced-K form where this version has one for the
+// geometry, else the inflating MFMA kernel, the tiled one, the plain one).
+struct DwPlan {
+    enum { kReduced, kMfma, kTiled, kPlain } kind;
+    DwRkPlan rk;
+    DwMfmaPlan mfma;
+    DwTiledPlan tiled;
+    size_t bytes; // partial sums of the pixel slices
+};
+static void plan_weight_gradient(const Geom &g, int dtype, DwPlan *plan)
 {
-    return (workspace_bytes(g, dtype, CAC_OP_BWD_WEIGHT_COMPRESSED) + 255) & ~(size_t)255;
+    if (reduced_k_plan(g, dtype, &plan->rk)) {
+        plan->kind = DwPlan::kReduced;
+        plan->bytes = plan->rk.partial_bytes;
+    } else if (dw_mfma_plan(g, dtype, &plan->mfma)) {
+        plan->kind = DwPlan::kMfma;
+        plan->bytes = plan->mfma.partial_bytes;
+    } else if (dw_tiled_plan(g, dtype, &plan->tiled)) {
+        plan->kind = DwPlan::kTiled;
+        plan->bytes = plan->tiled.partial_bytes;
+    } else {
+        plan->kind = DwPlan::kPlain;
+        plan->bytes = 0;
+    }
 }
+// Part of the combined backward call's workspace that the weight gradient uses (the data
+// gradient's part starts behind it, 256-byte aligned).
+static size_t both_dw_bytes(size_t dw) { return (dw + 255) & ~(size_t)255; }
 
 static size_t workspace_bytes(const Geom &g, int dtype, int op)
 {
     if (op == CAC_OP_BWD_WEIGHT_COMPRESSED) {
-        DwRkPlan rk;
-        if (reduced_k_plan(g, dtype, &rk)) return rk.partial_bytes;
-        DwMfmaPlan plan;
-        if (dw_mfma_plan(g, dtype, &plan)) return plan.partial_bytes; // partial sums of the pixel slices
-        DwTiledPlan tl;
-        if (dw_tiled_plan(g, dtype, &tl)) return tl.partial_bytes;
+        DwPlan plan;
+        plan_weight_gradient(g, dtype, &plan);
+        return plan.bytes;
     }
     // channels-last copy of the input and the repacked filter
     if (op == CAC_OP_FWD_AND_COMPRESS) return conv_mfma_workspace(g, dtype, false);
@@ -146,15 +161,13 @@ static size_t workspace_bytes(const Geom &g, int dtype, int op)
     if (op == CAC_OP_GRAD_COSINE) return cosine_workspace((long)g.K * g.C * g.R * g.S);
     // both gradients in one call: the partial sums are still being read when the repacks are written
     if (op == CAC_OP_BWD_WEIGHT_AND_DATA)
-        return both_dw_bytes(g, dtype) + workspace_bytes(g, dtype, CAC_OP_BWD_DATA);
+        return both_dw_bytes(workspace_bytes(g, dtype, CAC_OP_BWD_WEIGHT_COMPRESSED)) + workspace_bytes(g, dtype, CAC_OP_BWD_DATA);
     if (op == CAC_OP_BN_BWD) return bn_bwd_workspace_bytes(g, dtype);
     return 0;
 }
 
-static int check_ws(const Geom &g, int dtype, int op, const void *ws, size_t ws_bytes, size_t *need_out)
+static int check_ws(size_t need, const void *ws, size_t ws_bytes)
 {
-    size_t need = workspace_bytes(g, dtype, op);
-    if (need_out) *need_out = need;
     if (need == 0) return CAC_OK;
     if (!ws) return fail(CAC_ERR_WORKSPACE_TOO_SMALL, "workspace is NULL, %zu bytes needed", need);
     if (((uintptr_t)ws) & 15) return fail(CAC_ERR_ALIGNMENT, "workspace is not 16-byte aligned");
@@ -169,21 +182,16 @@ static hipError_t do_compress(const Geom &g, int dtype, const void *X, void *Z, 
     return launch_compress_generic(g, dtype, X, Z, st);
 }
 
-// The weight gradient with the kernel the descriptor asks for (the reduced-K form where this
-// version has one for the geometry, else the inflating MFMA kernel, else the plain one).
-static int launch_weight_gradient(const Geom &g, int dtype, const void *Z, const void *dY, float *dW, void *ws, hipStream_t st,
-                                  DwReduceTail *defer, const RepackParams *rep = nullptr, bool *rep_done = nullptr)
+static int launch_weight_gradient(const Geom &g, int dtype, const DwPlan &plan, const void *Z, const void *dY, float *dW, void *ws,
+                                  hipStream_t st, DwReduceTail *defer, const RepackParams *rep = nullptr, bool *rep_done = nullptr)
 {
     if (defer) defer->blocks = 0;
-    DwRkPlan rk;
-    if (reduced_k_plan(g, dtype, &rk))
-        return launched(launch_dw_rk(rk, Z, dY, dW, ws, st, defer), "weight gradient (reduced K)");
-    DwMfmaPlan plan;
-    if (dw_mfma_plan(g, dtype, &plan)) 
-        return launched(launch_dw_mfma(plan, Z, dY, dW, ws, st, defer, rep, rep_done), "weight gradient (MFMA)");
-    DwTiledPlan tl;
-    if (dw_tiled_plan(g, dtype, &tl)) return launched(launch_dw_tiled(tl, dtype, Z, dY, dW, ws, st, defer), "weight gradient (tiled)");
-    return launched(launch_dw_generic(g, dtype, Z, dY, dW, st), "weight gradient");
+    switch (plan.kind) {
+    case DwPlan::kReduced: return launched(launch_dw_rk(plan.rk, Z, dY, dW, ws, st, defer), "weight gradient (reduced K)");
+    case DwPlan::kMfma: return launched(launch_dw_mfma(plan.mfma, Z, dY, dW, ws, st, defer, rep, rep_done), "weight gradient (MFMA)");
+    case DwPlan::kTiled: return launched(launch_dw_tiled(plan.tiled, dtype, Z, dY, dW, ws, st, defer), "weight gradient (tiled)");
+    default: return launched(launch_dw_generic(g, dtype, Z, dY, dW, st), "weight gradient");
+    }
 }
 
 // ---- scratch of the entry point that allocates nothing ------------------------------------
@@ -319,7 +327,7 @@ int cac_describe_plan(const cac_desc *d, int op, char *buf, size_t buf_len)
         const bool split = (reduced_k_plan(g, d->dtype, &rk)) ? !rk.p.direct
                                                                                            : (dw_mfma_plan(g, d->dtype, &plan) && !plan.p.direct);
         DxPlan dxp;
-        const bool planned = plan_dx_mfma(g, d->dtype, nullptr, nullptr, nullptr, nullptr, &dxp);
+        const bool planned = plan_dx_mfma(g, d->dtype, &dxp);
         const bool with_dw = planned && !reduced_k_plan(g, d->dtype, &rk) && dw_mfma_plan(g, d->dtype, &plan) && dw_takes_repack(plan, dxp.rep);
         if (!planned || !(split || with_dw)) snprintf(buf, buf_len, "weight gradient, then data gradient, as in the separate calls");
         else if (with_dw) snprintf(buf, buf_len, "weight gradient with the data gradient's repack in its launch, then data gradient%s",
@@ -340,12 +348,14 @@ int conv_fwd_and_compress(const cac_desc *d, const void *X, const void *W, const
     if ((rc = check_ptr(X, "X")) || (rc = check_ptr(W, "W")) || (rc = check_ptr(Y, "Y")) || (rc = check_ptr(Z, "Z")))
         return rc;
     if (d->has_bias && (rc = check_ptr(b, "b"))) return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_FWD_AND_COMPRESS, ws, ws_bytes, nullptr))) return rc;
+    FwdPlan plan;
+    const bool mfma = plan_fwd_mfma(g, d->dtype, &plan);
+    if ((rc = check_ws(mfma ? plan.ws_bytes : 0, ws, ws_bytes))) return rc;
     hipStream_t st = (hipStream_t)stream;
     hipError_t e = hipSuccess;
     bool pooled = false;
-    if (!launch_fwd_mfma(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, Z, ws, st, &e, &pooled) &&
-        !launch_fwd_lds(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, st, &e))
+    if (mfma) e = launch_fwd_mfma(g, plan, X, W, d->has_bias ? b : nullptr, Y, Z, ws, st, &pooled);
+    else if (!launch_fwd_lds(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, st, &e))
         e = launch_fwd_generic(g, d->dtype, X, W, d->has_bias ? b : nullptr, Y, st);
     if ((rc = launched(e, "forward convolution"))) return rc;
     if (pooled) return CAC_OK;
@@ -368,8 +378,10 @@ int conv_bwd_weight_compressed(const cac_desc *d, const void *Z, const void *dY,
     int rc = make_geom(d, &g, true);
     if (rc) return rc;
     if ((rc = check_ptr(Z, "Z")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dW, "dW"))) return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_WEIGHT_COMPRESSED, ws, ws_bytes, nullptr))) return rc;
-    return launch_weight_gradient(g, d->dtype, Z, dY, (float *)dW, ws, (hipStream_t)stream, nullptr);
+    DwPlan plan;
+    plan_weight_gradient(g, d->dtype, &plan);
+    if ((rc = check_ws(plan.bytes, ws, ws_bytes))) return rc;
+    return launch_weight_gradient(g, d->dtype, plan, Z, dY, (float *)dW, ws, (hipStream_t)stream, nullptr);
 }
 
 int conv_bwd_weight_compressed_noalloc(const cac_desc *d, const void *Z, const void *dY, void *dW, void *stream)
@@ -378,7 +390,9 @@ int conv_bwd_weight_compressed_noalloc(const cac_desc *d, const void *Z, const v
     int rc = make_geom(d, &g, true);
     if (rc) return rc;
     if ((rc = check_ptr(Z, "Z")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dW, "dW"))) return rc;
-    const size_t need = workspace_bytes(g, d->dtype, CAC_OP_BWD_WEIGHT_COMPRESSED);
+    DwPlan plan;
+    plan_weight_gradient(g, d->dtype, &plan);
+    const size_t need = plan.bytes;
     if (need > kScratchBytes)
         return fail(CAC_ERR_UNSUPPORTED,
                     "this layer's weight gradient needs %zu bytes of scratch, the built-in buffer has %zu: "
@@ -388,7 +402,7 @@ int conv_bwd_weight_compressed_noalloc(const cac_desc *d, const void *Z, const v
     if (need && (rc = scratch_of_current_device(&ws))) return rc;
     // (nothing in the buffer has to start as zero: every pixel slice writes the whole of its
     // partial sums before the slice sum reads them)
-    return launch_weight_gradient(g, d->dtype, Z, dY, (float *)dW, ws, (hipStream_t)stream, nullptr);
+    return launch_weight_gradient(g, d->dtype, plan, Z, dY, (float *)dW, ws, (hipStream_t)stream, nullptr);
 }
 
 int conv_bwd_data(const cac_desc *d, const void *W, const void *dY, void *dX, void *ws, size_t ws_bytes,
@@ -398,12 +412,14 @@ int conv_bwd_data(const cac_desc *d, const void *W, const void *dY, void *dX, vo
     int rc = make_geom(d, &g, true);
     if (rc) return rc;
     if ((rc = check_ptr(W, "W")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dX, "dX"))) return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_DATA, ws, ws_bytes, nullptr))) return rc;
-    hipError_t e = hipSuccess;
     DxPlan dx;
-    if (plan_dx_mfma(g, d->dtype, W, dY, dX, ws, &dx))
+    const bool mfma = plan_dx_mfma(g, d->dtype, &dx);
+    if ((rc = check_ws(mfma ? dx.ws_bytes : 0, ws, ws_bytes))) return rc;
+    hipError_t e = hipSuccess;
+    if (mfma) {
+        bind_dx_mfma(&dx, W, dY, dX, ws);
         e = launch_dx_mfma(dx, false, nullptr, (hipStream_t)stream);
-    else if (!launch_dx_lds(g, d->dtype, W, dY, dX, (hipStream_t)stream, &e))
+    } else if (!launch_dx_lds(g, d->dtype, W, dY, dX, (hipStream_t)stream, &e))
         e = launch_dx_generic(g, d->dtype, W, dY, dX, (hipStream_t)stream);
     return launched(e, "data gradient");
 }
@@ -417,16 +433,18 @@ int conv_bwd_weight_and_data(const cac_desc *d, const void *Z, const void *W, co
     if ((rc = check_ptr(Z, "Z")) || (rc = check_ptr(W, "W")) || (rc = check_ptr(dY, "dY")) || (rc = check_ptr(dW, "dW")) ||
         (rc = check_ptr(dX, "dX")))
         return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_BWD_WEIGHT_AND_DATA, ws, ws_bytes, nullptr))) return rc;
+    DwPlan dw;
+    DxPlan dx;
+    plan_weight_gradient(g, d->dtype, &dw);
+    const bool planned = plan_dx_mfma(g, d->dtype, &dx);
+    if ((rc = check_ws(both_dw_bytes(dw.bytes) + (planned ? dx.ws_bytes : 0), ws, ws_bytes))) return rc;
     hipStream_t st = (hipStream_t)stream;
-    void *ws_dx = ws ? (char *)ws + both_dw_bytes(g, d->dtype) : nullptr;
     // Two launches where the weight gradient's has room for the repacks of the data gradient: the slice sum rides with the data
     // gradient then, else with the repacks.
-    DxPlan dx;
-    const bool planned = plan_dx_mfma(g, d->dtype, W, dY, dX, ws_dx, &dx);
+    if (planned) bind_dx_mfma(&dx, W, dY, dX, ws ? (char *)ws + both_dw_bytes(dw.bytes) : nullptr);
     DwReduceTail tail{};
     bool repacked = false;
-    if ((rc = launch_weight_gradient(g, d->dtype, Z, dY, (float *)dW, ws, st, &tail, planned ? &dx.rep : nullptr, &repacked))) return rc;
+    if ((rc = launch_weight_gradient(g, d->dtype, dw, Z, dY, (float *)dW, ws, st, &tail, planned ? &dx.rep : nullptr, &repacked))) return rc;
     if (planned) return launched(launch_dx_mfma(dx, repacked, &tail, st), "data gradient");
     if ((rc = launched(launch_dw_reduce(tail, st), "weight gradient (slice sum)"))) return rc;
     hipError_t e = hipSuccess;
@@ -461,7 +479,7 @@ int cac_bn_bwd_compressed(const cac_desc *d, const void *Z_in, const void *dY, c
         (rc = check_ptr(invstd, "invstd")) || (rc = check_ptr(gamma, "gamma")) || (rc = check_ptr(dgamma, "dgamma")) ||
         (rc = check_ptr(dbeta, "dbeta")) || (rc = check_ptr(dX, "dX")))
         return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_BN_BWD, ws, ws_bytes, nullptr))) return rc;
+    if ((rc = check_ws(workspace_bytes(g, d->dtype, CAC_OP_BN_BWD), ws, ws_bytes))) return rc;
     hipError_t e = hipSuccess;
     if (launch_bn_bwd_fast(g, d->dtype, Z_in, dY, mean, invstd, gamma, dgamma, dbeta, dX, ws, (hipStream_t)stream, &e))
         return launched(e, "batch normalisation backward");
@@ -498,7 +516,7 @@ int cac_grad_cosine(const cac_desc *d, const void *dW_a, const void *dW_b, void 
     int rc = make_geom(d, &g, true);
     if (rc) return rc;
     if ((rc = check_ptr(dW_a, "dW_a")) || (rc = check_ptr(dW_b, "dW_b")) || (rc = check_ptr(out, "out"))) return rc;
-    if ((rc = check_ws(g, d->dtype, CAC_OP_GRAD_COSINE, ws, ws_bytes, nullptr))) return rc;
+    if ((rc = check_ws(workspace_bytes(g, d->dtype, CAC_OP_GRAD_COSINE), ws, ws_bytes))) return rc;
     return launched(launch_cosine((const float *)dW_a, (const float *)dW_b, (long)g.K * g.C * g.R * g.S, (float *)out, ws,
                                   (hipStream_t)stream),
                     "gradient cosine");

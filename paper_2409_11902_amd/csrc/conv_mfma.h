@@ -101,18 +101,27 @@ bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *
 hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st);
 int describe_pw(const GatherParams &p, int variant, char *buf, size_t len);
 
-size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
-// Text description of the launch shape(s) chosen; false when the geometry is not covered.
-bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, size_t len);
-bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, void *Z, void *ws,
-                     hipStream_t st, hipError_t *err, bool *pooled);
-// A data gradient, planned: what has to be laid out ahead of it (rep), and its launches.
+// A forward pass and a data gradient, planned; the latter with what has to be laid out ahead of it (rep).
+struct FwdPlan {
+    GatherParams p;
+    int variant;
+    size_t ws_in, ws_wt, ws_bytes; // workspace: of the channels-last input, of the repacked filter, in all
+};
 struct DxPlan {
     GatherParams cls[4];
     int variant[4], ncls;
+    bool direct, empty_class; // dY is read where it lies; some pixels have no tap
+    size_t ws_in, ws_wt, ws_bytes;
     RepackParams rep;
 };
-bool plan_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, DxPlan *plan);
+bool plan_fwd_mfma(const Geom &g, int dtype, FwdPlan *plan);
+hipError_t launch_fwd_mfma(const Geom &g, FwdPlan &plan, const void *X, const void *W, const void *b, void *Y, void *Z, void *ws, hipStream_t st,
+                           bool *pooled);
+bool plan_dx_mfma(const Geom &g, int dtype, DxPlan *plan);
+void bind_dx_mfma(DxPlan *plan, const void *W, const void *dY, void *dX, void *ws);
 hipError_t launch_dx_mfma(DxPlan &plan, bool repacked, const DwReduceTail *tail, hipStream_t st);
+size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad);
+// Text description of the launch shape(s) chosen; false when the geometry is not covered.
+bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, size_t len);
 
 } // namespace cac

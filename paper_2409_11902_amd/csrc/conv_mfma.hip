@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(256) repack_kernel(RepackParams p)
 }
 
 // The input and filter repacks of one call.
-// Z, Wimg: see RepackParams (Z null: no pooling; else HW must be a multiple of 2*Wimg and Wimg 4 or a multiple of 8).
+// N 0: the filter alone.  Z, Wimg: see RepackParams (Z null: no pooling; else HW must be a multiple of 2*Wimg and Wimg 4 or a multiple of 8).
 RepackParams make_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, int Cp, const bf16_t *W, bf16_t *Wt, int O,
                          int Cw, int RS, int Mp, int KCp, int transpose, bf16_t *Z, int Wimg, int decim = 0)
 {
@@ -56,7 +56,6 @@ RepackParams make_repack(const bf16_t *in, bf16_t *out, int N, int C, int HW, in
     p.in = in; p.out = out; p.N = N; p.C = C; p.HW = HW; p.Cp = Cp;
     p.Z = Z; p.Wimg = Wimg; p.decim = decim;
     p.fast = HW % 2 == 0; // planes start at multiples of 4 bytes: 16-byte loads need no more
-    if (!in) N = 0;       // filter only
     const int cgs = Cp / 8, cgw = cgs < 8 ? cgs : 8;
     const long items = p.fast ? (long)N * ((cgs + cgw - 1) / cgw) * cgw * (Z && Wimg != 4 ? HW / 16 : (HW + 7) / 8) : 0;
     // (a thread's loads are all in flight at once, so a small input is bound by latency, not by
@@ -1072,90 +1071,102 @@ bool describe_conv_mfma(const Geom &g, int dtype, bool data_grad, char *buf, siz
 
 size_t conv_mfma_workspace(const Geom &g, int dtype, bool data_grad)
 {
-    GatherParams p{}, cls[4];
-    int variant[4], ncls = 0;
-    bool empty = false;
-    if (!(data_grad ? plan_dx(g, dtype, p, cls, variant, &ncls, &empty) : plan_fwd(g, dtype, p, &variant[0]))) return 0;
-    const WsLayout l = data_grad ? dx_layout(g, p, cls, ncls) : fwd_layout(g, p);
-    return l.in + l.wt + l.part;
+    FwdPlan fwd;
+    DxPlan dx;
+    if (data_grad) return plan_dx_mfma(g, dtype, &dx) ? dx.ws_bytes : 0;
+    return plan_fwd_mfma(g, dtype, &fwd) ? fwd.ws_bytes : 0;
 }
 
 // Forward: Y = X * W + b.  False when the geometry is not covered.
+bool plan_fwd_mfma(const Geom &g, int dtype, FwdPlan *plan)
+{
+    if (!plan_fwd(g, dtype, plan->p, &plan->variant)) return false;
+    const WsLayout l = fwd_layout(g, plan->p);
+    plan->ws_in = l.in;
+    plan->ws_wt = l.wt;
+    plan->ws_bytes = l.in + l.wt + l.part;
+    return true;
+}
+
 // *pooled: Z has been written on the way (the channels-last repack reads X anyway); otherwise
 // the caller runs the compress kernel.
-bool launch_fwd_mfma(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, void *Z, void *ws,
-                     hipStream_t st, hipError_t *err, bool *pooled)
+hipError_t launch_fwd_mfma(const Geom &g, FwdPlan &plan, const void *X, const void *W, const void *b, void *Y, void *Z, void *ws, hipStream_t st,
+                           bool *pooled)
 {
-    *pooled = false;
-    GatherParams p{};
-    int variant;
-    if (!plan_fwd(g, dtype, p, &variant)) return false;
-    const WsLayout l = fwd_layout(g, p);
-    bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
-    p.part = l.part ? (float *)((char *)ws + l.in + l.wt) : nullptr;
+    GatherParams &p = plan.p;
+    hipError_t e = hipSuccess;
+    bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + plan.ws_in);
+    p.part = p.ksplit > 1 ? (float *)((char *)ws + plan.ws_in + plan.ws_wt) : nullptr;
     const bool fuse = Z && record_in_repack(g); // (with `direct` the repack launch forms Z without writing the channels-last copy)
     const bool direct = fwd_reads_in_place(g, p), with_filter = Z && record_with_filter(g, p);
     *pooled = with_filter;
+    // nothing to do for the input but the record: the filter's blocks go ahead of the pooling ones in one launch
+    const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0};
     if (p.tile == 3) {
         // the input as it lies, the record on the way where the items are row pairs, the filter as it lies where its rows are whole fragments
         if (!p.w_direct) {
-            const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0};
-            if (with_filter) *err = launch_compress_repack(g, X, Z, f, st);
-            else *err = launch_repack(make_repack(nullptr, in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W), st);
+            if (with_filter) e = launch_compress_repack(g, X, Z, f, st);
+            else e = launch_repack(make_repack(nullptr, in, 0, g.C, g.H * g.W, p.KCp, f.W, wt, g.K, g.C, 1, p.Mp, p.KCp, 0, nullptr, g.W), st);
         }
-        if (*err != hipSuccess) return true;
+        if (e != hipSuccess) return e;
         p.in = (const bf16_t *)X;
         p.wt = p.w_direct ? (const bf16_t *)W : wt;
         p.bias = (const bf16_t *)b; p.out = (bf16_t *)Y;
         p.Z = p.pw_pool ? (bf16_t *)Z : nullptr;
         *pooled = *pooled || p.Z;
-        *err = run_gather(p, variant, st);
-        return true;
+        return run_gather(p, plan.variant, st);
     }
-    // nothing to do for the input but the record: the filter's blocks go ahead of the pooling ones in one launch
-    const FilterRepack f{(const bf16_t *)W, wt, g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0};
     if (with_filter) {
-        *err = launch_compress_repack(g, X, Z, f, st);
+        e = launch_compress_repack(g, X, Z, f, st);
     } else {
-        *err = launch_repack(make_repack(direct && !fuse ? nullptr : (const bf16_t *)X, direct ? nullptr : in, g.N, g.C, g.H * g.W, p.KCp, f.W, wt,
-                                         g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, p.decim), st);
+        e = launch_repack(make_repack((const bf16_t *)X, direct ? nullptr : in, direct && !fuse ? 0 : g.N, g.C, g.H * g.W, p.KCp, f.W, wt,
+                                      g.K, g.C, p.ntaps_total, p.Mp, p.KCp, 0, fuse ? (bf16_t *)Z : nullptr, g.W, p.decim), st);
         *pooled = fuse;
     }
-    if (*err != hipSuccess) return true;
+    if (e != hipSuccess) return e;
     p.in = direct ? (const bf16_t *)X : in;
     p.nchw = direct;
     p.KCin = g.C;
     p.wt = wt; p.bias = (const bf16_t *)b; p.out = (bf16_t *)Y;
-    *err = run_gather(p, variant, st);
-    return true;
+    return run_gather(p, plan.variant, st);
 }
 
-// Data gradient: dX = W^T * dY.  False when the geometry is not covered; nothing has been launched then.
-bool plan_dx_mfma(const Geom &g, int dtype, const void *W, const void *dY, void *dX, void *ws, DxPlan *plan)
+// Data gradient: dX = W^T * dY.  False when the geometry is not covered.
+bool plan_dx_mfma(const Geom &g, int dtype, DxPlan *plan)
 {
     GatherParams base{}, (&cls)[4] = plan->cls;
-    bool empty_class = false;
-    if (!plan_dx(g, dtype, base, cls, plan->variant, &plan->ncls, &empty_class)) return false;
-    const int ncls = plan->ncls;
-    const WsLayout l = dx_layout(g, base, cls, ncls);
-    bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + l.in);
-    const bool direct = dx_reads_in_place(g, cls, ncls);
-    for (int k = 0; k < ncls; ++k) {
-        cls[k].part = cls[k].ksplit > 1 ? (float *)((char *)ws + l.in + l.wt) : nullptr;
-        cls[k].in = direct ? (const bf16_t *)dY : in;
-        cls[k].nchw = direct;
-        cls[k].KCin = g.K;
-        cls[k].wt = wt; cls[k].bias = nullptr; cls[k].out = (bf16_t *)dX;
-    }
-    plan->rep = make_repack(direct ? nullptr : (const bf16_t *)dY, in, g.N, g.K, g.P * g.Q, base.KCp, (const bf16_t *)W, wt, g.K, g.C,
+    plan->empty_class = false;
+    if (!plan_dx(g, dtype, base, cls, plan->variant, &plan->ncls, &plan->empty_class)) return false;
+    const WsLayout l = dx_layout(g, base, cls, plan->ncls);
+    plan->ws_in = l.in;
+    plan->ws_wt = l.wt;
+    plan->ws_bytes = l.in + l.wt + l.part;
+    plan->direct = dx_reads_in_place(g, cls, plan->ncls);
+    plan->rep = make_repack(nullptr, nullptr, plan->direct ? 0 : g.N, g.K, g.P * g.Q, base.KCp, nullptr, nullptr, g.K, g.C,
                             base.ntaps_total, base.Mp, base.KCp, 1, nullptr, 0);
     // pixels no output pixel's tap reaches (possible when stride > filter) stay zero
     // (cleared by blocks of a kernel, not by a memset node: callers may capture this call in a HIP graph)
-    if (empty_class) {
-        plan->rep.zero = (bf16_t *)dX;
-        plan->rep.zero_n = (long)g.N * g.C * g.H * g.W;
-    }
+    if (plan->empty_class) plan->rep.zero_n = (long)g.N * g.C * g.H * g.W;
     return true;
+}
+
+// The plan's tensors and its part of the workspace.
+void bind_dx_mfma(DxPlan *plan, const void *W, const void *dY, void *dX, void *ws)
+{
+    bf16_t *in = (bf16_t *)ws, *wt = (bf16_t *)((char *)ws + plan->ws_in);
+    for (int k = 0; k < plan->ncls; ++k) {
+        GatherParams &p = plan->cls[k];
+        p.part = p.ksplit > 1 ? (float *)((char *)ws + plan->ws_in + plan->ws_wt) : nullptr;
+        p.in = plan->direct ? (const bf16_t *)dY : in;
+        p.nchw = plan->direct;
+        p.wt = wt; p.bias = nullptr; p.out = (bf16_t *)dX;
+    }
+    RepackParams &r = plan->rep;
+    r.in = (const bf16_t *)dY;
+    r.out = in;
+    r.f.W = (const bf16_t *)W;
+    r.f.Wt = wt;
+    r.zero = plan->empty_class ? (bf16_t *)dX : nullptr;
 }
 
 // tail: a weight gradient's slice sum, or null.  repacked: plan.rep has run already, in the weight gradient's launch; the sum then

@@ -1182,7 +1182,7 @@ int dw_takes_repack(const DwMfmaPlan &plan, const RepackParams &rep)
     if (plan.threads != 256) return 0;
     if (plan.grid <= 192) return 1;
     const int blocks = (int)f.blocks();
-    if (rep.in_blocks || rep.zero || blocks < 256 || blocks > 2 * repack_waves(p, f) * p.total_wg || f.Cw % 32 || f.Cw * f.RS % 8) return 0;
+    if (rep.in_blocks || rep.zero_n || blocks < 256 || blocks > 2 * repack_waves(p, f) * p.total_wg || f.Cw % 32 || f.Cw * f.RS % 8) return 0;
     return repack_past(p, f) && 2 * (p.XW + 2 * buffer_elems(p) + 4 * repack_elems(f)) > 160 * 1024 ? 0 : 2;
 }
 

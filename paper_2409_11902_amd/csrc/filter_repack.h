@@ -135,9 +135,9 @@ struct RepackParams {
     int Wimg;           // image width (only with Z)
     int decim;          // with Z: `out` takes pixel (2h, 2w) of every 2 x 2 tile only, as an image of half the extent
     FilterRepack f;
-    bf16_t *zero;       // zero_n elements to clear, 2048 to a block, or null
+    bf16_t *zero;       // zero_n elements to clear, 2048 to a block (zero_n 0: none)
     long zero_n;
-    unsigned blocks() const { return in_blocks + f.blocks() + (zero ? (unsigned)((zero_n / 8 + 256) / 256) : 0u); }
+    unsigned blocks() const { return in_blocks + f.blocks() + (zero_n ? (unsigned)((zero_n / 8 + 256) / 256) : 0u); }
 };
 
 constexpr int kRepackElems = kFilterElems > 64 * 66 ? kFilterElems : 64 * 66; // LDS of a block
@@ -149,7 +149,7 @@ __device__ __forceinline__ void repack_body(const RepackParams &p, const int bid
         const int fb = (p.f.Mp / 32) * (p.f.KCp / 16);
         if (bid - p.in_blocks < fb) {
             filter_repack(p.f, bid - p.in_blocks, sm, tid);
-        } else if (p.zero) { // whole 16-byte units, then the (up to 7) elements that remain -- not a byte past the tensor
+        } else if (p.zero_n) { // whole 16-byte units, then the (up to 7) elements that remain -- not a byte past the tensor
             const long i = (long)(bid - p.in_blocks - fb) * 256 + tid, n16 = p.zero_n / 8;
             if (i < n16) ((u32x4 *)p.zero)[i] = u32x4{0, 0, 0, 0};
             if (i < p.zero_n - n16 * 8) p.zero[n16 * 8 + i] = (bf16_t)0;
