@@ -238,7 +238,7 @@ const Shape kShapes[] = {{1, 4, launch_shape<1, 4>}, {2, 2, launch_shape<2, 2>}}
 
 // Plans the launch; false when the geometry is not its own.  p: N, M (= C_in), Mp, KCin (= C_out), Hin, Win (of dY),
 // Hout, Wout (of dX) are filled in.
-bool shape_dx2(const Geom &g, GatherParams &p, int *variant)
+bool shape_dx2(const Geom &g, GatherParams &p, int *variant, double *cost_out)
 {
     if (g.R != 3 || g.S != 3 || g.sh != 2 || g.sw != 2 || g.ph != 1 || g.pw != 1 || g.W % 2) return false;
     GatherParams b = p;
@@ -300,6 +300,7 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant)
         }
     if (best_cost > 1e299) return false;
     p = best;
+    *cost_out = best_cost;
     return true;
 }
 

@@ -36,7 +36,7 @@ struct GatherParams {
     uint32_t m_wc, m_ppi, m_pwd, m_kbs, m_img; // division magics of Wc, Hc*Wc, PWd, kbs, PH*PWd
     uint32_t m_gx, m_ph;                       // ... of the 8-pixel groups of an input row and of PH (in-place copy)
     // conv_tile.hip
-    int tile;           // the launch runs there (2: in conv_dx2.hip, 3: in conv_pw.hip, 4: in conv_wave.hip)
+    int tile;           // the launch runs there (2: in conv_dx2.hip, 3: in conv_pw.hip, 4, 5: in conv_wave.hip)
     int gw, GX;         // pixels of a staged item; items of an input row
     int store_px;       // pixels per store of the epilogue: 8, 4, 2 or 1
     int buf_bytes, lds_bytes; // a staging buffer; all of the workgroup's LDS
@@ -89,13 +89,16 @@ bool shape_tile(GatherParams &p, int *variant, double *cost);
 hipError_t launch_tile(const GatherParams &p, int variant, hipStream_t st);
 int describe_tile(const GatherParams &p, int variant, char *buf, size_t len);
 // conv_dx2.hip: the 3 x 3 stride-2 data gradient, all parity classes in one launch
-bool shape_dx2(const Geom &g, GatherParams &p, int *variant);
+bool shape_dx2(const Geom &g, GatherParams &p, int *variant, double *cost);
 hipError_t launch_dx2(const GatherParams &p, int variant, hipStream_t st);
 int describe_dx2(const GatherParams &p, int variant, char *buf, size_t len);
 // conv_wave.hip: nine-tap launches with few pixels
 bool shape_wave(GatherParams &p, int *variant, double *cost);
 hipError_t launch_wave(const GatherParams &p, int variant, hipStream_t st);
 int describe_wave(const GatherParams &p, int variant, char *buf, size_t len);
+bool shape_wave_dx2(const Geom &g, GatherParams &p, int *variant, double *cost);
+hipError_t launch_wave_dx2(const GatherParams &p, int variant, hipStream_t st);
+int describe_wave_dx2(const GatherParams &p, int variant, char *buf, size_t len);
 // conv_pw.hip: 1 x 1 stride-1 layers
 bool shape_pw(GatherParams &p, bool pool, bool record_free, int *variant, bool *gather, bool *gather_whole);
 hipError_t launch_pw(const GatherParams &p, int variant, hipStream_t st);

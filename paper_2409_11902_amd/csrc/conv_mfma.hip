@@ -804,6 +804,7 @@ hipError_t run_gather(const GatherParams &p, int variant, hipStream_t st)
     case 2: return launch_dx2(p, variant, st);
     case 3: return launch_pw(p, variant, st);
     case 4: return launch_wave(p, variant, st);
+    case 5: return launch_wave_dx2(p, variant, st);
     }
     switch (variant) {
     case 0: return launch_gather<2, 1, 4>(p, st);
@@ -945,10 +946,23 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
     base.os = g.sh; base.is = 1; base.ntaps_total = g.R * g.S;
     *ncls = 0;
     *empty_class = false;
-    if (GatherParams p = base; p.KCin = g.K, use_tile() && shape_dx2(g, p, &variant[0])) {
-        p.tile = 2;
+    // One launch for the four classes: by waves or with shared stages.  The two estimates, in cycles, cross where the measured
+    // times do: over 142 random layers that both take, waves needed 0.37 to 0.82 of the other kernel's time where the ratio of the
+    // estimates is below 0.5 (79 layers, the worst 0.98), 0.99 up to 0.6, 1.0 up to 0.7 and up to twice the time above (short sums over
+    // many tiles: 1760 -> 32 at 28 x 26 of dY, batch 9, 41 us there, 89 by waves).  Odd rows only waves take.
+    GatherParams wave = base, dx2 = base;
+    wave.KCin = dx2.KCin = g.K;
+    int wave_variant;
+    double wave_cost, dx2_cost = 1e300;
+    const bool have_dx2 = use_tile() && shape_dx2(g, dx2, &variant[0], &dx2_cost);
+    bool have_wave = use_tile() && shape_wave_dx2(g, wave, &wave_variant, &wave_cost);
+    if (have_wave && have_dx2) have_wave = wave_cost < 0.5 * dx2_cost;
+    if (have_wave || have_dx2) {
+        GatherParams &p = cls[(*ncls)++];
+        p = have_wave ? wave : dx2;
+        p.tile = have_wave ? 5 : 2;
+        if (have_wave) variant[0] = wave_variant;
         base.KCp = p.KCp;
-        cls[(*ncls)++] = p;
         return true;
     }
     for (int a0 = 0; a0 < g.sh; ++a0)
@@ -995,6 +1009,7 @@ int describe_one(const GatherParams &p, int variant, char *buf, size_t len)
 {
     if (p.tile == 3) return describe_pw(p, variant, buf, len);
     if (p.tile == 4) return describe_wave(p, variant, buf, len);
+    if (p.tile == 5) return describe_wave_dx2(p, variant, buf, len);
     if (p.tile) return p.tile == 2 ? describe_dx2(p, variant, buf, len) : describe_tile(p, variant, buf, len);
     static const int shape[6][3] = {{2, 1, 4}, {2, 2, 2}, {2, 4, 1}, {1, 1, 4}, {1, 2, 2}, {1, 4, 1}}; // NI, WM, WN
     const int *v = shape[variant];

@@ -1,5 +1,5 @@
-// Nine-tap gather GEMM (3 x 3 forward convolution, stride 1 or 2, and 3 x 3 stride-1 data gradient) for layers with few
-// pixels: every wave stages for itself, the waves of a workgroup share a tile's channels.
+// Nine-tap gather GEMM (3 x 3 forward convolution and data gradient, stride 1 or 2) for layers with few pixels: every wave stages
+// for itself, the waves of a workgroup share a tile's channels.
 //
 // The sum is the one of conv_mfma.hip, filter fragments and taps as there.  Where pixels are few, what bounds the other
 // kernels is latency: a barrier between any two stages, one workgroup or less to a compute unit, a channels-last copy of the
@@ -38,48 +38,58 @@ typedef __attribute__((address_space(3))) f32x4 *lds_f32x4_ptr;
 
 constexpr int red_bytes(int MI, int KS) { return (KS - 1) * MI * NI * 4 * 1024; }
 
-// ITEMS: 8 channels x GW pixels that a lane stages per stage.
-template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bounds__(64 * KS, 2) conv_wave_kernel(GatherParams p)
+// (a wave reads what it wrote itself: LDS serves a wave's requests in order)
+__device__ __forceinline__ void wave_sync()
 {
-    constexpr int KSTEPS = KC / 16, STEPS = TAPS * KSTEPS, KCS = KC + 8, OCT = KC / 8;
-    constexpr int D = 9; // steps of filter fragments in flight
-    static_assert(STEPS % D == 0, "ring slots must not move from stage to stage");
-    extern __shared__ __align__(16) unsigned char smem[];
-    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
-    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int bx, by, bz;
-    if (!conv_block(p, smem, bx, by, bz)) return;
-    const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3);
-    if (v >= p.tiles_per_img * p.mtiles) return; // (tiles_per_img: pixel tiles of all images)
-    const int mt = v / p.tiles_per_img, m0 = mt * 32 * MI, F = (v - mt * p.tiles_per_img) * PT; // first pixel, over all images
-    const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb, plane = p.Hin * p.Win;
-    const int n0 = F / ppi, px0 = F - n0 * ppi, i0 = fdiv(px0, p.m_wc);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-    // ---- this lane's items: rows of the images from the first one the tile reaches on, one after the other
-    const int co = lane & (OCT - 1), hfirst = max(0, i0 * p.is + p.dhmin);
-    const uint32_t wbase = lds0 + ks * p.buf_bytes, dump = lds0 + KS * p.buf_bytes + threadIdx.x * 16;
-    uint32_t e0[ITEMS], l0[ITEMS], m8[ITEMS];
-#pragma unroll
-    for (int q = 0; q < ITEMS; ++q) {
-        const int it = lane + 64 * q, rest = it / OCT;
-        const int row = fdiv(rest, p.m_gx), gx = rest - row * p.GX;
-        const int gi = fdiv(hfirst + row, p.m_ph), hin = hfirst + row - gi * p.Hin, vi = hin - p.dhmin;
-        const int lr = gi * p.VH + vi - i0 * p.is, w0 = gx * GW;
-        const bool ok = (row < p.IR) & (n0 + gi < p.N) & (vi >= 0) & (vi < p.VH) & (lr >= 0) & (lr < p.PH);
-        uint32_t m = 0;
-#pragma unroll
-        for (int k = 0; k < GW; ++k) {
-            const int w = w0 + k;
-            m |= (ok & (w < p.Win) & (w >= p.dwmin) & (w < p.dwmin + p.PWd)) ? 1u << k : 0u;
-        }
-        m8[q] = m;
-        e0[q] = ok ? (uint32_t)(((n0 + gi) * K + co * 8) * p.Hin + hin) * p.Win + w0 : kNoElem;
-        l0[q] = wbase + (uint32_t)((lr * p.PWd + (w0 - p.dwmin)) * KCS + co * 8) * 2u;
-    }
-    const rsrc_t rs_in = make_rsrc(p.in, (uint32_t)p.N * K * plane * 2u);
+// A wave's staging: KC channels of the rows that its tile reaches, in LDS as [pixel][KC + 8].  An item is 8 channels x GW pixels of
+// one row (8; 7 in rows of odd length, read from the dword below an odd element); a lane has ITEMS of them.
+template <int KC, int ITEMS, int GW> struct WaveStage {
+    static constexpr int KCS = KC + 8, OCT = KC / 8;
+    uint32_t e0[ITEMS], l0[ITEMS], m8[ITEMS], dump;
     u32x4 r[ITEMS][8];
-    auto fetch = [&](int s) {
+    int co, K, nkb, plane;
+    rsrc_t rs_in;
+
+    // rows of the images from the first one the tile reaches on, one after the other
+    __device__ __forceinline__ void init(const GatherParams &p, uint32_t wbase, uint32_t dump_at, int n0, int i0)
+    {
+        const int lane = threadIdx.x & 63, hfirst = max(0, i0 * p.is + p.dhmin);
+        co = lane & (OCT - 1);
+        K = p.KCin;
+        nkb = p.nkb;
+        plane = p.Hin * p.Win;
+        dump = dump_at;
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const int it = lane + 64 * q, rest = it / OCT;
+            const int row = fdiv(rest, p.m_gx), gx = rest - row * p.GX;
+            const int gi = fdiv(hfirst + row, p.m_ph), hin = hfirst + row - gi * p.Hin, vi = hin - p.dhmin;
+            const int lr = gi * p.VH + vi - i0 * p.is, w0 = gx * GW;
+            const bool ok = (row < p.IR) & (n0 + gi < p.N) & (vi >= 0) & (vi < p.VH) & (lr >= 0) & (lr < p.PH);
+            uint32_t m = 0;
+#pragma unroll
+            for (int k = 0; k < GW; ++k) {
+                const int w = w0 + k;
+                m |= (ok & (w < p.Win) & (w >= p.dwmin) & (w < p.dwmin + p.PWd)) ? 1u << k : 0u;
+            }
+            m8[q] = m;
+            e0[q] = ok ? (uint32_t)(((n0 + gi) * K + co * 8) * p.Hin + hin) * p.Win + w0 : kNoElem;
+            l0[q] = wbase + (uint32_t)((lr * p.PWd + (w0 - p.dwmin)) * KCS + co * 8) * 2u;
+        }
+        rs_in = make_rsrc(p.in, (uint32_t)p.N * K * plane * 2u);
+    }
+    __device__ __forceinline__ void clear(uint32_t wbase, uint32_t bytes)
+    {
+        for (uint32_t i = threadIdx.x & 63; i < bytes / 16; i += 64) *(lds_u32x4_ptr)(uintptr_t)(wbase + 16 * i) = u32x4{0, 0, 0, 0};
+        wave_sync();
+    }
+    __device__ __forceinline__ void fetch(int s)
+    {
         const uint32_t sbase = (uint32_t)(s * KC) * plane;
         const int nvalid = s < nkb ? K - (s * KC + co * 8) : 0; // channels that exist
 #pragma unroll
@@ -93,8 +103,9 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
                 e += plane;
             }
         }
-    };
-    auto put = [&](int s) {
+    }
+    __device__ __forceinline__ void put(int s)
+    {
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             if constexpr (GW == 7) { // (read from the dword below an odd element: down by one)
@@ -119,13 +130,30 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
                 *(lds_u32x4_ptr)(uintptr_t)((m8[q] & (1u << px)) ? l0[q] + px * (KCS * 2) : dump) = x;
             }
         }
-    };
-    // (a wave reads what it wrote itself: LDS serves a wave's requests in order)
-    auto wave_sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
+    }
+};
+
+// ITEMS: 8 channels x GW pixels that a lane stages per stage.
+template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bounds__(64 * KS, 2) conv_wave_kernel(GatherParams p)
+{
+    constexpr int KSTEPS = KC / 16, STEPS = TAPS * KSTEPS, KCS = KC + 8;
+    constexpr int D = 9; // steps of filter fragments in flight
+    static_assert(STEPS % D == 0, "ring slots must not move from stage to stage");
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3);
+    if (v >= p.tiles_per_img * p.mtiles) return; // (tiles_per_img: pixel tiles of all images)
+    const int mt = v / p.tiles_per_img, m0 = mt * 32 * MI, F = (v - mt * p.tiles_per_img) * PT; // first pixel, over all images
+    const int ppi = p.Hc * p.Wc, nkb = p.nkb;
+    const int n0 = F / ppi, px0 = F - n0 * ppi, i0 = fdiv(px0, p.m_wc);
+
+    WaveStage<KC, ITEMS, GW> in;
+    const uint32_t wbase = lds0 + ks * p.buf_bytes;
+    in.init(p, wbase, lds0 + KS * p.buf_bytes + threadIdx.x * 16, n0, i0);
 
     const rsrc_t rs_w = make_rsrc(p.wt, (uint32_t)TAPS * p.Mp * p.KCp * 2u);
     const uint32_t kstep = (p.Mp / 32) * kFrag, wlane = (uint32_t)(mt * MI) * kFrag + lane * 16u;
@@ -138,7 +166,7 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
             for (int j = 0; j < 16; ++j) acc[ni][mi][j] = 0.f;
     u32x4 wr[D][MI];
     if (ks < nkb) {
-        fetch(ks);
+        in.fetch(ks);
 #pragma unroll
         for (int q = 0; q < D; ++q)
 #pragma unroll
@@ -160,13 +188,12 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
         const uint32_t at = (uint32_t)(((gi * p.VH + (i - i0) * p.is) * p.PWd + j * p.is) * KCS * 2);
         pbase[ni] = wbase + 16u * half + (n0 + gi < p.N ? at : 0u);
     }
-    for (uint32_t i = lane; i < (uint32_t)p.buf_bytes / 16; i += 64) *(lds_u32x4_ptr)(uintptr_t)(wbase + 16 * i) = u32x4{0, 0, 0, 0};
-    wave_sync();
+    in.clear(wbase, p.buf_bytes);
 
     for (int s = ks; s < nkb; s += KS) {
-        put(s);
+        in.put(s);
         wave_sync();
-        fetch(s + KS); // (past the end: nothing is loaded)
+        in.fetch(s + KS); // (past the end: nothing is loaded)
         uint32_t so = (uint32_t)s * KSTEPS * kstep;
         opaque_s(so);
         u32x4 bq[2][NI];
@@ -254,6 +281,146 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
     else store(std::integral_constant<int, 1>{});
 }
 
+// The 3 x 3 stride-2 data gradient, padding 1: all parity classes of dX in one launch.  Pixel (2i + a, 2j + b) has the taps with r = 1 (a = 0)
+// or r = 0, 2 (a = 1), s likewise, of dY at (i + (r == 0), j + (s == 0)): a step of 16 channels is nine products for every block of 32
+// pixels of dY, over four shifts of it.  A tile is 32 input channels x 32 * BL pixels of dY x 4 classes; the two classes of a row of dX
+// leave side by side.  128 accumulators and nine filter fragments ahead make 2 waves to a SIMD; what bounds it is the wait for a
+// stage.  Per call: 69 input and 1472 output channels at 26 x 49, batch 30, 154 -> 49 us against four launches of the gather;
+// 423 and 408 at 13 x 13, batch 2, 53 -> 14.5; over 158 random layers (odd rows) 0.35 of its time, none slower.  Against conv_dx2.hip:
+// 44 and 1888 at 6 x 6, batch 125, 93 -> 26 us.
+constexpr int kPairRow(int BL) { return 32 * BL * 4 + 16; } // LDS bytes of a channel's pairs of pixels
+constexpr int red2_bytes(int BL, int KS) { return (KS - 1) * 2 * BL * 4 * 1024; }
+
+template <int BL, int KC, int GW, int KS> __global__ void __launch_bounds__(64 * KS, 2) conv_wave_dx2_kernel(GatherParams p)
+{
+    constexpr int KSTEPS = KC / 16, KCS = KC + 8, PT = 32 * BL;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    int bx, by, bz;
+    if (!conv_block(p, smem, bx, by, bz)) return;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3);
+    if (v >= p.tiles_per_img * p.mtiles) return;
+    const int mt = v / p.tiles_per_img, m0 = mt * 32, F = (v - mt * p.tiles_per_img) * PT;
+    const int ppi = p.Hc * p.Wc, nkb = p.nkb;
+    const int n0 = F / ppi, px0 = F - n0 * ppi, i0 = fdiv(px0, p.m_wc);
+    WaveStage<KC, 1, GW> in;
+    const uint32_t wbase = lds0 + ks * p.buf_bytes;
+    in.init(p, wbase, lds0 + KS * p.buf_bytes + threadIdx.x * 16, n0, i0);
+    const rsrc_t rs_w = make_rsrc(p.wt, (uint32_t)TAPS * p.Mp * p.KCp * 2u);
+    const uint32_t kstep = (p.Mp / 32) * kFrag, wlane = (uint32_t)mt * kFrag + lane * 16u;
+    // class 2 * a + b of a tap, and its shift of dY, 2 * (r == 0) + (s == 0)
+    constexpr auto cls = [](int t) { return 2 * (t / 3 != 1) + (t % 3 != 1); };
+    constexpr auto shift = [](int t) { return 2 * (t / 3 == 0) + (t % 3 == 0); };
+    f32x16 acc[4][BL];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int bl = 0; bl < BL; ++bl)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[c][bl][j] = 0.f;
+    u32x4 wr[TAPS];
+    if (ks < nkb) {
+        in.fetch(ks);
+#pragma unroll
+        for (int t = 0; t < TAPS; ++t) wr[t] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, p.wofs[t] + ks * KSTEPS * kstep, 0);
+    }
+    uint32_t pbase[BL];
+#pragma unroll
+    for (int bl = 0; bl < BL; ++bl) {
+        const int f = px0 + bl * 32 + l32;
+        const int gi = fdiv(f, p.m_ppi), px = f - gi * ppi, i = fdiv(px, p.m_wc), j = px - i * p.Wc;
+        pbase[bl] = wbase + 16u * half + (n0 + gi < p.N ? (uint32_t)(((gi * p.VH + i - i0) * p.PWd + j) * KCS * 2) : 0u);
+    }
+    in.clear(wbase, p.buf_bytes);
+    for (int s = ks; s < nkb; s += KS) {
+        in.put(s);
+        wave_sync();
+        in.fetch(s + KS); // (past the end: nothing is loaded)
+        uint32_t so = (uint32_t)s * KSTEPS * kstep;
+        opaque_s(so);
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            u32x4 bq[4][BL];
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int bl = 0; bl < BL; ++bl) bq[h][bl] = lds16(pbase[bl] + ((h >> 1) * p.PWd + (h & 1)) * (KCS * 2) + 32 * kk);
+            __builtin_amdgcn_sched_barrier(0);
+            const uint32_t so2 = so + (kk + 1 < KSTEPS ? kk + 1 : KS * KSTEPS) * kstep; // the next step's fragments (past the last: never used)
+#pragma unroll
+            for (int t = 0; t < TAPS; ++t) {
+#pragma unroll
+                for (int bl = 0; bl < BL; ++bl) {
+                    union { u32x4 u; bf16x8 v; } af, bf;
+                    af.u = wr[t];
+                    bf.u = bq[shift(t)][bl];
+                    acc[cls(t)][bl] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf.v, af.v, acc[cls(t)][bl], 0, 0, 0);
+                }
+                wr[t] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, p.wofs[t] + so2, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wave_sync();
+    }
+    // ---- the sums of the KS waves, the two classes of a row of dX at a time, as in the kernel above
+    constexpr int G = 2 * BL * 4, GK = G / KS;
+    static_assert(G % KS == 0, "");
+    const uint32_t out = lds0 + red2_bytes(BL, KS); // [channel][pixel][b], bfloat16
+    const rsrc_t rs_out = make_rsrc(p.out, (uint32_t)p.N * p.M * p.Hout * p.Wout * 2u);
+    __syncthreads(); // (all staging buffers are dead)
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) { // g = 2 * (4 * block + group of four pixels) + b
+            const int dst = g / GK;
+            const f32x16 &c = acc[2 * a + (g & 1)][g / 8];
+            const int jq = g / 2 % 4;
+            if (dst != ks)
+                *(lds_f32x4_ptr)(uintptr_t)(lds0 + (uint32_t)(((dst * (KS - 1) + (ks < dst ? ks : ks - 1)) * GK + g % GK) * 1024) + lane * 16) =
+                    f32x4{c[4 * jq], c[4 * jq + 1], c[4 * jq + 2], c[4 * jq + 3]};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            if (g / GK != ks) continue;
+            const f32x16 &c = acc[2 * a + (g & 1)][g / 8];
+            const int jq = g / 2 % 4;
+            f32x4 sum;
+#pragma unroll
+            for (int src = 0; src < KS; ++src) {
+                f32x4 t = f32x4{c[4 * jq], c[4 * jq + 1], c[4 * jq + 2], c[4 * jq + 3]};
+                if (src != ks) t = *(lds_f32x4_ptr)(uintptr_t)(lds0 + (uint32_t)(((ks * (KS - 1) + (src < ks ? src : src - 1)) * GK + g % GK) * 1024) + lane * 16);
+                if (src == 0) sum = t;
+                else sum += t;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *(lds_u16_ptr)(uintptr_t)(out + (uint32_t)(l32 * kPairRow(BL) + (g / 8 * 32 + 8 * jq + 4 * half + e) * 4 + (g & 1) * 2)) = f32_to_bf16(sum[e]);
+        }
+        __syncthreads();
+        // a lane per pixel of dY: its pair of dX
+        const int seg = threadIdx.x % PT, f = px0 + seg;
+        const int gi = fdiv(f, p.m_ppi), px = f - gi * ppi, i = fdiv(px, p.m_wc), j = px - i * p.Wc, n = n0 + gi, h = 2 * i + a;
+        const bool ok = (n < p.N) & (h < p.Hout);
+        const uint32_t base = ((uint32_t)(n * p.M + m0) * p.Hout + h) * p.Wout + 2 * j, step = (uint32_t)p.Hout * p.Wout;
+        constexpr int RPI = 64 * KS / PT; // rows at a time
+#pragma unroll
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int row = it * RPI + threadIdx.x / PT;
+            const uint32_t pair = *(lds_u32_ptr)(uintptr_t)(out + row * kPairRow(BL) + seg * 4);
+            const uint32_t off = ok && m0 + row < p.M ? (base + row * step) * 2u : kNoLoad;
+            if (p.Wout % 2 == 0) {
+                __builtin_amdgcn_raw_buffer_store_b32(pair, rs_out, off, 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)pair, rs_out, off, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(pair >> 16), rs_out, 2 * j + 1 < p.Wout ? off + 2 : kNoLoad, 0, 0);
+            }
+        }
+    }
+}
+
 template <int MI, int KC, int ITEMS, int GW, int KS> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
 {
     auto kern = conv_wave_kernel<MI, KC, ITEMS, GW, KS>;
@@ -271,6 +438,23 @@ template <int MI, int KC, int ITEMS, int KS> hipError_t launch_shape(const Gathe
     return p.gw == 8 ? launch_fixed<MI, KC, ITEMS, 8, KS>(p, st) : launch_fixed<MI, KC, ITEMS, 7, KS>(p, st);
 }
 
+template <int BL, int KC, int GW, int KS> hipError_t launch_dx2_fixed(const GatherParams &p, hipStream_t st)
+{
+    auto kern = conv_wave_dx2_kernel<BL, KC, GW, KS>;
+    static std::once_flag attr_once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
+    if (attr_err != hipSuccess) return attr_err;
+    GatherParams q = p;
+    const dim3 grid = share_grid(q, dim3((unsigned)((p.tiles_per_img * p.mtiles + 7) / 8 * 8)), 64 * KS);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * KS), p.lds_bytes, st, q);
+    return hipGetLastError();
+}
+template <int BL, int KC, int KS> hipError_t launch_dx2_shape(const GatherParams &p, hipStream_t st)
+{
+    return p.gw == 8 ? launch_dx2_fixed<BL, KC, 8, KS>(p, st) : launch_dx2_fixed<BL, KC, 7, KS>(p, st);
+}
+
 struct Shape { int mi, kc, items, ks; hipError_t (*launch)(const GatherParams &, hipStream_t); };
 const Shape kShapes[] = {
     {2, 32, 1, 4, launch_shape<2, 32, 1, 4>}, {2, 16, 1, 4, launch_shape<2, 16, 1, 4>}, {2, 16, 2, 4, launch_shape<2, 16, 2, 4>},
@@ -278,6 +462,32 @@ const Shape kShapes[] = {
     {2, 32, 1, 8, launch_shape<2, 32, 1, 8>}, {2, 16, 1, 8, launch_shape<2, 16, 1, 8>}, {2, 16, 2, 8, launch_shape<2, 16, 2, 8>},
     {1, 32, 1, 8, launch_shape<1, 32, 1, 8>}, {1, 16, 1, 8, launch_shape<1, 16, 1, 8>}, {1, 16, 2, 8, launch_shape<1, 16, 2, 8>},
 };
+
+struct Dx2Shape { int bl, kc, ks; hipError_t (*launch)(const GatherParams &, hipStream_t); };
+const Dx2Shape kDx2Shapes[] = {
+    {2, 32, 4, launch_dx2_shape<2, 32, 4>}, {2, 16, 4, launch_dx2_shape<2, 16, 4>}, {1, 32, 4, launch_dx2_shape<1, 32, 4>}, {1, 16, 4, launch_dx2_shape<1, 16, 4>},
+    {2, 32, 8, launch_dx2_shape<2, 32, 8>}, {2, 16, 8, launch_dx2_shape<2, 16, 8>}, {1, 32, 8, launch_dx2_shape<1, 32, 8>}, {1, 16, 8, launch_dx2_shape<1, 16, 8>},
+};
+
+// Rows and images that a tile of pt pixels can reach: it starts at a multiple of pt pixels, counted over all images.  tall: rows of the
+// input that an output row meets.  False where the kernels' divisions by multiplication would not be exact.
+bool span_of_tile(GatherParams &p, int pt, int tall)
+{
+    const int ppi = p.Hc * p.Wc;
+    const long tiles = ((long)p.N * ppi + pt - 1) / pt;
+    if (tiles > 1 << 24) return false;
+    const int gr = std::gcd(pt, p.Wc), gi = std::gcd(pt, ppi);
+    const int rows = (p.Wc - gr + pt - 1) / p.Wc + 1, cross = (ppi - gi + pt - 1) / ppi;
+    p.VH = (p.Hc - 1) * p.is + tall;
+    p.PH = (rows - 1 - min(cross, rows - 1)) * p.is + cross * tall + tall;
+    p.IR = min((rows - 1) * p.is + cross * max(0, p.Hin - p.Hc * p.is) + tall, (cross + 1) * p.Hin);
+    p.tiles_per_img = (int)tiles;
+    p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(ppi); p.m_ph = magic_of(p.Hin);
+    p.gw = p.Win % 2 ? 7 : 8;
+    p.GX = (p.Win + p.gw - 1) / p.gw;
+    p.m_gx = magic_of(p.GX);
+    return divides_exactly(ppi + pt, ppi) && divides_exactly(ppi, p.Wc) && divides_exactly(p.Hin + p.IR, p.Hin);
+}
 
 } // namespace
 
@@ -295,21 +505,9 @@ bool shape_wave(GatherParams &p, int *variant, double *cost_out)
     }
     const int ppi = p.Hc * p.Wc, tall = dhmax - b.dhmin + 1;
     b.PWd = (p.Wc - 1) * p.is + (dwmax - b.dwmin) + 1;
-    b.VH = (p.Hc - 1) * p.is + tall;
     b.ksplit = 1; b.T = 1; b.part = nullptr; b.gpw = 1; b.IPT = 1;
-    const long tiles = ((long)p.N * ppi + PT - 1) / PT;
-    if (tiles > 1 << 24) return false;
-    // Rows and images that 64 pixels can reach: a tile starts at a multiple of 64 pixels, counted over all images.
-    const int gr = std::gcd(PT, p.Wc), gi = std::gcd(PT, ppi);
-    const int rows = (p.Wc - gr + PT - 1) / p.Wc + 1, cross = (ppi - gi + PT - 1) / ppi;
-    b.PH = (rows - 1 - min(cross, rows - 1)) * p.is + cross * tall + tall;
-    b.IR = min((rows - 1) * p.is + cross * max(0, p.Hin - p.Hc * p.is) + tall, (cross + 1) * p.Hin);
-    b.tiles_per_img = (int)tiles;
-    if (!divides_exactly(ppi + PT, ppi) || !divides_exactly(ppi, p.Wc) || !divides_exactly(p.Hin + b.IR, p.Hin)) return false;
-    b.m_wc = magic_of(p.Wc); b.m_ppi = magic_of(ppi); b.m_ph = magic_of(p.Hin);
-    b.gw = p.Win % 2 ? 7 : 8;
-    b.GX = (p.Win + b.gw - 1) / b.gw;
-    b.m_gx = magic_of(b.GX);
+    if (!span_of_tile(b, PT, tall)) return false;
+    const long tiles = b.tiles_per_img;
     b.store_px = ppi % 8 == 0 ? 8 : ppi % 4 == 0 ? 4 : ppi % 2 == 0 ? 2 : 1;
     int force = -1;
 #ifdef CAC_TUNING
@@ -350,6 +548,63 @@ bool shape_wave(GatherParams &p, int *variant, double *cost_out)
     p = best;
     *cost_out = best_cost;
     return true;
+}
+
+// ... of the 3 x 3 stride-2 data gradient with padding 1.  p: N, M (= C_in), Mp, KCin (= C_out), Hin, Win (of dY), Hout, Wout (of dX) are filled in.
+bool shape_wave_dx2(const Geom &g, GatherParams &p, int *variant, double *cost_out)
+{
+    if (g.R != 3 || g.S != 3 || g.sh != 2 || g.sw != 2 || g.ph != 1 || g.pw != 1) return false;
+    GatherParams b = p;
+    b.Hc = g.P; b.Wc = g.Q;
+    b.dhmin = b.dwmin = 0;
+    b.PWd = g.Q + 1;
+    b.os = 2; b.is = 1; b.ntaps = b.ntaps_total = TAPS;
+    b.ksplit = 1; b.T = 1; b.part = nullptr; b.gpw = 1; b.IPT = 1;
+    int force = -1;
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_WAVE_DX2_SHAPE")) force = atoi(f);
+#endif
+    GatherParams best{};
+    double best_cost = 1e300;
+    for (int v = 0; v < (int)(sizeof(kDx2Shapes) / sizeof(kDx2Shapes[0])); ++v) {
+        const Dx2Shape &sh = kDx2Shapes[v];
+        if (force >= 0 && v != force) continue;
+        GatherParams q = b;
+        if (!span_of_tile(q, 32 * sh.bl, 2) || q.IR * q.GX * (sh.kc / 8) > 64) continue;
+        const int kcs = sh.kc + 8;
+        q.patch_px = q.PH * q.PWd;
+        q.buf_bytes = (q.patch_px * kcs * 2 + 15) / 16 * 16;
+        q.lds_bytes = max(sh.ks * (q.buf_bytes + 64 * 16), red2_bytes(sh.bl, sh.ks) + 32 * kPairRow(sh.bl));
+        if (q.lds_bytes > 160 * 1024) continue;
+        q.KCp = (p.KCin + sh.kc - 1) / sh.kc * sh.kc;
+        q.nkb = q.KCp / sh.kc;
+        q.kbs = (q.nkb + sh.ks - 1) / sh.ks;
+        q.mtiles = (p.M + 31) / 32;
+        for (int t = 0; t < TAPS; ++t) q.wofs[t] = (uint32_t)t * (q.KCp / 16) * (q.Mp / 32) * kFrag;
+        const int resident = min(8 / sh.ks, 160 * 1024 / q.lds_bytes);
+        const long wgs = (long)q.tiles_per_img * q.mtiles, rounds = (wgs + 256L * resident - 1) / (256L * resident);
+        const double busy = (double)min((long)resident * sh.ks, ((wgs + 255) / 256) * sh.ks) / 4;
+        const double step = max(TAPS * 32.0 * sh.bl * max(1.0, busy), 800.0); // of 16 channels
+        const double cost = rounds * (q.kbs * ((sh.kc / 16) * step + 800.0) + 6500.0 + (sh.ks == 8 ? 800.0 : 0.0));
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = q;
+            *variant = v;
+        }
+    }
+    if (best_cost > 1e299) return false;
+    p = best;
+    *cost_out = best_cost;
+    return true;
+}
+
+hipError_t launch_wave_dx2(const GatherParams &p, int variant, hipStream_t st) { return kDx2Shapes[variant].launch(p, st); }
+
+int describe_wave_dx2(const GatherParams &p, int variant, char *buf, size_t len)
+{
+    const Dx2Shape &v = kDx2Shapes[variant];
+    return snprintf(buf, len, "tile=32ch x 4 x %dpx by waves (four parity classes, %d share the channels, stages of %d) taps=9 rows/tile=%d grid=%dx%dx1 lds=%dB",
+                    32 * v.bl, v.ks, v.kc, p.IR, p.tiles_per_img, p.mtiles, p.lds_bytes);
 }
 
 hipError_t launch_wave(const GatherParams &p, int variant, hipStream_t st) { return kShapes[variant].launch(p, st); }

@@ -19,8 +19,9 @@ CASES = [
     ("gather in place", 16, 32, 32, 16, 16, 3, 1, (ROOM, SUM)),
     ("gather, channels-last copy by elements", 24, 45, 39, 7, 9, 3, 1, (ROOM, SUM)),
     ("gather, channels-last copy in blocks", 6, 70, 37, 6, 6, 3, 1, (ROOM,)),
-    ("gather, four classes", 19, 40, 48, 9, 11, 3, 2, (ROOM, SUM)),
-    ("four parity classes", 19, 40, 48, 10, 12, 3, 2, (ROOM, SUM)),
+    ("by waves, four classes", 19, 40, 48, 9, 11, 3, 2, (ROOM, SUM)),
+    ("four parity classes", 30, 64, 32, 16, 24, 3, 2, (ROOM, SUM)),
+    ("gather, four classes", 2, 40, 48, 9, 149, 3, 2, (ROOM, SUM)),
     ("pixels to clear", 30, 40, 48, 10, 11, 1, 2, (ROOM, SUM)),
     ("pointwise", 40, 40, 24, 24, 20, 1, 1, (ROOM, SUM)),
     ("pointwise by waves", 40, 40, 300, 7, 7, 1, 1, (ROOM, SUM)),

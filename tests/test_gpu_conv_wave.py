@@ -27,9 +27,13 @@ CASES = [
     ("two items to a lane, odd rows", 3, 300, 64, 9, 55, 3, 3, 1, 1, 1, True, True),
     ("eight waves, one tile", 1, 1000, 16, 5, 5, 3, 3, 1, 1, 1, True, False),
     ("eight waves, 32 channels", 2, 24, 700, 9, 9, 3, 3, 1, 1, 1, True, True),
-    ("stride 2", 16, 72, 160, 28, 28, 3, 3, 1, 1, 2, True, False),
-    ("stride 2, odd extents", 17, 90, 193, 15, 27, 3, 3, 1, 1, 2, True, False),
-    ("stride 2, maps of 4 pixels", 8, 464, 64, 4, 5, 3, 3, 1, 1, 2, True, False),
+    ("stride 2", 16, 72, 160, 28, 28, 3, 3, 1, 1, 2, True, True),
+    ("stride 2, odd extents", 17, 90, 193, 15, 27, 3, 3, 1, 1, 2, True, True),
+    ("stride 2, maps of 4 pixels", 8, 464, 64, 4, 5, 3, 3, 1, 1, 2, True, True),
+    ("stride 2, one pixel", 5, 40, 70, 1, 1, 3, 3, 1, 1, 2, False, True),
+    ("stride 2, last stage partial, M tail", 9, 69, 300, 14, 14, 3, 3, 1, 1, 2, True, True),
+    ("stride 2, odd rows of dY, even of dX", 33, 24, 97, 11, 18, 3, 3, 1, 1, 2, True, True),
+    ("stride 2, even rows of dY, odd of dX", 3, 33, 1000, 12, 15, 3, 3, 1, 1, 2, True, True),
     ("no padding", 12, 80, 72, 9, 10, 3, 3, 0, 0, 1, True, True),
     ("padding 2", 12, 80, 72, 9, 10, 3, 3, 2, 2, 1, True, True),
     ("padding 3 and 1", 12, 81, 72, 8, 11, 3, 3, 3, 1, 1, True, True),
@@ -65,3 +69,28 @@ def test_forward_and_data_gradient(case):
         for n in range(N):
             err = np.linalg.norm(got[n] - want[n]) / np.linalg.norm(want[n])
             assert err <= TOL, (name, n, err)
+
+
+# Layers beside the line that keep the stages shared (csrc/conv_dx2.hip): 16-byte and dword stores, a tile ending inside a block.
+SHARED = [("16-byte stores", 30, 64, 32, 16, 24), ("tile ends inside a block", 24, 130, 40, 30, 28), ("odd number of dY elements", 135, 33, 31, 13, 14)]
+
+
+@pytest.mark.parametrize("case", SHARED, ids=[c[0] for c in SHARED])
+def test_stride_2_data_gradient_with_shared_stages(case):
+    import torch
+    from gpu_util import Guarded, download, upload, workspace
+    name, N, C, K, H, W = case
+    d = B.make_desc(N, C, K, H, W, 3, 3, 2, 2, 1, 1)
+    plan = B.cac_describe_plan(d, B.OP_BWD_DATA)
+    assert "four parity classes" in plan and "by waves" not in plan, plan
+    P, Q = B.cac_out_shape(d)
+    rng = np.random.default_rng(N)
+    Wt, dY = (synth.to_storage(rng.standard_normal(s, dtype=np.float32), synth.BF16) for s in ((K, C, 3, 3), (N, K, P, Q)))
+    dX = Guarded((N, C, H, W), torch.bfloat16)
+    B.conv_bwd_data(d, upload(Wt, synth.BF16), upload(dY, synth.BF16), dX.t, workspace(d, B.OP_BWD_DATA))
+    torch.cuda.synchronize()
+    dX.check("dX")
+    want = oracle.conv_dx(oracle.ConvGeom(N, C, K, H, W, 3, 3, 2, 2, 1, 1), Wt.astype(np.float64), dY.astype(np.float64))
+    got = download(dX.t)
+    for n in range(N):
+        assert np.linalg.norm(got[n] - want[n]) <= TOL * np.linalg.norm(want[n]), (name, n)
