@@ -69,7 +69,8 @@ __device__ __forceinline__ u32x4 lds16(uint32_t addr) { return *(lds_u32x4_ptr)(
 
 // 16-byte items of dY and of Z a thread moves per chunk, at most (every chunk issues so many loads, wanted or not).
 // Uncompressed records of 3 x 3 stride-2 layers (pooling tiles of one column) hold many Z items to every dY item: with the
-// split of the others a chunk is one output row on wide maps, half of a row pair left empty.  WIDEZ 1 and 2 are the other splits:
+// split of the others a chunk is one output row on wide maps, half of a row pair left empty; under stride 1 they hold two rows more
+// than a chunk has of dY.  WIDEZ 1 and 2 are the other splits:
 // longer chunks, but a workgroup waits for more before its first; dw_mfma_plan draws the lines.
 constexpr int max_dy(int widez) { return 8 >> widez; }
 constexpr int max_z(int widez) { return 4 << widez; }
@@ -116,24 +117,27 @@ template <int NB, int SG, int PAD, int s> __device__ __forceinline__ bf16x8 make
 // smaller than 2 GiB; offsets from 2^31 on mean "no load").
 // Items are read with one 16-byte load each from the dword-aligned address at or below
 // their first element (rows of odd length start on odd elements).
-// The 8 elements themselves.  After an odd start everything moves down by one
+// The 8 elements themselves, of items `d` at elements e, e + step, ...  After an odd start everything moves down by one
 // element and the last one comes from the first dword of the next item of the
 // same row, which the next lane holds (the copy maps consecutive items of a row
 // to consecutive lanes; the last item of a row never needs it: a row of odd
-// length ends before its 8th element).  Then ANDed with `mask`: zero from the
+// length ends before its 8th element; `multi`: a row has several).  Then ANDed with `mask`: zero from the
 // row's end on, what follows belongs to another row.
-__device__ __forceinline__ u32x4 fix8(const u32x4 &d, uint32_t e, const u32x4 &mask, bool odd_possible)
+template <int N> __device__ __forceinline__ void fix8(u32x4 (&v)[N], const u32x4 (&d)[N], uint32_t e, uint32_t step, const u32x4 &mask, bool multi)
 {
-    u32x4 v = d;
-    if (odd_possible) {
-        const uint32_t next0 = __shfl_down(d[0], 1, 64);
-        const uint32_t sh = (e & 1u) * 16u;
-        v[0] = __builtin_amdgcn_alignbit(d[1], d[0], sh);
-        v[1] = __builtin_amdgcn_alignbit(d[2], d[1], sh);
-        v[2] = __builtin_amdgcn_alignbit(d[3], d[2], sh);
-        v[3] = __builtin_amdgcn_alignbit(next0, d[3], sh);
+    uint32_t next0[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) next0[i] = d[i][0];
+    if (multi) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) next0[i] = __shfl_down(d[i][0], 1, 64);
     }
-    return v & mask;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t sh = ((e + i * step) & 1u) * 16u;
+        v[i] = u32x4{__builtin_amdgcn_alignbit(d[i][1], d[i][0], sh), __builtin_amdgcn_alignbit(d[i][2], d[i][1], sh),
+                     __builtin_amdgcn_alignbit(d[i][3], d[i][2], sh), __builtin_amdgcn_alignbit(next0[i], d[i][3], sh)} & mask;
+    }
 }
 // Dword j of the mask keeps the elements 2j, 2j+1 that lie below `left`.
 __device__ __forceinline__ u32x4 mask8(int left)
@@ -147,12 +151,11 @@ __device__ __forceinline__ u32x4 mask8(int left)
     return m;
 }
 
-// FL: log2 of the columns of one phase that a pooled value covers (-1: half a column, an uncompressed record under stride
-// 2), built into the 3 x 3 stride-2 kernels; kAnyFl: read from the plan.  With all forms of the expansion in one kernel
-// the copy waves of two phases spilled 158 registers (WIDEZ: 233) to scratch, more traffic than the operands: 128 -> 256 at
-// 28 x 28, batch 128, uncompressed 61 -> 42 us; 150 random layers, tiles of 1, 2 and 4, 0.72 of the time, none slower.
-constexpr int kAnyFl = -2;
-
+// FL: log2 of the columns of one phase that a pooled value covers; -1: half a column, an uncompressed record under stride
+// 2.  Built in: with all forms of the expansion in one kernel the copy waves of two phases spilled 158 registers (WIDEZ: 233) to
+// scratch, more traffic than the operands -- 128 -> 256 at 28 x 28, batch 128, uncompressed 61 -> 42 us; 150 random layers, tiles of 1, 2
+// and 4, 0.72 of the time, none slower --, and those of one phase went through 70 KB of code, more than the instruction cache
+// holds (250 random 3 x 3 stride-1 layers, uncompressed: 0.92 of the time, none slower).
 // SC: the number of 8-pixel segments per output row when it is known at compile
 // time (0: read from the plan).  With SC the walk along a row is unrolled and the
 // segment offsets become immediates of the LDS reads.
@@ -173,6 +176,8 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     // [zero row][buffer 0: rows, sDY, sX][buffer 1: rows, sDY, sX]; offsets below are in
     // bf16 elements from the start of LDS, so offset 0 is the zero row
     bf16_t *sW = (bf16_t *)smem;
+    // Every cache line of the arguments is asked for here, in one go (each would be a round trip of its own where it is first needed).
+    asm volatile("" ::"s"(p.own_wgs), "s"(p.NBI), "s"(p.LDY), "s"(p.nchunks));
     const uint32_t rows_elems = p.LRpad * 8;                   // one 16-byte entry per row
     const uint32_t buf_elems = rows_elems + TILE_O * p.dy_ostride + TILE_C * p.x_cstride;
     const uint32_t slot_w = NPH * p.PW;                        // one xhat row: all phases
@@ -219,7 +224,9 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     if (wave_id >= NT / 64) {
         // =========================== copy waves ===========================================
         // They keep two chunks of global loads in flight and fill the LDS buffer the
-        // MFMA waves are not reading; the only hand-over is one barrier per chunk.
+        // MFMA waves are not reading; the only hand-over is one barrier per chunk.  Where a chunk has less than 3500 cycles of
+        // MFMAs these waves bound it, not by waiting for memory (100 cycles) but by what they issue: 1100-1900 cycles for dY, 1000-1500
+        // for Z, 800 for the loads, which the address unit takes at 64 bytes a cycle.
         const int tid = threadIdx.x - NT;
         // dY: LDY lanes share one output channel's rows; item j = (row rho, segment sg)
         const uint32_t dyj = tid & (p.LDY - 1), dyo = tid >> p.ldy_log2;
@@ -244,7 +251,6 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
         const uint32_t z_lds = rows_elems + TILE_O * p.dy_ostride + zc * p.x_cstride + z_row * slot_w;
         const uint32_t z_lstep = z_cpp * p.x_cstride;
         const bool dy_odd = p.Q & 1, z_odd = p.Wp & 1;
-        const int f_log2 = FL != kAnyFl ? FL : p.kw_log2 - (SG == 2 ? 1 : 0); // columns of one phase per pooled value, log2
         const bool ragged = (p.W & ((1 << p.kw_log2) - 1)) != 0; // the last pooling tile reaches past W
         const rsrc_t rs_dy = make_rsrc(p.dY, (uint32_t)p.N * p.K * p.P * p.Q * 2u);
         const rsrc_t rs_z = make_rsrc(p.Z, (uint32_t)p.N * p.C * p.Hp * p.Wp * 2u);
@@ -327,8 +333,10 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
             __builtin_amdgcn_s_waitcnt((kYounger & 0xF) | ((kYounger >> 4) << 14) | 0x0F70);
             const Src s = src_of(ci);
             // row table: entry rho = {dY row offset, xhat row offset per filter row (the zero
-            // slot for rows outside the image)}, in elements from the lane's channel base
-            if (cw == 0 && tid < p.LRpad) {
+            // slot for rows outside the image)}, in elements from the lane's channel base.  Chunks of whole images
+            // have the same one but for the last (400 cycles of the 3500 that a chunk takes this wave, which is behind the others by them)
+            const bool same = p.RB == 1 && ci >= ci_begin + 2 && s.n0 + p.NBI <= p.N;
+            if (cw == 0 && !same && tid < p.LRpad) {
                 const uint32_t rho = tid;
                 const uint32_t ni = fdiv(rho, p.m_pr);
                 const int pp = s.p0 + (int)(rho - ni * p.PR);
@@ -348,8 +356,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
             u32x4 val[kMaxDy];
             if constexpr (DYL) {
             } else if (dy_odd) {
-#pragma unroll
-                for (int i = 0; i < kMaxDy; ++i) val[i] = fix8(rdy[i], s.dy + dy_rel + i * dy_istep, dy_mask, true);
+                fix8(val, rdy, s.dy + dy_rel, dy_istep, dy_mask, p.SEGS > 1);
             } else {
 #pragma unroll
                 for (int i = 0; i < kMaxDy; ++i) val[i] = rdy[i] & dy_mask;
@@ -363,8 +370,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
             // Z
             u32x4 zz[kMaxZ];
             if (z_odd) {
-#pragma unroll
-                for (int i = 0; i < kMaxZ; ++i) zz[i] = fix8(rz[i], s.z + z_rel + i * z_istep, z_mask, true);
+                fix8(zz, rz, s.z + z_rel, z_istep, z_mask, p.ZV > 1);
             } else {
 #pragma unroll
                 for (int i = 0; i < kMaxZ; ++i) zz[i] = rz[i] & z_mask;
@@ -387,7 +393,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
         (void)dup;                                                                                 \
         __VA_ARGS__                                                                                \
     }
-                if (f_log2 < 0) {
+                if constexpr (FL < 0) {
                     // kw = 1, stride 2: even columns to phase 0, odd ones to phase 1
                     // (zeros past W come from the load)
                     const int j0 = z_zv * 4;
@@ -395,13 +401,13 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
                         *(u32x2 *)(dst + j0) = u32x2{halves<0, 0>(z[0], z[1]), halves<0, 0>(z[2], z[3])};
                         if (NPH > 1) *(u32x2 *)(dst + p.PW + j0) = u32x2{halves<1, 1>(z[0], z[1]), halves<1, 1>(z[2], z[3])};
                     })
-                } else if (f_log2 == 0) {
+                } else if constexpr (FL == 0) {
                     const int j0 = z_zv * 8;
                     CAC_Z_ITEMS({
                         _Pragma("unroll") for (int ph = 0; ph < NPH; ++ph)
                             *(u32x4 *)(dst + ph * p.PW + j0) = ragged ? z & rag[ph][0] : z;
                     })
-                } else if (f_log2 == 1) {
+                } else if constexpr (FL == 1) {
                     const int j0 = z_zv * 16;
                     CAC_Z_ITEMS({
                         const u32x4 lo = {dup(0), dup(1), dup(2), dup(3)}, hi = {dup(4), dup(5), dup(6), dup(7)};
@@ -410,7 +416,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
                             *(u32x4 *)(dst + ph * p.PW + j0 + 8) = ragged ? hi & rag[ph][1] : hi;
                         }
                     })
-                } else if (f_log2 == 2) {
+                } else if constexpr (FL == 2) {
                     const int j0 = z_zv * 32;
                     CAC_Z_ITEMS({
                         _Pragma("unroll") for (int g = 0; g < 4; ++g) {
@@ -438,38 +444,34 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
         fetch(ci_begin, true, dyA, zA); // (every workgroup has at least one chunk)
         fetch(ci_begin + 1, ci_begin + 1 < ci_end, dyB, zB);
         // what only the staging needs: the masks that cut an item at the end of its row, and,
-        // for the ragged case, the two blocks an item expands to when f_log2 <= 1
+        // for the ragged case, the two blocks an item expands to when FL <= 1
         dy_mask = mask8(p.Q - (int)dy_sg * 8);
         z_mask = mask8(p.Wp - (int)z_zv * 8);
 #pragma unroll
         for (int ph = 0; ph < 2; ++ph)
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                rag[ph][h] = mask8((p.W - ph + SG - 1) / SG - (int)(z_zv << (3 + max(f_log2, 0))) - 8 * h);
+                rag[ph][h] = mask8((p.W - ph + SG - 1) / SG - (int)(z_zv << (3 + max(FL, 0))) - 8 * h);
         if constexpr (DYL) load_dy(ci_begin, true, base0);
         zero_fill(); // in the shadow of the first loads
         __syncthreads();
-        stage(ci_begin, base0, dyA, zA);
-        fetch(ci_begin + 2, ci_begin + 2 < ci_end, dyA, zA);
-        if constexpr (DYL) dy_landed();
-        __syncthreads(); // buffer 0 holds the first chunk
-        for (int ci = ci_begin; ci < ci_end; ci += 2) {
-            // MFMA waves are on buffer 0 (chunk ci); set B holds chunk ci+1, set A chunk ci+2.
-            // (A chunk past the end is staged all the same -- zeros into a buffer nobody reads
-            // any more -- so that every path consumes every load.)
-            if constexpr (DYL) load_dy(ci + 1, ci + 1 < ci_end, base1); // (buffer 1 is free since the last barrier)
+        for (int ci = ci_begin;; ci += 2) {
+            // MFMA waves are on buffer 1 (chunk ci-1); set A holds chunk ci, set B chunk ci+1
+            if (DYL && ci != ci_begin) load_dy(ci, true, base0); // (buffer 0 is free since the last barrier)
+            stage(ci, base0, dyA, zA);
+            fetch(ci + 2, ci + 2 < ci_end, dyA, zA);
+            if constexpr (DYL) dy_landed();
+            __syncthreads();
+            if (ci + 1 >= ci_end) break;
+            // MFMA waves are on buffer 0 (chunk ci); set B holds chunk ci+1, set A chunk ci+2
+            if constexpr (DYL) load_dy(ci + 1, true, base1);
             stage(ci + 1, base1, dyB, zB);
             fetch(ci + 3, ci + 3 < ci_end, dyB, zB);
             if constexpr (DYL) dy_landed();
             __syncthreads();
-            if (ci + 1 >= ci_end) break;
-            // MFMA waves are on buffer 1 (chunk ci+1); set A holds chunk ci+2, set B chunk ci+3
-            if constexpr (DYL) load_dy(ci + 2, ci + 2 < ci_end, base0);
-            stage(ci + 2, base0, dyA, zA);
-            fetch(ci + 4, ci + 4 < ci_end, dyA, zA);
-            if constexpr (DYL) dy_landed();
-            __syncthreads();
+            if (ci + 2 >= ci_end) break;
         }
+        __syncthreads(); // the MFMA waves' last chunk
         if constexpr (KS > 1) __syncthreads(); // the barrier inside the MFMA waves' cross-wave sum
         return;
     }
@@ -755,12 +757,11 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     };
 
     __syncthreads(); // buffer 0 holds the first chunk
-    for (int ci = ci_begin; ci < ci_end; ci += 2) {
-        compute(base0);
+    uint32_t base = base0;
+    for (int ci = ci_begin; ci < ci_end; ++ci) {
+        compute(base);
         __syncthreads();
-        if (ci + 1 >= ci_end) break;
-        compute(base1);
-        __syncthreads();
+        base = base0 + base1 - base;
     }
 
     // ---- epilogue --------------------------------------------------------------------
@@ -770,10 +771,11 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     typedef f32x4 __attribute__((aligned(4))) f32x4_u;
     constexpr int G = MI * NI * T * 4;
     static_assert(KS == 1 || KS == 2 || KS == 4, "the K-split waves share the four row groups");
-    // The KS waves of a tile hold sums over different pixels.  Wave ks keeps the groups with
-    // j/4 in [ks*4/KS, (ks+1)*4/KS) and hands the others over through LDS (the staging buffers
-    // are dead: the loop above ends with a barrier), then adds what the other waves hand it, in
-    // wave order.  red[wm, wn][source wave][g][lane].
+    static_assert(KS == 1 || T != 9 || MI * NI * (4 / KS) == 1, "a wave's groups are read before their place is used again");
+    // The KS waves of a tile hold sums over different pixels.  They all leave them in LDS (the staging buffers
+    // are dead: the loop above ends with a barrier), and wave ks adds up the groups with j/4 in [ks*4/KS, (ks+1)*4/KS): its own, then
+    // the other waves', in wave order.  red[wm, wn][source wave][g][lane].  (Its own it could keep in registers, but which ones they
+    // are depends on the wave: KS copies of all that follows, and the code of a kernel that goes through it once comes from memory.)
     f32x4 *red = (f32x4 *)smem + ((wn * WM + wm) * KS) * (G * 64) + lane;
 #define CAC_G(mi, ni, t, jq) ((jq) * (G / 4) + ((mi) * NI + (ni)) * T + (t))
 #define CAC_GROUP(mi, ni, t, jq) \
@@ -786,8 +788,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
 #pragma unroll
                 for (int t = 0; t < T; ++t)
 #pragma unroll
-                    for (int jq = 0; jq < 4; ++jq)
-                        if (jq * KS / 4 != ks) red[(ks * G + CAC_G(mi, ni, t, jq)) * 64] = CAC_GROUP(mi, ni, t, jq);
+                    for (int jq = 0; jq < 4; ++jq) red[(ks * G + CAC_G(mi, ni, t, jq)) * 64] = CAC_GROUP(mi, ni, t, jq);
         __syncthreads();
     }
     // Output: dW itself (one slice), or this slice's partial sums in the workspace, in the same
@@ -799,7 +800,7 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
     // a wave-private 9 KB of LDS, [row][c][tap], and leaves as 16-byte stores in which the lanes
     // of a wave cover whole runs (a lane's own 36-byte runs, unaligned and 36 bytes apart, cost
     // the store unit 1.5 us per group).  The 9 KB: with the pixels split over the waves, the part
-    // of `red` reserved for the groups the wave keeps from itself, which nobody writes or reads;
+    // of `red` that holds the wave's share of its own groups, which it has read by then and nobody else reads;
     // otherwise the dead staging buffers.
     const bool runs16 = T == 9 && inside && (p.C & 3) == 0;
     float *tb = KS > 1 ? (float *)((f32x4 *)smem + (((wn * WM + wm) * KS + ks) * G + (ks * 4 / KS) * (G / 4)) * 64)
@@ -809,16 +810,17 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-            for (int jq = 0; jq < 4; ++jq) {
-                if (KS > 1 && jq * KS / 4 != ks) continue;
+            for (int jw = 0; jw < 4 / KS; ++jw) {
+                const int jq = KS > 1 ? ks * (4 / KS) + jw : jw;
                 f32x4 v[T];
 #pragma unroll
                 for (int t = 0; t < T; ++t) {
-                    v[t] = CAC_GROUP(mi, ni, t, jq);
-                    if constexpr (KS > 1) {
+                    if constexpr (KS == 1) {
+                        v[t] = CAC_GROUP(mi, ni, t, jw);
+                    } else {
+                        v[t] = red[(ks * G + CAC_G(mi, ni, t, jq)) * 64];
 #pragma unroll
-                        for (int k2 = 0; k2 < KS; ++k2)
-                            if (k2 != ks) v[t] += red[(k2 * G + CAC_G(mi, ni, t, jq)) * 64];
+                        for (int k2 = 0; k2 < KS - 1; ++k2) v[t] += red[((k2 + (k2 >= ks)) * G + CAC_G(mi, ni, t, jq)) * 64];
                     }
                 }
                 if (T == 9 && runs16) {
@@ -877,7 +879,7 @@ struct Variant {
     hipError_t (*launch)(const DwMfmaParams &, const RepackParams &, dim3, hipStream_t);
 };
 
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL = false, int WIDEZ = 0, int FL = kAnyFl>
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int SC, bool DYL, int WIDEZ, int FL>
 hipError_t launch_fixed(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
 {
     auto kern = dw_mfma_kernel<R, S, SG, PAD, MI, NI, WM, WN, KS, SC, DYL, WIDEZ, FL>;
@@ -889,40 +891,54 @@ hipError_t launch_fixed(const DwMfmaParams &p, const RepackParams &rep, dim3 gri
     hipLaunchKernelGGL(kern, grid, dim3(128 * WM * WN * KS), p.lds_bytes, st, p, rep);
     return hipGetLastError();
 }
-// Picks the instantiation with the row length built in when there is one.
-template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS>
-hipError_t launch_variant(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
+// Picks the instantiation with the width of a pooling tile and, where there is one, the row length built in.
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS, int FL>
+hipError_t launch_width(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
 {
-    if constexpr (S == 3 && SG == 1 && KS == 4) {
-        if (p.dy_direct) {
-            switch (p.SEGS) {
-            case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, true>(p, rep, grid, st);
-            case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, true>(p, rep, grid, st);
-            case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, true>(p, rep, grid, st);
-            default: break;
+    if constexpr (S == 3 && SG == 1) {
+        if constexpr (KS == 4) {
+            if (p.dy_direct) {
+                switch (p.SEGS) {
+                case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, true, 0, FL>(p, rep, grid, st);
+                case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, true, 0, FL>(p, rep, grid, st);
+                case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, true, 0, FL>(p, rep, grid, st);
+                default: break;
+                }
             }
         }
-    }
-    if constexpr (S == 3 && SG == 1) {
+        if constexpr (FL == 0) {
+            if (p.widez) {
+                switch (p.SEGS) {
+                case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, false, 1, FL>(p, rep, grid, st);
+                case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, false, 1, FL>(p, rep, grid, st);
+                case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, false, 1, FL>(p, rep, grid, st);
+                case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7, false, 1, FL>(p, rep, grid, st);
+                default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, FL>(p, rep, grid, st);
+                }
+            }
+        }
         switch (p.SEGS) {
-        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1>(p, rep, grid, st);
-        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2>(p, rep, grid, st);
-        case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4>(p, rep, grid, st);
-        case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7>(p, rep, grid, st);
+        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 1, false, 0, FL>(p, rep, grid, st);
+        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 2, false, 0, FL>(p, rep, grid, st);
+        case 4: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 4, false, 0, FL>(p, rep, grid, st);
+        case 7: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 7, false, 0, FL>(p, rep, grid, st);
         default: break;
         }
     }
-    if constexpr (S == 3 && SG == 2) {
-        if (p.widez == 2) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 2, -1>(p, rep, grid, st);
-        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, -1>(p, rep, grid, st);
-        switch (p.kw_log2) {
-        case 0: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, -1>(p, rep, grid, st);
-        case 1: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 0>(p, rep, grid, st);
-        case 2: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 1>(p, rep, grid, st);
-        default: return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, 2>(p, rep, grid, st);
-        }
-    } else {
-        return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0>(p, rep, grid, st);
+    if constexpr (S == 3 && SG == 2 && FL < 0) {
+        if (p.widez == 2) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 2, FL>(p, rep, grid, st);
+        if (p.widez) return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 1, FL>(p, rep, grid, st);
+    }
+    return launch_fixed<R, S, SG, PAD, MI, NI, WM, WN, KS, 0, false, 0, FL>(p, rep, grid, st);
+}
+template <int R, int S, int SG, int PAD, int MI, int NI, int WM, int WN, int KS>
+hipError_t launch_variant(const DwMfmaParams &p, const RepackParams &rep, dim3 grid, hipStream_t st)
+{
+    switch (p.kw_log2) {
+    case 0: return launch_width<R, S, SG, PAD, MI, NI, WM, WN, KS, 1 - SG>(p, rep, grid, st);
+    case 1: return launch_width<R, S, SG, PAD, MI, NI, WM, WN, KS, 2 - SG>(p, rep, grid, st);
+    case 2: return launch_width<R, S, SG, PAD, MI, NI, WM, WN, KS, 3 - SG>(p, rep, grid, st);
+    default: return launch_width<R, S, SG, PAD, MI, NI, WM, WN, KS, 4 - SG>(p, rep, grid, st);
     }
 }
 
@@ -1114,13 +1130,28 @@ bool dw_mfma_plan(const Geom &g, int dtype, DwMfmaPlan *plan)
     // has many (64 -> 128 at 56 x 56, batch 128: 50.3 -> 43.6; 224 -> 272 at 36 x 53, batch 97: 213 -> 163; a fifth fewer chunks 120 -> 140;
     // few chunks up to 1.3 times the time).  Where only a split fits -- long rows -- the kernel of dw_tiled.hip is the other choice:
     // four times as slow in the mean, but 12.4 against 19.3 us for 9 -> 9 at 82 x 82, batch 1.
-    const bool may_widen = f3 && g.sh == 2 && g.kw == 1;
+    //
+    // Under stride 1 a chunk of output rows needs two Z rows more than it has, and the usual split leaves half its loads of dY
+    // empty.  The first split is taken where it saves a quarter of the chunks, those of every tile counted: 102 of 400 random layers,
+    // 0.60 of the time, the worst 0.98 (112 -> 112 at 56 x 56, batch 93: 175 -> 83 us); up to a quarter fewer 0.94 and at most
+    // 1.13, more chunks 1.12 and up to 1.8.  On rows of 81 to 128 pixels only this split fits: 39 random layers 0.09 to 0.82 of the time of
+    // dw_tiled.hip (192 -> 96 at 88 x 88, batch 28: 2002 -> 194 us).
+    const bool may_widen = f3 && g.kw == 1;
+#ifdef CAC_TUNING
+    if (const char *f = getenv("CAC_DW_WIDE"); f && atoi(f) == 0) return plan_shape(g, 0, plan);
+#endif
     if (!plan_shape(g, 0, plan))
         return may_widen && 2.0 * g.N * g.P * g.Q * (double)g.K * g.C * 9 >= 1e8 && plan_shape(g, 1, plan);
-    if (!may_widen || plan->p.chunks_per_slice < 8) return true;
+    if (!may_widen) return true;
+    const auto work = [](const DwMfmaPlan &a) { return (double)a.p.nchunks * a.p.tiles_o * a.p.tiles_c; };
+    if (g.sh == 1) {
+        DwMfmaPlan wide;
+        if (plan_shape(g, 1, &wide) && 4 * work(wide) <= 3 * work(*plan)) *plan = wide;
+        return true;
+    }
+    if (plan->p.chunks_per_slice < 8) return true;
     const int usual = plan->variant;
     const auto small_tile = [](const DwMfmaPlan &a) { return kVariants[a.variant].KS > 1; };
-    const auto work = [](const DwMfmaPlan &a) { return (double)a.p.nchunks * a.p.tiles_o * a.p.tiles_c; };
     for (int w = 1; w <= 2; ++w) {
         if (w == 2 && plan->p.chunks_per_slice < 24) break;
         DwMfmaPlan wide;
