@@ -20,11 +20,11 @@
 #include <stdlib.h>
 
 #include <mutex>
-#include <numeric>
 
 #include "common.h"
 #include "conv_mfma.h"
 #include "tile_stage.h"
+#include "wave_rows.h"
 
 namespace cac {
 
@@ -35,6 +35,8 @@ constexpr int TAPS = 9, NI = 2, PT = 32 * NI; // pixels of a tile
 constexpr int kOutRow = PT * 2 + 16;          // LDS bytes of an output row: a channel's pixels
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((address_space(3))) f32x4 *lds_f32x4_ptr;
+
+__device__ __forceinline__ WaveRows rows_of(const GatherParams &p) { return WaveRows{p.VH, p.PH, p.IR}; }
 
 constexpr int red_bytes(int MI, int KS) { return (KS - 1) * MI * NI * 4 * 1024; }
 
@@ -58,7 +60,8 @@ template <int KC, int ITEMS, int GW> struct WaveStage {
     // rows of the images from the first one the tile reaches on, one after the other
     __device__ __forceinline__ void init(const GatherParams &p, uint32_t wbase, uint32_t dump_at, int n0, int i0)
     {
-        const int lane = threadIdx.x & 63, hfirst = max(0, i0 * p.is + p.dhmin);
+        const int lane = threadIdx.x & 63, hfirst = wave_first_row(i0, p.is, p.dhmin, p.Hin);
+        const WaveRows rows = rows_of(p);
         co = lane & (OCT - 1);
         K = p.KCin;
         nkb = p.nkb;
@@ -68,9 +71,9 @@ template <int KC, int ITEMS, int GW> struct WaveStage {
         for (int q = 0; q < ITEMS; ++q) {
             const int it = lane + 64 * q, rest = it / OCT;
             const int row = fdiv(rest, p.m_gx), gx = rest - row * p.GX;
-            const int gi = fdiv(hfirst + row, p.m_ph), hin = hfirst + row - gi * p.Hin, vi = hin - p.dhmin;
-            const int lr = gi * p.VH + vi - i0 * p.is, w0 = gx * GW;
-            const bool ok = (row < p.IR) & (n0 + gi < p.N) & (vi >= 0) & (vi < p.VH) & (lr >= 0) & (lr < p.PH);
+            const int gi = fdiv(hfirst + row, p.m_ph), w0 = gx * GW;
+            const WaveRow at = wave_row(rows, p.Hin, p.is, p.dhmin, i0, hfirst, row, gi);
+            const bool ok = at.ok & (n0 + gi < p.N);
             uint32_t m = 0;
 #pragma unroll
             for (int k = 0; k < GW; ++k) {
@@ -78,8 +81,8 @@ template <int KC, int ITEMS, int GW> struct WaveStage {
                 m |= (ok & (w < p.Win) & (w >= p.dwmin) & (w < p.dwmin + p.PWd)) ? 1u << k : 0u;
             }
             m8[q] = m;
-            e0[q] = ok ? (uint32_t)(((n0 + gi) * K + co * 8) * p.Hin + hin) * p.Win + w0 : kNoElem;
-            l0[q] = wbase + (uint32_t)((lr * p.PWd + (w0 - p.dwmin)) * KCS + co * 8) * 2u;
+            e0[q] = ok ? (uint32_t)(((n0 + gi) * K + co * 8) * p.Hin + at.hin) * p.Win + w0 : kNoElem;
+            l0[q] = wbase + (uint32_t)((at.lr * p.PWd + (w0 - p.dwmin)) * KCS + co * 8) * 2u;
         }
         rs_in = make_rsrc(p.in, (uint32_t)p.N * K * plane * 2u);
     }
@@ -185,7 +188,7 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
     for (int ni = 0; ni < NI; ++ni) {
         const int f = px0 + ni * 32 + l32;
         const int gi = fdiv(f, p.m_ppi), px = f - gi * ppi, i = fdiv(px, p.m_wc), j = px - i * p.Wc;
-        const uint32_t at = (uint32_t)(((gi * p.VH + (i - i0) * p.is) * p.PWd + j * p.is) * KCS * 2);
+        const uint32_t at = (uint32_t)((wave_pixel_row(rows_of(p), p.is, i0, gi, i) * p.PWd + j * p.is) * KCS * 2);
         pbase[ni] = wbase + 16u * half + (n0 + gi < p.N ? at : 0u);
     }
     in.clear(wbase, p.buf_bytes);
@@ -331,7 +334,7 @@ template <int BL, int KC, int GW, int KS> __global__ void __launch_bounds__(64 *
     for (int bl = 0; bl < BL; ++bl) {
         const int f = px0 + bl * 32 + l32;
         const int gi = fdiv(f, p.m_ppi), px = f - gi * ppi, i = fdiv(px, p.m_wc), j = px - i * p.Wc;
-        pbase[bl] = wbase + 16u * half + (n0 + gi < p.N ? (uint32_t)(((gi * p.VH + i - i0) * p.PWd + j) * KCS * 2) : 0u);
+        pbase[bl] = wbase + 16u * half + (n0 + gi < p.N ? (uint32_t)((wave_pixel_row(rows_of(p), 1, i0, gi, i) * p.PWd + j) * KCS * 2) : 0u);
     }
     in.clear(wbase, p.buf_bytes);
     for (int s = ks; s < nkb; s += KS) {
@@ -476,11 +479,8 @@ bool span_of_tile(GatherParams &p, int pt, int tall)
     const int ppi = p.Hc * p.Wc;
     const long tiles = ((long)p.N * ppi + pt - 1) / pt;
     if (tiles > 1 << 24) return false;
-    const int gr = std::gcd(pt, p.Wc), gi = std::gcd(pt, ppi);
-    const int rows = (p.Wc - gr + pt - 1) / p.Wc + 1, cross = (ppi - gi + pt - 1) / ppi;
-    p.VH = (p.Hc - 1) * p.is + tall;
-    p.PH = (rows - 1 - min(cross, rows - 1)) * p.is + cross * tall + tall;
-    p.IR = min((rows - 1) * p.is + cross * max(0, p.Hin - p.Hc * p.is) + tall, (cross + 1) * p.Hin);
+    const WaveRows r = wave_rows(p.Hin, p.Hc, p.Wc, p.is, tall, pt);
+    p.VH = r.VH; p.PH = r.PH; p.IR = r.IR;
     p.tiles_per_img = (int)tiles;
     p.m_wc = magic_of(p.Wc); p.m_ppi = magic_of(ppi); p.m_ph = magic_of(p.Hin);
     p.gw = p.Win % 2 ? 7 : 8;

@@ -39,6 +39,14 @@ CASES = [
     ("padding 3 and 1", 12, 81, 72, 8, 11, 3, 3, 3, 1, 1, True, True),
     ("1x9 padding 4", 12, 80, 72, 8, 13, 1, 9, 0, 4, 1, True, True),
     ("9x1 padding 4", 12, 80, 72, 13, 8, 9, 1, 4, 0, 1, True, True),
+    # rows of padding alone below an image, and a tile that starts in them
+    ("maps of 16 pixels, padding 4", 8, 128, 128, 4, 4, 3, 3, 4, 4, 1, True, False),
+    ("rows of 7, padding 5", 4, 256, 64, 7, 7, 3, 3, 5, 5, 1, True, False),
+    ("rows of 14, padding 4", 16, 64, 64, 14, 14, 3, 3, 4, 4, 1, True, True),
+    ("padding 5 and 1", 12, 80, 72, 9, 10, 3, 3, 5, 1, 1, True, True),
+    ("1x9 padding 2 and 4", 12, 80, 72, 8, 13, 1, 9, 2, 4, 1, True, True),
+    ("9x1 padding 12", 8, 100, 90, 3, 5, 9, 1, 12, 0, 1, True, False),
+    ("stride 2, padding 6 and 5", 12, 80, 72, 5, 6, 3, 3, 6, 5, 2, True, False),
 ]
 
 
