@@ -12,13 +12,16 @@ struct WaveRows {
 };
 
 // ... of tiles of pt pixels, which start at multiples of pt, on output planes of Hc x Wc; tall: input rows that an output row meets.
+// Going on to the next image takes `tall` rows of LDS where the next output row of the same image takes `is`: fewer where the filter is
+// flatter than the stride (1 x 9, stride 2), and the tallest tile is then one that stays in its image.
 constexpr WaveRows wave_rows(int Hin, int Hc, int Wc, int is, int tall, int pt)
 {
     // output rows that a tile meets, and how often it goes on to another image, at most
     const int rows = (Wc - std::gcd(pt, Wc) + pt - 1) / Wc + 1, cross = (Hc * Wc - std::gcd(pt, Hc * Wc) + pt - 1) / (Hc * Wc);
     const int gap = Hin - Hc * is > 0 ? Hin - Hc * is : 0; // input rows of an image that no output row starts at
     const int reach = (rows - 1) * is + cross * gap + tall, all = (cross + 1) * Hin;
-    return WaveRows{(Hc - 1) * is + tall, (rows - 1 - (cross < rows - 1 ? cross : rows - 1)) * is + cross * tall + tall, reach < all ? reach : all};
+    const int more = tall > is ? tall - is : 0;
+    return WaveRows{(Hc - 1) * is + tall, (rows - 1) * is + cross * more + tall, reach < all ? reach : all};
 }
 
 // First row staged: of the image that the tile starts in, at output row i0, or, where padding alone follows in that image, the first of

@@ -46,6 +46,9 @@ CASES = [
     ("padding 5 and 1", 12, 80, 72, 9, 10, 3, 3, 5, 1, 1, True, True),
     ("1x9 padding 2 and 4", 12, 80, 72, 8, 13, 1, 9, 2, 4, 1, True, True),
     ("9x1 padding 12", 8, 100, 90, 3, 5, 9, 1, 12, 0, 1, True, False),
+    ("1x9 stride 2", 12, 80, 72, 20, 28, 1, 9, 0, 4, 2, True, False),
+    ("1x9 stride 2, tall maps", 8, 256, 256, 40, 20, 1, 9, 0, 4, 2, True, False),
+    ("1x9 stride 2, padding 3 and 4", 12, 80, 72, 20, 28, 1, 9, 3, 4, 2, True, False),
     ("stride 2, padding 6 and 5", 12, 80, 72, 5, 6, 3, 3, 6, 5, 2, True, False),
 ]
 

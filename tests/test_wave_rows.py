@@ -22,6 +22,8 @@ def walk(tmp_path_factory):
     (3, 1, 3), (3, 2, 3), (9, 1, 9), (9, 2, 9), (1, 1, 1),
     # padding above the filter's height: a tile may start below its image's last row
     (3, 1, 14), (3, 2, 14), (9, 1, 14), (9, 2, 14), (1, 1, 14),
+    # a filter flatter than the stride
+    (1, 2, 1), (1, 2, 14),
 ])
 def test_a_tile_stages_the_rows_that_its_taps_meet(walk, taps, stride, pad):
     r = subprocess.run([walk, str(taps), str(stride), str(pad), "2000"], capture_output=True, text=True)
