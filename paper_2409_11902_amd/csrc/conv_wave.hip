@@ -197,8 +197,9 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
         in.put(s);
         wave_sync();
         in.fetch(s + KS); // (past the end: nothing is loaded)
-        uint32_t so = (uint32_t)s * KSTEPS * kstep;
+        uint32_t so = (uint32_t)s * KSTEPS * kstep, so_next = (uint32_t)wave_next_stage(s, KS, nkb) * KSTEPS * kstep;
         opaque_s(so);
+        opaque_s(so_next);
         u32x4 bq[2][NI];
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) bq[0][ni] = lds16(pbase[ni] + p.toff[0]);
@@ -218,9 +219,9 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
                     bf.u = bq[q & 1][ni];
                     acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf.v, af.v, acc[ni][mi], 0, 0, 0);
                 }
-            // refill the ring with the fragments of step q + D (past the wave's last stage: never used)
+            // refill the ring with the fragments of step q + D
             const int q2 = q + D < STEPS ? q + D : q + D - STEPS;
-            const uint32_t so2 = p.wofs[q2 / KSTEPS] + so + (q2 % KSTEPS + (q + D < STEPS ? 0 : KS * KSTEPS)) * kstep;
+            const uint32_t so2 = p.wofs[q2 / KSTEPS] + (q + D < STEPS ? so : so_next) + q2 % KSTEPS * kstep;
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) wr[q % D][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, wlane, so2 + mi * kFrag, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -341,8 +342,9 @@ template <int BL, int KC, int GW, int KS> __global__ void __launch_bounds__(64 *
         in.put(s);
         wave_sync();
         in.fetch(s + KS); // (past the end: nothing is loaded)
-        uint32_t so = (uint32_t)s * KSTEPS * kstep;
+        uint32_t so = (uint32_t)s * KSTEPS * kstep, so_next = (uint32_t)wave_next_stage(s, KS, nkb) * KSTEPS * kstep;
         opaque_s(so);
+        opaque_s(so_next);
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) {
             u32x4 bq[4][BL];
@@ -351,7 +353,7 @@ template <int BL, int KC, int GW, int KS> __global__ void __launch_bounds__(64 *
 #pragma unroll
                 for (int bl = 0; bl < BL; ++bl) bq[h][bl] = lds16(pbase[bl] + ((h >> 1) * p.PWd + (h & 1)) * (KCS * 2) + 32 * kk);
             __builtin_amdgcn_sched_barrier(0);
-            const uint32_t so2 = so + (kk + 1 < KSTEPS ? kk + 1 : KS * KSTEPS) * kstep; // the next step's fragments (past the last: never used)
+            const uint32_t so2 = kk + 1 < KSTEPS ? so + (kk + 1) * kstep : so_next; // the next step's fragments
 #pragma unroll
             for (int t = 0; t < TAPS; ++t) {
 #pragma unroll

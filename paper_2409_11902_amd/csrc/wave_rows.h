@@ -1,5 +1,5 @@
-// Rows of a tile of conv_wave.hip, in whole numbers: which input rows it reaches, where they lie in LDS.  (No HIP in here: planner,
-// kernels and a host test share it.)
+// Rows and stages of a tile of conv_wave.hip, in whole numbers: which input rows it reaches, where they lie in LDS, whose filter
+// fragments a wave asks for.  (No HIP in here: planner, kernels and a host test share it.)
 #pragma once
 #include <numeric>
 
@@ -47,5 +47,9 @@ constexpr WaveRow wave_row(const WaveRows &r, int Hin, int is, int dhmin, int i0
 
 // LDS row of the first tap row of output row i of image gi.
 constexpr int wave_pixel_row(const WaveRows &r, int is, int i0, int gi, int i) { return gi * r.VH + (i - i0) * is; }
+
+// The stage whose filter fragments a wave asks for during stage s: its next one; after its last that one's again, never used (a scalar
+// offset past the filter is not covered by the range check of the load).
+constexpr int wave_next_stage(int s, int KS, int nkb) { return s + KS < nkb ? s + KS : s; }
 
 } // namespace cac

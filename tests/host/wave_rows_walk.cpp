@@ -38,6 +38,19 @@ static bool tiles_ok(int N, int Hin, int Hc, int Wc, int taps, int is, int dhmin
     return true;
 }
 
+// Every filter fragment that the waves of a tile ask for, while they multiply and ahead of that, lies in the filter: stages of KC of
+// `channels`, KS waves.  (A tap's fragments are 16-channel steps of equal size; the last tap's end is the filter's.)
+static bool fragments_ok(int channels, int KC, int KS)
+{
+    const int nkb = (channels + KC - 1) / KC;
+    for (int ks = 0; ks < KS; ++ks)
+        for (int s = ks; s < nkb; s += KS) {
+            const int next = wave_next_stage(s, KS, nkb);
+            if (next < 0 || next >= nkb || (s + KS < nkb && next != s + KS)) return false;
+        }
+    return true;
+}
+
 int main(int argc, char **argv)
 {
     if (argc != 5) return 2;
@@ -45,6 +58,10 @@ int main(int argc, char **argv)
     std::mt19937 rng(7);
     auto pick = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
     int done = 0, wrong = 0;
+    for (int channels = 1; channels <= 1100; ++channels)
+        for (int KC : {16, 32})
+            for (int KS : {4, 8}) wrong += !fragments_ok(channels, KC, KS);
+    if (wrong) printf("filter fragments past the last stage\n");
     while (done < layers) {
         const int N = pick(1, 9), H = pick(1, 30), W = pick(1, 30), ph = pick(0, pad), pw = pick(0, pad), pt = pick(0, 2) ? 64 : 32;
         if (H + 2 * ph < R || W + 2 * pw < S) continue;
