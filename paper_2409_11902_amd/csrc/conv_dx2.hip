@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(256, 2) conv_dx2_kernel(GatherParams p)
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    int bx = blockIdx.x, by = blockIdx.y, bz = 0;
+    unsigned bx = blockIdx.x, by = blockIdx.y, bz = 0;
     if constexpr (TAIL) {
         if (!conv_block(p, smem, bx, by, bz)) return;
     }

@@ -68,7 +68,7 @@ inline dim3 share_grid(GatherParams &p, dim3 grid, int threads)
     return dim3(grid.x * grid.y * grid.z + p.tail_wgs);
 }
 // The workgroup's place in the launch's own grid; false when it had slices to add (done then).
-__device__ __forceinline__ bool conv_block(const GatherParams &p, unsigned char *lds, int &bx, int &by, int &bz)
+__device__ __forceinline__ bool conv_block(const GatherParams &p, unsigned char *lds, unsigned &bx, unsigned &by, unsigned &bz)
 {
     bx = blockIdx.x; by = blockIdx.y; bz = blockIdx.z;
     if (__builtin_expect(p.tail_wgs == 0, 1)) return true;

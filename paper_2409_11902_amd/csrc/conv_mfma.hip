@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(512) conv_gather_kernel(GatherParams p)
     const int KCT = KC << t_log2;                   // channels staged per pass
     const uint32_t buf_bytes = (uint32_t)p.patch_px * kcs * 2;
 
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tau = bx % p.tiles_per_img, run = bx / p.tiles_per_img;

@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int tau = bx % p.tiles_per_img, n_base = bx / p.tiles_per_img * p.IPT;
     const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb;
@@ -297,7 +297,7 @@ template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) con
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = wave % KS, pt = wave / KS;
     // every XCD works on consecutive pixel tiles, all output channels of one after the other: its L2 keeps the pixels
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3), mtiles = p.Mp / 64;
     if (v >= p.tiles_per_img * mtiles) return; // (tiles_per_img: groups of PT pixel tiles)

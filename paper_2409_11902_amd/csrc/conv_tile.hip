@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int wm = wave % WM, wn = wave / WM;
     // (an image's tiles are as far apart in dispatch order as can be: its last one often has less to do, and
     // neighbouring workgroups go to different XCDs in turn)
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int tau = bx / p.ngrp, n_base = (bx - tau * p.ngrp) * p.IPT;
     const int nkb = p.nkb;

@@ -146,7 +146,7 @@ template <int MI, int KC, int ITEMS, int GW, int KS> __global__ void __launch_bo
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3);
     if (v >= p.tiles_per_img * p.mtiles) return; // (tiles_per_img: pixel tiles of all images)
@@ -300,7 +300,7 @@ template <int BL, int KC, int GW, int KS> __global__ void __launch_bounds__(64 *
     constexpr int KSTEPS = KC / 16, KCS = KC + 8, PT = 32 * BL;
     extern __shared__ __align__(16) unsigned char smem[];
     const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    int bx, by, bz;
+    unsigned bx, by, bz;
     if (!conv_block(p, smem, bx, by, bz)) return;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
