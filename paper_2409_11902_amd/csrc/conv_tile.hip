@@ -43,8 +43,9 @@ constexpr int TAPS = 9;
 constexpr int kEpRow = 64 * 2 + 16;     // LDS bytes of an epilogue row: 64 pixels of one channel
 constexpr int kEpWave = 32 * kEpRow;    // 32 channels per pass
 
-// ITEMS, GW: see PatchStage; D: steps of filter fragments in flight; EPI: pixels per store.
-template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI>
+// ITEMS, GW: see PatchStage; D: steps of filter fragments in flight; EPI: pixels per store; TAIL: the launch may have workgroups that add
+// a weight gradient's slices (a form of its own: 64 -> 64 at 56 x 56, batch 128, a step 0.4-1 % less without the branch).
+template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI, bool TAIL>
 __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
 {
     constexpr int MI = 2;
@@ -61,8 +62,10 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     const int wm = wave % WM, wn = wave / WM;
     // (an image's tiles are as far apart in dispatch order as can be: its last one often has less to do, and
     // neighbouring workgroups go to different XCDs in turn)
-    unsigned bx, by, bz;
-    if (!conv_block(p, smem, bx, by, bz)) return;
+    unsigned bx = blockIdx.x, by = blockIdx.y, bz = 0;
+    if constexpr (TAIL) {
+        if (!conv_block(p, smem, bx, by, bz)) return;
+    }
     const int tau = bx / p.ngrp, n_base = (bx - tau * p.ngrp) * p.IPT;
     const int nkb = p.nkb;
     const int ppi = p.Hc * p.Wc;
@@ -236,9 +239,9 @@ __global__ void __launch_bounds__(256, 2) conv_tile_kernel(GatherParams p)
     else run_wave(std::integral_constant<int, 0>{});
 }
 
-template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI, bool TAIL> hipError_t launch_kernel(const GatherParams &p, hipStream_t st)
 {
-    auto kern = conv_tile_kernel<NI, WM, WN, KC, ITEMS, GW, D, EPI>;
+    auto kern = conv_tile_kernel<NI, WM, WN, KC, ITEMS, GW, D, EPI, TAIL>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
@@ -248,6 +251,10 @@ template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI> hip
     grid = share_grid(q, grid, 256);
     hipLaunchKernelGGL(kern, grid, dim3(256), p.lds_bytes, st, q);
     return hipGetLastError();
+}
+template <int NI, int WM, int WN, int KC, int ITEMS, int GW, int D, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+{
+    return p.tail.blocks ? launch_kernel<NI, WM, WN, KC, ITEMS, GW, D, EPI, true>(p, st) : launch_kernel<NI, WM, WN, KC, ITEMS, GW, D, EPI, false>(p, st);
 }
 template <int NI, int WM, int WN, int KC, int D, int EPI> hipError_t launch_items(const GatherParams &p, hipStream_t st)
 {
