@@ -334,8 +334,10 @@ __global__ void __launch_bounds__(128 * WM * WN * KS) dw_mfma_kernel(DwMfmaParam
             const Src s = src_of(ci);
             // row table: entry rho = {dY row offset, xhat row offset per filter row (the zero
             // slot for rows outside the image)}, in elements from the lane's channel base.  Chunks of whole images
-            // have the same one but for the last (400 cycles of the 3500 that a chunk takes this wave, which is behind the others by them)
-            const bool same = p.RB == 1 && ci >= ci_begin + 2 && s.n0 + p.NBI <= p.N;
+            // have the same one but for the last (400 cycles of the 3500 that a chunk takes this wave, which is behind the others by them;
+            // under stride 2, where chunks of parts of an image are the rule, the question alone costs 128 -> 256 at 28 x 28, batch 128,
+            // uncompressed, 43.8 against 43.4 us, and 60 random layers are even without it)
+            const bool same = SG == 1 && p.RB == 1 && ci >= ci_begin + 2 && s.n0 + p.NBI <= p.N;
             if (cw == 0 && !same && tid < p.LRpad) {
                 const uint32_t rho = tid;
                 const uint32_t ni = fdiv(rho, p.m_pr);
