@@ -210,11 +210,13 @@ int conv_bwd_data(const cac_desc *d, const void *W, const void *dY, void *dX,
 /* Both gradients of a layer in one call: exactly the results of
  * conv_bwd_weight_compressed followed by conv_bwd_data (same kernels, same
  * summation orders, bit-identical outputs), with the small launches of the two
- * shared where they are independent -- the sum over the weight gradient's pixel
- * slices runs in the launch that repacks the data gradient's operands.  A
- * backward pass that needs both (the usual case; the gradient formulas of the
- * compression figure) saves a launch per layer.  `ws` needs
- * cac_workspace_size(CAC_OP_BWD_WEIGHT_AND_DATA) bytes. */
+ * shared where they are independent -- the data gradient's operands are repacked
+ * in the weight gradient's launch where that has room, and the sum over the weight
+ * gradient's pixel slices runs in the data gradient's launch then, else in that of
+ * the repack.  A backward pass that needs both (the usual case; the gradient
+ * formulas of the compression figure) saves a launch or two per layer.  As in the
+ * separate calls dX may take the place of Z, which has been read by then.  `ws`
+ * needs cac_workspace_size(CAC_OP_BWD_WEIGHT_AND_DATA) bytes. */
 int conv_bwd_weight_and_data(const cac_desc *d, const void *Z, const void *W, const void *dY, void *dW,
                              void *dX, void *ws, size_t ws_bytes, void *stream);
 

@@ -97,6 +97,11 @@ static int check_ptr(const void *p, const char *name)
     return CAC_OK;
 }
 
+static bool share_memory(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 static int launched(hipError_t e, const char *what)
 {
     if (e != hipSuccess) return fail(CAC_ERR_LAUNCH_FAILED, "%s: %s", what, hipGetErrorString(e));
@@ -444,7 +449,9 @@ int conv_bwd_weight_and_data(const cac_desc *d, const void *Z, const void *W, co
     if (planned) bind_dx_mfma(&dx, W, dY, dX, ws ? (char *)ws + both_dw_bytes(dw.bytes) : nullptr);
     DwReduceTail tail{};
     bool repacked = false;
-    if ((rc = launch_weight_gradient(g, d->dtype, dw, Z, dY, (float *)dW, ws, st, &tail, planned ? &dx.rep : nullptr, &repacked))) return rc;
+    // (Nothing of dX is cleared while the weight gradient still reads the record in whose place dX comes.)
+    const bool early = planned && !(dx.rep.zero_n && share_memory(dX, 2 * (size_t)dx.rep.zero_n, Z, 2 * (size_t)g.N * g.C * g.Hp * g.Wp));
+    if ((rc = launch_weight_gradient(g, d->dtype, dw, Z, dY, (float *)dW, ws, st, &tail, early ? &dx.rep : nullptr, &repacked))) return rc;
     if (planned) return launched(launch_dx_mfma(dx, repacked, &tail, st), "data gradient");
     if ((rc = launched(launch_dw_reduce(tail, st), "weight gradient (slice sum)"))) return rc;
     hipError_t e = hipSuccess;

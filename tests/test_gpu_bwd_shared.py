@@ -60,3 +60,28 @@ def test_shared_launches_are_bit_identical_to_the_separate_calls(case):
         out.append((dW.t.view(torch.int32), dX.t.view(torch.int16)))
     for o in out[1:]:
         assert torch.equal(out[0][0], o[0]) and torch.equal(out[0][1], o[1]), name
+
+
+@pytest.mark.parametrize("k", [1, 2])
+def test_data_gradient_may_take_the_place_of_the_record(k):
+    """Pixels without a tap are cleared, and not while the weight gradient reads the record that lies there."""
+    import torch
+    from gpu_util import upload, workspace
+    N, C, K, H, W = 30, 40, 48, 10, 12
+    spec = synth.LayerSpec("in place", N, C, K, H, W, 1, 1, 2, 0)
+    d = B.desc_from_spec(spec, pool_kh=k, pool_kw=k)
+    assert ROOM in B.cac_describe_plan(d, B.OP_BWD_WEIGHT_AND_DATA)
+    t = synth.make_inputs(spec, "bwd-in-place", tensors=("X", "W", "dY"))
+    X, Wt, dY = (upload(t[n], spec.dtype) for n in ("X", "W", "dY"))
+    hp, wp, _, _ = B.cac_pooled_shape(d)
+    Z = torch.empty((N, C, hp, wp), dtype=torch.bfloat16, device="cuda:0")
+    B.cac_compress(d, X, Z)
+    dW, dX = torch.empty((K, C, 1, 1), dtype=torch.float32, device="cuda:0"), torch.empty_like(X)
+    B.conv_bwd_weight_compressed(d, Z, dY, dW, workspace(d, B.OP_BWD_WEIGHT_COMPRESSED))
+    B.conv_bwd_data(d, Wt, dY, dX, workspace(d, B.OP_BWD_DATA))
+    dW2, dX2 = torch.empty_like(dW), torch.empty_like(dX)
+    Z2 = dX2.view(-1)[dX2.numel() - Z.numel():]   # the record lies in the last bytes of dX
+    Z2.copy_(Z.view(-1))
+    B.conv_bwd_weight_and_data(d, Z2, Wt, dY, dW2, dX2, workspace(d, B.OP_BWD_WEIGHT_AND_DATA))
+    torch.cuda.synchronize()
+    assert torch.equal(dW.view(torch.int32), dW2.view(torch.int32)) and torch.equal(dX.view(torch.int16), dX2.view(torch.int16))
