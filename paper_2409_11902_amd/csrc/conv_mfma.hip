@@ -864,9 +864,13 @@ bool plan_other(GatherParams &p, bool fwd, int *variant)
     // less than 0.1 GFLOP, launches and start-up either way, where it shares the channels over workgroups.
     const long px = (long)p.N * p.Hc * p.Wc;
     const bool few = (p.KCin <= 48 && (!fwd || px >= 4096)) || (p.KCin <= 256 && (px + 63) / 64 * (p.Mp / 64) <= 12 && 18.0 * px * p.KCin * p.M < 1e8);
-    // Long sums of a stride-2 layer over few workgroups: twelve stages and more to a wave, which stages twice the rows of a stride-1
-    // tile, against the gather with shared-out channels: 1.0 to 1.5 of its time (1600 -> 41 at 12 x 12, batch 22: 25 against 39 us).
-    if (GatherParams gather = p; have_wave && p.is == 2 && wave.kbs >= 12 && !have_tile && shape_gather(gather, variant) && gather.ksplit > 1) {
+    // Long sums of a stride-2 layer over few workgroups: a wave stages twice the rows of a stride-1 tile, stage after stage, where the
+    // gather shares the channels out.  From twelve stages a wave on the waves took 1.0 to 1.5 of its time (1600 -> 41 at 12 x 12, batch
+    // 22: 39 against 25 us).  Of 196 random layers with fewer, the 40 with six and more, at most 32 workgroups and an input whose
+    // copy the gather makes in whole items took 1.1 (592 -> 27 at 5 x 48, batch 2: 23.6 against 17.0; four below 0.95), the others 0.81
+    // (10 over 1.05).
+    const bool long_sums = wave.kbs >= 12 || (wave.kbs >= 6 && wave.tiles_per_img * wave.mtiles <= 32 && p.Hin * p.Win % 2 == 0);
+    if (GatherParams gather = p; have_wave && p.is == 2 && long_sums && !have_tile && shape_gather(gather, variant) && gather.ksplit > 1) {
         p = gather;
         return true;
     }

@@ -104,3 +104,19 @@ def test_pointwise_wave_tiles_of_odd_planes(shape, pixels):
     d = B.make_desc(*shape, 1, 1, pool_kh=2, pool_kw=2)
     got = B.cac_describe_plan(d, B.OP_FWD_AND_COMPRESS)
     assert got.startswith("pointwise by waves tile=64ch x " + pixels), got
+
+
+@pytest.mark.parametrize("shape,waves", [
+    # N, C, K, H, W.  3 x 3 stride 2, few workgroups: the gather shares long sums out, six stages a wave and more
+    ((2, 592, 27, 5, 48), False),
+    ((2, 592, 27, 5, 47), True),       # ... not where its copy of the input moves single elements,
+    ((2, 320, 27, 5, 48), True),       # nor up to five stages
+    ((2, 321, 27, 5, 48), False),
+    ((4, 592, 300, 5, 48), False),
+    ((5, 592, 400, 5, 48), True),      # nor past 32 workgroups
+    ((1, 704, 27, 5, 47), True),      # from twelve stages on wherever it can
+    ((1, 705, 27, 5, 47), False),
+])
+def test_long_sums_of_stride_2_layers(shape, waves):
+    got = B.cac_describe_plan(B.make_desc(*shape, 3, 3, 2, 2, 1, 1), B.OP_FWD_AND_COMPRESS)
+    assert ("by waves" in got) == waves and got.startswith("gather") != waves, got
