@@ -864,13 +864,16 @@ bool plan_other(GatherParams &p, bool fwd, int *variant)
     // less than 0.1 GFLOP, launches and start-up either way, where it shares the channels over workgroups.
     const long px = (long)p.N * p.Hc * p.Wc;
     const bool few = (p.KCin <= 48 && (!fwd || px >= 4096)) || (p.KCin <= 256 && (px + 63) / 64 * (p.Mp / 64) <= 12 && 18.0 * px * p.KCin * p.M < 1e8);
-    // Long sums of a stride-2 layer over few workgroups: a wave stages twice the rows of a stride-1 tile, stage after stage, where the
-    // gather shares the channels out.  From twelve stages a wave on the waves took 1.0 to 1.5 of its time (1600 -> 41 at 12 x 12, batch
-    // 22: 39 against 25 us).  Of 196 random layers with fewer, the 40 with six and more, at most 32 workgroups and an input whose
-    // copy the gather makes in whole items took 1.1 (592 -> 27 at 5 x 48, batch 2: 23.6 against 17.0; four below 0.95), the others 0.81
-    // (10 over 1.05).
-    const bool long_sums = wave.kbs >= 12 || (wave.kbs >= 6 && wave.tiles_per_img * wave.mtiles <= 32 && p.Hin * p.Win % 2 == 0);
-    if (GatherParams gather = p; have_wave && p.is == 2 && long_sums && !have_tile && shape_gather(gather, variant) && gather.ksplit > 1) {
+    // Long sums over few workgroups where a lane stages two items of eight channels, under stride 2 (twice the rows) and on rows past 40
+    // pixels or so: stage after stage of a wave, where the gather shares the channels out.  Under stride 2 the waves took 1.0 to 1.5 of
+    // its time from twelve stages a wave on (1600 -> 41 at 12 x 12, batch 22: 39 against 25 us).  Of 196 random layers with
+    // fewer, the 40 with six and more, at most 32 workgroups and an input whose copy the gather makes in whole items took 1.1 (592 -> 27
+    // at 5 x 48, batch 2: 23.6 against 17.0; four below 0.95), the others 0.81 (10 over 1.05).  Under stride 1 the three such layers of
+    // 1000 took 1.03, 1.10 and 1.45 (data gradient of 32 -> 1344 at 16 x 47, batch 2: 30.1 against 20.8).
+    const bool two = have_wave && wave.IR * wave.GX * (wave.KCp / wave.nkb) > 64 * 8;
+    const bool long_sums = (p.is == 2 && wave.kbs >= 12) ||
+                           ((p.is == 2 || two) && wave.kbs >= 6 && wave.tiles_per_img * wave.mtiles <= 32 && p.Hin * p.Win % 2 == 0);
+    if (GatherParams gather = p; have_wave && long_sums && !have_tile && shape_gather(gather, variant) && gather.ksplit > 1) {
         p = gather;
         return true;
     }
@@ -881,9 +884,11 @@ bool plan_other(GatherParams &p, bool fwd, int *variant)
             return true;
         }
     }
-    // Against conv_tile.hip: 200 random layers, by the ratio of the two planners' cycles; below 0.55 the waves take 0.76 of the
-    // time (48 layers, 2 of them over 1.05), up to 0.7 it is 1.0, above 1.0 1.6.
-    if (have_wave && have_tile) have_wave = wave_cost < 0.55 * tile_cost;
+    // Against conv_tile.hip by the ratio of the two planners' cycles, which counts a stage alike for one item to a lane and for two.
+    // One: 200 random layers, below 0.55 the waves take 0.76 of the time (48 layers, 2 of them over 1.05), up to 0.7 it is 1.0, above 1.0
+    // 1.6.  Two: under stride 1 0.8 below 0.45 and 1.04 from there to 0.55 (19 layers; data gradient of 67 -> 464 at 51 x 51, batch 7:
+    // 44.7 against 39.1 us), under stride 2 0.8 below 0.50 and 1.0 from there to 0.55 (57 layers).
+    if (have_wave && have_tile) have_wave = wave_cost < (!two ? 0.55 : p.is == 1 ? 0.45 : 0.50) * tile_cost;
 #ifdef CAC_TUNING
     if (const char *f = getenv("CAC_WAVE"); f && atoi(f) == 0) have_wave = false;
 #endif

@@ -120,3 +120,19 @@ def test_pointwise_wave_tiles_of_odd_planes(shape, pixels):
 def test_long_sums_of_stride_2_layers(shape, waves):
     got = B.cac_describe_plan(B.make_desc(*shape, 3, 3, 2, 2, 1, 1), B.OP_FWD_AND_COMPRESS)
     assert ("by waves" in got) == waves and got.startswith("gather") != waves, got
+
+
+@pytest.mark.parametrize("shape,op,waves", [
+    # N, C, K, H, W.  3 x 3 stride 1, rows that give a lane two items a stage: the line to the large tiles lies lower
+    ((7, 67, 464, 51, 51), B.OP_BWD_DATA, False),
+    ((30, 176, 118, 5, 47), B.OP_BWD_DATA, True),
+    ((39, 725, 19, 23, 47), B.OP_FWD_AND_COMPRESS, False),
+    ((9, 560, 148, 20, 55), B.OP_FWD_AND_COMPRESS, True),
+    # ... and few workgroups with long sums leave them to the gather, as under stride 2
+    ((2, 32, 1344, 16, 47), B.OP_BWD_DATA, False),
+    ((2, 32, 1344, 15, 47), B.OP_BWD_DATA, True),
+    ((2, 32, 1344, 16, 39), B.OP_BWD_DATA, True),
+])
+def test_two_items_to_a_lane(shape, op, waves):
+    got = B.cac_describe_plan(B.make_desc(*shape, 3, 3, 1, 1, 1, 1), op)
+    assert ("by waves" in got) == waves, got
