@@ -84,6 +84,14 @@ __device__ __forceinline__ bool conv_block(const GatherParams &p, unsigned char 
     return true;
 }
 
+// conv_gather.hip, conv_gather_tail.hip: the gather GEMM (conv_gather.h)
+namespace gather {
+constexpr int KC = 32;        // channels staged per pass
+constexpr int KCS = KC + 8;   // LDS elements per patch pixel: 80 bytes, an odd number of 16-byte units
+constexpr int kMaxItems = 12; // 16-byte patch items a copy thread moves per stage, at most (kernel parameter ITEMS: 6 or 12)
+}
+hipError_t launch_conv_gather(const GatherParams &p, int variant, hipStream_t st);
+hipError_t launch_conv_gather_tail(const GatherParams &p, int variant, hipStream_t st);
 // conv_tile.hip: nine-tap launches with large wave tiles (see there)
 bool shape_tile(GatherParams &p, int *variant, double *cost);
 hipError_t launch_tile(const GatherParams &p, int variant, hipStream_t st);

@@ -41,8 +41,9 @@ constexpr int kEpRow = 64 * 2 + 16, kEpWave = 32 * kEpRow;
 constexpr int kBuf = kPT * KCS * 2 + kPT / 4 * 16; // (with the largest padding, see pad_of)
 
 // FUSE: items of 2 rows x 4 pixels, Z written on the way.  GW: pixels of an item otherwise: 8, or 7 for planes of odd
-// size (read from the dword below an odd start).  EPI: pixels per store.
-template <int NI, int WM, int WN, bool FUSE, int GW, int EPI>
+// size (read from the dword below an odd start).  EPI: pixels per store.  TAIL: the launch may have workgroups that add a weight
+// gradient's slices (here and below a form of its own: forward passes of 1056 -> 976 at 4 x 4, batch 1, 9.2 us with the branch, 8.7 without).
+template <int NI, int WM, int WN, bool FUSE, int GW, int EPI, bool TAIL>
 __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
 {
     constexpr int MI = 2;
@@ -52,8 +53,10 @@ __global__ void __launch_bounds__(256, 2) conv_pw_kernel(GatherParams p)
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
-    unsigned bx, by, bz;
-    if (!conv_block(p, smem, bx, by, bz)) return;
+    unsigned bx = blockIdx.x, by = blockIdx.y, bz = 0;
+    if constexpr (TAIL) {
+        if (!conv_block(p, smem, bx, by, bz)) return;
+    }
     const int tau = bx % p.tiles_per_img, n_base = bx / p.tiles_per_img * p.IPT;
     const int ppi = p.Hc * p.Wc, K = p.KCin, nkb = p.nkb;
     const int pix0 = p.IPT > 1 ? 0 : tau * p.tile_px;
@@ -288,7 +291,7 @@ constexpr int wt_lds(int KS)
     return red > 4 * kWtBytes ? red : 4 * kWtBytes;
 }
 
-template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) conv_pw_wave_kernel(GatherParams p)
+template <int KS, int GW, int EPI, bool TAIL> __global__ void __launch_bounds__(256, 3) conv_pw_wave_kernel(GatherParams p)
 {
     constexpr int PT = 4 / KS, KEEP = 4 / KS; // pixel tiles of a workgroup; blocks of 32 x 32 that a wave finishes
     extern __shared__ __align__(16) unsigned char smem[];
@@ -297,8 +300,10 @@ template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) con
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ks = wave % KS, pt = wave / KS;
     // every XCD works on consecutive pixel tiles, all output channels of one after the other: its L2 keeps the pixels
-    unsigned bx, by, bz;
-    if (!conv_block(p, smem, bx, by, bz)) return;
+    unsigned bx = blockIdx.x, by = 0, bz = 0;
+    if constexpr (TAIL) {
+        if (!conv_block(p, smem, bx, by, bz)) return;
+    }
     const int per_xcd = p.gx >> 3, v = (bx & 7) * per_xcd + (bx >> 3), mtiles = p.Mp / 64;
     if (v >= p.tiles_per_img * mtiles) return; // (tiles_per_img: groups of PT pixel tiles)
     const int grp = v / mtiles, m0 = (v - grp * mtiles) * 64;
@@ -499,9 +504,9 @@ template <int KS, int GW, int EPI> __global__ void __launch_bounds__(256, 3) con
     }
 }
 
-template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherParams &p, hipStream_t st)
+template <int KS, int GW, int EPI, bool TAIL> hipError_t launch_wave_kernel(const GatherParams &p, hipStream_t st)
 {
-    auto kern = conv_pw_wave_kernel<KS, GW, EPI>;
+    auto kern = conv_pw_wave_kernel<KS, GW, EPI, TAIL>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
@@ -512,6 +517,10 @@ template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherPara
     hipLaunchKernelGGL(kern, grid, dim3(256), wt_lds(KS), st, q);
     return hipGetLastError();
 }
+template <int KS, int GW, int EPI> hipError_t launch_wave_fixed(const GatherParams &p, hipStream_t st)
+{
+    return p.tail.blocks ? launch_wave_kernel<KS, GW, EPI, true>(p, st) : launch_wave_kernel<KS, GW, EPI, false>(p, st);
+}
 template <int KS> hipError_t launch_wave(const GatherParams &p, hipStream_t st)
 {
     if constexpr (KS > 1)
@@ -521,9 +530,9 @@ template <int KS> hipError_t launch_wave(const GatherParams &p, hipStream_t st)
                                                                                   : launch_wave_fixed<KS, 8, 2>(p, st);
 }
 
-template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+template <int NI, int WM, int WN, bool FUSE, int GW, int EPI, bool TAIL> hipError_t launch_kernel(const GatherParams &p, hipStream_t st)
 {
-    auto kern = conv_pw_kernel<NI, WM, WN, FUSE, GW, EPI>;
+    auto kern = conv_pw_kernel<NI, WM, WN, FUSE, GW, EPI, TAIL>;
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(attr_once, [&] { attr_err = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); });
@@ -533,6 +542,12 @@ template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_
     grid = share_grid(q, grid, 256);
     hipLaunchKernelGGL(kern, grid, dim3(256), 2 * kBuf, st, q);
     return hipGetLastError();
+}
+template <int NI, int WM, int WN, bool FUSE, int GW, int EPI> hipError_t launch_fixed(const GatherParams &p, hipStream_t st)
+{
+    if constexpr (!FUSE) // (a forward pass)
+        if (p.tail.blocks) return launch_kernel<NI, WM, WN, FUSE, GW, EPI, true>(p, st);
+    return launch_kernel<NI, WM, WN, FUSE, GW, EPI, false>(p, st);
 }
 template <int NI, int WM, int WN> hipError_t launch_shape(const GatherParams &p, hipStream_t st)
 {
