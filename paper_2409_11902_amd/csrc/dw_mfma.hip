@@ -1205,7 +1205,8 @@ static int repack_waves(const DwMfmaParams &p, const FilterRepack &f) { return r
 // Whether the kernel's launch has room for the data gradient's repacks, which cost 4-10 us in one of their own.
 // 1: with 64 compute units and more to spare, in workgroups of their own there (18 random layers: 0.62-0.93 of the backward pass).
 // 2: a filter of 256 blocks and more, read in 16-byte pieces: every MFMA wave lays out two of them at most while it waits for its
-// first chunk (512 -> 2048, 1 x 1 at 7 x 7, batch 64: backwards 47.3 -> 44.7 us, 512 -> 512, 3 x 3 at 7 x 7, batch 256: 122.2 -> 120.5).
+// first chunk (66 random layers: 0.962 of the backward pass, none over 1.02; 512 -> 2048, 1 x 1 at 7 x 7, batch 64: 43.8 -> 40.7 us, 512 ->
+// 512, 3 x 3 at 7 x 7, batch 256: 1 to 4 %).
 // Else neither: smaller filters and element-wise ones delay the waves that have a block by 4-6 us (224 -> 32, 1 x 1 at 34 x 34, batch 93,
 // 41.0 -> 43.6), and workgroups behind 256 of the kernel's are a tail as long as the launch.
 int dw_takes_repack(const DwMfmaPlan &plan, const RepackParams &rep)
