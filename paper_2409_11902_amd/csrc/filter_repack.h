@@ -17,7 +17,7 @@ struct FilterRepack {
 };
 constexpr int kFilterElems = 32 * (16 * 9 + 2); // LDS: a 32 x 16 block of (o, c) pairs, 9 taps, padded rows
 
-// NT threads, 256 or one wave, by themselves.  (A block past the last one: nothing is stored.)
+// NT threads, 256 or one wave, by themselves.
 template <int NT> __device__ __forceinline__ void filter_repack_by(const FilterRepack &p, const int b, bf16_t *sm, const int tid)
 {
     typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -102,7 +102,7 @@ template <int NT> __device__ __forceinline__ void filter_repack_by(const FilterR
             }
             v[k] = h[0] | (h[1] << 16);
         }
-        if (kblk < kblks) ((u32x4 *)p.Wt)[((long)(tap * kblks + kblk) * mblks + mblk) * 64 + lane] = v;
+        ((u32x4 *)p.Wt)[((long)(tap * kblks + kblk) * mblks + mblk) * 64 + lane] = v;
     }
 }
 
