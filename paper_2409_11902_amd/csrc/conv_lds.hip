@@ -154,6 +154,7 @@ __global__ void __launch_bounds__(256, (PX == 4 ? 3 : 4) - (TAPS == 9)) conv_lds
     uint32_t off[2][8];
     int w1, r1; // of the second batch
     at(1, w1, r1);
+    if (CC <= p.KC) // (a pass that is not full reckons for itself: 0.85 to 0.9 of the time where there is no other)
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         off[0][q] = offset_of(0, dwmin + (lane & cmask), rbase + 4 * q * rpw);
