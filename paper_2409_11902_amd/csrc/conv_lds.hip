@@ -366,10 +366,11 @@ __global__ void __launch_bounds__(256, (PX == 4 ? 3 : 4) - (TAPS == 9)) conv_lds
     }
 }
 
-// A launch of the kernel: its parameters but for the tensors, pixels per thread, channels per pass.
+// A launch of the kernel: its parameters but for the tensors, pixels per thread, channels per pass, taps in registers.
 struct ConvLdsPlan {
     ConvLdsParams p;
-    int px, cc, lds_bytes;
+    int px, cc, taps, lds_bytes;
+    double now; // see cost_lds
     dim3 grid;
 };
 
@@ -397,7 +398,12 @@ bool shape_lds(const Geom &g, int dtype, bool dx, int px, int cc, ConvLdsPlan *p
     const long rows = p.IPT > 1 ? p.Hc : std::min((long)p.Hc, (long)(pt + p.Wc - 2) / p.Wc + 1);
     const long ph = std::max(2L, (rows - 1) * is_h + span_h), pw = (long)(p.Wc - 1) * is_w + span_w;
     if ((long)p.tiles * p.ngrp > 0x7fffffffL) return false;
-    const long bytes = 4 * ((long)g.R * g.S * cc * kTMP + (long)cc * p.IPT * ph * pw + 64);
+    // Float filters of 3 x 3 and 1 x 1 are read as they lie, their taps in registers.  (Strides of 1 and 2: the kernels know the taps of a
+    // parity class.  A 3 x 3 data gradient with four pixels per thread would take 256 registers and spill 59: 33.7 us against 31.3,
+    // 64 -> 20 at 38 x 38, batch 20; its filter goes through LDS.)
+    const bool nine = g.R == 3 && g.S == 3, known = dtype == CAC_F32 && cc == 16 && g.sh <= 2 && g.sw <= 2 && (nine || g.R * g.S == 1);
+    const int taps = !known ? 0 : !nine ? 1 : dx && px == 4 ? 0 : 9;
+    const long bytes = 4 * ((taps ? 0L : (long)g.R * g.S * cc * kTMP) + (long)cc * p.IPT * ph * pw + 64);
     if (bytes > 64 * 1024) return false;
     p.PH = (int)ph; p.PWd = (int)pw;
     p.cw_log2 = 0;
@@ -407,32 +413,27 @@ bool shape_lds(const Geom &g, int dtype, bool dx, int px, int cc, ConvLdsPlan *p
     plan->p = p;
     plan->px = px;
     plan->cc = cc;
+    plan->taps = taps;
+    plan->now = known && min(p.KC, p.M) >= 16 ? 0.62 : 1.0;
     plan->lds_bytes = (int)bytes;
     plan->grid = dim3(p.tiles * p.ngrp, mblocks, classes);
     return true;
-}
-
-// Taps of the kernels with the filter in registers, 0 for a layer that they do not take.  (Strides of 1 and 2: they know the taps of
-// a parity class.)
-int taps_in_registers(const ConvLdsParams &p, int cc, size_t elem)
-{
-    if (elem != 4 || cc != 16 || p.sh > 2 || p.sw > 2) return 0;
-    return p.R == 3 && p.S == 3 ? 9 : p.R * p.S == 1 ? 1 : 0;
 }
 
 // Microseconds of a launch, and of the plain kernel on the same layer: a pass costs its batches of eight loads of the
 // patch, its loads of the filter and its taps x channels, once as the latency of a workgroup and once as the work of 256
 // compute units; a step of the plain kernel's loop likewise, and every channel (forward) a new line of the input.  Fitted to
 // 10000 random layers in each direction (1-256 channels, maps of 2-400, filters of 1-11, strides 1-3, both types): 15 %
-// and 19 % rms for this kernel, 25 % and 22 % for the plain one -- when the sums were multiply-adds: 40 random layers of 16 to 64
-// channels take 0.64 (forward) and 0.59 of that time with the filter in registers.
+// and 19 % rms for this kernel, 25 % and 22 % for the plain one -- when the sums were multiply-adds.  `now` is what float layers of 16
+// channels and more take of that time since they are the matrix instruction's, of 1800 random ones: 3 x 3 0.6 (0.72 where the filter
+// goes through LDS), 1 x 1 by the number of passes, 1.0 for one, 0.85 for two, 0.6 for many (see plan_lds).
 struct LdsCost { double start, x, f, mul1, mul4, wg, wx, wf, wmul1, wmul4; };
 const LdsCost kLdsCost[2] = {{0.0, 0.93, 0.0985, 0.0150, 0.0613, 0.06, 0.52, 0.0102, 0.0123, 0.0378},
                              {4.3, 1.39, 0.1067, 0.0344, 0.0851, 0.39, 0.42, 0.0543, 0.0153, 0.0380}};
 struct PlainCost { double start, step, line, wstep, wg; };
 const PlainCost kPlainCost[2] = {{0.5, 0.154, 0.194, 0.0715, 0.55}, {5.4, 0.125, 0.0, 0.0679, 0.41}};
 
-double cost_lds(const Geom &g, int dtype, bool dx, const ConvLdsPlan &l)
+double cost_lds(const Geom &g, bool dx, const ConvLdsPlan &l)
 {
     const LdsCost &c = kLdsCost[dx];
     auto cdiv = [](long a, long b) { return (double)((a + b - 1) / b); };
@@ -440,8 +441,7 @@ double cost_lds(const Geom &g, int dtype, bool dx, const ConvLdsPlan &l)
     const double passes = cdiv(l.p.KC, l.cc), nx = cdiv(l.p.PWd, 64) * cdiv((long)l.cc * l.p.IPT * l.p.PH, 32 * rpw);
     const double nf = cdiv((long)(dx ? 16 : l.cc) * RS, 128) * 2 * ((dx ? l.cc : 16) / 4), mul = (double)RS / l.grid.z * l.cc;
     const double wgs = (double)l.grid.x * l.grid.y * l.grid.z;
-    const double now = taps_in_registers(l.p, l.cc, dtype == CAC_F32 ? 4 : 2) && min(l.p.KC, l.p.M) >= 16 ? 0.62 : 1.0;
-    return c.start + now * hypot(passes * (c.x * nx + c.f * nf + mul * (l.px == 4 ? c.mul4 : c.mul1)),
+    return c.start + l.now * hypot(passes * (c.x * nx + c.f * nf + mul * (l.px == 4 ? c.mul4 : c.mul1)),
                            wgs / 256 * (c.wg * (l.px == 4 ? 2 : 1) + passes * (c.wx * nx + c.wf * nf + mul * (l.px == 4 ? c.wmul4 : c.wmul1))));
 }
 
@@ -470,14 +470,18 @@ bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
     const long plane = dx ? (long)((g.H + g.sh - 1) / g.sh) * ((g.W + g.sw - 1) / g.sw) : (long)g.P * g.Q;
     const long wgs4 = (plane + 255) / 256 * g.N * (((dx ? g.C : g.K) + 15) / 16) * (dx ? (long)g.sh * g.sw : 1);
     const int px0 = wgs4 >= 1024 ? 4 : 1, channels = dx ? g.K : g.C;
-    const double plain = cost_plain(g, dx);
+    // 1 x 1 layers of few channels have not gained on the plain kernel: data gradients took 1.0 to 1.4 of its time up to two passes, and
+    // up to three with four pixels per thread (54 <- 20 at 14 x 32, batch 1: 6.0 against 5.2 us; 144 <- 30 at 73 x 73, batch 12: 60
+    // against 44), forward passes up to two with one pixel.
+    const int kept = g.R * g.S > 1 || dtype != CAC_F32 || max(g.sh, g.sw) > 2 || min(g.C, g.K) < 16 ? 0 : px0 == 1 ? 32 : dx ? 48 : 0;
+    const double plain = cost_plain(g, dx) * (channels <= kept ? 0.8 : 1.0);
     double usual = 0, least = plain; // (usual: of the first possible shape with px0 pixels, 0 while there is none)
     ConvLdsPlan first{}, best{};
     for (int px : {px0, 5 - px0})
         for (int cc : {16, 4}) {
             ConvLdsPlan l;
             if (!shape_lds(g, dtype, dx, px, cc, &l)) continue;
-            const double cost = cost_lds(g, dtype, dx, l);
+            const double cost = cost_lds(g, dx, l);
             if (px == px0 && usual == 0) { usual = cost; first = l; }
             if (cost < least) { least = cost; best = l; }
             if (channels > 8) break; // (passes of four only where those of sixteen do not fit: the same work in more passes)
@@ -491,13 +495,11 @@ bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
 template <typename T, bool DX> hipError_t launch(const ConvLdsPlan &l, hipStream_t st)
 {
 #define CAC_LDS(PX, CC, TAPS) hipLaunchKernelGGL((conv_lds_kernel<T, PX, DX, CC, TAPS>), l.grid, dim3(256), l.lds_bytes, st, l.p)
-    const int taps = taps_in_registers(l.p, l.cc, sizeof(T));
     if constexpr (sizeof(T) == 4) {
-        if (taps) {
-            if (taps == 9) {
+        if (l.taps) {
+            if (l.taps == 9) {
                 if (l.px == 1) CAC_LDS(1, 16, 9);
-                else if constexpr (DX) CAC_LDS(4, 16, 0); // (256 registers and 59 spilled: 33.7 us against 31.3, 64 -> 20 at 38 x 38, batch 20)
-                else CAC_LDS(4, 16, 9);
+                else if constexpr (!DX) CAC_LDS(4, 16, 9);
             } else {
                 if (l.px == 4) CAC_LDS(4, 16, 1); else CAC_LDS(1, 16, 1);
             }

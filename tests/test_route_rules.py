@@ -136,3 +136,18 @@ def test_long_sums_of_stride_2_layers(shape, waves):
 def test_two_items_to_a_lane(shape, op, waves):
     got = B.cac_describe_plan(B.make_desc(*shape, 3, 3, 1, 1, 1, 1), op)
     assert ("by waves" in got) == waves, got
+
+
+@pytest.mark.parametrize("shape,stride,op,lds", [
+    # N, C, K, H, W.  1 x 1 in float: the plain kernel keeps data gradients of few outputs ...
+    ((1, 54, 20, 14, 32), 1, B.OP_BWD_DATA, False),
+    ((1, 54, 20, 14, 32), 2, B.OP_BWD_DATA, False),
+    ((2, 102, 48, 26, 26), 1, B.OP_BWD_DATA, True),
+    ((12, 144, 30, 73, 73), 1, B.OP_BWD_DATA, False),   # (... further on with four pixels per thread)
+    ((21, 107, 59, 53, 53), 1, B.OP_BWD_DATA, True),
+    # ... and strides past 2 are none of its business
+    ((4, 16, 19, 13, 17), 3, B.OP_FWD_AND_COMPRESS, True),
+])
+def test_pointwise_float_layers(shape, stride, op, lds):
+    got = B.cac_describe_plan(B.make_desc(*shape, 1, 1, stride, stride, dtype=B.F32), op)
+    assert got.startswith("conv_lds") == lds, got
