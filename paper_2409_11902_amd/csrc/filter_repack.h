@@ -29,23 +29,26 @@ template <int NT> __device__ __forceinline__ void filter_repack_by(const FilterR
     const int mblks = p.Mp / 32, kblks = p.KCp / 16, mblk = b % mblks, kblk = b / mblks;
     const int rows = p.transpose ? 16 : 32, cols = p.transpose ? 32 : 16; // o rows, c columns
     const int o0 = p.transpose ? kblk * 16 : mblk * 32, c0 = p.transpose ? mblk * 32 : kblk * 16;
+    // (A wave has rows past the last channel left out: they are of outputs that nobody stores, and as the partial block that they are,
+    // read element by element, they held it up by 4-7 us.)
+    if (NT == 64 && p.transpose && c0 >= p.Cw) return;
     const int L = cols * p.RS, Lp = L + 2;
     const int wv = tid >> 6, ln = tid & 63;
     // a wave takes every fourth row; all of a thread's loads are issued before the first is
     // used (at most 8 rows of 3 x 64 elements, or 4 rows of 5 x 64; a wave by itself: 8 rows at a time)
     constexpr int kRowsPerWave = 8, kMaxX = 5, kWaves = NT / 64;
     const rsrc_t rs = make_rsrc(p.W, (uint32_t)p.O * p.Cw * p.RS * 2u);
-    // Whole blocks -- or none of it, past the last column -- whose runs are multiples of 16 bytes and start on such (every row
-    // of W does when Cw * RS is a multiple of 8): 16-byte loads, at most 3 per thread, instead of up to 40
+    // Whole blocks whose runs are multiples of 16 bytes and start on such (every row of W does
+    // when Cw * RS is a multiple of 8): 16-byte loads, at most 3 per thread, instead of up to 40
     // loads of one element each.
     const int segs = L >> 3;
-    if ((L & 7) == 0 && ((p.Cw * p.RS) & 7) == 0 && (c0 + cols <= p.Cw || c0 >= p.Cw)) {
+    if ((L & 7) == 0 && ((p.Cw * p.RS) & 7) == 0 && c0 + cols <= p.Cw) {
         constexpr int kLoads = 768 / NT;
         u32x4 t4[kLoads];
 #pragma unroll
         for (int q = 0; q < kLoads; ++q) {
             const int it = tid + NT * q, r = it / segs, sg = it - r * segs, o = o0 + r;
-            const bool ok = it < rows * segs && o < p.O && c0 < p.Cw;
+            const bool ok = it < rows * segs && o < p.O;
             t4[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, ok ? ((uint32_t)(o * p.Cw + c0) * p.RS) * 2u + sg * 16u : kNoLoad, 0, 0);
         }
 #pragma unroll

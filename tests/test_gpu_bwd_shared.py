@@ -28,6 +28,7 @@ CASES = [
     ("filter by the waves that wait", 112, 512, 512, 7, 7, 3, 1, (ROOM,)),
     ("filter by the waves that wait, 1x1", 64, 512, 2048, 7, 7, 1, 1, (ROOM, SUM)),
     ("filter by the waves that wait, rows past the last channel", 1, 1056, 976, 4, 4, 1, 1, (ROOM,)),
+    ("filter by the waves that wait, rows past the last channel, 3x3", 5, 672, 304, 12, 12, 3, 1, (ROOM,)),
     ("no room", 64, 100, 130, 28, 28, 3, 1, ("in the launch of the data gradient's repack",)),
 ]
 
