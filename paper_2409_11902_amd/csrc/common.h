@@ -74,6 +74,8 @@ bool launch_compress_fast(const Geom &g, int dtype, const void *X, void *Z, hipS
 struct FilterRepack;
 hipError_t launch_compress_repack(const Geom &g, const void *X, void *Z, const FilterRepack &f, hipStream_t st);
 hipError_t launch_compress_generic(const Geom &g, int dtype, const void *X, void *Z, hipStream_t st);
+// conv_lds.hip: microseconds of a forward pass or data gradient there or by the plain kernel, whichever takes the layer, roughly
+double cost_without_mfma(const Geom &g, int dtype, bool dx);
 // conv_lds.hip: false when the geometry does not fit LDS (status in *err otherwise)
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err);
 bool launch_dx_lds(const Geom &g, int dtype, const void *W, const void *dY, void *dX, hipStream_t st, hipError_t *err);

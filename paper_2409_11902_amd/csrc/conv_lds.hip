@@ -465,7 +465,7 @@ double cost_plain(const Geom &g, bool dx)
 // 64 -> 3 31 / 14 / 15; 3 -> 64 at 224 x 224, batch 2, bfloat16, data gradient 305 / 150 / 150), and for a few long rows
 // (4 -> 4 at 3 x 900 21 / 11 / 11).  On 7000 random layers other than those of the fit, 31 % ran more than 5 % slower
 // than on the plain kernel with this shape alone and 3 % do as planned; 16 -> 16 at 32 x 32, batch 8, 32 (plain) / 11.5.
-bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
+bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan, double *cost_out = nullptr)
 {
     const long plane = dx ? (long)((g.H + g.sh - 1) / g.sh) * ((g.W + g.sw - 1) / g.sw) : (long)g.P * g.Q;
     const long wgs4 = (plane + 255) / 256 * g.N * (((dx ? g.C : g.K) + 15) / 16) * (dx ? (long)g.sh * g.sw : 1);
@@ -486,7 +486,9 @@ bool plan_lds(const Geom &g, int dtype, bool dx, ConvLdsPlan *plan)
             if (cost < least) { least = cost; best = l; }
             if (channels > 8) break; // (passes of four only where those of sixteen do not fit: the same work in more passes)
         }
-    if (least < 0.9 * (usual > 0 ? usual : plain)) *plan = best;
+    const double otherwise = usual > 0 ? usual : plain;
+    if (cost_out) *cost_out = least < 0.9 * otherwise ? least : otherwise;
+    if (least < 0.9 * otherwise) *plan = best;
     else if (usual > 0) *plan = first;
     else return false;
     return plan->px != 0;
@@ -516,6 +518,14 @@ template <typename T, bool DX> hipError_t launch(const ConvLdsPlan &l, hipStream
 }
 
 } // namespace
+
+double cost_without_mfma(const Geom &g, int dtype, bool dx)
+{
+    ConvLdsPlan l;
+    double cost;
+    plan_lds(g, dtype, dx, &l, &cost);
+    return cost;
+}
 
 bool launch_fwd_lds(const Geom &g, int dtype, const void *X, const void *W, const void *b, void *Y, hipStream_t st, hipError_t *err)
 {

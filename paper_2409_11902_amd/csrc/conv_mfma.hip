@@ -252,7 +252,7 @@ bool plan_pw(GatherParams &p, bool pool, bool record_free, int *variant)
 }
 
 // A launch with other filters: nine taps go to conv_tile.hip, or with few pixels to conv_wave.hip, what they leave to the gather.
-bool plan_other(GatherParams &p, bool fwd, int *variant)
+bool plan_other(const Geom &g, GatherParams &p, bool fwd, int *variant)
 {
     GatherParams wave = p, tile = p;
     int wave_variant;
@@ -285,6 +285,15 @@ bool plan_other(GatherParams &p, bool fwd, int *variant)
             return true;
         }
     }
+    // What only the waves take with matrix instructions (few pixels or few channels) is theirs where conv_lds.hip or the plain kernel are not
+    // faster: few terms, or more padding than channels.  A forward pass has the filter laid out in the launch that pools, a data gradient by
+    // a launch of its own, 5 us, or for nothing in that of the weight gradient.  363 random layers, by waves against without: data gradients 1.01
+    // of the time, half of them over 1.05 (3 -> 3 at 1 x 1, batch 6, 10.7 against 3.9 us), forward passes 0.54, a third over 1.05 (1 -> 6 at
+    // 56 x 56, stride 2, batch 221, 69 against 11); with this line 0.73 (3 of 87 over 1.05, the worst 1.17) and 0.48 (none).  Both gradients
+    // in a call 0.73 by waves, 18 of 87 over 1.05; 0.71 and none.
+    if (GatherParams gather = p; have_wave && !have_tile && cost_without_mfma(g, CAC_BF16, !fwd) < 0.85e-3 * wave_cost + (fwd ? 0.0 : 5.0) &&
+                                 !shape_gather(gather, variant))
+        return false;
     // Against conv_tile.hip by the ratio of the two planners' cycles, which counts a stage alike for one item to a lane and for two.
     // One: 200 random layers, below 0.55 the waves take 0.76 of the time (48 layers, 2 of them over 1.05), up to 0.7 it is 1.0, above 1.0
     // 1.6.  Two: under stride 1 0.8 below 0.45 and 1.04 from there to 0.55 (19 layers; data gradient of 67 -> 464 at 51 x 51, batch 7:
@@ -341,7 +350,7 @@ bool plan_fwd(const Geom &g, int dtype, GatherParams &p, int *variant)
         p.w_bytes = p.w_direct ? (uint32_t)g.K * g.C * 2u : (uint32_t)p.Mp * p.KCp * 2u;
         return true;
     }
-    return plan_other(p, true, variant);
+    return plan_other(g, p, true, variant);
 }
 
 // Data gradient: one gather GEMM (input channels x input pixels) per parity class of the input
@@ -396,7 +405,7 @@ bool plan_dx(const Geom &g, int dtype, GatherParams &base, GatherParams (&cls)[4
                 p.w_direct = 0;
                 p.w_kstep = (uint32_t)p.Mp * 32u;
                 p.w_bytes = (uint32_t)p.Mp * p.KCp * 2u;
-            } else if (!plan_other(p, false, &variant[*ncls])) return false;
+            } else if (!plan_other(g, p, false, &variant[*ncls])) return false;
             else if (p.tile) base.KCp = p.KCp; // (nine taps of one class are all taps: it is the only one)
             cls[(*ncls)++] = p;
         }

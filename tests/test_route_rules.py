@@ -151,3 +151,19 @@ def test_two_items_to_a_lane(shape, op, waves):
 def test_pointwise_float_layers(shape, stride, op, lds):
     got = B.cac_describe_plan(B.make_desc(*shape, 1, 1, stride, stride, dtype=B.F32), op)
     assert got.startswith("conv_lds") == lds, got
+
+
+@pytest.mark.parametrize("shape,stride,op,waves", [
+    # N, C, K, H, W.  3 x 3 layers that only the waves take with matrix instructions: not where a launch without any is faster
+    ((6, 3, 3, 1, 1), 1, B.OP_BWD_DATA, False),
+    ((2, 52, 1, 1, 1), 1, B.OP_BWD_DATA, False),
+    ((7, 5, 259, 1, 1), 1, B.OP_BWD_DATA, True),
+    ((72, 21, 6, 2, 1), 1, B.OP_FWD_AND_COMPRESS, True),
+    ((228, 2, 1, 42, 42), 2, B.OP_FWD_AND_COMPRESS, False),
+    ((3, 2, 6, 5, 3), 2, B.OP_FWD_AND_COMPRESS, False),
+    ((156, 178, 57, 4, 4), 2, B.OP_FWD_AND_COMPRESS, True),
+    ((90, 29, 27, 3, 3), 2, B.OP_FWD_AND_COMPRESS, True),
+])
+def test_layers_of_few_terms_go_without_matrix_instructions(shape, stride, op, waves):
+    got = B.cac_describe_plan(B.make_desc(*shape, 3, 3, stride, stride, 1, 1), op)
+    assert ("by waves" in got) == waves and got.startswith(("conv_lds", "generic")) != waves, got
