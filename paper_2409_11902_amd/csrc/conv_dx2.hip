@@ -289,7 +289,7 @@ bool shape_dx2(const Geom &g, GatherParams &p, int *variant, double *cost_out)
             const bool pairs = wgs > 256 && q.lds_bytes <= 80 * 1024;
             const double k = (double)((wgs + 255) / 256);
             // (128 accumulators, nine filter and six pixel fragments leave too little of 256 registers for the staging: one item
-            // per thread spills 4 to 13 of them, two up to 40)
+            // per thread spills 4 to 15 of them, two up to 40)
             const double spilled = items <= 256 ? 1.0 : 1.2;
             const double cost = k * q.nkb * spilled * (18.0 * 32 * 2 * t / (pairs ? 0.5 : 0.35) + (pairs ? 300 : 600)) + (pairs ? (k + 1) / 2 : k) * 8000.0;
             if (cost < best_cost) {

@@ -20,7 +20,7 @@
 // 98 -> 71 us; 128 -> 128 at 28 x 28, batch 128, 51 -> 36 us; 64 -> 64 at 56 x 56, batch 64, 43 -> 28 us.
 // Eight steps of filter fragments in flight instead of three, or a whole stage fetched at once through 32
 // registers, measured the same or slower; 64 x 224 pixels per wave with 512 registers does not fit (spills).  Two 7-pixel
-// items per thread spill 10 to 14 registers, one in stages of 16 channels 2 to 4.
+// items per thread spill 10 to 15 registers, one in stages of 16 channels 2 to 4.
 // 64 output channels x 512 pixels in stages of 16 channels (a patch of 32 leaves LDS for one workgroup only):
 // 64 -> 64 at 56 x 56, batch 128, data gradient 47 -> 40 us against 256 pixels in stages of 32.
 #include <stdio.h>

@@ -12,9 +12,9 @@
 //     halo rows and columns are zeros from the start and never written;
 //   - filter fragments come from global memory, D steps ahead in registers, no two waves of a workgroup the same ones; an
 //     XCD works on all pixel tiles of one block of output channels after the other, so that its L2 keeps the filter.
-// Measured per call (repack launch included): 512 -> 512 at 4 x 4, batch 128, a step 71 -> 62 us; long sums for few tiles, 1380 -> 32
+// Measured per call (repack launch included): 512 -> 512 at 4 x 4, batch 128, a step 71 -> 60 us; long sums for few tiles, 1380 -> 32
 // at 5 x 5, batch 1: 69 -> 19; 528 -> 388 at 7 x 7, batch 42, data gradient: 40 -> 22 (conv_tile.hip).  In the mean over random
-// layers 0.59 of the gather's time.  242 registers bound the waves (two to a SIMD); filter fragments are what a compute unit
+// layers 0.59 of the gather's time.  Up to 256 registers (none spilled) bound the waves, two to a SIMD; filter fragments are what a compute unit
 // asks L2 for: 1 KiB per wave and two MFMAs.
 #include <stdio.h>
 #include <stdlib.h>
